@@ -20,6 +20,7 @@
 #include "dynlp_frontier.h"
 #include "dynlp_components.h"
 #include "dynlp_binned.h"
+#include "dynlp_packed.h"
 
 using namespace dynlp;
 
@@ -185,6 +186,16 @@ struct dynlp_ctx {
     int pb_parts = 1;
     int pb_part_bin[kPbMaxParts + 1] = {};
     int pb_part_chunk[kPbMaxParts][2] = {};
+    // packed rounds for label rows (dynlp_packed.h)
+    bool pk_built = false;  // the arrays below describe the graph as it stands
+    int pk_rows = 0, pk_parts = 0, pk_bits = 0;  // vertices per part, parts, bits of a neighbour id in an entry
+    PkEntry* pk_ent = nullptr;
+    int64_t pk_ent_cap = 0;
+    int32_t* pk_len = nullptr;
+    unsigned int* pk_upd = nullptr;
+    int64_t pk_vcap = 0;
+    unsigned int* pk_tab = nullptr;  // per part: its first entry; all entries; the largest part
+    int64_t pk_tab_cap = 0;
     // label initialisation of inserted vertices (dynlp_components.h)
     int init_mode = DYNLP_INIT_UNIFORM;
     float tau = 0.f;
@@ -1055,6 +1066,161 @@ void launch_binned_round(dynlp_ctx* c, const PullRoundArgs& a, int round, bool f
     close_timed_span(c, e1);
 }
 
+// ---- packed rounds (dynlp_packed.h) -----------------------------------------------------------------
+// Below kPackedMinRows a round over all rows is a launch and its drain whichever kernel it runs (20,000 vertices of
+// degree 8: 9 us with the row update) and the layout of the entries is one more thing to wait for.
+constexpr unsigned int kPackedMinRows = 32768;
+// kPackedShare: see packed_rounds_pay; kPackedUneven: a part with more than this many times the mean entries would keep
+// the round waiting for one CU.
+constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
+struct PackedPlan {
+    int rows, parts, col_bits, bucket_bits;
+};
+
+int packed_stride(const dynlp_ctx* c) { return c->Cs == 1 ? 1 : (c->Cs + 1) / 2 * 2; }
+
+// Whether Jacobi rounds over nearly all vertices should run as packed rounds, and how the graph is cut for them.
+bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan* plan) {
+    // (a caller who fixes the lanes per row asks for the row update)
+    if (c->group_lanes != 0 || (c->CP == 1 && c->binned != 0) || universe.size() < kPackedMinRows || c->entries >= ((int64_t)1 << 31)) return false;
+    // parts: as many generations of one workgroup per CU as the sums need, of equal size
+    const int row_bits8 = packed_stride(c) * 32 + 2;  // bits of LDS per row: the sums, "in V_aff", "moved"
+    const int64_t rows_max = (int64_t)(kPkLds - kPkFixedLds) * 8 / row_bits8 / 32 * 32;
+    const int64_t wide = c->num_cu;
+    const int64_t gens = ceil_div(c->n, wide * rows_max);
+    const int64_t rows = round_up(ceil_div(c->n, wide * gens), 32);
+    int row_bits = 5, col_bits = 1;
+    while (((int64_t)1 << row_bits) < rows) ++row_bits;
+    while (((int64_t)1 << col_bits) < c->n) ++col_bits;
+    if (row_bits + col_bits > 32) return false;
+    int bucket_bits = 0;
+    while (((c->n - 1) >> bucket_bits) >= kPkBuckets) ++bucket_bits;
+    if (c->n * c->CP * 4 >= ((int64_t)1 << 32)) return false;  // byte offsets of label rows are 32-bit
+    // Bytes over the fabric: every XCD reads the label matrix once per generation; the row update reads one or two
+    // lines per entry.  Measured (share of the row update's bytes, time packed / ordinary): 1,000,000 vertices of degree
+    // 20 with 10 columns 0.20, 0.45; 300,000 of degree 16 with 29 columns 0.50, 0.65; 1,000,000 of degree 38 with 50
+    // columns would need 5 generations: 1.05 (not faster).
+    const double packed = 8.0 * (double)gens * (double)c->n * c->CP * 4.0;
+    const double ordinary = (double)c->entries * std::max(128.0, c->CP * 4.0);
+    if (packed > kPackedShare * ordinary) return false;
+    *plan = PackedPlan{(int)rows, (int)ceil_div(c->n, rows), col_bits, bucket_bits};
+    return true;
+}
+
+void free_packed(dynlp_ctx* c) {
+    dev_free(c, c->pk_ent);
+    dev_free(c, c->pk_len);
+    dev_free(c, c->pk_upd);
+    dev_free(c, c->pk_tab);
+    c->pk_ent = nullptr;
+    c->pk_len = nullptr;
+    c->pk_upd = c->pk_tab = nullptr;
+    c->pk_ent_cap = c->pk_vcap = c->pk_tab_cap = 0;
+    c->pk_built = false;
+}
+
+size_t packed_lds(const dynlp_ctx* c) { return (size_t)c->pk_rows * packed_stride(c) * 4 + (size_t)c->pk_rows / 32 * 8; }
+
+// Calls fn with the instantiation of the packed round for the context's columns.
+template <typename Fn>
+auto packed_kernel(const dynlp_ctx* c, Fn fn) {
+    switch (c->CP > 4 ? (c->Cs + 3) / 4 : c->CP == 4 ? 1 : -c->CP) {
+        case -1: return fn(k_pk_round<1, 1>);
+        case -2: return fn(k_pk_round<2, 1>);
+        case 1: return fn(k_pk_round<4, 1>);
+        case 2: return fn(k_pk_round<8, 2>);
+        case 3: return fn(k_pk_round<16, 3>);
+        case 4: return fn(k_pk_round<16, 4>);
+        case 5: return fn(k_pk_round<32, 5>);
+        case 6: return fn(k_pk_round<32, 6>);
+        case 7: return fn(k_pk_round<32, 7>);
+        case 8: return fn(k_pk_round<32, 8>);
+        case 9: return fn(k_pk_round<64, 9>);
+        case 10: return fn(k_pk_round<64, 10>);
+        case 11: return fn(k_pk_round<64, 11>);
+        case 12: return fn(k_pk_round<64, 12>);
+        case 13: return fn(k_pk_round<64, 13>);
+        case 14: return fn(k_pk_round<64, 14>);
+        case 15: return fn(k_pk_round<64, 15>);
+        default: return fn(k_pk_round<64, 16>);
+    }
+}
+
+// Lays the entries of the graph as it stands out for the packed rounds.  False (and nothing kept): no memory, or parts
+// so uneven that the largest would keep a round waiting; the caller then runs ordinary rounds.
+bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
+    const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), tab = parts + 2;
+    bool ok = true;
+    if (ent > c->pk_ent_cap) {
+        dev_free(c, c->pk_ent);
+        c->pk_ent = nullptr;
+        c->pk_ent_cap = 0;
+        ok = try_alloc_n(c, c->pk_ent, ent + ent / 8);
+        if (ok) c->pk_ent_cap = ent + ent / 8;
+    }
+    if (ok && c->n > c->pk_vcap) {
+        dev_free(c, c->pk_len);
+        dev_free(c, c->pk_upd);
+        c->pk_len = nullptr;
+        c->pk_upd = nullptr;
+        c->pk_vcap = 0;
+        ok = try_alloc_n(c, c->pk_len, c->n_cap) && try_alloc_n(c, c->pk_upd, c->n_cap / 32 + 64);
+        if (ok) c->pk_vcap = c->n_cap;
+    }
+    if (ok && tab > c->pk_tab_cap) {
+        dev_free(c, c->pk_tab);
+        c->pk_tab = nullptr;
+        c->pk_tab_cap = 0;
+        ok = try_alloc_n(c, c->pk_tab, tab + tab / 8);
+        if (ok) c->pk_tab_cap = tab + tab / 8;
+    }
+    c->pk_rows = plan.rows;
+    c->pk_parts = plan.parts;
+    c->pk_bits = plan.col_bits;
+    if (ok) {
+        const hipError_t e = packed_kernel(c, [&](auto kernel) {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)packed_lds(c));
+        });
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            ok = false;
+        }
+    }
+    if (!ok) {
+        free_packed(c);
+        return false;
+    }
+    unsigned int* start = c->pk_tab;
+    unsigned int* largest = start + parts + 1;
+    HIPCHK(c, hipMemsetAsync(start + parts, 0, 2 * sizeof(unsigned int), c->stream));
+    hipLaunchKernelGGL(k_pk_receivers, dim3(grid_for(round_up(c->n, 64))), dim3(kBlock), 0, c->stream, c->n, c->meta,
+                       c->seed_class, c->pk_len, c->pk_upd);
+    hipLaunchKernelGGL(k_pk_totals, dim3(plan.parts), dim3(kBlock), 0, c->stream, c->n, plan.rows, c->pk_len, start, largest);
+    hipLaunchKernelGGL(k_pb_scan_blocks, dim3(1), dim3(kBlock), 0, c->stream, parts + 1, start);
+    HIPCHK(c, hipGetLastError());
+    unsigned int most = 0;
+    HIPCHK(c, hipMemcpyAsync(&most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if ((double)most > kPackedUneven * (double)ent / (double)parts) return false;
+    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), 0, c->stream, c->n, plan.rows, plan.col_bits,
+                       plan.bucket_bits, c->meta, c->pool, c->pk_len, c->deg, start, c->pk_ent);
+    HIPCHK(c, hipGetLastError());
+    c->pk_built = true;
+    return true;
+}
+
+// One packed round (arguments as for the fused round).
+void launch_packed_round(dynlp_ctx* c, const PullRoundArgs& a, int round) {
+    hipEvent_t e1 = open_timed_span(c, round, 1);
+    const PkRound r{a.prev, a.ctr, a.ctr_zero, c->n, c->pk_rows, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab,
+                    c->pk_len, c->pk_upd, c->meta, c->pool, a.F_in, a.F_out, a.moved_prev, a.moved_cur, a.moved_clear,
+                    (unsigned int)c->moved_words, a.tol};
+    const dim3 grid((unsigned int)c->pk_parts), block(kPkThreads);
+    packed_kernel(c, [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, packed_lds(c), c->stream, r); });
+    HIPCHK(c, hipGetLastError());
+    close_timed_span(c, e1);
+}
+
 // Resolve the per-round events into the round log; returns the summed device time of all
 // row-update launches.
 float collect_kernel_ms(dynlp_ctx* c) {
@@ -1160,6 +1326,8 @@ constexpr double kDenseEnter = 0.90, kDenseLeave = 0.75;
 // synchronous 762 -> 738 ms, with supernode initialisation 367 -> 342 ms, in place with it 332 -> 270 ms (in place
 // from uniform rows V_aff collapses within one chain of rounds and nothing changes); 0.20 / 0.10 is no better.
 constexpr double kBinnedEnter = 0.35, kBinnedLeave = 0.20;
+// A packed round too costs the same whatever the size of V_aff, and about half an ordinary round over all rows.
+constexpr double kPackedEnter = 0.50, kPackedLeave = 0.35;
 
 // The ping-pong partner must agree with F on every row a full sweep does not write (seeds,
 // isolated vertices) before it can receive one.
@@ -1263,7 +1431,7 @@ void destroy_ctx(dynlp_ctx* c) {
                     c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
                     c->pb_src, c->pb_sp, c->pb_row0, c->pb_lpos, c->pb_tmp, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, c->pb_upd,
-                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table};
+                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_upd, c->pk_tab};
     for (void* p : ptrs) dev_free(c, p);
     const std::vector<void*> left(c->live.begin(), c->live.end());  // arrays an interrupted call never got to free
     for (void* p : left) dev_free(c, p);
@@ -1914,18 +2082,26 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
         all_rows.nl = c->h_slot[0].next_long;
         c->pb_built = false;
         const bool binned = !converged && binned_rounds_pay(c, all_rows) && build_binned(c);
+        PackedPlan pk_plan;
+        c->pk_built = false;
+        const bool packed = !converged && !in_place && !binned && packed_rounds_pay(c, all_rows, &pk_plan) && build_packed(c, pk_plan);
         bool pb_fresh = true;  // the slots of the binned rounds do not yet hold the current labels
-        if (binned) HIPCHK(c, hipMemsetAsync(c->moved[0], 0xff, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
+        if (binned || packed) HIPCHK(c, hipMemsetAsync(c->moved[0], 0xff, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
         while (!converged && it < max_iter) {
             // a chain of sweeps; each checks on the device whether its predecessor already met the stop rule
             const int r = std::min<int>(kChain, max_iter - it);
             const bool chain_binned = binned && !lazy;  // the averaged sweeps of a limit cycle are ordinary ones
+            const bool chain_packed = packed && !lazy;
             for (int i = 0; i < r; ++i) {
                 const int t = it + i;
                 c->ev_adjacent = i > 0;  // a chain of sweeps is nothing but these launches
-                if (chain_binned && t > 0) {
+                if ((chain_binned || chain_packed) && t > 0) {
                     const PullRoundArgs a{slot_of(c, t - 1), buf[t & 1], buf[(t + 1) & 1], c->moved[0], c->moved[1], c->moved[2],
                                           tol, slot_of(c, t), slot_of(c, t + 1)};
+                    if (chain_packed) {
+                        launch_packed_round(c, a, t);
+                        continue;
+                    }
                     launch_binned_round(c, a, t, t == 1 || pb_fresh);
                     pb_fresh = false;
                     continue;
@@ -1948,7 +2124,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
                 if (!rc.executed) break;
                 std::memcpy(&last, &rc.resid_bits, sizeof(float));
                 edges += (int64_t)(rc.edges + rc.edges_long);
-                c->log.push_back(round_info(rc, chain_binned && it > 0 ? 3 : 0, G));
+                c->log.push_back(round_info(rc, chain_binned && it > 0 ? 3 : 0, chain_packed && it > 0 ? 0 : G));
                 ++it;
                 same_run = rc.resid_bits == prev_bits ? same_run + 1 : 0;
                 prev_bits = rc.resid_bits;
@@ -2195,6 +2371,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         bool fused = false;     // the stretch's rounds evaluate V_aff themselves (no frontier list, no pull)
         bool binned = false;    // ... as scatter + gather passes (scalar labels)
         bool bin_failed = false;
+        bool packed = false;    // ... as packed rounds
+        bool pack_failed = false;
         // Rounds that repeat themselves exactly (same |V_aff|, rows moved and max change, 16 times in a row) are in
         // a period-2 cycle kept alive by float32 rounding (in-place rounds too: the few rows of such a V_aff run side
         // by side in one wave and read each other's old values); the rest of the batch's flag-marking rounds then
@@ -2202,7 +2380,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         int same_run = 0;
         bool lazy = false;
         unsigned int prev_sig[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-        c->pb_built = false;    // the batch changed the graph
+        c->pb_built = c->pk_built = false;    // the batch changed the graph
+        PackedPlan pk_plan{};
         c->persist_failed = false;
         c->persist_launches_last = c->persist_aborts_last = 0;
         const bool in_place = c->update_mode == DYNLP_UPDATE_IN_PLACE;
@@ -2225,20 +2404,29 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 bin_failed = true;  // no memory for the binned arrays: ordinary rounds for this batch
                 can_bin = false;
             }
+            bool can_pack = !pack_failed && !in_place && !can_bin && !persistent_rounds_pay(c, universe) &&
+                            packed_rounds_pay(c, universe, &pk_plan);
+            if (can_pack && !pingpong && !c->pk_built && (double)known >= kPackedEnter * (double)universe.size() &&
+                !build_packed(c, pk_plan)) {
+                pack_failed = true;
+                can_pack = false;
+            }
+            const double enter = can_bin ? kBinnedEnter : can_pack ? kPackedEnter : kDenseEnter;
             // graphs whose rounds run many per launch stay in one stretch from the first round to the last: a round
             // over a small V_aff costs them no more than a launch
             // (not once rounds repeat themselves exactly: the averaged rows that end such a cycle are staged rounds)
             const bool stay = !lazy && !can_bin && fused_rounds_pay(c, avg_len) && persistent_rounds_pay(c, universe);
-            if (!pingpong && (stay || (double)known >= (can_bin ? kBinnedEnter : kDenseEnter) * (double)universe.size())) {
+            if (!pingpong && (stay || (double)known >= enter * (double)universe.size())) {
                 if (!in_place) sync_partner(c);
                 for (unsigned int* mv : c->moved)
                     HIPCHK(c, hipMemsetAsync(mv, 0, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
                 pingpong = true;
                 stretch_start = it;
                 binned = can_bin;
-                fused = binned || fused_rounds_pay(c, avg_len);
+                packed = can_pack;
+                fused = binned || packed || fused_rounds_pay(c, avg_len);
             } else if (pingpong && !(stay && fused && !binned) &&
-                       (double)known < (binned ? kBinnedLeave : kDenseLeave) * (double)universe.size()) {
+                       (double)known < (binned ? kBinnedLeave : packed ? kPackedLeave : kDenseLeave) * (double)universe.size()) {
                 pingpong = false;
                 if (fused) {
                     // rows of the last round are in F (the buffers were swapped to make it so)
@@ -2315,6 +2503,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                                               c->moved[q % 3], c->moved[(q + 1) % 3], c->tol, slot, slot_of(c, t + 1)};
                         if (binned)
                             launch_binned_round(c, a, t, q == 1);
+                        else if (packed)
+                            launch_packed_round(c, a, t);
                         else
                             launch_update_pull(c, G, universe, a, t);
                     }
@@ -2353,7 +2543,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 edges += (int64_t)(rc.edges + rc.edges_long);
                 avg_len = nq ? (double)(rc.edges + rc.edges_long) / (double)nq : avg_len;
                 // the first round of a fused stretch still works on a frontier list
-                c->log.push_back(round_info(rc, !pingpong ? 1 : (fused && it + i > stretch_start ? (binned ? 3 : i >= persist_first ? 4 : 2) : 0), G));
+                c->log.push_back(round_info(rc, !pingpong ? 1 : (fused && it + i > stretch_start ? (binned ? 3 : i >= persist_first ? 4 : 2) : 0),
+                                            pingpong && packed && it + i > stretch_start ? 0 : G));
                 // inside a stretch the next V_aff is not counted: this round's size stands in for it while
                 // rows still move
                 known = pingpong && fused ? (rc.changed ? std::max(nq, 1u) : 0u) : rc.next_count + rc.next_long;

@@ -1,0 +1,464 @@
+// Packed rounds for label rows: Alg. 2 Step 3 / Eq. (1) over nearly all vertices with the sums of all rows on the chip
+// and the gathers served by the L2s.
+//
+// A gather of a random neighbour's row costs one 128-byte line whatever the kernel around it: about 250 G rows/s when
+// the lines are in the L2s and 55 G rows/s when they come over the fabric (random whole-row reads of 64 bytes, nothing
+// else, tables of 0.25 ... 4 MB against 64 MB; 8 / 16 / 32 MB: 203 / 104 / 68 G).  The ordinary row update walks a row
+// at a time, so its gathers go all over the label matrix, and a row's chain of dependent reads (list, record, entries,
+// neighbours, next entries, old row) keeps it below even that rate on graphs whose labels do fit the caches.
+//
+// While the graph does not change (all rounds of a batch, all sweeps of a static solve) the entries are laid out once
+// for the order the chip wants to read them in:
+//   parts    ranges of consecutive vertices, one workgroup each; the sums of all its rows stay in the workgroup's LDS
+//            from the first entry to the last (256 CUs x 160 KB hold 1,000,000 rows of 10 columns);
+//   buckets  a part's entries are in ascending order of neighbour id (512 ranges of ids).  Every workgroup goes through
+//            the ids in the same order, and since all parts hold about the same number of entries per range, the
+//            workgroups of an XCD read the same few hundred KB of label rows at about the same time: a line comes over
+//            the fabric once per XCD and round instead of once per entry.  Nothing keeps the workgroups together
+//            (those that lag find their lines in the L2 and catch up); drifting apart costs misses, never correctness.
+// Entries are handled one by one, whatever row they belong to (no lanes idle at the ends of rows, a hub row costs what
+// its entries cost): a wave reads 64 entries with one load, hands them round with shuffles, LANES lanes read one
+// neighbour row, multiply it by w / deg and add it to the row's sums in LDS.
+//
+// The sums are 32-bit fixed-point numbers (unit 2^-30; the terms w / deg * F of a row add up to at most 1): integer
+// additions commute, so a round is bit-reproducible although the order of the LDS atomics is not.  Rounding a term to
+// 2^-31 is finer than the float32 sum of the ordinary row update.
+//
+// Bound: the vector memory path of the CUs (a line of 128 bytes per gather through the L1; leaving out the LDS atomics
+// changes nothing, leaving out the gathers takes away half).  One round over all rows, row update -> packed round, us:
+//   1,000,000 vertices, degree 20, 10 columns (64 MB of label rows)   400 -> 178   (TCC misses 18.3M -> 6.4M)
+//     400,000 vertices, degree 20, 10 columns                         147 ->  77
+//     150,000 vertices, power law, degree 30, 20 columns              90 ->  62
+//     300,000 vertices, degree 16, 29 columns                        109 ->  71
+//     100,000 vertices, kNN, mean degree 18, 10 columns               38 ->  27
+// What it took: without the barriers in the loop the oldest waves of a CU run ahead and the L2s hit 20% instead of 72%
+// (1,000,000 vertices: 320 us); with every lane group loading its own entries the loads of entries cost as much as the
+// gathers (195 us).
+#pragma once
+
+#include "dynlp_device.h"
+
+namespace dynlp {
+
+constexpr int kPkThreads = 1024;
+constexpr int kPkLds = 160 * 1024;     // LDS of one workgroup, everything included: one workgroup per CU
+constexpr int kPkFixedLds = 1024;      // of it: reductions at the end of the kernel (static arrays)
+constexpr unsigned int kPkWindow = 2688;  // entries between barriers (see k_pk_round)
+constexpr int kPkBuckets = 512;        // ranges of neighbour ids a part's entries are ordered by
+constexpr float kPkUnit = 1073741824.0f;  // 2^30
+
+// One entry of the packed stream: receiving row (offset in its part) << col_bits | neighbour, and
+// w / deg(row) * 2^30.
+struct __attribute__((aligned(8))) PkEntry {
+    unsigned int at;
+    float wn;
+};
+
+// Reads through a buffer descriptor: addresses are 32-bit offsets, reads past the end return 0.
+__device__ inline __amdgpu_buffer_rsrc_t pk_buffer(const void* p, unsigned int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// The entry stream is read once per round and should not push label rows out of the L2: non-temporal.
+__device__ inline PkEntry pk_load_entry(__amdgpu_buffer_rsrc_t b, unsigned int at) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, (int)at, 0, 2);
+    return PkEntry{v.x, __uint_as_float(v.y)};
+}
+
+template <int V>
+__device__ inline Vec<V> pk_load_piece(__amdgpu_buffer_rsrc_t b, unsigned int at) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    Vec<V> r;
+    if constexpr (V == 1) {
+        r.v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)at, 0, 0));
+    } else if constexpr (V == 2) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, (int)at, 0, 0);
+        r.v[0] = __uint_as_float(v.x);
+        r.v[1] = __uint_as_float(v.y);
+    } else {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(b, (int)at, 0, 0);
+        r.v[0] = __uint_as_float(v.x);
+        r.v[1] = __uint_as_float(v.y);
+        r.v[2] = __uint_as_float(v.z);
+        r.v[3] = __uint_as_float(v.w);
+    }
+    return r;
+}
+
+__device__ inline void clear_round_slot(RoundCtr* slot) {  // called by one workgroup
+    if (threadIdx.x == 0) {
+        slot->next_count = 0;
+        slot->next_long = 0;
+        slot->executed = 0;
+        slot->rows_short = 0;
+        slot->rows_long = 0;
+        slot->any_moved = 0;
+    }
+    if (threadIdx.x < kCtrLanes) {
+        RoundPart* p = &slot->part[threadIdx.x];
+        p->resid_bits = 0;
+        p->changed = 0;
+        p->edges = 0;
+        p->edges_long = 0;
+        p->rows_short = 0;
+        p->rows_long = 0;
+    }
+}
+
+// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0; the same as one bit per vertex.
+__global__ void __launch_bounds__(kBlock) k_pk_receivers(int64_t n, const RowMeta* __restrict__ meta,
+                                                        const int32_t* __restrict__ seed_class,
+                                                        int32_t* __restrict__ len, unsigned int* __restrict__ upd) {
+    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    int l = 0;
+    if (v < n && seed_class[v] < 0) l = meta[v].len;
+    if (v < n) len[v] = l;
+    const unsigned long long b = __ballot(l > 0);
+    const int lane = lane_id();
+    if ((lane == 0 || lane == 32) && v < ((n + 31) & ~(int64_t)31)) upd[v >> 5] = (unsigned int)(lane == 0 ? b : b >> 32);
+}
+
+// part_total[p] = the entries of the updatable rows of part p; *largest = the largest part.
+__global__ void __launch_bounds__(kBlock) k_pk_totals(int64_t n, int rows, const int32_t* __restrict__ len,
+                                                     unsigned int* __restrict__ part_total,
+                                                     unsigned int* __restrict__ largest) {
+    __shared__ unsigned int smem[kBlock / kWave + 1];
+    const int64_t base = (int64_t)blockIdx.x * rows;
+    const int64_t end = base + rows < n ? base + rows : n;
+    unsigned int v = 0;
+    for (int64_t u = base + threadIdx.x; u < end; u += kBlock) v += (unsigned int)len[u];
+    unsigned int total;
+    (void)block_exclusive_scan<unsigned int>(v, smem, &total);
+    if (threadIdx.x == 0) {
+        part_total[blockIdx.x] = total;
+        atomicMax(largest, total);
+    }
+}
+
+// Place of the i-th entry of a bucket of L: entries of one row arrive one after the other and would meet at the row's
+// sums in LDS; steps of about 0.618 L (coprime to L) spread them over the bucket.
+__device__ inline unsigned int pk_spread(unsigned int L) {
+    for (unsigned int s = (unsigned int)(0.618 * (double)L) | 1u;; s += 2u) {
+        unsigned int x = L, y = s;
+        while (y) {
+            const unsigned int t = x % y;
+            x = y;
+            y = t;
+        }
+        if (x == 1u) return s;
+    }
+}
+
+// The entries of part p to its stretch of the stream, start[p] .. start[p + 1] - 1 (exclusive scan of part_total), in
+// ascending order of neighbour >> bucket_bits.  Which of a bucket's places an entry gets depends on timing and has no
+// influence on results.  One workgroup per part, 16 lanes per row.
+__global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, int rows, int col_bits, int bucket_bits,
+                                                        const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                                        const int32_t* __restrict__ len, const float* __restrict__ deg,
+                                                        const unsigned int* __restrict__ start,
+                                                        PkEntry* __restrict__ ent) {
+    __shared__ unsigned int cur[kPkBuckets];  // entries per bucket, then entries placed
+    __shared__ unsigned int seg0[kPkBuckets], seg_len[kPkBuckets], step[kPkBuckets];
+    __shared__ unsigned int wave_tot[kPkBuckets / kWave];
+    static_assert(kPkBuckets <= kPkThreads, "one thread per bucket");
+    if (threadIdx.x < kPkBuckets) cur[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * rows;
+    const int64_t end = base + rows < n ? base + rows : n;
+    const int gl = threadIdx.x & 15;
+    for (int64_t u = base + (threadIdx.x >> 4); u < end; u += kPkThreads / 16) {
+        const int l = len[u];
+        if (l == 0) continue;
+        const Edge* __restrict__ row = pool + meta[u].off;
+        for (int j = gl; j < l; j += 16) atomicAdd(&cur[(unsigned int)row[j].col >> bucket_bits], 1u);
+    }
+    __syncthreads();
+    unsigned int v = 0, inc = 0;
+    if (threadIdx.x < kPkBuckets) {
+        v = cur[threadIdx.x];
+        inc = wave_inclusive_scan(v);
+        if (lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = inc;
+        seg_len[threadIdx.x] = v;
+        step[threadIdx.x] = v > 0u ? pk_spread(v) : 1u;
+        cur[threadIdx.x] = 0u;
+    }
+    __syncthreads();
+    if (threadIdx.x < kPkBuckets) {
+        unsigned int before = start[blockIdx.x];
+        for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) before += wave_tot[w];
+        seg0[threadIdx.x] = before + inc - v;
+    }
+    __syncthreads();
+    for (int64_t u = base + (threadIdx.x >> 4); u < end; u += kPkThreads / 16) {
+        const int l = len[u];
+        if (l == 0) continue;
+        const Edge* __restrict__ row = pool + meta[u].off;
+        const float d = deg[u];
+        const unsigned int r = (unsigned int)(u - base) << col_bits;
+        for (int j = gl; j < l; j += 16) {
+            const Edge e = row[j];
+            const unsigned int b = (unsigned int)e.col >> bucket_bits;
+            PkEntry x;
+            x.at = r | (unsigned int)e.col;
+            x.wn = e.w / d * kPkUnit;
+            const unsigned int i = atomicAdd(&cur[b], 1u);
+            ent[seg0[b] + (unsigned int)((unsigned long long)i * step[b] % seg_len[b])] = x;
+        }
+    }
+}
+
+struct PkRound {
+    const RoundCtr* prev;
+    RoundCtr* ctr;
+    RoundCtr* ctr_zero;
+    int64_t n;
+    int rows;  // per part, a multiple of 32
+    int C;     // stored columns that are in use
+    int stride;  // sums per row in LDS: C, rounded up to even where a row has several columns
+    int col_bits;
+    const PkEntry* ent;
+    const unsigned int* start;  // per part: its first entry; the last word: the number of entries
+    const int32_t* len;
+    const unsigned int* upd;
+    const RowMeta* meta;
+    const Edge* pool;
+    const float* F_in;
+    float* F_out;
+    const unsigned int* moved_prev;  // bitmap of the rows that moved in the previous round
+    unsigned int* moved_cur;         // ... in this round (every word of a part is written by its workgroup)
+    unsigned int* moved_clear;
+    unsigned int words;
+    float tol;
+};
+
+// One round.  V_aff is decided per row as in k_row_update_pull: u is in it iff u or a neighbour moved in the previous
+// round; rows outside it are copied to F_out.  Does nothing if the previous round did not run or moved no row.
+// LANES: lanes that read one neighbour row (those of its CP columns that are in use).
+template <int CP, int LANES>
+__global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
+    constexpr int T = kPkThreads;
+    constexpr int NW = T / kWave;
+    constexpr int VEC = CP >= 4 ? 4 : CP;
+    constexpr int LPN = CP / VEC;
+    extern __shared__ __align__(16) unsigned int pk_lds[];
+    __shared__ float sm_r[NW];
+    __shared__ unsigned long long sm_e[NW], sm_c[NW];
+    if (a.ctr_zero && blockIdx.x == 0) clear_round_slot(a.ctr_zero);
+    // a static sweep finds the size of its row list in its predecessor's slot: hand it on (0 in batch rounds)
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.ctr->next_count = a.prev->next_count;
+        a.ctr->next_long = a.prev->next_long;
+    }
+    // the first entries are asked for before anything that has to be waited for
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    constexpr int SLOTS = kWave / LANES;  // neighbour rows per gather
+    constexpr int GATHERS = kWave / SLOTS;
+    constexpr int TILE = SLOTS * GATHERS;  // entries a wave reads at once, one per lane
+    constexpr int TILES = GATHERS >= 3 ? 1 : 4 / GATHERS;
+    constexpr unsigned int kStep = NW * TILES * TILE;  // entries the workgroup takes at a time
+    const int mslot = lane_id() / LANES, mchunk = lane_id() % LANES;
+    const unsigned int mask = (1u << a.col_bits) - 1u;
+    const unsigned int stride = (unsigned int)a.stride * 4u;  // bytes of a row's sums
+    const unsigned int piece = (unsigned int)mchunk * VEC * 4u;
+    char* const sums = reinterpret_cast<char*>(pk_lds) + piece;
+    const bool second = mchunk * VEC + 2 < a.C;  // the upper two columns of a piece of four are in use
+    const unsigned int first = __builtin_amdgcn_readfirstlane(a.start[blockIdx.x]);
+    const unsigned int count = __builtin_amdgcn_readfirstlane(a.start[blockIdx.x + 1]) - first;
+    // buffer reads: one address register, and reads past the part's last entry return an entry of weight 0
+    const __amdgpu_buffer_rsrc_t ent = pk_buffer(a.ent + first, count * (unsigned int)sizeof(PkEntry));
+    const __amdgpu_buffer_rsrc_t rows = pk_buffer(a.F_in, (unsigned int)a.n * (unsigned int)(CP * 4));
+    const unsigned int own = (unsigned int)(wave * TILES * TILE + (lane_id() < TILE ? lane_id() : TILE - 1)) * (unsigned int)sizeof(PkEntry);
+    PkEntry e[TILES];
+#pragma unroll
+    for (int q = 0; q < TILES; ++q) e[q] = pk_load_entry(ent, own + q * TILE * (unsigned int)sizeof(PkEntry));
+    if (!a.prev->executed || a.prev->any_moved == 0u) return;
+#pragma unroll 1
+    for (unsigned int w = blockIdx.x * T + threadIdx.x; w < a.words; w += gridDim.x * T) a.moved_clear[w] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->executed = 1;
+
+    const int chunk = threadIdx.x % LPN;
+    const int64_t base = (int64_t)blockIdx.x * a.rows;
+    const int nr = (int)(a.n - base < a.rows ? a.n - base : a.rows);  // the host launches no part without rows
+    const int nwords = (nr + 31) / 32;
+    unsigned int* const acc = pk_lds;
+    unsigned int* const in = pk_lds + a.rows * a.stride;  // rows in V_aff
+    unsigned int* const mv = in + a.rows / 32;            // rows that move in this round
+#pragma unroll 1
+    for (int i = threadIdx.x; i < a.rows * a.stride; i += T) acc[i] = 0u;
+#pragma unroll 1
+    for (int w = threadIdx.x; w < nwords; w += T) {
+        in[w] = a.moved_prev[(base >> 5) + w] & a.upd[(base >> 5) + w];
+        mv[w] = 0u;
+    }
+    __syncthreads();
+    // rows that did not move themselves: 16 lanes look their neighbours up until one that moved is found
+    {
+        const int gl = threadIdx.x & 15;
+#pragma unroll 1
+        for (int r = threadIdx.x >> 4; r < nr; r += T / 16) {
+            if ((in[r >> 5] >> (r & 31)) & 1u) continue;
+            const int l = a.len[base + r];
+            if (l == 0) continue;
+            const Edge* __restrict__ row = a.pool + a.meta[base + r].off;
+            bool hit = false;
+#pragma unroll 1
+            for (int j0 = 0; j0 < l && !hit; j0 += 16) {  // uniform in the group of 16 lanes
+                const int j = j0 + gl;
+                const int32_t v = row[j < l ? j : l - 1].col;
+                const unsigned long long b = __ballot((a.moved_prev[(unsigned int)v >> 5] >> ((unsigned int)v & 31u)) & 1u);
+                hit = ((b >> (lane_id() & 48)) & 0xffffull) != 0ull;
+            }
+            if (hit && gl == 0) atomicOr(&in[r >> 5], 1u << (r & 31));
+        }
+    }
+    unsigned int since = 0;
+#pragma unroll 1
+    for (unsigned int i0 = 0; i0 < count; i0 += kStep) {  // uniform in the workgroup
+        since += kStep;
+        if (since > kPkWindow) {  // keeps the waves of the workgroup within kPkWindow entries of each other
+            __syncthreads();
+            since = kStep;
+        }
+        PkEntry cur[TILES];
+#pragma unroll
+        for (int q = 0; q < TILES; ++q) {
+            cur[q] = e[q];
+            e[q] = pk_load_entry(ent, own + (i0 + kStep + q * TILE) * (unsigned int)sizeof(PkEntry));
+        }
+        constexpr int ALL = TILES * GATHERS;
+        constexpr int UN = ALL <= 8 ? ALL : ALL % 8 == 0 ? 8 : ALL % 6 == 0 ? 6 : ALL % 5 == 0 ? 5 : ALL;
+        static_assert(ALL % UN == 0, "whole groups of gathers");
+#pragma unroll
+        for (int g0 = 0; g0 < ALL; g0 += UN) {
+            Vec<VEC> f[UN];
+            unsigned int to[UN];
+            float wn[UN];
+#pragma unroll
+            for (int t = 0; t < UN; ++t) {
+                const int q = (g0 + t) / GATHERS, src = (g0 + t) % GATHERS * SLOTS + mslot;
+                unsigned int at = cur[q].at;
+                wn[t] = cur[q].wn;
+                if constexpr (LANES > 1) {
+                    at = __shfl(at, src);
+                    wn[t] = __shfl(wn[t], src);
+                }
+                f[t] = pk_load_piece<VEC>(rows, (at & mask) * (unsigned int)(CP * 4) + piece);
+                to[t] = at >> a.col_bits;
+            }
+            if (mslot >= SLOTS) continue;  // the lanes left over
+#pragma unroll
+            for (int t = 0; t < UN; ++t) {
+                unsigned int byte = __umul24(to[t], stride);
+                asm("" : "+v"(byte));  // computed once, outside the masked half below
+                char* const dst = sums + byte;
+                unsigned int x[VEC];
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) x[k] = (unsigned int)__builtin_rintf(wn[t] * f[t].v[k]);
+                if constexpr (VEC == 1) {
+                    atomicAdd(reinterpret_cast<unsigned int*>(dst), x[0]);
+                } else {
+                    // two columns per atomic: sums stay below 2^32, nothing carries over
+                    atomicAdd(reinterpret_cast<unsigned long long*>(dst), x[0] | ((unsigned long long)x[1] << 32));
+                    if constexpr (VEC == 4)
+                        if (second) atomicAdd(reinterpret_cast<unsigned long long*>(dst) + 1, x[2] | ((unsigned long long)x[3] << 32));
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int cols = a.C - chunk * VEC;  // columns of this lane's piece of a row that are in use (may be <= 0)
+    float rmax = 0.f;
+    unsigned int edges = 0, edges_long = 0;
+    unsigned int nchanged = 0, nrows = 0, nrows_long = 0;
+    constexpr int RPP = T / LPN;  // rows per pass
+    constexpr int UF = 4;         // passes whose reads are in flight together
+#pragma unroll 1
+    for (int r0 = 0; r0 < nr; r0 += UF * RPP) {
+        int l[UF];
+        Vec<VEC> old[UF];
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            const int r = r0 + q * RPP + (int)threadIdx.x / LPN;
+            l[q] = r < nr ? a.len[base + r] : 0;
+            if (l[q] > 0) old[q] = load_vec<VEC>(a.F_in + (size_t)(base + r) * CP + chunk * VEC);
+        }
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            const int r = r0 + q * RPP + (int)threadIdx.x / LPN;
+            if (l[q] == 0) continue;  // the same for the lanes of a row
+            float* const out = a.F_out + (size_t)(base + r) * CP + chunk * VEC;
+            if (!((in[r >> 5] >> (r & 31)) & 1u)) {
+                if (a.F_out != a.F_in) store_vec<VEC>(out, old[q]);
+                continue;
+            }
+            Vec<VEC> fn;
+            float d = 0.f;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                fn.v[k] = k < cols ? fminf((float)acc[r * a.stride + chunk * VEC + k] * (1.0f / kPkUnit), 1.0f) : 0.f;
+                d = fmaxf(d, fabsf(fn.v[k] - old[q].v[k]));
+            }
+#pragma unroll
+            for (int s = 1; s < LPN; s <<= 1) d = fmaxf(d, __shfl_xor(d, s, LPN));
+            store_vec<VEC>(out, fn);
+            if (chunk == 0) {
+                rmax = fmaxf(rmax, d);
+                if (d > a.tol) {
+                    atomicOr(&mv[r >> 5], 1u << (r & 31));
+                    nchanged += 1u;
+                }
+                if (l[q] > 128) {
+                    edges_long += (unsigned int)l[q];
+                    nrows_long += 1u;
+                } else {
+                    edges += (unsigned int)l[q];
+                    nrows += 1u;
+                }
+            }
+        }
+    }
+    // per workgroup: at most 2^31 entries and 2^16 rows
+    unsigned long long both_edges = edges | ((unsigned long long)edges_long << 32);
+    unsigned long long counts = nchanged | ((unsigned long long)nrows << 20) | ((unsigned long long)nrows_long << 40);
+    rmax = wave_max(rmax);
+    both_edges = wave_sum(both_edges);
+    counts = wave_sum(counts);
+    if (lane_id() == 0) {
+        sm_r[wave] = rmax;
+        sm_e[wave] = both_edges;
+        sm_c[wave] = counts;
+    }
+    __syncthreads();
+    for (int w = threadIdx.x; w < nwords; w += T) a.moved_cur[(base >> 5) + w] = mv[w];
+    if (threadIdx.x >= NW) return;
+    rmax = sm_r[threadIdx.x];
+    both_edges = sm_e[threadIdx.x];
+    counts = sm_c[threadIdx.x];
+#pragma unroll
+    for (int d = NW / 2; d > 0; d >>= 1) {
+        rmax = fmaxf(rmax, __shfl_xor(rmax, d, NW));
+        both_edges += __shfl_xor(both_edges, d, NW);
+        counts += __shfl_xor(counts, d, NW);
+    }
+    if (threadIdx.x == 0) {
+        edges = (unsigned int)both_edges;
+        edges_long = (unsigned int)(both_edges >> 32);
+        nchanged = (unsigned int)(counts & 0xfffffu);
+        nrows = (unsigned int)((counts >> 20) & 0xfffffu);
+        nrows_long = (unsigned int)(counts >> 40);
+        RoundPart* p = &a.ctr->part[blockIdx.x & (kCtrLanes - 1)];
+        if (rmax > 0.f) atomicMax(&p->resid_bits, __float_as_uint(rmax));
+        if (edges) atomicAdd(&p->edges, (unsigned long long)edges);
+        if (edges_long) atomicAdd(&p->edges_long, (unsigned long long)edges_long);
+        if (nchanged) {
+            atomicAdd(&p->changed, nchanged);
+            a.ctr->any_moved = 1u;
+        }
+        if (nrows) atomicAdd(&p->rows_short, nrows);
+        if (nrows_long) atomicAdd(&p->rows_long, nrows_long);
+    }
+}
+
+}  // namespace dynlp

@@ -1,0 +1,107 @@
+"""GPU parity of the packed rounds (label rows of graphs of 32,768 updatable vertices or more: entries ordered by
+neighbour id, sums of a part's rows in LDS): sweeps of the static solve and the rounds of a batch against the oracle,
+for every way a label row is read (1 to 16 lanes, odd column counts, the scalar layout), odd sizes and hub rows.
+
+Tolerances: one round rounds each term w / d * F to 2^-31 and w / d to float32, less than the 1e-6 that a float32 round
+is allowed; the bars of the ordinary rounds (test_gpu_parity) apply.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import native as ON
+from oracle import reference as R
+import paper_2604_06596_amd as P
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+ROUNDS_ATOL = 5e-6
+
+
+def _problem(kind, n, C, deg, seed):
+    if kind == "hub":
+        return W.chung_lu(n, C, deg, 2.1, 1200, 0.8, 0.03, seed)
+    return W.sbm(n, C, deg, 8.0, 0.03, seed)
+
+
+def _batch(kind, p, k, deg):
+    return W.chung_lu_vertex_batch(p, k, 0.02) if kind == "hub" else W.sbm_vertex_batch(p, k, deg, 0.02)
+
+
+def _make(p, **kw):
+    return P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, **kw)
+
+
+def _is_packed(r):
+    return r.group_lanes == 0
+
+
+@pytest.mark.parametrize("kind,n,C,deg,scalar", [
+    ("sbm", 36001, 2, 12, True), ("sbm", 36001, 2, 12, False), ("sbm", 35213, 3, 12, False), ("sbm", 36000, 5, 12, False),
+    ("sbm", 34817, 10, 20, False), ("sbm", 36007, 12, 20, False), ("sbm", 36007, 16, 20, False), ("sbm", 36000, 17, 20, False),
+    ("sbm", 36000, 24, 20, False), ("sbm", 36000, 29, 20, False), ("sbm", 35000, 33, 20, False), ("sbm", 35000, 50, 24, False),
+    ("sbm", 34999, 64, 24, False), ("hub", 40000, 20, 30, False)])
+def test_packed_rounds_match_the_oracle(kind, n, C, deg, scalar):
+    p, p0 = _problem(kind, n, C, deg, 31 + C), _problem(kind, n, C, deg, 31 + C)
+    b = _batch(kind, p, 2500, deg)
+    g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
+    rp, col, w = g.csr()
+    F = R.initial_labels(g.seed_class, C)
+    for _ in range(12):
+        F, _ = ON.itlp_sweep(rp, col, w, F, g.seed_class)
+    runs = []
+    for _ in range(2):
+        with _make(p0, binary_scalar=scalar) as d:
+            st, s = d.static_solve(1e-9, 12)
+            assert st == 1 and s.iterations == 12
+            assert [_is_packed(r) for r in d.round_log_full()] == [False] + [True] * 11
+            cold, _ = d.get_labels()
+            d.static_solve(TOL, 20000)
+            soft0, _ = d.get_labels()
+            d.set_params(TOL, 14)
+            st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            soft, hard = d.get_labels()
+            log = d.round_log_full()
+            sizes, deltas = d.round_log()
+        runs.append((cold, soft0, soft))
+    assert np.max(np.abs(cold - F)) <= ROUNDS_ATOL
+    assert any(_is_packed(r) and r.staged == 2 for r in log), "the case is meant to reach packed rounds"
+    n_old = g.n
+    g.insert(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+    rp, col, w = g.csr()
+    A0 = ON.affected_set(rp, col, g.seed_class, n_old, b.eu, b.ev, b.seed_vertex)
+    F = np.concatenate([soft0.astype(np.float64), np.full((b.num_new_vertices, C), 1.0 / C)])
+    F[b.seed_vertex] = np.eye(C)[b.seed_class]
+    o2 = ON.step3_propagate(rp, col, w, F, g.seed_class, A0, TOL, 14)
+    print(kind, C, "packed rounds", sum(map(_is_packed, log)), "sizes", sizes.tolist(), "oracle", o2["frontier_sizes"].tolist())
+    assert s.iterations == o2["rounds"]
+    # a row that moves by almost exactly the threshold may fall on either side of it: float32 against float64
+    assert np.all(np.abs(sizes - o2["frontier_sizes"]) <= 2e-3 * np.maximum(o2["frontier_sizes"], 1000))
+    np.testing.assert_allclose(deltas, o2["max_changes"], atol=1e-6)
+    assert np.max(np.abs(soft - o2["F"])) <= ROUNDS_ATOL
+    assert soft.min() >= 0 and np.max(np.abs(soft.sum(1) - 1)) < 1e-5
+    for x, y in zip(*runs):
+        assert np.array_equal(x, y), "the order of the LDS atomics must not show"
+
+
+def test_a_part_with_most_of_the_entries_keeps_the_ordinary_rounds():
+    """A hub that holds many times a part's share of the entries: the round must not wait for one workgroup."""
+    rng = np.random.default_rng(5)
+    n = 40000
+    eu = np.concatenate([np.arange(n - 1), np.zeros(30000, dtype=np.int64), rng.integers(0, n, 4 * n)])
+    ev = np.concatenate([np.arange(1, n), rng.permutation(np.arange(2, n))[:30000], rng.integers(0, n, 4 * n)])
+    keep = eu != ev
+    rp, col, w = W.edges_to_csr(n, eu[keep], ev[keep], rng.uniform(0.1, 1, int(keep.sum())).astype(np.float32))
+    sv = rng.permutation(np.arange(1, n))[:800].astype(np.int32)
+    sc = rng.integers(0, 5, 800).astype(np.int32)
+    with P.DynLP(n, rp, col, w, 5, sv, sc) as d:
+        d.static_solve(1e-9, 6)
+        assert not any(_is_packed(r) for r in d.round_log_full())
+        soft, _ = d.get_labels()
+    seed_class = np.full(n, -1, dtype=np.int32)
+    seed_class[sv] = sc
+    F = R.initial_labels(seed_class, 5)
+    for _ in range(6):
+        F, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), F, seed_class)
+    assert np.max(np.abs(soft - F)) <= ROUNDS_ATOL
