@@ -158,6 +158,11 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  *       and same stop rule (a row leaves V_aff when it moves by <= tol), about 1.5x fewer rounds, no
  *       second label buffer traffic; which mix of old and new neighbour rows a row reads depends on
  *       scheduling, so two runs agree only within the convergence tolerance, not bit for bit.
+ *       On graphs of 32,768 updatable vertices or more with 2e-7 <= tol <= 1e-5, rounds while V_aff holds nearly
+ *       every vertex update all rows from the round-start labels and relax them (new = omega * weighted mean +
+ *       (1 - omega) * row of the round before, kept in [0, 1]): same fixed point, several times fewer rounds.  An
+ *       ordinary round over all rows follows, decides V_aff and starts the rounds described above, so that the stop
+ *       rule is the same.
  * Applies to dynlp_static_solve and dynlp_apply_batch calls that follow.
  */
 typedef enum dynlp_update_mode { DYNLP_UPDATE_SYNCHRONOUS = 0, DYNLP_UPDATE_IN_PLACE = 1 } dynlp_update_mode;
@@ -361,7 +366,8 @@ typedef struct dynlp_round_info {
                               as a binned round (scalar labels: scatter pass + gather pass, see
                               dynlp_options.binned_rounds); 4: as 2, one of several rounds run by one launch
                               (dynlp_options.persistent_rounds; ms_update is that launch's time divided by its rounds) */
-    int32_t group_lanes;   /* lanes per row the short-row kernel ran with */
+    int32_t group_lanes;   /* lanes per row the short-row kernel ran with; 0: the round read its entries in the order of the
+                              neighbours, not row by row */
 } dynlp_round_info;
 
 /*

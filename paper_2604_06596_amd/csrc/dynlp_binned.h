@@ -370,7 +370,9 @@ __global__ void __launch_bounds__(kBlock) k_pb_normalise(int bin_bits, const uns
 }
 
 // Early-exit test shared by both passes: a round runs iff the previous one ran and moved at least one row.
-__device__ inline bool pb_round_runs(const RoundCtr* __restrict__ prev) { return prev->executed && prev->any_moved != 0u; }
+__device__ inline bool pb_round_runs(const RoundCtr* __restrict__ prev, int flags) {
+    return (flags & kRoundForce) || (prev->executed && prev->any_moved != 0u);
+}
 
 // Scatter pass, one workgroup per chunk: stage[lpos[i]] = F[src[i]] (sign bit: src[i] moved in the previous round)
 // for the chunk's entries i; then the staged values of bin b (positions loff[b] .. loff[b + 1] - 1, loff = running
@@ -399,7 +401,8 @@ __global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr
                                                       const unsigned int* __restrict__ moved_prev,
                                                       const unsigned int* __restrict__ moved_also,
                                                       unsigned int* __restrict__ moved_clear, unsigned int words,
-                                                      unsigned int* __restrict__ val, RoundCtr* __restrict__ ctr_zero) {
+                                                      unsigned int* __restrict__ val, int flags,
+                                                      RoundCtr* __restrict__ ctr_zero) {
     // chunks chunk0 .. chunk0 + chunks - 1; moved_prev (and moved_also, if not NULL): the bitmaps whose bits travel
     // with the labels ("the sender moved"); moved_clear / ctr_zero may be NULL
     __shared__ unsigned int stage[kPbChunk];
@@ -427,7 +430,7 @@ __global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr
             p->rows_long = 0;
         }
     }
-    if (!pb_round_runs(prev)) return;
+    if (!pb_round_runs(prev, flags)) return;
     if (moved_clear)
         for (unsigned int w = blockIdx.x * T + threadIdx.x; w < words; w += gridDim.x * T) moved_clear[w] = 0u;
     const unsigned int per_xcd = (chunks + 7u) / 8u;
@@ -479,7 +482,7 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
                                                                const int32_t* __restrict__ len, const float* F_in,
                                                                float* F_out, const unsigned int* __restrict__ moved_prev,
                                                                unsigned int* __restrict__ moved_cur, float tol,
-                                                               RoundCtr* __restrict__ ctr) {
+                                                               int flags, float omega, RoundCtr* __restrict__ ctr) {
     constexpr int T = kPbGatherThreads;
     constexpr int NW = T / kWave;
     __shared__ unsigned int acc[1 << kPbMaxBinBits];
@@ -495,7 +498,7 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
         ctr->next_count = prev->next_count;
         ctr->next_long = prev->next_long;
     }
-    if (!pb_round_runs(prev)) return;
+    if (!pb_round_runs(prev, flags)) return;
     if (bin == 0 && threadIdx.x == 0) ctr->executed = 1;
     const int size = 1 << bin_bits;
     const int64_t first = (int64_t)bin << bin_bits;
@@ -506,7 +509,7 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
     for (int d = threadIdx.x; d < size / 32; d += T) {
         nb[d] = 0u;
         const int64_t v0 = first + (int64_t)d * 32;
-        own[d] = v0 < n_words_end ? moved_prev[v0 >> 5] : 0u;
+        own[d] = v0 < n_words_end ? (flags & kRoundAll ? ~0u : moved_prev[v0 >> 5]) : 0u;
     }
     __syncthreads();
     const unsigned int lo = bin_off[bin], hi = bin_off[bin + 1];
@@ -556,7 +559,8 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
             if (l[q] > 0) {
                 const bool in_front = ((own[d >> 5] | nb[d >> 5]) >> (d & 31)) & 1u;
                 if (in_front) {
-                    const float fn = fminf((float)acc[d] * (1.0f / kPbUnit), 1.0f);
+                    float fn = fminf((float)acc[d] * (1.0f / kPbUnit), 1.0f);
+                    if (omega != 1.f) fn = relax(fn, F_out[v], omega);
                     const float r = fabsf(fn - old[q]);
                     F_out[v] = fn;
                     big = r > tol;

@@ -83,6 +83,16 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned int sort_pad;
 };
 
+// Rounds over all updatable rows (see accelerate in dynlp.hip).  kRoundAll: every updatable row is updated, whatever moved
+// before; kRoundForce: the round runs even if its predecessor moved no row.
+constexpr int kRoundAll = 1, kRoundForce = 2;
+
+// New value of a label entry from the weighted mean of its neighbours and the row of the round before the last: one step
+// of the second-order Richardson iteration (Golub and Varga 1961), kept inside [0, 1] like every label.  omega = 1: the mean.
+__device__ inline float relax(float mean, float before, float omega) {
+    return fminf(fmaxf(omega * mean + (1.f - omega) * before, 0.f), 1.f);
+}
+
 enum ValidationError : int {
     kErrNone = 0,
     kErrRowPtr = 1,

@@ -441,6 +441,7 @@ __device__ inline unsigned int flush_round_counters(float rmax, unsigned long lo
 //            are in V_aff: u is updated iff u or one of its neighbours moved by more than tol in the previous
 //            round (bitmap moved_prev) - Alg. 2 Step 3's V_aff, evaluated where the row is read anyway.  A row
 //            outside V_aff is copied to F_out when that is another buffer, so the two keep agreeing there.
+//            flags / omega: rounds over all rows (kRoundAll) that relax (F_out then holds the rows of the round before).
 constexpr int kRowByVertex = 1, kRowLazy = 2;
 
 template <int CP, int G, bool STAGED, bool PULL = false, bool COH = false>
@@ -450,7 +451,7 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
                                         float* F_out, int by_vertex, uint8_t* __restrict__ flag,
                                         unsigned int* __restrict__ moved, float tol,
                                         RoundCtr* __restrict__ ctr,
-                                        const unsigned int* moved_prev = nullptr) {
+                                        const unsigned int* moved_prev = nullptr, int flags = 0, float omega = 1.f) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int GPB = kBlock / G;
@@ -467,7 +468,7 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         const RowMeta m = meta[u];
         const Edge* __restrict__ row = pool + m.off;
         if (PULL) {
-            bool in_front = moved_bit_c<COH>(moved_prev, u);
+            bool in_front = (flags & kRoundAll) || moved_bit_c<COH>(moved_prev, u);
             for (int base = 0; base < m.len && !in_front; base += G) {  // uniform in the group
                 const int idx = base + gl;
                 const bool hit = idx < m.len && moved_bit_c<COH>(moved_prev, row[idx].col);
@@ -491,11 +492,13 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         e.w = 0.f;
         accumulate_row<CP, G, COH>(row, m.len, 0, 1, u, F_in, gl, acc, s, e);
         const Vec<VEC> old = load_row<VEC, COH>(F_in + (size_t)u * CP + chunk * VEC);
-        Vec<VEC> fn;
+        Vec<VEC> fn, before = old;
         float r = 0.f;
+        if (PULL && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
             fn.v[k] = acc.v[k] / s;
+            if (PULL && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
             if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
             r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
         }
@@ -546,7 +549,7 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
                                        float* F_out, int by_vertex, uint8_t* __restrict__ flag,
                                        unsigned int* __restrict__ moved, float tol,
                                        RoundCtr* __restrict__ ctr,
-                                       const unsigned int* moved_prev = nullptr) {
+                                       const unsigned int* moved_prev = nullptr, int flags = 0, float omega = 1.f) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int G = LPN > 16 ? LPN : 16;
@@ -568,7 +571,7 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
         const RowMeta m = meta[u];
         const Edge* __restrict__ row = pool + m.off;
         if (PULL) {  // every decision below is uniform across the workgroup
-            bool in_front = moved_bit_c<COH>(moved_prev, u);
+            bool in_front = (flags & kRoundAll) || moved_bit_c<COH>(moved_prev, u);
             for (int base = 0; base < m.len && !in_front; base += kBlock) {
                 const int idx = base + (int)threadIdx.x;
                 in_front = __syncthreads_or(idx < m.len && moved_bit_c<COH>(moved_prev, row[idx].col)) != 0;
@@ -605,11 +608,13 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
                 st += part_s[q];
             }
             const Vec<VEC> old = load_row<VEC, COH>(F_in + (size_t)u * CP + chunk * VEC);
-            Vec<VEC> fn;
+            Vec<VEC> fn, before = old;
             float r = 0.f;
+            if (PULL && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {
                 fn.v[k] = tot.v[k] / st;
+                if (PULL && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
                 if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
                 r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
             }
@@ -725,8 +730,8 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
                                                            float* F_out, const unsigned int* __restrict__ moved_prev,
                                                            unsigned int* __restrict__ moved_cur,
                                                            unsigned int* __restrict__ moved_clear, unsigned int words,
-                                                           float tol, RoundCtr* __restrict__ ctr,
-                                                           RoundCtr* __restrict__ ctr_zero) {
+                                                           float tol, int flags, float omega,
+                                                           RoundCtr* __restrict__ ctr, RoundCtr* __restrict__ ctr_zero) {
     if (ctr_zero && blockIdx.x == 0) {
         if (threadIdx.x == 0) {
             ctr_zero->next_count = 0;
@@ -748,16 +753,16 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
     }
     // did the previous round move a row?  (one word of its header instead of its 32 partial records: thousands of
     // short-lived workgroups each reading 32 lines was a fifth of the launch on a 100K-vertex graph)
-    if (!prev->executed || prev->any_moved == 0u) return;
+    if (!(flags & kRoundForce) && (!prev->executed || prev->any_moved == 0u)) return;
     for (unsigned int w = blockIdx.x * kBlock + threadIdx.x; w < words; w += gridDim.x * kBlock) moved_clear[w] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctr->executed = 1;
     const unsigned int long_blocks = nl < long_blocks_max ? nl : long_blocks_max;
     if (blockIdx.x < long_blocks)
         row_update_long<CP, false, true>(blockIdx.x, long_blocks, back, nl, ns, meta, pool, F_in, F_out, 1, nullptr,
-                                         moved_cur, tol, ctr, moved_prev);
+                                         moved_cur, tol, ctr, moved_prev, flags, omega);
     else
         row_update_short<CP, G, false, true>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool,
-                                             F_in, F_out, 1, nullptr, moved_cur, tol, ctr, moved_prev);
+                                             F_in, F_out, 1, nullptr, moved_cur, tol, ctr, moved_prev, flags, omega);
 }
 
 // =================================================================================================

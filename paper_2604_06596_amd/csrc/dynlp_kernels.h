@@ -906,4 +906,41 @@ __global__ void __launch_bounds__(kBlock) k_export_rows(int64_t n, const RowMeta
     }
 }
 
+// Every step-th updatable row (list: short rows from the front, long rows from the back): out[0] += weight of its edges to
+// labelled vertices, out[1] += weight of all its edges.  16 lanes per row.
+__global__ void __launch_bounds__(kBlock) k_labelled_share(unsigned int ns, unsigned int nl, unsigned int step,
+                                                          const int32_t* __restrict__ front, const int32_t* __restrict__ back,
+                                                          const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                                          const int32_t* __restrict__ seed_class, float* __restrict__ out) {
+    __shared__ float sm[2][kBlock / kWave];
+    const unsigned long long pos = (unsigned long long)((blockIdx.x * kBlock + threadIdx.x) / 16u) * step;
+    float labelled = 0.f, all = 0.f;
+    if (pos < (unsigned long long)ns + nl) {
+        const int32_t u = pos < ns ? front[pos] : back[-(long long)(pos - ns)];
+        const RowMeta m = meta[u];
+        for (int j = (int)(threadIdx.x & 15u); j < m.len; j += 16) {
+            const Edge e = pool[m.off + j];
+            all += e.w;
+            if (seed_class[e.col] >= 0) labelled += e.w;
+        }
+    }
+    labelled = wave_sum(labelled);
+    all = wave_sum(all);
+    if (lane_id() == 0) {
+        sm[0][threadIdx.x / kWave] = labelled;
+        sm[1][threadIdx.x / kWave] = all;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBlock / kWave; ++i) {
+            labelled += sm[0][i];
+            all += sm[1][i];
+        }
+        if (all > 0.f) {
+            atomicAdd(&out[0], labelled);
+            atomicAdd(&out[1], all);
+        }
+    }
+}
+
 }  // namespace dynlp

@@ -20,9 +20,9 @@
 // its entries cost): a wave reads 64 entries with one load, hands them round with shuffles, LANES lanes read one
 // neighbour row, multiply it by w / deg and add it to the row's sums in LDS.
 //
-// The sums are 32-bit fixed-point numbers (unit 2^-30; the terms w / deg * F of a row add up to at most 1): integer
+// The sums are 32-bit fixed-point numbers (unit 2^-31; the terms w / deg * F of a row add up to at most 1): integer
 // additions commute, so a round is bit-reproducible although the order of the LDS atomics is not.  Rounding a term to
-// 2^-31 is finer than the float32 sum of the ordinary row update.
+// 2^-32 is finer than the float32 sum of the ordinary row update.
 //
 // Bound: the vector memory path of the CUs (a line of 128 bytes per gather through the L1; leaving out the LDS atomics
 // changes nothing, leaving out the gathers takes away half).  One round over all rows, row update -> packed round, us:
@@ -45,10 +45,10 @@ constexpr int kPkLds = 160 * 1024;     // LDS of one workgroup, everything inclu
 constexpr int kPkFixedLds = 1024;      // of it: reductions at the end of the kernel (static arrays)
 constexpr unsigned int kPkWindow = 2688;  // entries between barriers (see k_pk_round)
 constexpr int kPkBuckets = 512;        // ranges of neighbour ids a part's entries are ordered by
-constexpr float kPkUnit = 1073741824.0f;  // 2^30
+constexpr float kPkUnit = 2147483648.0f;  // 2^31: a row of ones sums to 2^31 and a few units, far from 2^32
 
 // One entry of the packed stream: receiving row (offset in its part) << col_bits | neighbour, and
-// w / deg(row) * 2^30.
+// w / deg(row) * 2^31.
 struct __attribute__((aligned(8))) PkEntry {
     unsigned int at;
     float wn;
@@ -107,17 +107,11 @@ __device__ inline void clear_round_slot(RoundCtr* slot) {  // called by one work
     }
 }
 
-// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0; the same as one bit per vertex.
+// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0.
 __global__ void __launch_bounds__(kBlock) k_pk_receivers(int64_t n, const RowMeta* __restrict__ meta,
-                                                        const int32_t* __restrict__ seed_class,
-                                                        int32_t* __restrict__ len, unsigned int* __restrict__ upd) {
+                                                        const int32_t* __restrict__ seed_class, int32_t* __restrict__ len) {
     const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int l = 0;
-    if (v < n && seed_class[v] < 0) l = meta[v].len;
-    if (v < n) len[v] = l;
-    const unsigned long long b = __ballot(l > 0);
-    const int lane = lane_id();
-    if ((lane == 0 || lane == 32) && v < ((n + 31) & ~(int64_t)31)) upd[v >> 5] = (unsigned int)(lane == 0 ? b : b >> 32);
+    if (v < n) len[v] = seed_class[v] < 0 ? meta[v].len : 0;
 }
 
 // part_total[p] = the entries of the updatable rows of part p; *largest = the largest part.
@@ -221,7 +215,6 @@ struct PkRound {
     const PkEntry* ent;
     const unsigned int* start;  // per part: its first entry; the last word: the number of entries
     const int32_t* len;
-    const unsigned int* upd;
     const RowMeta* meta;
     const Edge* pool;
     const float* F_in;
@@ -231,6 +224,8 @@ struct PkRound {
     unsigned int* moved_clear;
     unsigned int words;
     float tol;
+    int flags;    // kRoundAll, kRoundForce
+    float omega;  // relaxation; 1: none, else F_out holds the rows of the round before the last
 };
 
 // One round.  V_aff is decided per row as in k_row_update_pull: u is in it iff u or a neighbour moved in the previous
@@ -273,7 +268,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
     PkEntry e[TILES];
 #pragma unroll
     for (int q = 0; q < TILES; ++q) e[q] = pk_load_entry(ent, own + q * TILE * (unsigned int)sizeof(PkEntry));
-    if (!a.prev->executed || a.prev->any_moved == 0u) return;
+    if (!(a.flags & kRoundForce) && (!a.prev->executed || a.prev->any_moved == 0u)) return;
 #pragma unroll 1
     for (unsigned int w = blockIdx.x * T + threadIdx.x; w < a.words; w += gridDim.x * T) a.moved_clear[w] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->executed = 1;
@@ -289,12 +284,12 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
     for (int i = threadIdx.x; i < a.rows * a.stride; i += T) acc[i] = 0u;
 #pragma unroll 1
     for (int w = threadIdx.x; w < nwords; w += T) {
-        in[w] = a.moved_prev[(base >> 5) + w] & a.upd[(base >> 5) + w];
+        in[w] = a.flags & kRoundAll ? ~0u : a.moved_prev[(base >> 5) + w];
         mv[w] = 0u;
     }
     __syncthreads();
     // rows that did not move themselves: 16 lanes look their neighbours up until one that moved is found
-    {
+    if (!(a.flags & kRoundAll)) {
         const int gl = threadIdx.x & 15;
 #pragma unroll 1
         for (int r = threadIdx.x >> 4; r < nr; r += T / 16) {
@@ -393,11 +388,13 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
                 if (a.F_out != a.F_in) store_vec<VEC>(out, old[q]);
                 continue;
             }
-            Vec<VEC> fn;
+            Vec<VEC> fn, before = old[q];
             float d = 0.f;
+            if (a.omega != 1.f) before = load_vec<VEC>(out);
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {
                 fn.v[k] = k < cols ? fminf((float)acc[r * a.stride + chunk * VEC + k] * (1.0f / kPkUnit), 1.0f) : 0.f;
+                if (a.omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], a.omega);
                 d = fmaxf(d, fabsf(fn.v[k] - old[q].v[k]));
             }
 #pragma unroll

@@ -2,7 +2,7 @@
 neighbour id, sums of a part's rows in LDS): sweeps of the static solve and the rounds of a batch against the oracle,
 for every way a label row is read (1 to 16 lanes, odd column counts, the scalar layout), odd sizes and hub rows.
 
-Tolerances: one round rounds each term w / d * F to 2^-31 and w / d to float32, less than the 1e-6 that a float32 round
+Tolerances: one round rounds each term w / d * F to 2^-32 and w / d to float32, less than the 1e-6 that a float32 round
 is allowed; the bars of the ordinary rounds (test_gpu_parity) apply.
 """
 import numpy as np
@@ -48,14 +48,14 @@ def test_packed_rounds_match_the_oracle(kind, n, C, deg, scalar):
     g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
     rp, col, w = g.csr()
     F = R.initial_labels(g.seed_class, C)
-    for _ in range(12):
+    for _ in range(20):
         F, _ = ON.itlp_sweep(rp, col, w, F, g.seed_class)
     runs = []
     for _ in range(2):
         with _make(p0, binary_scalar=scalar) as d:
-            st, s = d.static_solve(1e-9, 12)
-            assert st == 1 and s.iterations == 12
-            assert [_is_packed(r) for r in d.round_log_full()] == [False] + [True] * 11
+            st, s = d.static_solve(1e-9, 20)
+            assert st == 1 and s.iterations == 20
+            assert [_is_packed(r) for r in d.round_log_full()] == [False] * 8 + [True] * 12
             cold, _ = d.get_labels()
             d.static_solve(TOL, 20000)
             soft0, _ = d.get_labels()
@@ -96,12 +96,12 @@ def test_a_part_with_most_of_the_entries_keeps_the_ordinary_rounds():
     sv = rng.permutation(np.arange(1, n))[:800].astype(np.int32)
     sc = rng.integers(0, 5, 800).astype(np.int32)
     with P.DynLP(n, rp, col, w, 5, sv, sc) as d:
-        d.static_solve(1e-9, 6)
+        d.static_solve(1e-9, 14)
         assert not any(_is_packed(r) for r in d.round_log_full())
         soft, _ = d.get_labels()
     seed_class = np.full(n, -1, dtype=np.int32)
     seed_class[sv] = sc
     F = R.initial_labels(seed_class, 5)
-    for _ in range(6):
+    for _ in range(14):
         F, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), F, seed_class)
     assert np.max(np.abs(soft - F)) <= ROUNDS_ATOL

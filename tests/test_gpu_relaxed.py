@@ -1,0 +1,122 @@
+"""GPU tests of the relaxed rounds of the in-place mode (graphs of 32,768 updatable vertices or more, tight thresholds):
+whatever kernel runs them (packed rounds, row update, binned rounds), a static solve and a batch end under the same stop
+rule as without them, at labels within the same certificate of the exact ones, in fewer rounds than the synchronous mode;
+a round cap inside the phase leaves labels in [0, 1]; components that never settle by relaxation do not keep the call.
+"""
+import numpy as np
+import pytest
+
+import certify as Cf
+import workloads as W
+from oracle import reference as R
+import paper_2604_06596_amd as P
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+
+
+def _make(p, mode=P.UPDATE_IN_PLACE, **kw):
+    d = P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, **kw)
+    d.set_update_mode(mode)
+    return d
+
+
+def _problem(kind, C):
+    if kind == "hub":
+        return W.chung_lu(40000, C, 30.0, 2.1, 1200, 0.8, 0.02, 77 + C)
+    return W.sbm(36011, C, 16.0, 8.0, 0.02, 78 + C)
+
+
+def _check(soft, hard, g, bar, what):
+    rp, col, w = g.csr()
+    exact, moved = Cf.exact_labels(rp, col, w, g.seed_class, g.C)
+    cert = Cf.certificate(rp, col, w, g.seed_class, soft)
+    Cf.check_against_exact(soft, exact, moved, cert, what)
+    Cf.check_hard(hard, exact, cert)
+    assert cert.res <= bar
+    assert soft.min() >= 0 and soft.max() <= 1 and np.max(np.abs(soft.sum(1) - 1)) < 2e-5
+    return cert
+
+
+@pytest.mark.parametrize("kind,C,kw,kernel", [
+    ("sbm", 10, {}, "packed"), ("sbm", 3, {}, "packed"), ("hub", 20, {}, "packed"), ("hub", 50, dict(group_lanes=16), "rows"),
+    ("sbm", 10, dict(group_lanes=32), "rows"), ("sbm", 2, dict(binary_scalar=True), "packed"),
+    ("sbm", 2, dict(binary_scalar=True, binned_rounds=9), "binned")])
+def test_static_solve_and_batch_end_under_the_same_stop_rule(kind, C, kw, kernel):
+    p, p0 = _problem(kind, C), _problem(kind, C)
+    b = W.chung_lu_vertex_batch(p, 1500, 0.02) if kind == "hub" else W.sbm_vertex_batch(p, 1500, 16, 0.02)
+    g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
+    iterations = {}
+    for mode in (P.UPDATE_SYNCHRONOUS, P.UPDATE_IN_PLACE):
+        g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
+        with _make(p0, mode, **kw) as d:
+            st, s = d.static_solve(TOL, 20000)
+            assert st == 0 and s.converged == 1 and s.final_max_delta <= TOL
+            cold = s.iterations
+            soft, hard = d.get_labels()
+            _check(soft, hard, g, Cf.stop_rule_residual(TOL), f"{kind} {C} static")
+            st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            assert st == 0 and s.converged == 1
+            soft, hard = d.get_labels()
+            log = d.round_log_full()
+            assert s.iterations == len(log) and s.rows_updated == sum(r.rows_short + r.rows_long for r in log)
+            assert s.edges_traversed == sum(r.entries_short + r.entries_long for r in log)
+        g.insert(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        _check(soft, hard, g, Cf.local_stop_residual(TOL, s.iterations, Cf.stop_rule_residual(TOL)), f"{kind} {C} batch")
+        iterations[mode] = (cold, s.iterations)
+        if mode == P.UPDATE_IN_PLACE:
+            dense = [r for r in log if r.staged in (2, 3)]
+            assert len(dense) > 8, "the case is meant to reach relaxed rounds"
+            how = {"packed": (2, True), "rows": (2, False), "binned": (3, False)}[kernel]
+            assert all((r.staged, r.group_lanes == 0) == how for r in dense)
+    print(kind, C, kernel, "sweeps and rounds, synchronous", iterations[P.UPDATE_SYNCHRONOUS], "in place", iterations[P.UPDATE_IN_PLACE])
+    assert iterations[P.UPDATE_IN_PLACE][0] < iterations[P.UPDATE_SYNCHRONOUS][0]
+
+
+@pytest.mark.parametrize("cap", [1, 2, 9, 10, 24])
+def test_a_round_cap_inside_the_phase(cap):
+    p, p0 = _problem("sbm", 10), _problem("sbm", 10)
+    b = W.sbm_vertex_batch(p, 3000, 16, 0.02)
+    with _make(p0) as d:
+        st, s = d.static_solve(TOL, cap)
+        assert st == 1 and s.iterations == cap and s.converged == 0
+        d.static_solve(TOL, 20000)
+        d.set_params(TOL, cap)
+        st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        assert st == 1 and s.iterations == cap and len(d.round_log()[0]) == cap
+        soft, hard = d.get_labels()
+        assert soft.min() >= 0 and soft.max() <= 1 and np.array_equal(hard, np.argmax(soft, 1))
+        d.set_params(TOL, 20000)  # an empty batch keeps what is there: V_aff is empty
+        assert d.apply_batch(0, None, None, None)[0] == 0
+        assert d.static_solve(TOL, 20000)[0] == 0
+
+
+def test_components_without_a_label_do_not_keep_the_call():
+    """Half of the graph lies in bipartite components without a labelled vertex whose rows start uneven (their labels were
+    deleted): eigenvalues 1 and -1, which relaxation does not damp.  The labelled half must still converge, and the call
+    must end as it does for rows updated in place."""
+    rng = np.random.default_rng(11)
+    p = _problem("sbm", 4)
+    m = 40000  # ladder of 20,000 + 20,000 vertices, edges only between the sides
+    left, right = p.n + np.arange(m // 2), p.n + m // 2 + np.arange(m // 2)
+    rows = np.repeat(np.arange(p.n), np.diff(p.row_ptr))
+    up = rows < p.col
+    eu = np.concatenate([rows[up], np.repeat(left, 6)])
+    ev = np.concatenate([p.col[up], rng.choice(right, 6 * (m // 2))])
+    ew = np.concatenate([p.w[up], rng.uniform(0.1, 1, 6 * (m // 2)).astype(np.float32)]).astype(np.float32)
+    rp, col, w = W.edges_to_csr(p.n + m, eu, ev, ew)
+    extra = rng.permutation(np.concatenate([left, right]))[:1500].astype(np.int32)
+    sv = np.concatenate([p.seed_vertex, extra]).astype(np.int32)
+    sc = np.concatenate([p.seed_class, rng.integers(0, 4, extra.size)]).astype(np.int32)
+    with P.DynLP(p.n + m, rp, col, w, 4, sv, sc) as d:
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        assert d.static_solve(TOL, 20000)[0] == 0
+        st, s = d.apply_update(extra)
+        assert st == 0 and s.iterations < 5000
+        soft, hard = d.get_labels()
+        erp, ecol, ew_, _, esc = d.export_graph()
+    cert = Cf.certificate(erp, ecol, ew_, esc, soft)
+    exact, moved = Cf.exact_labels(erp, ecol, ew_.astype(np.float64), esc, 4)
+    Cf.check_against_exact(soft, exact, moved, cert, "labelled half")
+    assert soft.min() >= 0 and soft.max() <= 1
