@@ -726,7 +726,8 @@ void launch_update_pull_inst(dynlp_ctx* c, const Frontier& universe, const PullR
     const unsigned int short_blocks =
         (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div((int64_t)universe.ns, GPB), cap));
     const unsigned int long_max = (unsigned int)std::min<int64_t>((int64_t)universe.nl, cap / 2);
-    hipLaunchKernelGGL((k_row_update_pull<CP, G>), dim3(short_blocks + long_max), dim3(kBlock), 0, c->stream, a.prev, long_max,
+    auto kernel = a.flags & kRoundAll ? k_row_update_pull<CP, G, true> : k_row_update_pull<CP, G, false>;
+    hipLaunchKernelGGL(kernel, dim3(short_blocks + long_max), dim3(kBlock), 0, c->stream, a.prev, long_max,
                        universe.front, universe.back, universe.ns, universe.nl, c->meta, c->pool, a.F_in, a.F_out,
                        a.moved_prev, a.moved_cur, a.moved_clear, (unsigned int)c->moved_words, a.tol, a.flags, a.omega, a.ctr,
                        a.ctr_zero);
@@ -764,6 +765,71 @@ void launch_update_pull(dynlp_ctx* c, int G, const Frontier& universe, const Pul
         case 16: launch_update_pull_cp<16>(c, G, universe, a); break;
         case 32: launch_update_pull_cp<32>(c, G, universe, a); break;
         default: launch_update_pull_cp<64>(c, G, universe, a); break;
+    }
+    HIPCHK(c, hipGetLastError());
+    close_timed_span(c, e1);
+}
+
+// ---- many rounds over a small V_aff in one launch (k_tail_rounds) -----------------------------------------------
+// One CU gathers about 0.4 rows per clock and looks up every neighbour it marks; the launches of an ordinary round take
+// 12 to 14 us whatever their size.  Measured per round: 3,000 vertices with one label column, up to 886 rows and 6,000
+// entries, 15 -> 8 us (whole batch 534 -> 436 us); 24,000 vertices with 5 columns, rounds of 4,000 to 8,000 entries, 12 ->
+// 16 us: the limits depend on the columns.  A launch pays when it runs several rounds, so a V_aff that is about to outgrow
+// the limits (every row may bring its neighbours) is left to ordinary rounds.
+constexpr int kTailRounds = 32;
+
+void tail_limits(const dynlp_ctx* c, unsigned int* rows, unsigned int* entries) {
+    *rows = c->CP <= 2 ? 1024 : c->CP <= 16 ? 512 : 256;
+    *entries = c->CP <= 2 ? 8192 : c->CP <= 16 ? 3072 : 1536;
+}
+
+bool tail_rounds_pay(const dynlp_ctx* c, unsigned int known, unsigned int before, double avg_len) {
+    unsigned int rows, entries;
+    tail_limits(c, &rows, &entries);
+    if (known > rows || (double)known * avg_len > (double)entries) return false;
+    return before >= known || (double)known * avg_len <= (double)rows;
+}
+
+template <int CP>
+void launch_tail_cp(dynlp_ctx* c, int G, const TailArgs& a) {
+    if constexpr (CP <= 4) {
+        if (G == 4) {
+            hipLaunchKernelGGL((k_tail_rounds<CP, 4>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_tail_rounds<CP, 16>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
+}
+
+// Rounds [round, round + count) at most; the list of the first one is that of parity `cur`.
+void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vertex) {
+    TailArgs a{};
+    a.ring = c->ring;
+    a.t0 = round;
+    a.rounds = count;
+    for (int i = 0; i < 2; ++i) {
+        const Frontier f = frontier_of(c, cur ^ i);
+        a.front[i] = f.front;
+        a.back[i] = f.back;
+    }
+    a.meta = c->meta;
+    a.pool = c->pool;
+    a.seed_class = c->seed_class;
+    a.F = c->F;
+    a.staged = c->F2;
+    a.by_vertex = by_vertex;
+    a.flag = c->flag;
+    a.tol = c->tol;
+    tail_limits(c, &a.max_rows, &a.max_entries);
+    hipEvent_t e1 = open_timed_span(c, round, count);
+    switch (c->CP) {
+        case 1: launch_tail_cp<1>(c, G, a); break;
+        case 2: launch_tail_cp<2>(c, G, a); break;
+        case 4: launch_tail_cp<4>(c, G, a); break;
+        case 8: launch_tail_cp<8>(c, G, a); break;
+        case 16: launch_tail_cp<16>(c, G, a); break;
+        case 32: launch_tail_cp<32>(c, G, a); break;
+        default: launch_tail_cp<64>(c, G, a); break;
     }
     HIPCHK(c, hipGetLastError());
     close_timed_span(c, e1);
@@ -1087,7 +1153,7 @@ bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan*
     if (c->group_lanes != 0 || (c->CP == 1 && c->binned != 0) || universe.size() < kPackedMinRows || c->entries >= ((int64_t)1 << 31)) return false;
     // parts: as many generations of one workgroup per CU as the sums need, of equal size
     const int row_bits8 = packed_stride(c) * 32 + 2;  // bits of LDS per row: the sums, "in V_aff", "moved"
-    const int64_t rows_max = (int64_t)(kPkLds - kPkFixedLds) * 8 / row_bits8 / 32 * 32;
+    const int64_t rows_max = std::min<int64_t>((int64_t)(kPkLds - kPkFixedLds) * 8 / row_bits8 / 32 * 32, kPkMaxRows);
     const int64_t wide = c->num_cu;
     const int64_t gens = ceil_div(c->n, wide * rows_max);
     const int64_t rows = round_up(ceil_div(c->n, wide * gens), 32);
@@ -1177,9 +1243,14 @@ bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
     c->pk_parts = plan.parts;
     c->pk_bits = plan.col_bits;
     if (ok) {
-        const hipError_t e = packed_kernel(c, [&](auto kernel) {
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)packed_lds(c));
+        // always the same value: the attribute belongs to the kernel, not to this context
+        hipError_t e = packed_kernel(c, [&](auto kernel) {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kPkLds - kPkFixedLds);
         });
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pk_place), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (kPkMaxRows + 1) * (int)sizeof(unsigned int));
         if (e != hipSuccess) {
             (void)hipGetLastError();
             ok = false;
@@ -1201,7 +1272,7 @@ bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
     HIPCHK(c, hipMemcpyAsync(&most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if ((double)most > kPackedUneven * (double)ent / (double)parts) return false;
-    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), 0, c->stream, c->n, plan.rows, plan.col_bits,
+    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), (size_t)(plan.rows + 1) * 4, c->stream, c->n, plan.rows, plan.col_bits,
                        plan.bucket_bits, c->meta, c->pool, c->pk_len, c->deg, start, c->pk_ent);
     HIPCHK(c, hipGetLastError());
     c->pk_built = true;
@@ -1425,7 +1496,7 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
     {
         float* d_sums = reinterpret_cast<float*>(&c->bc->scan_total);
         HIPCHK(c, hipMemsetAsync(d_sums, 0, sizeof sums, c->stream));
-        const unsigned int step = std::max(1u, universe.size() / 32768u);
+        const unsigned int step = std::max(1u, universe.size() / 8192u);
         hipLaunchKernelGGL(k_labelled_share, dim3(grid_for((int64_t)(universe.size() / step + 1) * 16)), dim3(kBlock), 0, c->stream,
                            universe.ns, universe.nl, step, universe.front, universe.back, c->meta, c->pool, c->seed_class, d_sums);
         HIPCHK(c, hipGetLastError());
@@ -2482,6 +2553,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         const int64_t frontier_initial = known;
         int64_t peak = known, rows = 0, edges = 0;
         int it = 0, cur = 0;  // round `it` reads the frontier of parity `cur`
+        unsigned int known_before = 0;  // |V_aff| when the chain before was queued
         float last = 0.f;
         double avg_len = c->n > 0 ? (double)c->entries / (double)c->n : 1.0;
         bool pingpong = false;
@@ -2587,13 +2659,23 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // a stretch of short rounds runs many rounds per launch (k_rounds_persistent); its first round, which still
             // works on a frontier list, is an ordinary launch
             const bool persist = pingpong && fused && !binned && persistent_rounds_pay(c, universe);
-            const int r = std::min<int>(persist ? kPersistRounds : kChain, c->max_iter - it);
+            // (callers who fix the lanes per row or ask for binned rounds get them; rows so long that they are worth more
+            // than 16 lanes do not come in numbers that one CU should handle)
+            const bool tail = !pingpong && c->group_lanes == 0 && G <= 16 && !(can_bin && c->binned > 0) &&
+                              tail_rounds_pay(c, known, known_before, avg_len);
+            // where every row that is affected now may bring its neighbours and V_aff then holds nearly every vertex, the
+            // first chain is short: the relaxed rounds over all rows that follow cost half a flag-marking round
+            const bool short_first = it == 0 && !pingpong && relaxed_rounds_pay(c, universe, c->tol) &&
+                                     (double)known * avg_len >= (double)universe.size();
+            const int r = std::min<int>(persist ? kPersistRounds : tail ? kTailRounds : short_first ? 2 : kChain, c->max_iter - it);
             const size_t first_pair = c->events_used / 2;
             // ping-pong: round it+i reads buf[i & 1], writes buf[(i + 1) & 1]; in place: always F
             float* const buf[2] = {c->F, in_place ? c->F : c->F2};
             bool persist_launched = false;
             int persist_first = r;  // chain position of the first round that ran inside a persistent launch
-            for (int i = 0; i < r; ++i) {
+            known_before = known;
+            if (tail) launch_tail(c, G, cur, it, r, (in_place ? kRowByVertex : 0) | (lazy ? kRowLazy : 0));
+            for (int i = 0; i < (tail ? 0 : r); ++i) {
                 const int t = it + i;
                 RoundCtr* slot = slot_of(c, t);
                 const Frontier f = frontier_of(c, cur);
@@ -2708,6 +2790,10 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // a persistent launch that gave up at a barrier stops short without V_aff being empty
             const bool cut_short = persist_launched && executed < r && executed > 0 && c->h_slot[executed - 1].changed != 0u;
             it += executed;
+            if (tail) {
+                cur ^= executed & 1;
+                continue;  // V_aff is empty, has outgrown the launch, or the launch has run all its rounds
+            }
             if (cut_short) continue;
             if (executed < r) known = 0;  // a round found V_aff empty
         }

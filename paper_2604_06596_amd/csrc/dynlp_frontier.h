@@ -441,17 +441,17 @@ __device__ inline unsigned int flush_round_counters(float rmax, unsigned long lo
 //            are in V_aff: u is updated iff u or one of its neighbours moved by more than tol in the previous
 //            round (bitmap moved_prev) - Alg. 2 Step 3's V_aff, evaluated where the row is read anyway.  A row
 //            outside V_aff is copied to F_out when that is another buffer, so the two keep agreeing there.
-//            flags / omega: rounds over all rows (kRoundAll) that relax (F_out then holds the rows of the round before).
+//   RELAX (with PULL): every listed row is updated, and relaxed by omega (F_out then holds the rows of the round before).
 constexpr int kRowByVertex = 1, kRowLazy = 2;
 
-template <int CP, int G, bool STAGED, bool PULL = false, bool COH = false>
+template <int CP, int G, bool STAGED, bool PULL = false, bool COH = false, bool RELAX = false>
 __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ front,
                                         unsigned int ns, const RowMeta* __restrict__ meta,
                                         const Edge* __restrict__ pool, const float* F_in,
                                         float* F_out, int by_vertex, uint8_t* __restrict__ flag,
                                         unsigned int* __restrict__ moved, float tol,
                                         RoundCtr* __restrict__ ctr,
-                                        const unsigned int* moved_prev = nullptr, int flags = 0, float omega = 1.f) {
+                                        const unsigned int* moved_prev = nullptr, float omega = 1.f) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int GPB = kBlock / G;
@@ -468,7 +468,7 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         const RowMeta m = meta[u];
         const Edge* __restrict__ row = pool + m.off;
         if (PULL) {
-            bool in_front = (flags & kRoundAll) || moved_bit_c<COH>(moved_prev, u);
+            bool in_front = RELAX || moved_bit_c<COH>(moved_prev, u);
             for (int base = 0; base < m.len && !in_front; base += G) {  // uniform in the group
                 const int idx = base + gl;
                 const bool hit = idx < m.len && moved_bit_c<COH>(moved_prev, row[idx].col);
@@ -490,15 +490,16 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         Edge e;
         e.col = u;
         e.w = 0.f;
+        // asked for before the neighbours' rows, so that the row does not wait for one more read at its end
         accumulate_row<CP, G, COH>(row, m.len, 0, 1, u, F_in, gl, acc, s, e);
         const Vec<VEC> old = load_row<VEC, COH>(F_in + (size_t)u * CP + chunk * VEC);
         Vec<VEC> fn, before = old;
         float r = 0.f;
-        if (PULL && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
+        if (RELAX && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
             fn.v[k] = acc.v[k] / s;
-            if (PULL && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
+            if (RELAX && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
             if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
             r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
         }
@@ -542,14 +543,14 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
 // Long rows: one workgroup per row (body; k_row_update dispatches to it).  Its kBlock/G groups take the row's chunks round-robin; their
 // partial sums meet in LDS and are added in group order (a fixed order: results do not depend on
 // timing).  Position of long row j is pos_base + j.
-template <int CP, bool STAGED, bool PULL = false, bool COH = false>
+template <int CP, bool STAGED, bool PULL = false, bool COH = false, bool RELAX = false>
 __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ back,
                                        unsigned int nl, unsigned int pos_base, const RowMeta* __restrict__ meta,
                                        const Edge* __restrict__ pool, const float* F_in,
                                        float* F_out, int by_vertex, uint8_t* __restrict__ flag,
                                        unsigned int* __restrict__ moved, float tol,
                                        RoundCtr* __restrict__ ctr,
-                                       const unsigned int* moved_prev = nullptr, int flags = 0, float omega = 1.f) {
+                                       const unsigned int* moved_prev = nullptr, float omega = 1.f) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int G = LPN > 16 ? LPN : 16;
@@ -571,7 +572,7 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
         const RowMeta m = meta[u];
         const Edge* __restrict__ row = pool + m.off;
         if (PULL) {  // every decision below is uniform across the workgroup
-            bool in_front = (flags & kRoundAll) || moved_bit_c<COH>(moved_prev, u);
+            bool in_front = RELAX || moved_bit_c<COH>(moved_prev, u);
             for (int base = 0; base < m.len && !in_front; base += kBlock) {
                 const int idx = base + (int)threadIdx.x;
                 in_front = __syncthreads_or(idx < m.len && moved_bit_c<COH>(moved_prev, row[idx].col)) != 0;
@@ -602,6 +603,8 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
 #pragma unroll
             for (int k = 0; k < VEC; ++k) tot.v[k] = 0.f;
             float st = 0.f;
+            constexpr int UQ = CP >= 32 ? 4 : NG;  // all partial sums of wide rows at once would cost half the waves
+#pragma unroll UQ
             for (int q = 0; q < NG; ++q) {
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) tot.v[k] += part[q][chunk * VEC + k];
@@ -610,11 +613,11 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
             const Vec<VEC> old = load_row<VEC, COH>(F_in + (size_t)u * CP + chunk * VEC);
             Vec<VEC> fn, before = old;
             float r = 0.f;
-            if (PULL && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
+            if (RELAX && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {
                 fn.v[k] = tot.v[k] / st;
-                if (PULL && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
+                if (RELAX && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
                 if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
                 r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
             }
@@ -721,7 +724,9 @@ __global__ void __launch_bounds__(kBlock) k_row_update(const RoundCtr* __restric
 // (front, back, ns, nl) is the list of all updatable vertices; moved_prev has the bits of the rows that moved
 // in the previous round, moved_cur receives this round's, moved_clear (the bitmap of the round after) is
 // zeroed.  The round does nothing if the previous one did not run or moved no row (V_aff is empty then).
-template <int CP, int G>
+// RELAX: a round over all rows with relaxation (flags: kRoundForce); an instance of its own, because the second row per
+// lane doubles the registers of the plain one (60 -> 121 with 16 columns: half the waves).
+template <int CP, int G, bool RELAX>
 __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __restrict__ prev, unsigned int long_blocks_max,
                                                            const int32_t* __restrict__ front,
                                                            const int32_t* __restrict__ back, unsigned int ns,
@@ -758,11 +763,225 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
     if (blockIdx.x == 0 && threadIdx.x == 0) ctr->executed = 1;
     const unsigned int long_blocks = nl < long_blocks_max ? nl : long_blocks_max;
     if (blockIdx.x < long_blocks)
-        row_update_long<CP, false, true>(blockIdx.x, long_blocks, back, nl, ns, meta, pool, F_in, F_out, 1, nullptr,
-                                         moved_cur, tol, ctr, moved_prev, flags, omega);
+        row_update_long<CP, false, true, false, RELAX>(blockIdx.x, long_blocks, back, nl, ns, meta, pool, F_in, F_out, 1, nullptr,
+                                         moved_cur, tol, ctr, moved_prev, omega);
     else
-        row_update_short<CP, G, false, true>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool,
-                                             F_in, F_out, 1, nullptr, moved_cur, tol, ctr, moved_prev, flags, omega);
+        row_update_short<CP, G, false, true, false, RELAX>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool,
+                                             F_in, F_out, 1, nullptr, moved_cur, tol, ctr, moved_prev, omega);
+}
+
+// =================================================================================================
+// Rounds over a small V_aff: many per launch, on one workgroup
+// =================================================================================================
+// A round over a few hundred rows is three launches (update, commit, and a compaction that scans the marks of every
+// vertex) for one or two microseconds of work: 13 us on 2,000 vertices, 14 to 20 us on 3,000,000, and the last rounds of
+// a batch are all of that kind.  One workgroup runs up to `rounds` of them in one launch: it reads a list of rows,
+// updates them exactly as a flag-marking round does (same sums in the same order, new rows staged by position and
+// committed after a barrier, or written in place), and appends the vertices it marks for the first time straight to the next list, so that nothing
+// scans the marks; those it has set it clears again.  All data between rounds stays with one CU: a workgroup's own
+// stores are visible to it after a barrier.  Measured: see tail_rounds_pay in dynlp.hip.
+// The launch ends when V_aff is empty, after `rounds` rounds, or when V_aff or its entries outgrow one CU; the list of
+// the next round is then where an ordinary round expects it.
+constexpr int kTailThreads = 1024;
+
+struct TailArgs {
+    RoundCtr* ring;
+    int t0, rounds;               // rounds t0 .. t0 + rounds - 1 at most; rounds < kRing - 1
+    int32_t* front[2];            // list of round t0: front[0] / back[0]; the two arrays take turns
+    int32_t* back[2];
+    const RowMeta* meta;
+    const Edge* pool;
+    const int32_t* seed_class;
+    float* F;
+    float* staged;                // rows by position (synchronous mode)
+    int by_vertex;                // kRowByVertex: in place; kRowLazy
+    uint8_t* flag;
+    float tol;
+    unsigned int max_rows, max_entries;
+};
+
+template <int CP, int G>
+__global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
+    constexpr int VEC = RowShape<CP>::VEC;
+    constexpr int LPN = RowShape<CP>::LPN;
+    constexpr int GL = LPN > 16 ? LPN : 16, NG = kBlock / GL;  // long rows: as in row_update_long
+    constexpr int TEAMS = kTailThreads / kBlock;
+    __shared__ float part[TEAMS][NG][CP + 1];
+    __shared__ float part_s[TEAMS][NG];
+    __shared__ unsigned int big[TEAMS];
+    __shared__ unsigned int count[2];       // rows of the running round: short, long
+    __shared__ unsigned int next[3];        // of the next one: short, long, their entries
+    __shared__ unsigned int moved, resid;
+    __shared__ unsigned int entries[2];     // of the running round: in short rows, in long rows
+    {
+        // the slots of all rounds this launch may run, and of the round after
+        constexpr int kWords = sizeof(RoundCtr) / 4;
+        for (int i = threadIdx.x; i < (a.rounds + 1) * kWords; i += kTailThreads)
+            reinterpret_cast<unsigned int*>(a.ring + (a.t0 + i / kWords) % kRing)[i % kWords] = 0u;
+        if (threadIdx.x == 0) {
+            const RoundCtr* prev = a.ring + (a.t0 + kRing - 1) % kRing;
+            count[0] = (a.t0 == 0 ? a.ring + kRing : prev)->next_count;
+            count[1] = (a.t0 == 0 ? a.ring + kRing : prev)->next_long;
+            next[2] = 0u;
+        }
+    }
+    __syncthreads();
+    for (int r = 0; r < a.rounds; ++r) {
+        const unsigned int ns = count[0], nl = count[1];  // uniform from here on
+        if (ns + nl == 0u || (r > 0 && (ns + nl > a.max_rows || next[2] > a.max_entries))) return;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            next[0] = next[1] = next[2] = 0u;
+            moved = resid = 0u;
+            entries[0] = entries[1] = 0u;
+        }
+        __syncthreads();
+        const int32_t* front = a.front[r & 1];
+        const int32_t* back = a.back[r & 1];
+        int32_t* nfront = a.front[(r + 1) & 1];
+        int32_t* nback = a.back[(r + 1) & 1];
+        float rmax = 0.f;
+        unsigned int nmoved = 0, nent[2] = {0u, 0u};
+        auto mark = [&](int32_t v) {  // v joins the next V_aff, once
+            if (a.seed_class[v] >= 0) return;
+            const unsigned int bit = 1u << (((unsigned int)v & 3u) * 8u);
+            if (atomicOr(reinterpret_cast<unsigned int*>(a.flag) + ((unsigned int)v >> 2), bit) & bit) return;
+            const int len = a.meta[v].len;
+            atomicAdd(&next[2], (unsigned int)len);
+            if (len > kLongRow) nback[-(long long)atomicAdd(&next[1], 1u)] = v;
+            else nfront[atomicAdd(&next[0], 1u)] = v;
+        };
+        // the new row from the sums of its entries (the lanes of slot 0 hold acc and s), by the LPN lanes of one slot
+        auto finish = [&](unsigned int pos, int32_t u, int chunk, const Vec<VEC>& acc, float s, const Vec<VEC>& old) {
+            Vec<VEC> fn;
+            float d = 0.f;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                fn.v[k] = acc.v[k] / s;
+                if (a.by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
+                d = fmaxf(d, fabsf(fn.v[k] - old.v[k]));
+            }
+#pragma unroll
+            for (int k = 1; k < LPN; k <<= 1) d = fmaxf(d, __shfl_xor(d, k, LPN));
+            float* const out = a.by_vertex & kRowByVertex ? a.F + (size_t)u * CP : a.staged + (size_t)pos * CP;
+            store_vec<VEC>(out + chunk * VEC, fn);
+            return d;
+        };
+        // long rows: four at a time, 256 threads each, summed in the order k_row_update sums them
+        for (unsigned int j0 = 0; j0 < nl; j0 += TEAMS) {
+            const int team = threadIdx.x / kBlock, tid = threadIdx.x % kBlock;
+            const unsigned int j = j0 + team;
+            const int gi = tid / GL, gl = tid % GL, slot = gl / LPN, chunk = gl % LPN;
+            const int32_t u = j < nl ? back[-(long long)j] : 0;
+            const RowMeta m = a.meta[u];
+            const int len = j < nl ? m.len : 0;
+            const Edge* __restrict__ row = a.pool + m.off;
+            Vec<VEC> acc;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
+            float s = 0.f;
+            Edge e;
+            e.col = u;
+            e.w = 0.f;
+            accumulate_row<CP, GL>(row, len, gi, NG, u, a.F, gl, acc, s, e);
+            if (slot == 0) {
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) part[team][gi][chunk * VEC + k] = acc.v[k];
+                if (gl == 0) part_s[team][gi] = s;
+            }
+            __syncthreads();
+            if (gi == 0 && slot == 0 && j < nl) {
+                Vec<VEC> tot;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) tot.v[k] = 0.f;
+                float st = 0.f;
+#pragma unroll 4
+                for (int q = 0; q < NG; ++q) {
+#pragma unroll
+                    for (int k = 0; k < VEC; ++k) tot.v[k] += part[team][q][chunk * VEC + k];
+                    st += part_s[team][q];
+                }
+                const float d = finish(ns + j, u, chunk, tot, st, load_vec<VEC>(a.F + (size_t)u * CP + chunk * VEC));
+                if (gl == 0) {
+                    rmax = fmaxf(rmax, d);
+                    nent[1] += (unsigned int)len;
+                    nmoved += d > a.tol ? 1u : 0u;
+                    big[team] = d > a.tol ? 1u : 0u;
+                }
+            }
+            __syncthreads();
+            if (j < nl && big[team]) {
+                if (tid == 0) mark(u);
+                for (int k = tid; k < len; k += kBlock) mark(row[k].col);
+            }
+            __syncthreads();
+        }
+        for (unsigned int i = threadIdx.x / G; i < ns; i += kTailThreads / G) {
+            const int32_t u = front[i];
+            const int gl = threadIdx.x % G, slot = gl / LPN, chunk = gl % LPN;
+            const RowMeta m = a.meta[u];
+            const Edge* __restrict__ row = a.pool + m.off;
+            Vec<VEC> acc;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
+            float s = 0.f;
+            Edge e;
+            e.col = u;
+            e.w = 0.f;
+            const Vec<VEC> old = load_vec<VEC>(a.F + (size_t)u * CP + chunk * VEC);
+            accumulate_row<CP, G>(row, m.len, 0, 1, u, a.F, gl, acc, s, e);
+            float d = 0.f;
+            if (slot == 0) d = finish(i, u, chunk, acc, s, old);
+            d = __shfl(d, 0, G);
+            if (gl == 0) {
+                rmax = fmaxf(rmax, d);
+                nent[0] += (unsigned int)m.len;
+                nmoved += d > a.tol ? 1u : 0u;
+            }
+            if (d > a.tol) {
+                if (gl == 0) mark(u);
+                for (int j = gl; j < m.len; j += G) mark(row[j].col);
+            }
+        }
+        rmax = wave_max(rmax);
+        nmoved = wave_sum(nmoved);
+        nent[0] = wave_sum(nent[0]);
+        nent[1] = wave_sum(nent[1]);
+        if (lane_id() == 0) {
+            atomicMax(&resid, __float_as_uint(rmax));
+            if (nmoved) atomicAdd(&moved, nmoved);
+            if (nent[0]) atomicAdd(&entries[0], nent[0]);
+            if (nent[1]) atomicAdd(&entries[1], nent[1]);
+        }
+        __syncthreads();
+        if (!(a.by_vertex & kRowByVertex)) {
+            constexpr unsigned int PER = CP / VEC;
+            for (unsigned int i = threadIdx.x; i < (ns + nl) * PER; i += kTailThreads) {
+                const unsigned int pos = i / PER;
+                store_vec<VEC>(a.F + (size_t)frontier_vertex(front, back, ns, pos) * CP + (i % PER) * VEC,
+                               load_vec<VEC>(a.staged + (size_t)pos * CP + (i % PER) * VEC));
+            }
+        }
+        for (unsigned int i = threadIdx.x; i < next[0] + next[1]; i += kTailThreads)
+            a.flag[frontier_vertex(nfront, nback, next[0], i)] = 0;
+        if (threadIdx.x == 0) {
+            RoundCtr* slot = a.ring + (a.t0 + r) % kRing;
+            slot->next_count = next[0];
+            slot->next_long = next[1];
+            slot->executed = 1u;
+            slot->rows_short = ns;
+            slot->rows_long = nl;
+            slot->any_moved = moved ? 1u : 0u;
+            RoundPart* p = &slot->part[0];
+            p->resid_bits = resid;
+            p->changed = moved;
+            p->edges = entries[0];
+            p->edges_long = entries[1];
+            count[0] = next[0];
+            count[1] = next[1];
+        }
+        __syncthreads();
+    }
 }
 
 // =================================================================================================

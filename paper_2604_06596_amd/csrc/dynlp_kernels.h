@@ -907,7 +907,7 @@ __global__ void __launch_bounds__(kBlock) k_export_rows(int64_t n, const RowMeta
 }
 
 // Every step-th updatable row (list: short rows from the front, long rows from the back): out[0] += weight of its edges to
-// labelled vertices, out[1] += weight of all its edges.  16 lanes per row.
+// labelled vertices, out[1] += weight of all its edges (the first 128 of a longer row's).  16 lanes per row.
 __global__ void __launch_bounds__(kBlock) k_labelled_share(unsigned int ns, unsigned int nl, unsigned int step,
                                                           const int32_t* __restrict__ front, const int32_t* __restrict__ back,
                                                           const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
@@ -918,7 +918,7 @@ __global__ void __launch_bounds__(kBlock) k_labelled_share(unsigned int ns, unsi
     if (pos < (unsigned long long)ns + nl) {
         const int32_t u = pos < ns ? front[pos] : back[-(long long)(pos - ns)];
         const RowMeta m = meta[u];
-        for (int j = (int)(threadIdx.x & 15u); j < m.len; j += 16) {
+        for (int j = (int)(threadIdx.x & 15u); j < (m.len < 128 ? m.len : 128); j += 16) {
             const Edge e = pool[m.off + j];
             all += e.w;
             if (seed_class[e.col] >= 0) labelled += e.w;

@@ -147,26 +147,67 @@ __device__ inline unsigned int pk_spread(unsigned int L) {
 
 // The entries of part p to its stretch of the stream, start[p] .. start[p + 1] - 1 (exclusive scan of part_total), in
 // ascending order of neighbour >> bucket_bits.  Which of a bucket's places an entry gets depends on timing and has no
-// influence on results.  One workgroup per part, 16 lanes per row.
+// influence on results.  One workgroup per part, one lane per entry (running row lengths in LDS tell its row): the reads
+// of eight entries per lane are in flight together and a hub row is as quick as any other (1,000,000 vertices of degree
+// 20, 16 lanes per row: 667 us).
+constexpr int kPkMaxRows = 32768;  // their running lengths fit the LDS
+
 __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, int rows, int col_bits, int bucket_bits,
                                                         const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
                                                         const int32_t* __restrict__ len, const float* __restrict__ deg,
                                                         const unsigned int* __restrict__ start,
                                                         PkEntry* __restrict__ ent) {
+    constexpr int T = kPkThreads;
+    constexpr int NW = T / kWave;
+    constexpr int UN = 4;
+    extern __shared__ __align__(16) unsigned int pk_lds[];  // rows + 1 words: entries in the part's rows before
     __shared__ unsigned int cur[kPkBuckets];  // entries per bucket, then entries placed
     __shared__ unsigned int seg0[kPkBuckets], seg_len[kPkBuckets], step[kPkBuckets];
-    __shared__ unsigned int wave_tot[kPkBuckets / kWave];
-    static_assert(kPkBuckets <= kPkThreads, "one thread per bucket");
-    if (threadIdx.x < kPkBuckets) cur[threadIdx.x] = 0u;
-    __syncthreads();
+    __shared__ unsigned int wave_tot[NW];
+    static_assert(kPkBuckets <= T, "one thread per bucket");
+    unsigned int* const pre = pk_lds;
     const int64_t base = (int64_t)blockIdx.x * rows;
-    const int64_t end = base + rows < n ? base + rows : n;
-    const int gl = threadIdx.x & 15;
-    for (int64_t u = base + (threadIdx.x >> 4); u < end; u += kPkThreads / 16) {
-        const int l = len[u];
-        if (l == 0) continue;
-        const Edge* __restrict__ row = pool + meta[u].off;
-        for (int j = gl; j < l; j += 16) atomicAdd(&cur[(unsigned int)row[j].col >> bucket_bits], 1u);
+    const int nr = (int)(n - base < rows ? n - base : rows);
+    if (threadIdx.x < kPkBuckets) cur[threadIdx.x] = 0u;
+    // running row lengths: every thread sums a run of rows, the runs are scanned
+    const int per = (nr + T - 1) / T;
+    const int r0 = (int)threadIdx.x * per < nr ? (int)threadIdx.x * per : nr;
+    const int r1 = r0 + per < nr ? r0 + per : nr;
+    unsigned int sum = 0;
+    for (int r = r0; r < r1; ++r) sum += (unsigned int)len[base + r];
+    const unsigned int scan = wave_inclusive_scan(sum);
+    if (lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = scan;
+    __syncthreads();
+    unsigned int before = scan - sum;
+    for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) before += wave_tot[w];
+    for (int r = r0; r < r1; ++r) {
+        pre[r] = before;
+        before += (unsigned int)len[base + r];
+    }
+    const unsigned int count = start[blockIdx.x + 1] - start[blockIdx.x];
+    if (threadIdx.x == 0) pre[nr] = count;
+    __syncthreads();
+    auto row_of = [&](unsigned int i) {  // the last row r with pre[r] <= i (rows without entries share their start with the next)
+        int lo = 0, hi = nr;             // pre[lo] <= i < pre[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= i) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (unsigned int i0 = threadIdx.x; i0 < count; i0 += UN * T) {
+        int r[UN];
+        Edge e[UN];
+#pragma unroll
+        for (int t = 0; t < UN; ++t) {
+            const unsigned int i = i0 + t * T < count ? i0 + t * T : count - 1;
+            r[t] = row_of(i);
+            e[t] = pool[meta[base + r[t]].off + (i - pre[r[t]])];
+        }
+#pragma unroll
+        for (int t = 0; t < UN; ++t)
+            if (i0 + t * T < count) atomicAdd(&cur[(unsigned int)e[t].col >> bucket_bits], 1u);
     }
     __syncthreads();
     unsigned int v = 0, inc = 0;
@@ -176,29 +217,36 @@ __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, int rows, in
         if (lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = inc;
         seg_len[threadIdx.x] = v;
         step[threadIdx.x] = v > 0u ? pk_spread(v) : 1u;
-        cur[threadIdx.x] = 0u;
     }
     __syncthreads();
     if (threadIdx.x < kPkBuckets) {
-        unsigned int before = start[blockIdx.x];
-        for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) before += wave_tot[w];
-        seg0[threadIdx.x] = before + inc - v;
+        unsigned int at = start[blockIdx.x];
+        for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) at += wave_tot[w];
+        seg0[threadIdx.x] = at + inc - v;
+        cur[threadIdx.x] = 0u;
     }
     __syncthreads();
-    for (int64_t u = base + (threadIdx.x >> 4); u < end; u += kPkThreads / 16) {
-        const int l = len[u];
-        if (l == 0) continue;
-        const Edge* __restrict__ row = pool + meta[u].off;
-        const float d = deg[u];
-        const unsigned int r = (unsigned int)(u - base) << col_bits;
-        for (int j = gl; j < l; j += 16) {
-            const Edge e = row[j];
-            const unsigned int b = (unsigned int)e.col >> bucket_bits;
+    for (unsigned int i0 = threadIdx.x; i0 < count; i0 += UN * T) {
+        int r[UN];
+        Edge e[UN];
+        float d[UN];
+#pragma unroll
+        for (int t = 0; t < UN; ++t) {
+            const unsigned int i = i0 + t * T < count ? i0 + t * T : count - 1;
+            r[t] = row_of(i);
+            e[t] = pool[meta[base + r[t]].off + (i - pre[r[t]])];
+            d[t] = deg[base + r[t]];
+        }
+#pragma unroll
+        for (int t = 0; t < UN; ++t) {
+            if (i0 + t * T >= count) continue;
+            const unsigned int b = (unsigned int)e[t].col >> bucket_bits;
             PkEntry x;
-            x.at = r | (unsigned int)e.col;
-            x.wn = e.w / d * kPkUnit;
-            const unsigned int i = atomicAdd(&cur[b], 1u);
-            ent[seg0[b] + (unsigned int)((unsigned long long)i * step[b] % seg_len[b])] = x;
+            x.at = ((unsigned int)r[t] << col_bits) | (unsigned int)e[t].col;
+            x.wn = e[t].w / d[t] * kPkUnit;
+            const unsigned int k = atomicAdd(&cur[b], 1u), L = seg_len[b];
+            const unsigned int place = L < 65536u ? k * step[b] % L : (unsigned int)((unsigned long long)k * step[b] % L);
+            ent[seg0[b] + place] = x;
         }
     }
 }

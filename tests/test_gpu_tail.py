@@ -1,0 +1,70 @@
+"""GPU parity of the rounds over a small V_aff that run many per launch on one workgroup (k_tail_rounds): same V_aff every
+round, same labels as the oracle's Step 3 and as the ordinary launches (a fixed number of lanes per row keeps those), in
+batches whose V_aff stays small, outgrows the launch and comes back, or is cut by the round cap inside a launch.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import native as ON
+from oracle import reference as R
+import paper_2604_06596_amd as P
+
+pytestmark = pytest.mark.gpu
+
+ROUNDS_ATOL = 5e-6  # as for the first rounds of a batch in test_gpu_parity
+
+
+def _run(p, b, tol, cap, mode, **kw):
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, **kw) as d:
+        d.static_solve(1e-7, 20000)
+        start, _ = d.get_labels()
+        d.set_update_mode(mode)
+        d.set_params(tol, cap)
+        st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        soft, hard = d.get_labels()
+        sizes, deltas = d.round_log()
+        st2, s2 = d.apply_batch(0, None, None, None)  # no mark may be left behind
+        assert cap < 20000 or (st2 == 0 and s2.iterations == 0)
+    return start, st, s, soft, hard, sizes, deltas
+
+
+# deg: frontier rows of about that many entries, far from 8, where narrow rows change between 4 and 16 lanes
+@pytest.mark.parametrize("kind,C,scalar,deg,lanes", [
+    ("random", 1, False, 16, 16), ("random", 2, True, 16, 16), ("random", 2, True, 3, 4), ("random", 2, False, 3, 4),
+    ("random", 3, False, 3, 4), ("random", 3, False, 16, 16), ("random", 7, False, 5, 16), ("random", 16, False, 5, 16),
+    ("hub", 20, False, 10, 16), ("hub", 50, False, 10, 16), ("hub", 64, False, 10, 16)])
+@pytest.mark.parametrize("tol,cap", [(1e-3, 20000), (1e-4, 20000), (1e-4, 3), (1e-4, 7)])
+def test_small_rounds_match_the_oracle_and_the_ordinary_launches(kind, C, scalar, deg, lanes, tol, cap):
+    def make():
+        return W.chung_lu(4000, C, 10.0, 2.1, 600, 0.8, 0.05, 55) if kind == "hub" else W.small_random(3001, C, float(deg), 200, 55 + C)
+
+    p, p0 = make(), make()
+    b = W.chung_lu_vertex_batch(p, 2, 0.0) if kind == "hub" else W.small_random_batch(p, 1, deg, 0, num_extra_edges=3, num_revealed=1)
+    start, st, s, soft, hard, sizes, deltas = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar)
+    _, st1, s1, soft1, hard1, sizes1, _ = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar, group_lanes=lanes)
+    assert (st, s.iterations, s.rows_updated, s.edges_traversed) == (st1, s1.iterations, s1.rows_updated, s1.edges_traversed)
+    assert sizes.tolist() == sizes1.tolist() and np.array_equal(soft, soft1)
+    g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
+    n_old = g.n
+    g.insert(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+    rp, col, w = g.csr()
+    A0 = ON.affected_set(rp, col, g.seed_class, n_old, b.eu, b.ev, b.seed_vertex)
+    F = np.concatenate([start.astype(np.float64), np.full((b.num_new_vertices, C), 1.0 / C)])
+    if len(b.seed_vertex):
+        F[b.seed_vertex] = np.eye(C)[b.seed_class]
+    if cap < 20000:
+        # (the end of a run is left to the comparison above: a row that moves by the threshold to within float32 rounding
+        # stays in V_aff on one side only, against the float64 oracle, and the runs part there)
+        o2 = ON.step3_propagate(rp, col, w, F, g.seed_class, A0, tol, cap)
+        osz = o2["frontier_sizes"][:o2["rounds"]]
+        assert s.iterations == o2["rounds"] and (s.iterations == cap or C == 1)
+        # (the same row-at-the-threshold effect within the first rounds: such a row and the neighbours it brings)
+        assert np.all(np.abs(sizes.astype(np.int64) - osz.astype(np.int64)) <= 10 + osz // 500)
+        np.testing.assert_allclose(deltas, o2["max_changes"][:o2["rounds"]], atol=1e-6)
+        # (a row that stays out of V_aff keeps a value within tol of its new one)
+        assert np.max(np.abs(soft - o2["F"])) <= (ROUNDS_ATOL if sizes.tolist() == osz.tolist() else ROUNDS_ATOL + 2 * tol)
+    else:
+        # rows updated in place take another path to labels that stopped under the same rule
+        _, st2, s2, soft2, _, sizes2, _ = _run(p0, b, tol, cap, P.UPDATE_IN_PLACE, binary_scalar=scalar)
+        assert st2 == 0 and sizes2[0] == sizes[0] and np.max(np.abs(soft2 - soft)) <= 100 * tol
