@@ -1141,6 +1141,11 @@ constexpr unsigned int kPackedMinRows = 32768;
 // kPackedShare: see packed_rounds_pay; kPackedUneven: a part with more than this many times the mean entries would keep
 // the round waiting for one CU.
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
+// Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk
+// to a labelled vertex) that the last bits of a row decide visibly where: a row that moves by the threshold to within
+// rounding enters V_aff or not and takes its neighbours along.  With tol = 1e-4 on 1,000,000 vertices two solves that
+// agree to 7e-8 are 1.4e-4 apart after a batch (2-norm, relative).  Such runs keep the sums of the row update.
+constexpr float kPackedMaxTol = 1e-5f;
 struct PackedPlan {
     int rows, parts, col_bits, bucket_bits;
 };
@@ -1151,6 +1156,7 @@ int packed_stride(const dynlp_ctx* c) { return c->Cs == 1 ? 1 : (c->Cs + 1) / 2 
 bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan* plan) {
     // (a caller who fixes the lanes per row asks for the row update)
     if (c->group_lanes != 0 || (c->CP == 1 && c->binned != 0) || universe.size() < kPackedMinRows || c->entries >= ((int64_t)1 << 31)) return false;
+    if (c->tol > kPackedMaxTol) return false;
     // parts: as many generations of one workgroup per CU as the sums need, of equal size
     const int row_bits8 = packed_stride(c) * 32 + 2;  // bits of LDS per row: the sums, "in V_aff", "moved"
     const int64_t rows_max = std::min<int64_t>((int64_t)(kPkLds - kPkFixedLds) * 8 / row_bits8 / 32 * 32, kPkMaxRows);

@@ -105,3 +105,24 @@ def test_a_part_with_most_of_the_entries_keeps_the_ordinary_rounds():
     for _ in range(14):
         F, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), F, seed_class)
     assert np.max(np.abs(soft - F)) <= ROUNDS_ATOL
+
+
+@pytest.mark.parametrize("C,scalar,tol", [(10, False, 1e-4), (2, True, 1e-4), (3, False, 2e-5)])
+def test_loose_thresholds_keep_the_sums_of_the_row_update(C, scalar, tol):
+    """Where the last bits of a row show in the result, a synchronous run is the same whether or not packed rounds are
+    possible (a fixed number of lanes per row excludes them)."""
+    p0 = _problem("sbm", 36001, C, 20, 131 + C)
+    runs = []
+    for kw in ({}, dict(group_lanes=16)):
+        p = _problem("sbm", 36001, C, 20, 131 + C)
+        b = _batch("sbm", p, 2500, 20)
+        with _make(p0, binary_scalar=scalar, **kw) as d:
+            d.static_solve(tol, 20000)
+            out = [d.get_labels()]
+            assert not any(_is_packed(r) for r in d.round_log_full()) and len(d.round_log_full()) > 8
+            d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            out.append(d.get_labels())
+            assert not any(_is_packed(r) for r in d.round_log_full())
+        runs.append(out)
+    for x, y in zip(*runs):
+        assert np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1])
