@@ -552,6 +552,9 @@ void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, c
 // ---- frontier launches ---------------------------------------------------------------------------
 int lanes_per_neighbour(int CP) { return CP >= 4 ? CP / 4 : 1; }
 
+// mean row length up to which narrow rows get 4 lanes, and from which rows get more than 16
+constexpr unsigned int kGroupLen4 = 8, kGroupLen32 = 96;
+
 int choose_group(const dynlp_ctx* c, double avg_len) {
     const int lpn = lanes_per_neighbour(c->CP);
     if (c->group_lanes) return std::max(c->group_lanes, lpn);
@@ -561,8 +564,8 @@ int choose_group(const dynlp_ctx* c, double avg_len) {
     int g = 16;
     // rows of a few entries with one to four label columns (50M vertices of degree 5, one column: 6.2 / 6.3 / 6.5 ms
     // per round over all rows with 4 / 8 / 16 lanes): narrow groups leave fewer lanes idle
-    if (avg_len < 8.0 && c->CP <= 4) g = 4;
-    if (avg_len >= 96.0) g = 32;
+    if (avg_len < (double)kGroupLen4 && c->CP <= 4) g = 4;
+    if (avg_len >= (double)kGroupLen32) g = 32;
     if (avg_len >= 384.0) g = 64;
     return std::max(g, lpn);
 }
@@ -770,6 +773,11 @@ void launch_update_pull(dynlp_ctx* c, int G, const Frontier& universe, const Pul
     close_timed_span(c, e1);
 }
 
+// Rounds queued per host round trip.
+constexpr int kChain = 8;
+// Rounds in a row that repeat themselves exactly before the rows are averaged (see dynlp_apply_update).
+constexpr int kSameRounds = 16;
+
 // ---- many rounds over a small V_aff in one launch (k_tail_rounds) -----------------------------------------------
 // One CU gathers about 0.4 rows per clock and looks up every neighbour it marks; the launches of an ordinary round take
 // 12 to 14 us whatever their size.  Measured per round: 3,000 vertices with one label column, up to 886 rows and 6,000
@@ -801,9 +809,18 @@ void launch_tail_cp(dynlp_ctx* c, int G, const TailArgs& a) {
     hipLaunchKernelGGL((k_tail_rounds<CP, 16>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
 }
 
-// Rounds [round, round + count) at most; the list of the first one is that of parity `cur`.
-void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vertex) {
+// Rounds [round, round + count) at most; the list of the first one is that of parity `cur`.  chain_off: rounds of the
+// running chain of kChain that came before; same_run, sig: the batch's run of rounds that repeat themselves so far.
+void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vertex, int chain_off, int same_run,
+                 const unsigned int (&sig)[3]) {
     TailArgs a{};
+    a.chain = kChain;
+    a.chain_off = chain_off;
+    a.len_lo = G == 4 || c->CP > 4 ? 0u : kGroupLen4;
+    a.len_hi = G == 4 ? kGroupLen4 : kGroupLen32;
+    a.same_run = same_run;
+    a.same_max = kSameRounds;
+    for (int i = 0; i < 3; ++i) a.sig[i] = sig[i];
     a.ring = c->ring;
     a.t0 = round;
     a.rounds = count;
@@ -1446,9 +1463,6 @@ void read_slots(dynlp_ctx* c, int t0, int count) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (int i = 0; i < count; ++i) fold_slot(c->h_slot[i]);
 }
-
-// Rounds queued per host round trip.
-constexpr int kChain = 8;
 
 void read_slots_start(dynlp_ctx* c) {
     HIPCHK(c, hipMemcpyAsync(c->h_slot, c->ring + kRing, sizeof(RoundCtr), hipMemcpyDeviceToHost, c->stream));
@@ -2323,7 +2337,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
                 ++it;
                 same_run = rc.resid_bits == prev_bits ? same_run + 1 : 0;
                 prev_bits = rc.resid_bits;
-                if (same_run >= 16) lazy = true;
+                if (same_run >= kSameRounds) lazy = true;
                 if (last <= tol) {
                     converged = true;
                     break;
@@ -2586,10 +2600,16 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         int final_checks = 0, check_round = -1;
         bool relaxed = false;  // the batch has had its relaxed rounds (accelerate)
         bool verified = !c->final_check;
+        // How the rounds run (lanes per row, stretches, averaged rows) is decided where a chain begins, every kChain
+        // rounds from round chain0 on.  A launch of k_tail_rounds that ends inside a chain leaves the rest of it to
+        // ordinary rounds, so that the order of every row's sum is the same whether or not rounds share launches.
+        int chain0 = 0, G = 16;
         for (;;) {
         while (known > 0 && it < c->max_iter) {
-            const int G = choose_group(c, avg_len);
-            if (!relaxed && it != check_round && (double)known >= kRelaxEnter * (double)universe.size() &&
+            const int chain_off = (it - chain0) % kChain;
+            const bool new_chain = chain_off == 0;
+            if (new_chain) G = choose_group(c, avg_len);
+            if (new_chain && !relaxed && it != check_round && (double)known >= kRelaxEnter * (double)universe.size() &&
                 relaxed_rounds_pay(c, universe, c->tol)) {
                 relaxed = true;
                 const bool use_bins = binned_rounds_pay(c, universe) && (c->pb_built || build_binned(c));
@@ -2616,6 +2636,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                     read_slots(c, it - 1, 1);
                     known = c->h_slot[0].next_count + c->h_slot[0].next_long;
                 }
+                chain0 = it;
                 continue;
             }
             // A stretch of ping-pong rounds starts when V_aff covers nearly every updatable vertex (one copy
@@ -2625,14 +2646,14 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // later ones evaluate V_aff = {u : u or a neighbour moved in the previous round} per row, from
             // the bitmap of moved rows.  Leaving a stretch pulls the list out of the last bitmap once.
             bool can_bin = !bin_failed && binned_rounds_pay(c, universe);
-            if (can_bin && !pingpong && !c->pb_built && (double)known >= kBinnedEnter * (double)universe.size() &&
+            if (can_bin && new_chain && !pingpong && !c->pb_built && (double)known >= kBinnedEnter * (double)universe.size() &&
                 !build_binned(c)) {
                 bin_failed = true;  // no memory for the binned arrays: ordinary rounds for this batch
                 can_bin = false;
             }
             bool can_pack = !pack_failed && !in_place && !can_bin && !persistent_rounds_pay(c, universe) &&
                             packed_rounds_pay(c, universe, &pk_plan);
-            if (can_pack && !pingpong && !c->pk_built && (double)known >= kPackedEnter * (double)universe.size() &&
+            if (can_pack && new_chain && !pingpong && !c->pk_built && (double)known >= kPackedEnter * (double)universe.size() &&
                 !build_packed(c, pk_plan)) {
                 pack_failed = true;
                 can_pack = false;
@@ -2642,7 +2663,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // over a small V_aff costs them no more than a launch
             // (not once rounds repeat themselves exactly: the averaged rows that end such a cycle are staged rounds)
             const bool stay = !lazy && !can_bin && fused_rounds_pay(c, avg_len) && persistent_rounds_pay(c, universe);
-            if (!pingpong && (stay || (double)known >= enter * (double)universe.size())) {
+            if (new_chain && !pingpong && (stay || (double)known >= enter * (double)universe.size())) {
                 if (!in_place) sync_partner(c);
                 for (unsigned int* mv : c->moved)
                     HIPCHK(c, hipMemsetAsync(mv, 0, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
@@ -2673,14 +2694,15 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // first chain is short: the relaxed rounds over all rows that follow cost half a flag-marking round
             const bool short_first = it == 0 && !pingpong && relaxed_rounds_pay(c, universe, c->tol) &&
                                      (double)known * avg_len >= (double)universe.size();
-            const int r = std::min<int>(persist ? kPersistRounds : tail ? kTailRounds : short_first ? 2 : kChain, c->max_iter - it);
+            const int r = std::min<int>(persist ? kPersistRounds : tail ? kTailRounds : short_first ? 2 : kChain - chain_off, c->max_iter - it);
             const size_t first_pair = c->events_used / 2;
             // ping-pong: round it+i reads buf[i & 1], writes buf[(i + 1) & 1]; in place: always F
             float* const buf[2] = {c->F, in_place ? c->F : c->F2};
             bool persist_launched = false;
             int persist_first = r;  // chain position of the first round that ran inside a persistent launch
             known_before = known;
-            if (tail) launch_tail(c, G, cur, it, r, (in_place ? kRowByVertex : 0) | (lazy ? kRowLazy : 0));
+            if (tail)
+                launch_tail(c, G, cur, it, r, (in_place ? kRowByVertex : 0) | (lazy ? kRowLazy : 0), chain_off, same_run, prev_sig);
             for (int i = 0; i < (tail ? 0 : r); ++i) {
                 const int t = it + i;
                 RoundCtr* slot = slot_of(c, t);
@@ -2788,7 +2810,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 const unsigned int sig[3] = {nq, rc.changed, rc.resid_bits};
                 same_run = std::memcmp(sig, prev_sig, sizeof sig) == 0 ? same_run + 1 : 0;
                 std::memcpy(prev_sig, sig, sizeof sig);
-                if (same_run >= 16) lazy = true;
+                if (same_run >= kSameRounds) lazy = true;
                 peak = std::max<int64_t>(peak, known);
             }
             if (pingpong && !in_place && (executed & 1)) std::swap(c->F, c->F2);  // the output of the last executed round
@@ -2800,6 +2822,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 cur ^= executed & 1;
                 continue;  // V_aff is empty, has outgrown the launch, or the launch has run all its rounds
             }
+            if (cut_short || short_first) chain0 = it;
             if (cut_short) continue;
             if (executed < r) known = 0;  // a round found V_aff empty
         }
@@ -2812,7 +2835,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             HIPCHK(c, hipMemsetAsync(slot, 0, sizeof(RoundCtr), c->stream));
             launch_compact(c, frontier_of(c, cur), &slot->next_count, &slot->next_long, 1);
             known = universe.size();
-            check_round = it;
+            check_round = chain0 = it;
             ++final_checks;
         }
         }

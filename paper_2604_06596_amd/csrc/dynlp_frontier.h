@@ -780,8 +780,9 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
 // committed after a barrier, or written in place), and appends the vertices it marks for the first time straight to the next list, so that nothing
 // scans the marks; those it has set it clears again.  All data between rounds stays with one CU: a workgroup's own
 // stores are visible to it after a barrier.  Measured: see tail_rounds_pay in dynlp.hip.
-// The launch ends when V_aff is empty, after `rounds` rounds, or when V_aff or its entries outgrow one CU; the list of
-// the next round is then where an ordinary round expects it.
+// The launch ends when V_aff is empty, after `rounds` rounds, when V_aff or its entries outgrow one CU, or where a chain of
+// ordinary rounds would go on with another number of lanes per row or with averaged rows (both decided by the host); the
+// list of the next round is then where an ordinary round expects it.
 constexpr int kTailThreads = 1024;
 
 struct TailArgs {
@@ -798,6 +799,10 @@ struct TailArgs {
     uint8_t* flag;
     float tol;
     unsigned int max_rows, max_entries;
+    int chain, chain_off;         // decisions are taken every `chain` rounds; the first comes after chain - chain_off rounds
+    unsigned int len_lo, len_hi;  // mean row lengths [len_lo, len_hi) keep the lanes per row of this launch
+    int same_run, same_max;       // rounds that repeated themselves before this launch, and how many make the rows averaged
+    unsigned int sig[3];          // rows, rows moved, max change of the round before
 };
 
 template <int CP, int G>
@@ -813,6 +818,10 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
     __shared__ unsigned int next[3];        // of the next one: short, long, their entries
     __shared__ unsigned int moved, resid;
     __shared__ unsigned int entries[2];     // of the running round: in short rows, in long rows
+    __shared__ bool leave;                  // the host has something to decide
+    int same_run = a.same_run;              // (thread 0)
+    bool repeats = false;
+    unsigned int sig[3] = {a.sig[0], a.sig[1], a.sig[2]};
     {
         // the slots of all rounds this launch may run, and of the round after
         constexpr int kWords = sizeof(RoundCtr) / 4;
@@ -823,12 +832,13 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             count[0] = (a.t0 == 0 ? a.ring + kRing : prev)->next_count;
             count[1] = (a.t0 == 0 ? a.ring + kRing : prev)->next_long;
             next[2] = 0u;
+            leave = false;
         }
     }
     __syncthreads();
     for (int r = 0; r < a.rounds; ++r) {
         const unsigned int ns = count[0], nl = count[1];  // uniform from here on
-        if (ns + nl == 0u || (r > 0 && (ns + nl > a.max_rows || next[2] > a.max_entries))) return;
+        if (ns + nl == 0u || leave || (r > 0 && (ns + nl > a.max_rows || next[2] > a.max_entries))) return;
         __syncthreads();
         if (threadIdx.x == 0) {
             next[0] = next[1] = next[2] = 0u;
@@ -979,6 +989,13 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             p->edges_long = entries[1];
             count[0] = next[0];
             count[1] = next[1];
+            same_run = ns + nl == sig[0] && moved == sig[1] && resid == sig[2] ? same_run + 1 : 0;
+            sig[0] = ns + nl;
+            sig[1] = moved;
+            sig[2] = resid;
+            repeats = repeats || (same_run >= a.same_max && !(a.by_vertex & kRowLazy));
+            const unsigned long long e = (unsigned long long)entries[0] + entries[1], n = ns + nl;
+            leave = (a.chain_off + r + 1) % a.chain == 0 && (repeats || e < n * a.len_lo || e >= n * a.len_hi);
         }
         __syncthreads();
     }

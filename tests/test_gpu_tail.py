@@ -68,3 +68,50 @@ def test_small_rounds_match_the_oracle_and_the_ordinary_launches(kind, C, scalar
         # rows updated in place take another path to labels that stopped under the same rule
         _, st2, s2, soft2, _, sizes2, _ = _run(p0, b, tol, cap, P.UPDATE_IN_PLACE, binary_scalar=scalar)
         assert st2 == 0 and sizes2[0] == sizes[0] and np.max(np.abs(soft2 - soft)) <= 100 * tol
+
+
+@pytest.mark.parametrize("C,scalar", [(2, True), (2, False), (3, False), (10, False)])
+def test_lanes_per_row_change_where_a_chain_of_rounds_begins(C, scalar):
+    """Rounds that share a launch sum their rows as ordinary rounds would: the lanes per row are chosen from the mean row
+    length of the round before, every 8 rounds (narrow rows: 4 lanes below a mean length of 8, else 16)."""
+    changes = 0
+    for deg, tol in [(deg, tol) for deg in (4.0, 4.5, 5.0, 5.5, 6.0) for tol in (1e-4, 1e-6)]:
+        p, p0 = W.small_random(3001, C, deg, 200, 155 + C), W.small_random(3001, C, deg, 200, 155 + C)
+        b = W.small_random_batch(p, 1, 3, 0)
+        with P.DynLP(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class, binary_scalar=scalar) as d:
+            d.static_solve(1e-7, 20000)
+            d.set_params(tol, 20000)
+            assert d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew)[0] == 0
+            mean = d.num_entries / d.num_vertices
+            log = d.round_log_full()
+        for t, r in enumerate(log):
+            if t % 8 == 0:
+                want = 4 if C <= 4 and mean < 8 else 16
+                changes += t > 0 and want != log[t - 1].group_lanes
+            assert r.group_lanes == want, (deg, tol, t, len(log), mean)
+            mean = (r.entries_short + r.entries_long) / (r.rows_short + r.rows_long)
+    print(C, scalar, "changes of the lanes per row", changes)
+    assert changes > 0 or C > 4, "the case is meant to change the lanes per row"
+
+
+@pytest.mark.parametrize("C", [5, 20])
+def test_averaged_rows_begin_where_ordinary_launches_begin_them(C):
+    """Two new vertices tied to each other by weight 1 and to two seeds by weight 0.001: rounds that repeat themselves
+    exactly.  The rows are averaged from the same round on as with ordinary launches."""
+    p = W.small_random(400, C, 6.0, 40, 4242)
+    a = int(p.seed_vertex[np.flatnonzero(p.seed_class == 0)[0]])
+    b = int(p.seed_vertex[np.flatnonzero(p.seed_class == 1)[0]])
+    u, v = p.n, p.n + 1
+    runs = []
+    for lanes in (0, 16):
+        with P.DynLP(p.n, p.row_ptr, p.col, p.w, C, p.seed_vertex, p.seed_class, group_lanes=lanes) as d:
+            d.static_solve(1e-6, 20000)
+            d.set_params(1e-6, 20000)
+            st, s = d.apply_batch(2, np.array([u, u, v], np.int32), np.array([v, a, b], np.int32),
+                                  np.array([1.0, 0.001, 0.001], np.float32))
+            assert st == 0
+            runs.append(d.get_labels() + d.round_log() + (s.iterations,))
+    (soft, hard, sizes, deltas, rounds), (soft1, hard1, sizes1, deltas1, rounds1) = runs
+    print(C, "rounds", rounds, rounds1)
+    assert rounds == rounds1 and sizes.tolist() == sizes1.tolist() and np.array_equal(deltas, deltas1)
+    assert np.array_equal(soft, soft1) and np.array_equal(hard, hard1)
