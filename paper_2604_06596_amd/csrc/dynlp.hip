@@ -1474,7 +1474,8 @@ void read_slots_start(dynlp_ctx* c) {
 // a label from the labelled vertices: 200 to 600 rounds at tol = 1e-6 on graphs with 1% labelled vertices.  While nearly
 // every row is in V_aff and the threshold is tight, the in-place mode therefore relaxes all rows together,
 //     F(k+1) = omega * (weighted mean of F(k)) + (1 - omega) * F(k-1)
-// (second-order Richardson iteration, Golub and Varga 1961): it converges for every 0 < omega < 2 because the
+// (second-order Richardson iteration, Golub and Varga 1961; the first round is an ordinary one, without which a component
+// that oscillates would start with omega / (2 - omega) times its amplitude): it converges for every 0 < omega < 2 because the
 // eigenvalues of the update lie in [-1, 1], and with omega = 2 / (1 + sqrt(1 - mu^2)) an error shrinks by
 // sqrt(omega - 1) per round instead of mu, the update's largest eigenvalue.  mu is at least the Rayleigh quotient of the
 // constant vector, 1 - (weight of the edges to labelled vertices) / (weight of all edges of updatable rows); kRelaxGap
@@ -1537,7 +1538,7 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
             PullRoundArgs a{slot_of(c, t - 1), buf[i & 1], buf[(i + 1) & 1], c->moved[(b + 2) % 3], c->moved[b % 3],
                             c->moved[(b + 1) % 3], tol, slot_of(c, t), slot_of(c, t + 1)};
             a.flags = kRoundAll | (finish || b == 0 ? kRoundForce : 0);
-            a.omega = finish ? 1.f : (float)omega;
+            a.omega = finish || b == 0 ? 1.f : (float)omega;
             c->ev_adjacent = i > 0;
             if (binned) launch_binned_round(c, a, t, false);
             else if (packed) launch_packed_round(c, a, t);

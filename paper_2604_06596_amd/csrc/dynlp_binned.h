@@ -560,7 +560,7 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
                 const bool in_front = ((own[d >> 5] | nb[d >> 5]) >> (d & 31)) & 1u;
                 if (in_front) {
                     float fn = fminf((float)acc[d] * (1.0f / kPbUnit), 1.0f);
-                    if (omega != 1.f) fn = relax(fn, F_out[v], omega);
+                    if (omega != 1.f) fn = relax_scalar(fn, F_out[v], omega);
                     const float r = fabsf(fn - old[q]);
                     F_out[v] = fn;
                     big = r > tol;

@@ -88,9 +88,13 @@ struct __attribute__((aligned(64))) BatchCtr {
 constexpr int kRoundAll = 1, kRoundForce = 2;
 
 // New value of a label entry from the weighted mean of its neighbours and the row of the round before the last: one step
-// of the second-order Richardson iteration (Golub and Varga 1961), kept inside [0, 1] like every label.  omega = 1: the mean.
-__device__ inline float relax(float mean, float before, float omega) {
-    return fminf(fmaxf(omega * mean + (1.f - omega) * before, 0.f), 1.f);
+// of the second-order Richardson iteration (Golub and Varga 1961).  omega = 1: the mean.  It may leave [0, 1]: see
+// relax_scalar and relax_row.
+__device__ inline float relax(float mean, float before, float omega) { return omega * mean + (1.f - omega) * before; }
+
+// The one stored column of a binary graph.
+__device__ inline float relax_scalar(float mean, float before, float omega) {
+    return fminf(fmaxf(relax(mean, before, omega), 0.f), 1.f);
 }
 
 enum ValidationError : int {
@@ -195,6 +199,25 @@ template <int V>
 struct Vec {
     float v[V];
 };
+
+// fn (the weighted means of a row's columns, V per lane in LPN neighbouring lanes) relaxed, and still a distribution:
+// columns below 0 are set to 0 and what that adds is taken from the others in proportion.  (The columns of fn and of
+// `before` sum to one, and relaxed columns would too.)  Cutting columns off one by one would add weight that nothing
+// takes away in a component without a labelled vertex.
+template <int V, int LPN>
+__device__ inline void relax_row(Vec<V>& fn, const Vec<V>& before, float omega) {
+    float cut = 0.f;
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        fn.v[k] = relax(fn.v[k], before.v[k], omega);
+        cut -= fminf(fn.v[k], 0.f);
+    }
+#pragma unroll
+    for (int s = 1; s < LPN; s <<= 1) cut += __shfl_xor(cut, s, LPN);
+    const float scale = cut > 0.f ? 1.f / (1.f + cut) : 1.f;
+#pragma unroll
+    for (int k = 0; k < V; ++k) fn.v[k] = fminf(fmaxf(fn.v[k], 0.f) * scale, 1.f);
+}
 
 template <int V>
 __device__ inline Vec<V> load_vec(const float* p);

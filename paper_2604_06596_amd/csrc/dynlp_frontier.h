@@ -497,9 +497,10 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         float r = 0.f;
         if (RELAX && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
+        for (int k = 0; k < VEC; ++k) fn.v[k] = acc.v[k] / s;
+        if (RELAX && omega != 1.f) relax_row<VEC, LPN>(fn, before, omega);
+#pragma unroll
         for (int k = 0; k < VEC; ++k) {
-            fn.v[k] = acc.v[k] / s;
-            if (RELAX && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
             if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
             r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
         }
@@ -615,9 +616,10 @@ __device__ inline unsigned int row_update_long(unsigned int bid, unsigned int nb
             float r = 0.f;
             if (RELAX && omega != 1.f) before = load_row<VEC, COH>(F_out + (size_t)u * CP + chunk * VEC);
 #pragma unroll
+            for (int k = 0; k < VEC; ++k) fn.v[k] = tot.v[k] / st;
+            if (RELAX && omega != 1.f) relax_row<VEC, LPN>(fn, before, omega);
+#pragma unroll
             for (int k = 0; k < VEC; ++k) {
-                fn.v[k] = tot.v[k] / st;
-                if (RELAX && omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], omega);
                 if (by_vertex & kRowLazy) fn.v[k] = 0.5f * (fn.v[k] + old.v[k]);
                 r = fmaxf(r, fabsf(fn.v[k] - old.v[k]));
             }

@@ -440,11 +440,11 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
             float d = 0.f;
             if (a.omega != 1.f) before = load_vec<VEC>(out);
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) {
+            for (int k = 0; k < VEC; ++k)
                 fn.v[k] = k < cols ? fminf((float)acc[r * a.stride + chunk * VEC + k] * (1.0f / kPkUnit), 1.0f) : 0.f;
-                if (a.omega != 1.f) fn.v[k] = relax(fn.v[k], before.v[k], a.omega);
-                d = fmaxf(d, fabsf(fn.v[k] - old[q].v[k]));
-            }
+            if (a.omega != 1.f) relax_row<VEC, LPN>(fn, before, a.omega);
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) d = fmaxf(d, fabsf(fn.v[k] - old[q].v[k]));
 #pragma unroll
             for (int s = 1; s < LPN; s <<= 1) d = fmaxf(d, __shfl_xor(d, s, LPN));
             store_vec<VEC>(out, fn);

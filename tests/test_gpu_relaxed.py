@@ -1,7 +1,8 @@
 """GPU tests of the relaxed rounds of the in-place mode (graphs of 32,768 updatable vertices or more, tight thresholds):
 whatever kernel runs them (packed rounds, row update, binned rounds), a static solve and a batch end under the same stop
 rule as without them, at labels within the same certificate of the exact ones, in fewer rounds than the synchronous mode;
-a round cap inside the phase leaves labels in [0, 1]; components that never settle by relaxation do not keep the call.
+a round cap inside the phase leaves distributions; components that never settle by relaxation do not keep the call and
+their rows stay distributions.
 """
 import numpy as np
 import pytest
@@ -14,6 +15,7 @@ import paper_2604_06596_amd as P
 pytestmark = pytest.mark.gpu
 
 TOL = 1e-6
+SUM_ATOL = 2e-5  # of a row's columns: float32 means over some hundred rounds
 
 
 def _make(p, mode=P.UPDATE_IN_PLACE, **kw):
@@ -35,7 +37,7 @@ def _check(soft, hard, g, bar, what):
     Cf.check_against_exact(soft, exact, moved, cert, what)
     Cf.check_hard(hard, exact, cert)
     assert cert.res <= bar
-    assert soft.min() >= 0 and soft.max() <= 1 and np.max(np.abs(soft.sum(1) - 1)) < 2e-5
+    assert soft.min() >= 0 and soft.max() <= 1 and np.max(np.abs(soft.sum(1) - 1)) < SUM_ATOL
     return cert
 
 
@@ -74,28 +76,37 @@ def test_static_solve_and_batch_end_under_the_same_stop_rule(kind, C, kw, kernel
     assert iterations[P.UPDATE_IN_PLACE][0] < iterations[P.UPDATE_SYNCHRONOUS][0]
 
 
-@pytest.mark.parametrize("cap", [1, 2, 9, 10, 24])
-def test_a_round_cap_inside_the_phase(cap):
-    p, p0 = _problem("sbm", 10), _problem("sbm", 10)
+@pytest.mark.parametrize("C,kw", [(10, {}), (10, dict(group_lanes=16)), (2, {}), (4, dict(group_lanes=16)), (29, {}),
+                                  (50, dict(group_lanes=16))])
+@pytest.mark.parametrize("cap", [1, 2, 3, 6, 9, 10, 24])
+def test_a_round_cap_inside_the_phase(C, kw, cap):
+    p, p0 = _problem("sbm", C), _problem("sbm", C)
     b = W.sbm_vertex_batch(p, 3000, 16, 0.02)
-    with _make(p0) as d:
+    with _make(p0, **kw) as d:
         st, s = d.static_solve(TOL, cap)
         assert st == 1 and s.iterations == cap and s.converged == 0
+        soft, _ = d.get_labels()
+        assert soft.min() >= 0 and np.max(np.abs(soft.sum(1) - 1)) < SUM_ATOL
         d.static_solve(TOL, 20000)
         d.set_params(TOL, cap)
         st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
         assert st == 1 and s.iterations == cap and len(d.round_log()[0]) == cap
         soft, hard = d.get_labels()
         assert soft.min() >= 0 and soft.max() <= 1 and np.array_equal(hard, np.argmax(soft, 1))
+        # (a row of more than one 64-byte piece that is read while it is written may come half old, half new: the rounds
+        # in place before and after the phase keep sums only as far as rows still move)
+        assert C > 16 or np.max(np.abs(soft.sum(1) - 1)) < SUM_ATOL
         d.set_params(TOL, 20000)  # an empty batch keeps what is there: V_aff is empty
         assert d.apply_batch(0, None, None, None)[0] == 0
         assert d.static_solve(TOL, 20000)[0] == 0
 
 
-def test_components_without_a_label_do_not_keep_the_call():
+@pytest.mark.parametrize("labels,by_side", [(1500, False), (12000, True)])
+def test_components_without_a_label_do_not_keep_the_call(labels, by_side):
     """Half of the graph lies in bipartite components without a labelled vertex whose rows start uneven (their labels were
-    deleted): eigenvalues 1 and -1, which relaxation does not damp.  The labelled half must still converge, and the call
-    must end as it does for rows updated in place."""
+    deleted; by side: one class on the left, the others on the right, so that the rows oscillate): eigenvalues 1 and -1, which
+    relaxation does not damp.  The labelled half must still converge, the call must end as it does for rows updated in
+    place, and all rows must stay distributions."""
     rng = np.random.default_rng(11)
     p = _problem("sbm", 4)
     m = 40000  # ladder of 20,000 + 20,000 vertices, edges only between the sides
@@ -106,17 +117,23 @@ def test_components_without_a_label_do_not_keep_the_call():
     ev = np.concatenate([p.col[up], rng.choice(right, 6 * (m // 2))])
     ew = np.concatenate([p.w[up], rng.uniform(0.1, 1, 6 * (m // 2)).astype(np.float32)]).astype(np.float32)
     rp, col, w = W.edges_to_csr(p.n + m, eu, ev, ew)
-    extra = rng.permutation(np.concatenate([left, right]))[:1500].astype(np.int32)
+    extra = rng.permutation(np.concatenate([left, right]))[:labels].astype(np.int32)
     sv = np.concatenate([p.seed_vertex, extra]).astype(np.int32)
-    sc = np.concatenate([p.seed_class, rng.integers(0, 4, extra.size)]).astype(np.int32)
+    sc = np.concatenate([p.seed_class, np.where(extra < right[0], 0, rng.integers(1, 4, extra.size)) if by_side else rng.integers(0, 4, extra.size)]).astype(np.int32)
     with P.DynLP(p.n + m, rp, col, w, 4, sv, sc) as d:
         d.set_update_mode(P.UPDATE_IN_PLACE)
         assert d.static_solve(TOL, 20000)[0] == 0
-        st, s = d.apply_update(extra)
+        d.set_params(TOL, 1)  # (the rest of the solve is left to static_solve, whose first sweep is over all rows)
+        assert d.apply_update(extra)[0] == 1
+        st, s = d.static_solve(TOL, 20000)
         assert st == 0 and s.iterations < 5000
+        assert sum(r.staged == 2 for r in d.round_log_full()) > 8, "the case is meant to reach relaxed rounds"
+        print("rounds", s.iterations, "of them relaxed", sum(r.staged == 2 for r in d.round_log_full()))
         soft, hard = d.get_labels()
         erp, ecol, ew_, _, esc = d.export_graph()
     cert = Cf.certificate(erp, ecol, ew_, esc, soft)
     exact, moved = Cf.exact_labels(erp, ecol, ew_.astype(np.float64), esc, 4)
     Cf.check_against_exact(soft, exact, moved, cert, "labelled half")
     assert soft.min() >= 0 and soft.max() <= 1
+    print("largest deviation of a row sum from 1", np.max(np.abs(soft.sum(1) - 1)))
+    assert np.max(np.abs(soft.sum(1) - 1)) < SUM_ATOL
