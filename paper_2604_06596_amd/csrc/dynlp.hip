@@ -193,7 +193,8 @@ struct dynlp_ctx {
     int64_t pk_ent_cap = 0;
     int32_t* pk_len = nullptr;
     int64_t pk_vcap = 0;
-    unsigned int* pk_tab = nullptr;  // per part: its first entry; all entries; the largest part
+    float* pk_deg = nullptr;         // degrees the weights are divided by
+    unsigned int* pk_tab = nullptr;  // per part: its first entry; all entries; the largest part; the longest row
     int64_t pk_tab_cap = 0;
     // label initialisation of inserted vertices (dynlp_components.h)
     int init_mode = DYNLP_INIT_UNIFORM;
@@ -1156,7 +1157,8 @@ void launch_binned_round(dynlp_ctx* c, const PullRoundArgs& a, int round, bool f
 // degree 8: 9 us with the row update) and the layout of the entries is one more thing to wait for.
 constexpr unsigned int kPackedMinRows = 32768;
 // kPackedShare: see packed_rounds_pay; kPackedUneven: a part with more than this many times the mean entries would keep
-// the round waiting for one CU.
+// the round waiting for one CU.  kPackedMaxRow: longer rows would show the unit of the packed sums (see dynlp_packed.h).
+constexpr unsigned int kPackedMaxRow = 8192;
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
 // Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk
 // to a labelled vertex) that the last bits of a row decide visibly where: a row that moves by the threshold to within
@@ -1201,9 +1203,11 @@ bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan*
 void free_packed(dynlp_ctx* c) {
     dev_free(c, c->pk_ent);
     dev_free(c, c->pk_len);
+    dev_free(c, c->pk_deg);
     dev_free(c, c->pk_tab);
     c->pk_ent = nullptr;
     c->pk_len = nullptr;
+    c->pk_deg = nullptr;
     c->pk_tab = nullptr;
     c->pk_ent_cap = c->pk_vcap = c->pk_tab_cap = 0;
     c->pk_built = false;
@@ -1236,10 +1240,11 @@ auto packed_kernel(const dynlp_ctx* c, Fn fn) {
     }
 }
 
-// Lays the entries of the graph as it stands out for the packed rounds.  False (and nothing kept): no memory, or parts
-// so uneven that the largest would keep a round waiting; the caller then runs ordinary rounds.
-bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
-    const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), tab = parts + 2;
+// Lays the entries of the graph as it stands out for the packed rounds (universe: all updatable vertices).  False: no
+// memory (and nothing kept), parts so uneven that the largest would keep a round waiting, or a row that is too long; the
+// caller then runs ordinary rounds.
+bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan) {
+    const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), tab = parts + 3;
     bool ok = true;
     if (ent > c->pk_ent_cap) {
         dev_free(c, c->pk_ent);
@@ -1250,9 +1255,11 @@ bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
     }
     if (ok && c->n > c->pk_vcap) {
         dev_free(c, c->pk_len);
+        dev_free(c, c->pk_deg);
         c->pk_len = nullptr;
+        c->pk_deg = nullptr;
         c->pk_vcap = 0;
-        ok = try_alloc_n(c, c->pk_len, c->n_cap);
+        ok = try_alloc_n(c, c->pk_len, c->n_cap) && try_alloc_n(c, c->pk_deg, c->n_cap);
         if (ok) c->pk_vcap = c->n_cap;
     }
     if (ok && tab > c->pk_tab_cap) {
@@ -1285,18 +1292,21 @@ bool build_packed(dynlp_ctx* c, const PackedPlan& plan) {
     }
     unsigned int* start = c->pk_tab;
     unsigned int* largest = start + parts + 1;
-    HIPCHK(c, hipMemsetAsync(start + parts, 0, 2 * sizeof(unsigned int), c->stream));
-    hipLaunchKernelGGL(k_pk_receivers, dim3(grid_for(c->n)), dim3(kBlock), 0, c->stream, c->n, c->meta, c->seed_class,
-                       c->pk_len);
+    HIPCHK(c, hipMemsetAsync(start + parts, 0, 3 * sizeof(unsigned int), c->stream));
+    hipLaunchKernelGGL(k_pk_receivers, dim3(grid_for(c->n)), dim3(kBlock), 0, c->stream, c->n, c->meta, c->seed_class, c->deg,
+                       c->pk_len, c->pk_deg);
     hipLaunchKernelGGL(k_pk_totals, dim3(plan.parts), dim3(kBlock), 0, c->stream, c->n, plan.rows, c->pk_len, start, largest);
     hipLaunchKernelGGL(k_pb_scan_blocks, dim3(1), dim3(kBlock), 0, c->stream, parts + 1, start);
     HIPCHK(c, hipGetLastError());
-    unsigned int most = 0;
-    HIPCHK(c, hipMemcpyAsync(&most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
+    unsigned int most[2] = {0, 0};
+    HIPCHK(c, hipMemcpyAsync(most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if ((double)most > kPackedUneven * (double)ent / (double)parts) return false;
+    if ((double)most[0] > kPackedUneven * (double)ent / (double)parts || most[1] > kPackedMaxRow) return false;
+    if (universe.nl)
+        hipLaunchKernelGGL(k_pk_long_degrees, dim3(std::min<unsigned int>(universe.nl, (unsigned int)c->num_cu * 8)), dim3(kBlock), 0,
+                           c->stream, universe.nl, universe.back, c->meta, c->pool, c->pk_deg);
     hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), (size_t)(plan.rows + 1) * 4, c->stream, c->n, plan.rows, plan.col_bits,
-                       plan.bucket_bits, c->meta, c->pool, c->pk_len, c->deg, start, c->pk_ent);
+                       plan.bucket_bits, c->meta, c->pool, c->pk_len, c->pk_deg, start, c->pk_ent);
     HIPCHK(c, hipGetLastError());
     c->pk_built = true;
     return true;
@@ -1622,7 +1632,7 @@ void destroy_ctx(dynlp_ctx* c) {
                     c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
                     c->pb_src, c->pb_sp, c->pb_row0, c->pb_lpos, c->pb_tmp, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, c->pb_upd,
-                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_tab};
+                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab};
     for (void* p : ptrs) dev_free(c, p);
     const std::vector<void*> left(c->live.begin(), c->live.end());  // arrays an interrupted call never got to free
     for (void* p : left) dev_free(c, p);
@@ -2276,7 +2286,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
         const bool relaxed = in_place && !converged && max_iter > 0 && relaxed_rounds_pay(c, all_rows, tol);
         const bool can_pack = !converged && !binned && (relaxed || !in_place) && packed_rounds_pay(c, all_rows, &pk_plan);
         // (synchronous sweeps: after the first chain, since a solve with a loose threshold may end within it)
-        bool packed = can_pack && relaxed && build_packed(c, pk_plan);
+        bool packed = can_pack && relaxed && build_packed(c, all_rows, pk_plan);
         bool pack_tried = packed || !can_pack || relaxed;
         if (relaxed) {
             const RelaxedRounds done = accelerate(c, all_rows, G, tol, 0, max_iter, binned, packed);
@@ -2298,7 +2308,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             const bool chain_binned = binned && !lazy;  // the averaged sweeps of a limit cycle are ordinary ones
             if (!pack_tried && it > 0) {
                 pack_tried = true;
-                packed = build_packed(c, pk_plan);
+                packed = build_packed(c, all_rows, pk_plan);
                 if (packed) HIPCHK(c, hipMemsetAsync(c->moved[0], 0xff, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
             }
             const bool chain_packed = packed && !in_place && !lazy;
@@ -2614,7 +2624,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 relaxed_rounds_pay(c, universe, c->tol)) {
                 relaxed = true;
                 const bool use_bins = binned_rounds_pay(c, universe) && (c->pb_built || build_binned(c));
-                const bool use_pack = !use_bins && packed_rounds_pay(c, universe, &pk_plan) && (c->pk_built || build_packed(c, pk_plan));
+                const bool use_pack = !use_bins && packed_rounds_pay(c, universe, &pk_plan) && (c->pk_built || build_packed(c, universe, pk_plan));
                 const size_t logged = c->log.size();
                 const RelaxedRounds done = accelerate(c, universe, G, c->tol, it, c->max_iter - it, use_bins, use_pack);
                 it += done.rounds;
@@ -2655,7 +2665,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             bool can_pack = !pack_failed && !in_place && !can_bin && !persistent_rounds_pay(c, universe) &&
                             packed_rounds_pay(c, universe, &pk_plan);
             if (can_pack && new_chain && !pingpong && !c->pk_built && (double)known >= kPackedEnter * (double)universe.size() &&
-                !build_packed(c, pk_plan)) {
+                !build_packed(c, universe, pk_plan)) {
                 pack_failed = true;
                 can_pack = false;
             }

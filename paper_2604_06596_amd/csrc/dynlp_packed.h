@@ -21,8 +21,14 @@
 // neighbour row, multiply it by w / deg and add it to the row's sums in LDS.
 //
 // The sums are 32-bit fixed-point numbers (unit 2^-31; the terms w / deg * F of a row add up to at most 1): integer
-// additions commute, so a round is bit-reproducible although the order of the LDS atomics is not.  Rounding a term to
-// 2^-32 is finer than the float32 sum of the ordinary row update.
+// additions commute, so a round is bit-reproducible although the order of the LDS atomics is not.
+// Rounding a term to the nearest unit is off by up to 2^-32, and where a hub's neighbours are alike by the same amount in
+// every term.  A fraction of a unit that depends on the neighbour's id is therefore added before rounding (pk_dither): the
+// error of d terms is then about 0.41 * sqrt(d) units, 2e-9 for 100 entries and 1.7e-8 for the longest row that is packed
+// (kPackedMaxRow in dynlp.hip).  Weights are divided by a degree summed in float32 over 16 lanes (rows of up to kLongRow
+// entries) or in 64 bits (longer ones, k_pk_long_degrees).  Largest error of one sweep against 64 bits, a hub of 8,000
+// equal weights with 20 nearly equal columns: 8.9e-7 with nearest units and float32 degrees, 3.7e-8 now; the row update
+// (a hub of 9,000) 1.3e-7.  The additions cost nothing that can be measured.
 //
 // Bound: the vector memory path of the CUs (a line of 128 bytes per gather through the L1; leaving out the LDS atomics
 // changes nothing, leaving out the gathers takes away half).  One round over all rows, row update -> packed round, us:
@@ -46,6 +52,7 @@ constexpr int kPkFixedLds = 1024;      // of it: reductions at the end of the ke
 constexpr unsigned int kPkWindow = 2688;  // entries between barriers (see k_pk_round)
 constexpr int kPkBuckets = 512;        // ranges of neighbour ids a part's entries are ordered by
 constexpr float kPkUnit = 2147483648.0f;  // 2^31: a row of ones sums to 2^31 and a few units, far from 2^32
+constexpr unsigned int kPkGolden = 5184445u;  // 0.618 * 2^23 (odd): multiples of it are spread evenly modulo 2^23
 
 // One entry of the packed stream: receiving row (offset in its part) << col_bits | neighbour, and
 // w / deg(row) * 2^31.
@@ -57,6 +64,11 @@ struct __attribute__((aligned(8))) PkEntry {
 // Reads through a buffer descriptor: addresses are 32-bit offsets, reads past the end return 0.
 __device__ inline __amdgpu_buffer_rsrc_t pk_buffer(const void* p, unsigned int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Between -0.5 and 0.5, evenly spread over the neighbours of a row; `lane` tells the pieces of a row apart.
+__device__ inline float pk_dither(unsigned int at, unsigned int lane) {
+    return __uint_as_float(((__umul24(at, kPkGolden) + lane) & 0x7fffffu) | 0x3f800000u) - 1.5f;
 }
 
 // The entry stream is read once per round and should not push label rows out of the L2: non-temporal.
@@ -107,27 +119,63 @@ __device__ inline void clear_round_slot(RoundCtr* slot) {  // called by one work
     }
 }
 
-// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0.
+// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0; pk_deg[v] = its degree.
 __global__ void __launch_bounds__(kBlock) k_pk_receivers(int64_t n, const RowMeta* __restrict__ meta,
-                                                        const int32_t* __restrict__ seed_class, int32_t* __restrict__ len) {
+                                                        const int32_t* __restrict__ seed_class,
+                                                        const float* __restrict__ deg, int32_t* __restrict__ len,
+                                                        float* __restrict__ pk_deg) {
     const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (v < n) len[v] = seed_class[v] < 0 ? meta[v].len : 0;
+    if (v >= n) return;
+    len[v] = seed_class[v] < 0 ? meta[v].len : 0;
+    pk_deg[v] = deg[v];
 }
 
-// part_total[p] = the entries of the updatable rows of part p; *largest = the largest part.
+// Degrees of the long rows (listed backwards from `back`), summed in 64 bits; one workgroup per row.
+__global__ void __launch_bounds__(kBlock) k_pk_long_degrees(unsigned int nl, const int32_t* __restrict__ back,
+                                                           const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                                           float* __restrict__ pk_deg) {
+    __shared__ double sm[kBlock / kWave];
+    for (unsigned int i = blockIdx.x; i < nl; i += gridDim.x) {
+        const int32_t u = back[-(long long)i];
+        const RowMeta m = meta[u];
+        double s = 0.0;
+        for (int j = threadIdx.x; j < m.len; j += kBlock) s += (double)pool[m.off + j].w;
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) s += __shfl_xor(s, d);
+        if (lane_id() == 0) sm[threadIdx.x / kWave] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBlock / kWave; ++w) s += sm[w];
+            pk_deg[u] = (float)s;
+        }
+        __syncthreads();
+    }
+}
+
+// part_total[p] = the entries of the updatable rows of part p; largest[0] = the largest part, largest[1] = the longest row.
 __global__ void __launch_bounds__(kBlock) k_pk_totals(int64_t n, int rows, const int32_t* __restrict__ len,
                                                      unsigned int* __restrict__ part_total,
                                                      unsigned int* __restrict__ largest) {
     __shared__ unsigned int smem[kBlock / kWave + 1];
     const int64_t base = (int64_t)blockIdx.x * rows;
     const int64_t end = base + rows < n ? base + rows : n;
-    unsigned int v = 0;
-    for (int64_t u = base + threadIdx.x; u < end; u += kBlock) v += (unsigned int)len[u];
+    unsigned int v = 0, longest = 0;
+    for (int64_t u = base + threadIdx.x; u < end; u += kBlock) {
+        const unsigned int l = (unsigned int)len[u];
+        v += l;
+        longest = longest > l ? longest : l;
+    }
     unsigned int total;
     (void)block_exclusive_scan<unsigned int>(v, smem, &total);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        const unsigned int o = (unsigned int)__shfl_xor((int)longest, d);
+        longest = longest > o ? longest : o;
+    }
+    if (lane_id() == 0) atomicMax(&largest[1], longest);
     if (threadIdx.x == 0) {
         part_total[blockIdx.x] = total;
-        atomicMax(largest, total);
+        atomicMax(&largest[0], total);
     }
 }
 
@@ -302,6 +350,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
     constexpr int TILES = GATHERS >= 3 ? 1 : 4 / GATHERS;
     constexpr unsigned int kStep = NW * TILES * TILE;  // entries the workgroup takes at a time
     const int mslot = lane_id() / LANES, mchunk = lane_id() % LANES;
+    const unsigned int lane_part = (unsigned int)mchunk * 2779933u;
     const unsigned int mask = (1u << a.col_bits) - 1u;
     const unsigned int stride = (unsigned int)a.stride * 4u;  // bytes of a row's sums
     const unsigned int piece = (unsigned int)mchunk * VEC * 4u;
@@ -377,7 +426,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
         for (int g0 = 0; g0 < ALL; g0 += UN) {
             Vec<VEC> f[UN];
             unsigned int to[UN];
-            float wn[UN];
+            float wn[UN], dither[UN];
 #pragma unroll
             for (int t = 0; t < UN; ++t) {
                 const int q = (g0 + t) / GATHERS, src = (g0 + t) % GATHERS * SLOTS + mslot;
@@ -389,6 +438,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
                 }
                 f[t] = pk_load_piece<VEC>(rows, (at & mask) * (unsigned int)(CP * 4) + piece);
                 to[t] = at >> a.col_bits;
+                dither[t] = pk_dither(at, lane_part);
             }
             if (mslot >= SLOTS) continue;  // the lanes left over
 #pragma unroll
@@ -398,7 +448,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
                 char* const dst = sums + byte;
                 unsigned int x[VEC];
 #pragma unroll
-                for (int k = 0; k < VEC; ++k) x[k] = (unsigned int)__builtin_rintf(wn[t] * f[t].v[k]);
+                for (int k = 0; k < VEC; ++k) x[k] = (unsigned int)__builtin_rintf(__builtin_fmaf(wn[t], f[t].v[k], dither[t]));
                 if constexpr (VEC == 1) {
                     atomicAdd(reinterpret_cast<unsigned int*>(dst), x[0]);
                 } else {

@@ -2,8 +2,8 @@
 neighbour id, sums of a part's rows in LDS): sweeps of the static solve and the rounds of a batch against the oracle,
 for every way a label row is read (1 to 16 lanes, odd column counts, the scalar layout), odd sizes and hub rows.
 
-Tolerances: one round rounds each term w / d * F to 2^-32 and w / d to float32, less than the 1e-6 that a float32 round
-is allowed; the bars of the ordinary rounds (test_gpu_parity) apply.
+Tolerances: one round rounds w / d to float32 and the sum of d terms to about 0.41 * sqrt(d) units of 2^-31, less than the
+1e-6 that a float32 round is allowed; the bars of the ordinary rounds (test_gpu_parity) apply.
 """
 import numpy as np
 import pytest
@@ -126,3 +126,40 @@ def test_loose_thresholds_keep_the_sums_of_the_row_update(C, scalar, tol):
         runs.append(out)
     for x, y in zip(*runs):
         assert np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1])
+
+
+@pytest.mark.parametrize("hub,C", [(8000, 20), (8000, 3), (8000, 64), (9000, 20)])
+def test_hub_rows_whose_neighbours_are_alike(hub, C):
+    """A hub of equal weights whose neighbours are nearly alike: rounding every term to the nearest unit would be off the
+    same way in all of them (8,000 terms: up to 2e-6).  Rows too long for the unit stay unpacked.
+    One sweep against the float64 sweep of the labels before.  Bar: four standard deviations of 0.41 * sqrt(d) units, and
+    w / d (degree, quotient) and the stored value rounded to float32, 2^-24 of the value each."""
+    rng = np.random.default_rng(7)
+    n = 36000
+    m = 65 * n
+    eu = np.concatenate([np.zeros(hub, dtype=np.int64), rng.integers(1, n, m)])
+    ev = np.concatenate([rng.permutation(np.arange(2, n))[:hub], rng.integers(1, n, m)])
+    key = np.unique(np.minimum(eu, ev)[eu != ev] * n + np.maximum(eu, ev)[eu != ev])
+    rp, col, w = W.edges_to_csr(n, key // n, key % n, np.full(key.size, 0.7, dtype=np.float32))
+    assert rp[1] - rp[0] == hub
+    sv = np.array([1], dtype=np.int32)  # one labelled vertex: the rows stay close to 1 / C
+    seed_class = np.full(n, -1, dtype=np.int32)
+    seed_class[sv] = 0
+
+    def sweeps(k):
+        with P.DynLP(n, rp, col, w, C, sv, np.zeros(1, dtype=np.int32)) as d:
+            d.static_solve(1e-12, k)
+            assert [_is_packed(r) for r in d.round_log_full()] == [hub <= 8192 and t >= 8 for t in range(k)]
+            return d.get_labels()[0].astype(np.float64)
+
+    before, worst, worst_sum = sweeps(9), 0.0, 0.0
+    for k in range(10, 14):
+        after = sweeps(k)
+        F, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), before, seed_class)
+        worst = max(worst, float(np.max(np.abs(after - F)[0])))
+        worst_sum = max(worst_sum, abs(float(after[0].sum() - F[0].sum())))
+        before = after
+    dither, value = 4 * 0.41 * np.sqrt(hub) * 2.0 ** -31, 3 * 2.0 ** -24
+    print(hub, C, "hub's row: error", worst, "bar", dither + value * F[0].max(), "sum", worst_sum, "bar", C * dither + value)
+    if hub <= 8192:
+        assert worst <= dither + value * F[0].max() and worst_sum <= C * dither + value
