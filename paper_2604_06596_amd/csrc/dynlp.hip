@@ -1510,14 +1510,15 @@ bool relaxed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, float tol)
 
 struct RelaxedRounds {
     int rounds = 0;             // executed, the ordinary round at the end included
-    bool settled = false;       // the ordinary round at the end was run
     float last = 0.f;           // max change of the last round
     unsigned int changed = 0;   // rows it moved
     unsigned int last_map = 0;  // the bitmap that holds them
     double avg_len = 0.0;
 };
 
-// Rounds it, it + 1, ... (at most `budget`): relaxed rounds over `universe`, then one ordinary round over all of it.
+// Rounds it, it + 1, ... (at most `budget`, which is not 0): relaxed rounds over `universe`, then one ordinary round over
+// all of it.  That one is always run: only its moves tell how far the rows are from their neighbours' means (a relaxed row
+// may stand still on its way past the fixed point).
 RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float tol, int it, int budget, bool binned, bool packed) {
     RelaxedRounds out;
     sync_partner(c);
@@ -1538,9 +1539,9 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
     const double omega = 2.0 / (1.0 + std::sqrt(gap * (2.0 - gap)));
     const int limit = (int)std::ceil(4.0 * 16.0 / -std::log(std::sqrt(omega - 1.0)));  // 16: log(1 / 1e-7)
     int q = 0;  // round of the stretch: bitmaps as in a fused stretch
-    bool finish = false;
-    while (q < budget) {
-        const int r = finish ? 1 : std::min(kChain, budget - q);
+    bool finish = budget == 1;
+    for (;;) {
+        const int r = finish ? 1 : std::min(kChain, budget - 1 - q);
         const size_t first_pair = c->events_used / 2;
         float* const buf[2] = {c->F, c->F2};
         for (int i = 0; i < r; ++i) {
@@ -1570,11 +1571,8 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
         if (c->time_kernels) trim_timed_spans(c, first_pair, it + q + executed);
         q += executed;
         out.last_map = (unsigned int)((q + 2) % 3);
-        if (finish) {
-            out.settled = true;
-            break;
-        }
-        finish = executed < r || (double)out.changed < kRelaxLeave * (double)universe.size() || q >= limit;
+        if (finish) break;
+        finish = executed < r || (double)out.changed < kRelaxLeave * (double)universe.size() || q >= limit || q >= budget - 1;
     }
     out.rounds = q;
     return out;
@@ -2292,7 +2290,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             const RelaxedRounds done = accelerate(c, all_rows, G, tol, 0, max_iter, binned, packed);
             it = done.rounds;
             last = done.last;
-            converged = done.settled && last <= tol;
+            converged = last <= tol;
             for (const dynlp_round_info& ri : c->log) edges += ri.entries_short + ri.entries_long;
             // the sweeps that follow find the size of their row list in the last slot
             HIPCHK(c, hipMemcpyAsync(&slot_of(c, it - 1)->next_count, &start->next_count, 2 * sizeof(unsigned int),
@@ -2638,7 +2636,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 }
                 pingpong = false;
                 known = done.changed;
-                if (done.settled && known > 0) {
+                if (known > 0) {
                     // V_aff after the ordinary round over all rows, as a list
                     RoundCtr* slot = slot_of(c, it - 1);
                     HIPCHK(c, hipMemsetAsync(&slot->next_count, 0, 2 * sizeof(unsigned int), c->stream));

@@ -137,3 +137,31 @@ def test_components_without_a_label_do_not_keep_the_call(labels, by_side):
     assert soft.min() >= 0 and soft.max() <= 1
     print("largest deviation of a row sum from 1", np.max(np.abs(soft.sum(1) - 1)))
     assert np.max(np.abs(soft.sum(1) - 1)) < SUM_ATOL
+
+
+def test_a_cap_at_a_round_that_stands_still_is_not_convergence():
+    """A ring whose vertices are all tied alike to a vertex of either class: all rows take the same way, and a relaxed step
+    passes zero while the rows are still 5 thresholds off.  Whatever the round cap, DYNLP_OK means that an ordinary round
+    moved no row by more than the threshold."""
+    n, tol = 36000, 2e-6
+    u = np.arange(n)
+    rp, col, w = W.edges_to_csr(n, u, (u + 1) % n, np.ones(n, dtype=np.float32))
+    eu = np.concatenate([u, u]).astype(np.int32)
+    ev = np.arange(n, 3 * n, dtype=np.int32)
+    ew = np.repeat([210.0 / 256, 70.0 / 256], n).astype(np.float32)
+    share = ew[0] + ew[n]
+    codes = []
+    for cap in range(2, 40):
+        with P.DynLP(n, rp, col, w, 2, None, None) as d:
+            d.set_update_mode(P.UPDATE_IN_PLACE)
+            d.set_params(tol, cap)
+            st, s = d.apply_batch(2 * n, eu, ev, ew, ev, np.repeat([1, 0], n).astype(np.int32))
+            soft = d.get_labels()[0][:n, 1].astype(np.float64)
+            assert all(r.staged == 2 for r in d.round_log_full()[:8]), "the case is meant to reach relaxed rounds"
+        mean = (np.roll(soft, 1) + np.roll(soft, -1) + ew[0]) / (2 + share)
+        codes.append(st)
+        if st == 0:
+            assert np.max(np.abs(mean - soft)) <= tol + 2.0 ** -22, cap
+        else:
+            assert s.iterations == cap and s.converged == 0
+    assert 1 in codes and 0 in codes
