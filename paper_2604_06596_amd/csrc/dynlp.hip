@@ -1495,12 +1495,16 @@ void read_slots_start(dynlp_ctx* c) {
 // labels).  Without a bound below, a graph with hardly any label would spend hundreds of rounds on errors that plain
 // rounds remove in tens.  When rows stop moving, one ordinary round over all rows decides what is in V_aff, and Step 3
 // goes on as it is listed: the stop rule and what it guarantees stay what they are without relaxation.  A phase that does
-// not settle within four times the rounds the theory gives for a factor of 1e-7 ends the same way.
+// not settle within four times the rounds the theory gives for a factor of 1e-7 ends the same way, and so does one in
+// which neither the largest move nor the number of rows that move has fallen by 1% in 32 rounds (128 while all rows move:
+// the others may be on their way behind a few that do not settle): components without a labelled vertex can oscillate for
+// ever (36,000 rows beside 39,000 such rows: 401 relaxed rounds without this rule, 105 with it).
 // Not used: on graphs whose rounds are launches and little else (kRelaxMinRows); for loose thresholds, where Step 3 is
 // over in ten or twenty rounds and the relaxed rows would only go on past it (kRelaxMaxTol); for thresholds below what
 // float32 rounding leaves moving (kRelaxMinTol).
 constexpr unsigned int kRelaxMinRows = 32768;
 constexpr float kRelaxMinTol = 2e-7f, kRelaxMaxTol = 1e-5f;
+constexpr double kRelaxStuck = 0.99;
 constexpr double kRelaxGap = 0.9, kRelaxMinGap = 2e-3, kRelaxEnter = 0.90, kRelaxLeave = 0.25;
 
 bool relaxed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, float tol) {
@@ -1540,6 +1544,11 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
     const int limit = (int)std::ceil(4.0 * 16.0 / -std::log(std::sqrt(omega - 1.0)));  // 16: log(1 / 1e-7)
     int q = 0;  // round of the stretch: bitmaps as in a fused stretch
     bool finish = budget == 1;
+    struct Progress {
+        float last;
+        unsigned int changed;
+    };
+    std::vector<Progress> chains;  // after every chain
     for (;;) {
         const int r = finish ? 1 : std::min(kChain, budget - 1 - q);
         const size_t first_pair = c->events_used / 2;
@@ -1572,7 +1581,11 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
         q += executed;
         out.last_map = (unsigned int)((q + 2) % 3);
         if (finish) break;
-        finish = executed < r || (double)out.changed < kRelaxLeave * (double)universe.size() || q >= limit || q >= budget - 1;
+        chains.push_back({out.last, out.changed});
+        const size_t k = chains.size(), back = (double)out.changed < kRelaxStuck * universe.size() ? 4 : 16;
+        const bool stuck = k > back && (double)out.last >= kRelaxStuck * chains[k - 1 - back].last &&
+                           (double)out.changed >= kRelaxStuck * chains[k - 1 - back].changed;
+        finish = stuck || executed < r || (double)out.changed < kRelaxLeave * (double)universe.size() || q >= limit || q >= budget - 1;
     }
     out.rounds = q;
     return out;

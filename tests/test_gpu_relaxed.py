@@ -126,9 +126,11 @@ def test_components_without_a_label_do_not_keep_the_call(labels, by_side):
         d.set_params(TOL, 1)  # (the rest of the solve is left to static_solve, whose first sweep is over all rows)
         assert d.apply_update(extra)[0] == 1
         st, s = d.static_solve(TOL, 20000)
+        relaxed = sum(r.staged == 2 for r in d.round_log_full())
+        print("rounds", s.iterations, "of them relaxed", relaxed)
         assert st == 0 and s.iterations < 5000
-        assert sum(r.staged == 2 for r in d.round_log_full()) > 8, "the case is meant to reach relaxed rounds"
-        print("rounds", s.iterations, "of them relaxed", sum(r.staged == 2 for r in d.round_log_full()))
+        # the labelled half settles within about 60 relaxed rounds; 32 more without progress end the phase
+        assert 8 < relaxed < 150
         soft, hard = d.get_labels()
         erp, ecol, ew_, _, esc = d.export_graph()
     cert = Cf.certificate(erp, ecol, ew_, esc, soft)
