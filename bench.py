@@ -210,6 +210,19 @@ def residual_after(base, applied, F_last, tol, rounds_total):
                 implied_by_stop_rule=(rounds_total + len(applied)) * tol + 2e-6)
 
 
+def round_kernel(staged: int, lanes: int, shared: bool, CP: int) -> str:
+    """Name of the kernel that ran a round of the library's log (dynlp_round_info)."""
+    if staged == 3:
+        return "k_pb_scatter + k_pb_gather"
+    if lanes == 0:
+        return f"k_pk_round<{CP}>"
+    if shared:
+        return f"k_rounds_persistent<{CP}, {lanes}>" if staged == 4 else f"k_tail_rounds<{CP}, {lanes}>"
+    if staged == 2:
+        return f"k_row_update_pull<{CP}, {lanes}>"
+    return f"k_row_update<{CP}, {lanes}, {'true' if staged else 'false'}>"
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -389,7 +402,7 @@ def main():
                                       hook_steps=int(ii.hook_steps), ms=round(float(ii.ms), 3)))
             info = d.round_log_full()
             for r in info:  # per kernel instantiation: launches, rows, entries, device ms
-                b = buckets.setdefault((int(r.staged), int(r.group_lanes)), [0, 0, 0, 0.0])
+                b = buckets.setdefault((int(r.staged), int(r.group_lanes), r.launch_rounds > 0), [0, 0, 0, 0.0])
                 b[0] += 1
                 b[1] += int(r.rows_short + r.rows_long)
                 b[2] += int(r.entries_short + r.entries_long)
@@ -444,7 +457,7 @@ def main():
             torch.cuda.synchronize()
             xs.append(dict(ms=(time.perf_counter() - t0) * 1e3, status=st, edges=b.num_edges, **s.as_dict()))
             for r in d.round_log_full():
-                q = xb.setdefault((int(r.staged), int(r.group_lanes)), [0, 0, 0, 0.0])
+                q = xb.setdefault((int(r.staged), int(r.group_lanes), r.launch_rounds > 0), [0, 0, 0, 0.0])
                 q[0] += 1
                 q[1] += int(r.rows_short + r.rows_long)
                 q[2] += int(r.entries_short + r.entries_long)
@@ -452,9 +465,8 @@ def main():
         progress(f"{len(xs)} batches at delta = 1e-4: {[round(x['ms'], 1) for x in xs]} ms")
         CPx = next(c for c in (1, 2, 4, 8, 16, 32, 64) if c >= Cs)
         kx = {}
-        for (staged, glanes), (cnt, rws, ent, ms) in xb.items():
-            name = ("k_pb_scatter + k_pb_gather" if staged == 3 else f"k_row_update_pull<{CPx}, {glanes}>" if staged == 2 else
-                    f"k_row_update<{CPx}, {glanes}, {'true' if staged else 'false'}>")
+        for (staged, glanes, shared), (cnt, rws, ent, ms) in xb.items():
+            name = round_kernel(staged, glanes, shared, CPx)
             kx[name] = dict(launches=cnt, rows=rws, entries=ent, device_ms=round(ms, 3), avg_launch_us=round(ms * 1e3 / max(1, cnt), 1),
                             algorithmic_GBs=round(algorithmic_bytes(rws, ent, Cs) / 1e6 / max(ms, 1e-9), 1))
         delta_block = dict(tol=1e-4, batches=len(xs), ms_per_batch=[round(x["ms"], 2) for x in xs],
@@ -473,9 +485,8 @@ def main():
     # The roofline entry is for the kernel that takes the most device time in the timed region.
     CP = next(c for c in (1, 2, 4, 8, 16, 32, 64) if c >= Cs)
     kstats = {}
-    for (staged, glanes), (cnt, rws, ent, ms) in buckets.items():
-        name = ("k_pb_scatter + k_pb_gather" if staged == 3 else f"k_row_update_pull<{CP}, {glanes}>" if staged == 2 else
-                f"k_row_update<{CP}, {glanes}, {'true' if staged else 'false'}>")
+    for (staged, glanes, shared), (cnt, rws, ent, ms) in buckets.items():
+        name = round_kernel(staged, glanes, shared, CP)
         ab = algorithmic_bytes(rws, ent, Cs)
         kstats[name] = dict(launches=cnt, rows=rws, entries=ent, device_ms=round(ms, 3),
                             avg_launch_us=round(ms * 1e3 / max(1, cnt), 1),

@@ -356,7 +356,9 @@ typedef struct dynlp_round_info {
     int64_t rows_moved;    /* rows with max_c |F'_u - F_u| > tol */
     float max_delta;       /* max_u max_c |F'_u - F_u| */
     float ms_update;       /* device time of the round's row-update launch (0 unless time_kernels) */
-    float reserved;
+    float launch_rounds;   /* 0: the round had launches of its own; else one launch ran this many rounds, this one among
+                              them (staged 4, and staged 1 where V_aff is small enough for one workgroup; ms_update is
+                              then that launch's time divided by its rounds) */
     int32_t staged;        /* 1: the round marked the next V_aff in per-vertex flags from inside the update
                               kernel (synchronous mode: rows staged by position and committed after the
                               kernel); 0: rows written by vertex and the next V_aff pulled from a bitmap of
@@ -365,7 +367,7 @@ typedef struct dynlp_round_info {
                               round's bitmap, whether the row is in V_aff (no frontier list in between); 3: as 2,
                               as a binned round (scalar labels: scatter pass + gather pass, see
                               dynlp_options.binned_rounds); 4: as 2, one of several rounds run by one launch
-                              (dynlp_options.persistent_rounds; ms_update is that launch's time divided by its rounds) */
+                              (dynlp_options.persistent_rounds) */
     int32_t group_lanes;   /* lanes per row the short-row kernel ran with; 0: the round read its entries in the order of the
                               neighbours, not row by row */
 } dynlp_round_info;

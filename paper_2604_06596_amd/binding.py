@@ -39,7 +39,7 @@ class Stats(ct.Structure):
 class RoundInfo(ct.Structure):
     _fields_ = [("rows_short", ct.c_int64), ("rows_long", ct.c_int64), ("entries_short", ct.c_int64),
                 ("entries_long", ct.c_int64), ("rows_moved", ct.c_int64), ("max_delta", ct.c_float),
-                ("ms_update", ct.c_float), ("reserved", ct.c_float), ("staged", ct.c_int32), ("group_lanes", ct.c_int32)]
+                ("ms_update", ct.c_float), ("launch_rounds", ct.c_float), ("staged", ct.c_int32), ("group_lanes", ct.c_int32)]
 
 
 class InitInfo(ct.Structure):

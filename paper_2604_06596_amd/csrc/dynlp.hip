@@ -2840,6 +2840,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             // a persistent launch that gave up at a barrier stops short without V_aff being empty
             const bool cut_short = persist_launched && executed < r && executed > 0 && c->h_slot[executed - 1].changed != 0u;
             it += executed;
+            for (int i = tail ? 0 : persist_first; i < executed; ++i)
+                c->log[c->log.size() - executed + i].launch_rounds = (float)(tail ? executed : executed - persist_first);
             if (tail) {
                 cur ^= executed & 1;
                 continue;  // V_aff is empty, has outgrown the launch, or the launch has run all its rounds

@@ -1,6 +1,7 @@
 """GPU parity of the rounds over a small V_aff that run many per launch on one workgroup (k_tail_rounds): same V_aff every
 round, same labels as the oracle's Step 3 and as the ordinary launches (a fixed number of lanes per row keeps those), in
-batches whose V_aff stays small, outgrows the launch and comes back, or is cut by the round cap inside a launch.
+batches whose V_aff stays small, outgrows the launch and comes back, or is cut by the round cap inside a launch.  The
+round log says which rounds shared a launch (launch_rounds).
 """
 import numpy as np
 import pytest
@@ -24,9 +25,11 @@ def _run(p, b, tol, cap, mode, **kw):
         st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
         soft, hard = d.get_labels()
         sizes, deltas = d.round_log()
+        log = d.round_log_full()
         st2, s2 = d.apply_batch(0, None, None, None)  # no mark may be left behind
         assert cap < 20000 or (st2 == 0 and s2.iterations == 0)
-    return start, st, s, soft, hard, sizes, deltas
+    assert len(log) == s.iterations
+    return start, st, s, soft, hard, sizes, deltas, log
 
 
 # deg: frontier rows of about that many entries, far from 8, where narrow rows change between 4 and 16 lanes
@@ -41,8 +44,17 @@ def test_small_rounds_match_the_oracle_and_the_ordinary_launches(kind, C, scalar
 
     p, p0 = make(), make()
     b = W.chung_lu_vertex_batch(p, 2, 0.0) if kind == "hub" else W.small_random_batch(p, 1, deg, 0, num_extra_edges=3, num_revealed=1)
-    start, st, s, soft, hard, sizes, deltas = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar)
-    _, st1, s1, soft1, hard1, sizes1, _ = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar, group_lanes=lanes)
+    start, st, s, soft, hard, sizes, deltas, log = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar)
+    _, st1, s1, soft1, hard1, sizes1, _, log1 = _run(p0, b, tol, cap, P.UPDATE_SYNCHRONOUS, binary_scalar=scalar, group_lanes=lanes)
+    shared = np.array([r.launch_rounds for r in log])
+    print(kind, C, tol, cap, "rounds that shared launches", shared.astype(int).tolist())
+    # a first V_aff that may bring its neighbours runs in a shared launch if those fit it
+    rows = 1024 if C <= 2 else 512 if C <= 16 else 256
+    mean = (p0.row_ptr[-1] + 2 * len(b.eu)) / (p0.n + b.num_new_vertices)
+    assert (shared[0] > 0) == (sizes[0] * mean <= rows)
+    if cap == 3 and lanes == 4:
+        assert shared.tolist() == [3, 3, 3], "the cap is meant to fall inside a launch"
+    assert not any(r.launch_rounds for r in log1)
     assert (st, s.iterations, s.rows_updated, s.edges_traversed) == (st1, s1.iterations, s1.rows_updated, s1.edges_traversed)
     assert sizes.tolist() == sizes1.tolist() and np.array_equal(soft, soft1)
     g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
@@ -66,7 +78,8 @@ def test_small_rounds_match_the_oracle_and_the_ordinary_launches(kind, C, scalar
         assert np.max(np.abs(soft - o2["F"])) <= (ROUNDS_ATOL if sizes.tolist() == osz.tolist() else ROUNDS_ATOL + 2 * tol)
     else:
         # rows updated in place take another path to labels that stopped under the same rule
-        _, st2, s2, soft2, _, sizes2, _ = _run(p0, b, tol, cap, P.UPDATE_IN_PLACE, binary_scalar=scalar)
+        _, st2, s2, soft2, _, sizes2, _, log2 = _run(p0, b, tol, cap, P.UPDATE_IN_PLACE, binary_scalar=scalar)
+        assert (log2[0].launch_rounds > 0) == (shared[0] > 0)
         assert st2 == 0 and sizes2[0] == sizes[0] and np.max(np.abs(soft2 - soft)) <= 100 * tol
 
 
@@ -115,3 +128,35 @@ def test_averaged_rows_begin_where_ordinary_launches_begin_them(C):
     print(C, "rounds", rounds, rounds1)
     assert rounds == rounds1 and sizes.tolist() == sizes1.tolist() and np.array_equal(deltas, deltas1)
     assert np.array_equal(soft, soft1) and np.array_equal(hard, hard1)
+
+
+@pytest.mark.parametrize("C", [2, 20, 50])
+def test_long_rows_leaving_and_coming_back(C):
+    """V_aff with rows of more than 128 entries, and one that outgrows the launch and comes back."""
+    p0 = W.chung_lu(4000, C, 10.0, 2.1, 600, 0.8, 0.05, 55)
+    hubs = np.argsort(-np.diff(p0.row_ptr), kind="stable")
+    is_seed = np.zeros(p0.n, dtype=bool)
+    is_seed[p0.seed_vertex] = True
+    hub = int(next(h for h in hubs if not is_seed[h] and p0.row_ptr[h + 1] - p0.row_ptr[h] <= 500))
+    assert p0.row_ptr[hub + 1] - p0.row_ptr[hub] > 128
+    seen = dict(long=False, back=False)
+    for tol in (3e-3, 1e-3, 3e-4, 1e-4):
+        for w in (0.01, 0.1, 1.0):
+            for cap in (20000, 3, 11):
+                runs = []
+                for lanes in (0, 16):
+                    with P.DynLP(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class, group_lanes=lanes) as d:
+                        d.static_solve(1e-7, 20000)
+                        d.set_params(tol, cap)
+                        d.apply_batch(1, np.array([p0.n], np.int32), np.array([hub], np.int32), np.array([w], np.float32),
+                                      np.array([p0.n], np.int32), np.array([C - 1], np.int32))
+                        runs.append((d.get_labels()[0], d.round_log()[0], d.round_log_full()))
+                assert np.array_equal(runs[0][0], runs[1][0]) or C <= 4  # narrow rows may take 4 lanes in the first run
+                assert runs[0][1].tolist() == runs[1][1].tolist() or C <= 4
+                log = runs[0][2]
+                shared = [r.launch_rounds > 0 for r in log]
+                seen["long"] |= any(r.rows_long > 0 and q for r, q in zip(log, shared))
+                first_out = shared.index(False) if False in shared else len(log)
+                seen["back"] |= any(shared[:first_out]) and any(shared[first_out:])
+    print(C, seen)
+    assert all(seen.values())
