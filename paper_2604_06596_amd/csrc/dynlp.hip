@@ -2626,6 +2626,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         // rounds from round chain0 on.  A launch of k_tail_rounds that ends inside a chain leaves the rest of it to
         // ordinary rounds, so that the order of every row's sum is the same whether or not rounds share launches.
         int chain0 = 0, G = 16;
+        // chains without a shared launch after one that found too many entries in its first list: 1, 2, 4, ... 64
+        int tail_wait = 0, tail_refused = 0;
         for (;;) {
         while (known > 0 && it < c->max_iter) {
             const int chain_off = (it - chain0) % kChain;
@@ -2710,7 +2712,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             const bool persist = pingpong && fused && !binned && persistent_rounds_pay(c, universe);
             // (callers who fix the lanes per row or ask for binned rounds get them; rows so long that they are worth more
             // than 16 lanes do not come in numbers that one CU should handle)
-            const bool tail = !pingpong && c->group_lanes == 0 && G <= 16 && !(can_bin && c->binned > 0) &&
+            if (new_chain && tail_wait > 0) --tail_wait;
+            const bool tail = !pingpong && tail_wait == 0 && c->group_lanes == 0 && G <= 16 && !(can_bin && c->binned > 0) &&
                               tail_rounds_pay(c, known, known_before, avg_len);
             // where every row that is affected now may bring its neighbours and V_aff then holds nearly every vertex, the
             // first chain is short: the relaxed rounds over all rows that follow cost half a flag-marking round
@@ -2844,6 +2847,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 c->log[c->log.size() - executed + i].launch_rounds = (float)(tail ? executed : executed - persist_first);
             if (tail) {
                 cur ^= executed & 1;
+                if (executed > 0) tail_refused = 0;
+                else tail_wait = 1 + (1 << std::min(tail_refused++, 6));
                 continue;  // V_aff is empty, has outgrown the launch, or the launch has run all its rounds
             }
             if (cut_short || short_first) chain0 = it;

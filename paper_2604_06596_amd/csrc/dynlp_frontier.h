@@ -782,10 +782,14 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
 // committed after a barrier, or written in place), and appends the vertices it marks for the first time straight to the next list, so that nothing
 // scans the marks; those it has set it clears again.  All data between rounds stays with one CU: a workgroup's own
 // stores are visible to it after a barrier.  Measured: see tail_rounds_pay in dynlp.hip.
-// The launch ends when V_aff is empty, after `rounds` rounds, when V_aff or its entries outgrow one CU, or where a chain of
+// The launch ends when V_aff is empty, after `rounds` rounds, when V_aff or its entries outgrow one CU (also before its
+// first round: the host knows how many rows there are, but not that a few of them are hubs), or where a chain of
 // ordinary rounds would go on with another number of lanes per row or with averaged rows (both decided by the host); the
 // list of the next round is then where an ordinary round expects it.
 constexpr int kTailThreads = 1024;
+
+// A row's entries, cut where they are beyond every limit: the sum over all rows a round may list fits 32 bits.
+__device__ inline unsigned int tail_entries(int len) { return len < 65536 ? (unsigned int)len : 65536u; }
 
 struct TailArgs {
     RoundCtr* ring;
@@ -838,9 +842,17 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
         }
     }
     __syncthreads();
+    if (count[0] + count[1] <= a.max_rows) {  // the entries of the first round (the host knows their number of rows)
+        unsigned int e = 0;
+        for (unsigned int i = threadIdx.x; i < count[0] + count[1]; i += kTailThreads)
+            e += tail_entries(a.meta[frontier_vertex(a.front[0], a.back[0], count[0], i)].len);
+        e = wave_sum(e);
+        if (lane_id() == 0) atomicAdd(&next[2], e);
+    }
+    __syncthreads();
     for (int r = 0; r < a.rounds; ++r) {
         const unsigned int ns = count[0], nl = count[1];  // uniform from here on
-        if (ns + nl == 0u || leave || (r > 0 && (ns + nl > a.max_rows || next[2] > a.max_entries))) return;
+        if (ns + nl == 0u || leave || ns + nl > a.max_rows || next[2] > a.max_entries) return;
         __syncthreads();
         if (threadIdx.x == 0) {
             next[0] = next[1] = next[2] = 0u;
@@ -859,7 +871,7 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             const unsigned int bit = 1u << (((unsigned int)v & 3u) * 8u);
             if (atomicOr(reinterpret_cast<unsigned int*>(a.flag) + ((unsigned int)v >> 2), bit) & bit) return;
             const int len = a.meta[v].len;
-            atomicAdd(&next[2], (unsigned int)len);
+            atomicAdd(&next[2], tail_entries(len));
             if (len > kLongRow) nback[-(long long)atomicAdd(&next[1], 1u)] = v;
             else nfront[atomicAdd(&next[0], 1u)] = v;
         };

@@ -160,3 +160,29 @@ def test_long_rows_leaving_and_coming_back(C):
                 seen["back"] |= any(shared[:first_out]) and any(shared[first_out:])
     print(C, seen)
     assert all(seen.values())
+
+
+@pytest.mark.parametrize("C,limit", [(2, 8192), (10, 3072), (50, 1536)])
+def test_a_few_hubs_are_not_left_to_one_workgroup(C, limit):
+    """A small V_aff of hubs holds far more entries than its number of rows says: such a round does not share a launch."""
+    p0 = W.chung_lu(20000, C, 30.0, 2.1, 6000, 0.8, 0.02, 56)
+    is_seed = np.zeros(p0.n, dtype=bool)
+    is_seed[p0.seed_vertex] = True
+    lens = np.diff(p0.row_ptr)
+    hubs = [int(h) for h in np.argsort(-lens, kind="stable") if not is_seed[h]][:8]
+    assert lens[hubs].sum() > limit
+    runs = []
+    for lanes in (0, 16):
+        with P.DynLP(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class, group_lanes=lanes) as d:
+            d.static_solve(1e-7, 20000)
+            for tol in (1e-1, 1e-3, 1e-4):
+                new = d.num_vertices
+                d.set_params(tol, 20000)
+                d.apply_batch(1, np.full(8, new, np.int32), np.array(hubs, np.int32), np.full(8, 0.05, np.float32),
+                              np.array([new], np.int32), np.array([0], np.int32))
+                log = d.round_log_full()
+                assert all(r.entries_short + r.entries_long <= limit for r in log if r.launch_rounds > 0)
+                assert log[0].entries_long > limit
+            runs.append((d.get_labels()[0], d.round_log()[0]))
+    if C > 4:
+        assert np.array_equal(runs[0][0], runs[1][0]) and runs[0][1].tolist() == runs[1][1].tolist()
