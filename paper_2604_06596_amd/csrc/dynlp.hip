@@ -256,8 +256,22 @@ void* dev_try_alloc(dynlp_ctx* c, size_t bytes) {
     return p;
 }
 
-void* dev_alloc(dynlp_ctx* c, size_t bytes) {
+void free_binned(dynlp_ctx* c);
+void free_packed(dynlp_ctx* c);
+
+// As dev_try_alloc, for an array that a call cannot do without: the arrays of the binned and packed rounds, which only
+// save time and are laid out again by the next solve or batch that wants them, give way to it.  (Called outside of rounds.)
+void* dev_alloc_or_reclaim(dynlp_ctx* c, size_t bytes) {
     void* p = dev_try_alloc(c, bytes);
+    if (p || (!c->pk_ent && !c->pb_src)) return p;
+    (void)hipStreamSynchronize(c->stream);
+    free_packed(c);
+    free_binned(c);
+    return dev_try_alloc(c, bytes);
+}
+
+void* dev_alloc(dynlp_ctx* c, size_t bytes) {
+    void* p = dev_alloc_or_reclaim(c, bytes);
     if (!p) {
         c->err = "device allocation of " + std::to_string(bytes) + " bytes failed";
         c->poisoned = true;
@@ -285,7 +299,7 @@ struct Temp {
     dynlp_ctx* c;
     T* ptr = nullptr;
     Temp(dynlp_ctx* ctx, int64_t count) : c(ctx) {
-        ptr = static_cast<T*>(dev_try_alloc(c, (size_t)std::max<int64_t>(count, 1) * sizeof(T)));
+        ptr = static_cast<T*>(dev_alloc_or_reclaim(c, (size_t)std::max<int64_t>(count, 1) * sizeof(T)));
         if (!ptr) {
             c->err = "device allocation of " + std::to_string((size_t)std::max<int64_t>(count, 1) * sizeof(T)) +
                      " bytes failed (the context is unchanged)";
@@ -1241,19 +1255,12 @@ auto packed_kernel(const dynlp_ctx* c, Fn fn) {
 }
 
 // Lays the entries of the graph as it stands out for the packed rounds (universe: all updatable vertices).  False: no
-// memory (and nothing kept), parts so uneven that the largest would keep a round waiting, or a row that is too long; the
-// caller then runs ordinary rounds.
+// memory, parts so uneven that the largest would keep a round waiting, or a row that is too long (no array of entries is
+// kept); the caller then runs ordinary rounds.
 bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan) {
     const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), tab = parts + 3;
     bool ok = true;
-    if (ent > c->pk_ent_cap) {
-        dev_free(c, c->pk_ent);
-        c->pk_ent = nullptr;
-        c->pk_ent_cap = 0;
-        ok = try_alloc_n(c, c->pk_ent, ent + ent / 8);
-        if (ok) c->pk_ent_cap = ent + ent / 8;
-    }
-    if (ok && c->n > c->pk_vcap) {
+    if (c->n > c->pk_vcap) {
         dev_free(c, c->pk_len);
         dev_free(c, c->pk_deg);
         c->pk_len = nullptr;
@@ -1301,7 +1308,18 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
     unsigned int most[2] = {0, 0};
     HIPCHK(c, hipMemcpyAsync(most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if ((double)most[0] > kPackedUneven * (double)ent / (double)parts || most[1] > kPackedMaxRow) return false;
+    const bool refused = (double)most[0] > kPackedUneven * (double)ent / (double)parts || most[1] > kPackedMaxRow;
+    if (refused || ent > c->pk_ent_cap) {
+        dev_free(c, c->pk_ent);
+        c->pk_ent = nullptr;
+        c->pk_ent_cap = 0;
+        if (refused) return false;
+        if (!try_alloc_n(c, c->pk_ent, ent + ent / 8)) {
+            free_packed(c);
+            return false;
+        }
+        c->pk_ent_cap = ent + ent / 8;
+    }
     if (universe.nl)
         hipLaunchKernelGGL(k_pk_long_degrees, dim3(std::min<unsigned int>(universe.nl, (unsigned int)c->num_cu * 8)), dim3(kBlock), 0,
                            c->stream, universe.nl, universe.back, c->meta, c->pool, c->pk_deg);

@@ -173,3 +173,66 @@ def test_calls_that_change_nothing_survive_an_allocator_without_memory():
         st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
         assert st == 0
     assert not a.live
+
+
+class BudgetAllocator(TorchAllocator):
+    """Refuses what would exceed ``budget`` bytes in all; ``peak``: the most it has handed out at a time."""
+
+    def __init__(self, budget):
+        super().__init__()
+        self.used = self.peak = 0
+        self.refuse = lambda nbytes: self.used + nbytes > budget
+
+    def alloc(self, nbytes):
+        ptr = super().alloc(nbytes)
+        if ptr:
+            self.used += self.live[ptr].numel()
+            self.peak = max(self.peak, self.used)
+        return ptr
+
+    def free(self, ptr):
+        self.used -= self.live[ptr].numel()
+        super().free(ptr)
+
+
+def test_arrays_of_packed_rounds_give_way_to_the_graph():
+    """An allocator with just the memory that solve and batch need without packed rounds (a fixed number of lanes per row
+    excludes them) is enough with them too: their arrays are given back when the batch's arrays and the larger pool of
+    edges do not fit beside them."""
+    def run(budget, **kw):
+        mk = lambda: W.sbm(36001, 10, 20, 8.0, 0.03, 41)
+        p, p0 = mk(), mk()
+        b = W.sbm_vertex_batch(p, 6000, 20, 0.02)
+        a = BudgetAllocator(budget)
+        with P.DynLP(p0.n, p0.row_ptr, p0.col, p0.w, p0.C, p0.seed_vertex, p0.seed_class, allocator=a, slack_factor=1.01, **kw) as d:
+            d.static_solve(TOL, 20000)
+            packed = any(r.group_lanes == 0 for r in d.round_log_full())
+            d.set_params(TOL, 20000)
+            st, _ = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            assert st == 0
+            soft, _ = d.get_labels()
+        assert not a.live
+        return soft, packed, a
+
+    soft0, packed0, a0 = run(1 << 40, group_lanes=16)
+    soft, packed, a = run(a0.peak + (1 << 20))
+    assert not packed0 and packed and a.refused > 0
+    assert np.max(np.abs(soft - soft0)) <= 100 * TOL  # packed and ordinary rounds end under the same stop rule
+
+
+def test_graphs_that_packed_rounds_refuse_keep_no_entries_for_them():
+    """A hub too long for the packed sums: the solve runs ordinary sweeps, and no array as large as the entries stays."""
+    rng = np.random.default_rng(5)
+    n = 40000
+    eu = np.concatenate([np.zeros(9000, dtype=np.int64), rng.integers(1, n, 12 * n)])
+    ev = np.concatenate([rng.permutation(np.arange(1, n))[:9000], rng.integers(1, n, 12 * n)])
+    keep = eu != ev
+    rp, col, w = W.edges_to_csr(n, eu[keep], ev[keep], rng.uniform(0.1, 1, int(keep.sum())).astype(np.float32))
+    sv = rng.permutation(np.arange(1, n))[:800].astype(np.int32)
+    a = TorchAllocator()
+    with P.DynLP(n, rp, col, w, 10, sv, rng.integers(0, 10, 800).astype(np.int32), allocator=a) as d:
+        before = sum(t.numel() for t in a.live.values())
+        d.static_solve(1e-9, 20)
+        assert not any(r.group_lanes == 0 for r in d.round_log_full())
+        assert sum(t.numel() for t in a.live.values()) - before < 4 * col.size
+    assert not a.live
