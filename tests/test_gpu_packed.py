@@ -163,3 +163,34 @@ def test_hub_rows_whose_neighbours_are_alike(hub, C):
     print(hub, C, "hub's row: error", worst, "bar", dither + value * F[0].max(), "sum", worst_sum, "bar", C * dither + value)
     if hub <= 8192:
         assert worst <= dither + value * F[0].max() and worst_sum <= C * dither + value
+
+
+def test_rows_that_take_several_generations_of_parts():
+    """64 columns: the sums of 155,648 rows fit the chip at a time, a graph of 158,001 takes two workgroups per CU one
+    after the other.  Sweeps and the rounds of a batch against the oracle."""
+    C, n = 64, 158001
+    p, p0 = (W.sbm(n, C, 34, 8.0, 0.03, 95) for _ in range(2))
+    b = W.sbm_vertex_batch(p, 1500, 34, 0.02)
+    g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, C, p0.seed_vertex, p0.seed_class)
+    rp, col, w = g.csr()
+    F = R.initial_labels(g.seed_class, C)
+    for _ in range(12):
+        F, _ = ON.itlp_sweep(rp, col, w, F, g.seed_class)
+    with _make(p0) as d:
+        d.static_solve(1e-9, 12)
+        assert [_is_packed(r) for r in d.round_log_full()] == [False] * 8 + [True] * 4
+        cold, _ = d.get_labels()
+        d.set_params(TOL, 10)
+        d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        assert any(_is_packed(r) for r in d.round_log_full())
+        soft, _ = d.get_labels()
+        sizes, _ = d.round_log()
+    assert np.max(np.abs(cold - F)) <= ROUNDS_ATOL
+    g.insert(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+    rp, col, w = g.csr()
+    A0 = ON.affected_set(rp, col, g.seed_class, n, b.eu, b.ev, b.seed_vertex)
+    F = np.concatenate([cold.astype(np.float64), np.full((b.num_new_vertices, C), 1.0 / C)])
+    F[b.seed_vertex] = np.eye(C)[b.seed_class]
+    o2 = ON.step3_propagate(rp, col, w, F, g.seed_class, A0, TOL, 10)
+    assert np.all(np.abs(sizes - o2["frontier_sizes"]) <= 2e-3 * np.maximum(o2["frontier_sizes"], 1000))
+    assert np.max(np.abs(soft - o2["F"])) <= ROUNDS_ATOL
