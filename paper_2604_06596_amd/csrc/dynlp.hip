@@ -1171,7 +1171,9 @@ void launch_binned_round(dynlp_ctx* c, const PullRoundArgs& a, int round, bool f
 // degree 8: 9 us with the row update) and the layout of the entries is one more thing to wait for.
 constexpr unsigned int kPackedMinRows = 32768;
 // kPackedShare: see packed_rounds_pay; kPackedUneven: a part with more than this many times the mean entries would keep
-// the round waiting for one CU.  kPackedMaxRow: longer rows would show the unit of the packed sums (see dynlp_packed.h).
+// the round waiting for one CU (us per round, row update / packed, largest part 1 / 2 / 3 / 4 times the mean: 150,000 vertices
+// of degree 20 with 10 columns 61 / 37, 61 / 56, 63 / 77, 64 / 93; with 29 columns 73 / 49, 73 / 75, 72 / 102, 74 / 128;
+// 400,000 with 10 columns 152 / 78, 151 / 133, 152 / 183, 155 / 235).  kPackedMaxRow: longer rows would show the unit of the packed sums (see dynlp_packed.h).
 constexpr unsigned int kPackedMaxRow = 8192;
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
 // Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk
@@ -1199,6 +1201,8 @@ bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan*
     int row_bits = 5, col_bits = 1;
     while (((int64_t)1 << row_bits) < rows) ++row_bits;
     while (((int64_t)1 << col_bits) < c->n) ++col_bits;
+    // an entry keeps its row's place in the part and its neighbour's id in one word, which ends the packed rounds at about
+    // 2^20 vertices with up to 15 columns, 2^21 with 17 to 33 and 2^22 with 50 and more
     if (row_bits + col_bits > 32) return false;
     int bucket_bits = 0;
     while (((c->n - 1) >> bucket_bits) >= kPkBuckets) ++bucket_bits;
@@ -1507,21 +1511,42 @@ void read_slots_start(dynlp_ctx* c) {
 // eigenvalues of the update lie in [-1, 1], and with omega = 2 / (1 + sqrt(1 - mu^2)) an error shrinks by
 // sqrt(omega - 1) per round instead of mu, the update's largest eigenvalue.  mu is at least the Rayleigh quotient of the
 // constant vector, 1 - (weight of the edges to labelled vertices) / (weight of all edges of updatable rows); kRelaxGap
-// times the sampled quotient's distance from 1, kept above kRelaxMinGap, sets omega (1,000,000 vertices with 10 / power
-// law with 50 classes / 100,000 kNN / 50M scalar, factor 0.8: 11.5 / 137 / 3.0 / 210 ms, 1.0: 12.0 / 165 / 3.2 / 192 ms,
-// 2.0: 12.8 / 244 / 4.3 / 194 ms; without relaxation 42 / 412 / 19 / 290 ms, and two to ten times further from the exact
-// labels).  Without a bound below, a graph with hardly any label would spend hundreds of rounds on errors that plain
-// rounds remove in tens.  When rows stop moving, one ordinary round over all rows decides what is in V_aff, and Step 3
-// goes on as it is listed: the stop rule and what it guarantees stay what they are without relaxation.  A phase that does
-// not settle within four times the rounds the theory gives for a factor of 1e-7 ends the same way, and so does one in
-// which neither the largest move nor the number of rows that move has fallen by 1% in 32 rounds (128 while all rows move:
-// the others may be on their way behind a few that do not settle): components without a labelled vertex can oscillate for
-// ever (36,000 rows beside 39,000 such rows: 401 relaxed rounds without this rule, 105 with it).
-// Not used: on graphs whose rounds are launches and little else (kRelaxMinRows); for loose thresholds, where Step 3 is
-// over in ten or twenty rounds and the relaxed rows would only go on past it (kRelaxMaxTol); for thresholds below what
-// float32 rounding leaves moving (kRelaxMinTol).
+// times the sampled quotient's distance from 1, kept above kRelaxMinGap, sets omega.  When rows stop moving, one ordinary
+// round over all rows decides what is in V_aff, and Step 3 goes on as it is listed: the stop rule and what it guarantees
+// stay what they are without relaxation.  A phase that does not settle within four times the rounds the theory gives for a
+// factor of 1e-7 ends the same way, and so does one in which neither the largest move nor the number of rows that move has
+// fallen by 1% in 32 rounds (128 while all rows move: the others may be on their way behind a few that do not settle):
+// components without a labelled vertex can oscillate for ever (36,000 rows beside 39,000 such rows: 401 relaxed rounds
+// without this rule, 105 with it).
+// Measured, ms per call at tol = 1e-6 (second row: distance from the exact labels, 2-norm, relative):
+//   kRelaxGap                       none     0.7     0.8     0.9     1.0    1.15     1.3     1.5     2.0
+//   1M planted blocks, 10 classes   41.2    11.3    11.3     9.9     9.9     9.8    10.1    10.1    10.8
+//                                 1.9e-4  3.7e-6  2.3e-6  6.7e-6  3.3e-5  4.6e-5  4.5e-5  5.2e-5  8.7e-5
+//   300K planted blocks, 29         35.1     8.3     7.8     7.6     7.4     7.4     7.4     7.8     8.6
+//   1M power law, 50 classes         627     114      98     115     124     134     144     157     183
+//                                 4.7e-4  9.0e-5  1.5e-5  2.3e-5  3.7e-5  7.4e-5  8.7e-5  1.0e-4  1.3e-4
+//   120K power law, 20 classes      24.4    3.70    3.42    3.73    3.85    4.12    4.28    4.54    5.20
+//   100K kNN, 10 classes            18.9    2.50    2.57    2.84    3.01    3.24    3.43    3.72    3.95
+//   50K kNN, 6 classes              12.4    1.75    1.71    1.92    2.01    2.15    2.36    2.50    2.77
+//   50M scalar, one batch            371     204     197     187     188     178     176     186     187
+// (50M: fastest of five; allocating its arrays takes 5 to 1,700 ms once the process has used all device memory before.)
+// kRelaxLeave, the share of moved rows below which the phase ends: 0.05 ... 0.25 within 12% of each other on these graphs;
+// 0.5: 100K kNN 2.85 -> 2.48 ms, but 50K kNN 1.84 -> 3.96 ms (201 rounds); 0.75: 5.5 and 5.4 ms.
+// kRelaxMinGap keeps omega from 2 where labels are scarce.  300K planted blocks, 0.1% labelled: 67 ms without relaxation,
+// 9.0 / 9.2 / 11.5 / 14.1 / 16.9 ms with 5e-4 / 1e-3 / 2e-3 / 4e-3 / 8e-3; 0.01%: 406 ms, 43 / 52 / 57 / 41 / 29 ms at
+// 1.3e-3 / 1.8e-3 / 3.6e-3 / 8.0e-3 / 1.5e-2 from the exact labels; 0.001%: 2.1 s without and with 2e-3, 51 ms with 1e-5.
+// Not used: for loose thresholds, where Step 3 is over in ten or twenty rounds and the relaxed rounds would only go on past
+// it (kRelaxMaxTol; tol = 3e-5, without and with: 300K planted blocks 2.6 / 5.5, 1M 3.2 / 5.5, 1M power law 80 / 67, 100K
+// kNN 7.2 / 1.9 ms); for thresholds below what float32 rounding leaves moving (kRelaxMinTol; tol = 1e-7: 100K kNN 37 / 7.0,
+// but one pass of five 141 ms, 50K kNN 19 / 29 ms).  Between kRelaxNowTol and kRelaxMaxTol a batch has one chain of ordinary
+// rounds first, in which V_aff collapses on the graphs that need no more (ms without / at once / after a chain; tol = 1e-5:
+// 1M planted blocks 3.7 / 6.9 / 3.3, 600K 2.1 / 3.7 / 1.9, 300K 15.9 / 6.1 / 4.9, 250K power law 9.1 / 3.6 / 4.2, 100K kNN
+// 10.5 / 2.1 / 2.5; 5e-6: 5.1 / 8.3 / 4.0, 3.5 / 3.8 / 2.2, 21 / 6.2 / 5.5, 12.6 / 4.2 / 4.5, 12.6 / 2.3 / 2.7; 3e-6: 6.8 /
+// 8.3 / 12.6, 8.5 / 4.4 / 4.7, 26 / 6.8 / 5.9, 14.6 / 4.2 / 4.8, 14.4 / 2.6 / 2.7; 2e-6, without / at once: 1M 24 / 9.5).
+// kRelaxMinRows is where packed rounds begin; smaller graphs would gain as well (8,000 planted vertices 8.2 -> 1.2 ms,
+// 16,000 kNN 7.1 -> 1.2 ms).
 constexpr unsigned int kRelaxMinRows = 32768;
-constexpr float kRelaxMinTol = 2e-7f, kRelaxMaxTol = 1e-5f;
+constexpr float kRelaxMinTol = 2e-7f, kRelaxNowTol = 4e-6f, kRelaxMaxTol = 1e-5f;
 constexpr double kRelaxStuck = 0.99;
 constexpr double kRelaxGap = 0.9, kRelaxMinGap = 2e-3, kRelaxEnter = 0.90, kRelaxLeave = 0.25;
 
@@ -2639,6 +2664,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         // more than tol (and their neighbours) start Step 3 again.  check_round = index of the running check round.
         int final_checks = 0, check_round = -1;
         bool relaxed = false;  // the batch has had its relaxed rounds (accelerate)
+        bool relax_now = c->tol <= kRelaxNowTol;  // else after one more chain, if V_aff is still that large
         bool verified = !c->final_check;
         // How the rounds run (lanes per row, stretches, averaged rows) is decided where a chain begins, every kChain
         // rounds from round chain0 on.  A launch of k_tail_rounds that ends inside a chain leaves the rest of it to
@@ -2651,8 +2677,11 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             const int chain_off = (it - chain0) % kChain;
             const bool new_chain = chain_off == 0;
             if (new_chain) G = choose_group(c, avg_len);
-            if (new_chain && !relaxed && it != check_round && (double)known >= kRelaxEnter * (double)universe.size() &&
-                relaxed_rounds_pay(c, universe, c->tol)) {
+            const bool may_relax = new_chain && !relaxed && it != check_round &&
+                                   (double)known >= kRelaxEnter * (double)universe.size() && relaxed_rounds_pay(c, universe, c->tol);
+            const bool relax = may_relax && relax_now;
+            relax_now = relax_now || may_relax;
+            if (relax) {
                 relaxed = true;
                 const bool use_bins = binned_rounds_pay(c, universe) && (c->pb_built || build_binned(c));
                 const bool use_pack = !use_bins && packed_rounds_pay(c, universe, &pk_plan) && (c->pk_built || build_packed(c, universe, pk_plan));

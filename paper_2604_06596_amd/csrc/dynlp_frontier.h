@@ -490,7 +490,6 @@ __device__ inline unsigned int row_update_short(unsigned int bid, unsigned int n
         Edge e;
         e.col = u;
         e.w = 0.f;
-        // asked for before the neighbours' rows, so that the row does not wait for one more read at its end
         accumulate_row<CP, G, COH>(row, m.len, 0, 1, u, F_in, gl, acc, s, e);
         const Vec<VEC> old = load_row<VEC, COH>(F_in + (size_t)u * CP + chunk * VEC);
         Vec<VEC> fn, before = old;

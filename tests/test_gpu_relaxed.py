@@ -167,3 +167,26 @@ def test_a_cap_at_a_round_that_stands_still_is_not_convergence():
         else:
             assert s.iterations == cap and s.converged == 0
     assert 1 in codes and 0 in codes
+
+
+@pytest.mark.parametrize("tol,relaxes", [(1e-6, True), (4e-6, True), (1e-5, False)])
+def test_between_tight_and_loose_thresholds_v_aff_may_collapse_first(tol, relaxes):
+    """Planted blocks and a small batch: V_aff reaches nearly all rows, and at a threshold of 1e-5 ordinary rounds shrink
+    it within a chain, so that relaxed rounds would only go on past it (packed rounds are relaxed ones in this mode)."""
+    p, p0 = (W.sbm(60000, 5, 12.0, 8.0, 0.02, 91) for _ in range(2))
+    b = W.sbm_vertex_batch(p, 120, 12, 0.02)
+    with _make(p0) as d:
+        assert d.static_solve(1e-6, 20000)[0] == 0
+        d.set_params(tol, 20000)
+        st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        sizes = [r.rows_short + r.rows_long for r in d.round_log_full()]
+        relaxed = sum(r.group_lanes == 0 for r in d.round_log_full())
+        soft, _ = d.get_labels()
+    print(tol, "rounds", len(sizes), "relaxed", relaxed, "sizes", sizes[:14])
+    assert st == 0 and max(sizes) > 0.95 * 58900, "the case is meant to reach nearly all rows"
+    assert (relaxed > 0) == relaxes
+    g = R.Graph(p0.n, p0.row_ptr, p0.col, p0.w, 5, p0.seed_vertex, p0.seed_class)
+    g.insert(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+    rp, col, w = g.csr()
+    cert = Cf.certificate(rp, col, w, g.seed_class, soft)
+    assert cert.res <= Cf.local_stop_residual(tol, s.iterations, Cf.stop_rule_residual(1e-6))
