@@ -52,7 +52,7 @@ constexpr int kPkFixedLds = 1024;      // of it: reductions at the end of the ke
 constexpr unsigned int kPkWindow = 2688;  // entries between barriers (see k_pk_round)
 constexpr int kPkBuckets = 512;        // ranges of neighbour ids a part's entries are ordered by
 constexpr float kPkUnit = 2147483648.0f;  // 2^31: a row of ones sums to 2^31 and a few units, far from 2^32
-constexpr unsigned int kPkGolden = 5184445u;  // 0.618 * 2^23 (odd): multiples of it are spread evenly modulo 2^23
+constexpr unsigned int kPkGolden = 3204163u;  // 0.382 * 2^23 (odd): multiples of it are spread evenly modulo 2^23
 
 // One entry of the packed stream: receiving row (offset in its part) << col_bits | neighbour, and
 // w / deg(row) * 2^31.
