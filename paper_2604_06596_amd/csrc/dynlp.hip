@@ -1451,8 +1451,14 @@ constexpr double kDenseEnter = 0.90, kDenseLeave = 0.75;
 // synchronous 762 -> 738 ms, with supernode initialisation 367 -> 342 ms, in place with it 332 -> 270 ms (in place
 // from uniform rows V_aff collapses within one chain of rounds and nothing changes); 0.20 / 0.10 is no better.
 constexpr double kBinnedEnter = 0.35, kBinnedLeave = 0.20;
-// A packed round too costs the same whatever the size of V_aff, and about half an ordinary round over all rows.
-constexpr double kPackedEnter = 0.50, kPackedLeave = 0.35;
+// A packed round costs about half an ordinary round over all rows while nearly all of them move; the fewer do, the more rows
+// must look their neighbours up to know whether they are in V_aff (us per round with V_aff = 99%, packed / fused, all rows
+// move - half do: 900,000 scalar rows of degree 6 56 / 77 - 94 / 88, two columns 58 / 96 - 104 / 104, 300,000 rows of 10
+// columns 54 / 113 - 69 / 113), and the layout of the entries has to be earned.  Stretches therefore begin at a chain whose
+// last round moved kPackedMoved of all rows (whole batches, without packed rounds / beginning at V_aff = 50% / now, tol =
+// 1e-6: 1M planted blocks 5.2 / 6.4 / 5.2 ms, 500K 8.1 / 9.4 / 8.2, 900K scalar 3.0 / 3.7 / 3.0, 400K scalar 14.7 / 11.2 /
+// 11.2, 60K kNN 20.6 / 17.2 / 17.2, 150K power law 38.7 / 29.9 / 30.5).
+constexpr double kPackedMoved = 0.97, kPackedLeave = 0.35;
 
 // The ping-pong partner must agree with F on every row a full sweep does not write (seeds,
 // isolated vertices) before it can receive one.
@@ -2648,6 +2654,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         bool bin_failed = false;
         bool packed = false;    // ... as packed rounds
         bool pack_failed = false;
+        unsigned int moved_last = 0;  // rows that the last round moved
+        bool pack_now = false;  // a stretch of packed rounds may begin
         // Rounds that repeat themselves exactly (same |V_aff|, rows moved and max change, 16 times in a row) are in
         // a period-2 cycle kept alive by float32 rounding (in-place rounds too: the few rows of such a V_aff run side
         // by side in one wave and read each other's old values); the rest of the batch's flag-marking rounds then
@@ -2722,14 +2730,16 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 bin_failed = true;  // no memory for the binned arrays: ordinary rounds for this batch
                 can_bin = false;
             }
-            bool can_pack = !pack_failed && !in_place && !can_bin && !persistent_rounds_pay(c, universe) &&
+            const bool can_pack = !pack_failed && !in_place && !can_bin && !persistent_rounds_pay(c, universe) &&
                             packed_rounds_pay(c, universe, &pk_plan);
-            if (can_pack && new_chain && !pingpong && !c->pk_built && (double)known >= kPackedEnter * (double)universe.size() &&
-                !build_packed(c, universe, pk_plan)) {
-                pack_failed = true;
-                can_pack = false;
+            if (new_chain) {
+                pack_now = can_pack && (double)moved_last >= kPackedMoved * (double)universe.size();
+                if (pack_now && !c->pk_built && !build_packed(c, universe, pk_plan)) {
+                    pack_failed = true;
+                    pack_now = false;
+                }
             }
-            const double enter = can_bin ? kBinnedEnter : can_pack ? kPackedEnter : kDenseEnter;
+            const double enter = can_bin ? kBinnedEnter : pack_now ? kPackedMoved : kDenseEnter;
             // graphs whose rounds run many per launch stay in one stretch from the first round to the last: a round
             // over a small V_aff costs them no more than a launch
             // (not once rounds repeat themselves exactly: the averaged rows that end such a cycle are staged rounds)
@@ -2741,8 +2751,10 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 pingpong = true;
                 stretch_start = it;
                 binned = can_bin;
-                packed = can_pack;
+                packed = pack_now;
                 fused = binned || packed || fused_rounds_pay(c, avg_len);
+            } else if (new_chain && pingpong && fused && !binned && !packed && pack_now) {
+                packed = true;  // the stretch goes on as packed rounds (same bitmaps, same buffers)
             } else if (pingpong && !(stay && fused && !binned) &&
                        (double)known < (binned ? kBinnedLeave : packed ? kPackedLeave : kDenseLeave) * (double)universe.size()) {
                 pingpong = false;
@@ -2877,6 +2889,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                                             pingpong && packed && it + i > stretch_start ? 0 : G));
                 // inside a stretch the next V_aff is not counted: this round's size stands in for it while
                 // rows still move
+                moved_last = rc.changed;
                 known = pingpong && fused ? (rc.changed ? std::max(nq, 1u) : 0u) : rc.next_count + rc.next_long;
                 if (it + i == check_round) verified = rc.changed == 0u;  // the check round moved no row by more than tol
                 const unsigned int sig[3] = {nq, rc.changed, rc.resid_bits};

@@ -194,3 +194,31 @@ def test_rows_that_take_several_generations_of_parts():
     o2 = ON.step3_propagate(rp, col, w, F, g.seed_class, A0, TOL, 10)
     assert np.all(np.abs(sizes - o2["frontier_sizes"]) <= 2e-3 * np.maximum(o2["frontier_sizes"], 1000))
     assert np.max(np.abs(soft - o2["F"])) <= ROUNDS_ATOL
+
+
+@pytest.mark.parametrize("kind,C,scalar", [("random", 2, True), ("random", 2, False), ("sbm", 10, False)])
+def test_packed_stretches_begin_while_nearly_all_rows_move(kind, C, scalar):
+    """Rows that did not move themselves look their neighbours up in a packed round: a V_aff of nearly all rows of which
+    fewer and fewer move is left to the ordinary rounds."""
+    def make():
+        return W.small_random(60000, 2, 6.0, 3000, 57) if kind == "random" else W.sbm(60000, C, 16.0, 8.0, 0.05, 58)
+
+    late = 0
+    for tol in (1e-6, 3e-6, 1e-5):
+        p, p0 = make(), make()
+        b = W.small_random_batch(p, 100, 6, 5) if kind == "random" else W.sbm_vertex_batch(p, 100, 16, 0.02)
+        with _make(p0, binary_scalar=scalar) as d:
+            d.static_solve(1e-6, 20000)
+            d.set_params(tol, 20000)
+            assert d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)[0] == 0
+            log = d.round_log_full()
+        rows = max(r.rows_short + r.rows_long for r in log)
+        for t, r in enumerate(log):
+            start = t - t % 8
+            if _is_packed(r) and not _is_packed(log[t - 1]):
+                assert start > 0 and log[start - 1].rows_moved >= 0.969 * rows, (tol, t)
+            if t == start and t > 0 and r.rows_short + r.rows_long > 0.6 * rows and log[t - 1].rows_moved < 0.9 * rows:
+                late += 1
+        print(kind, C, scalar, tol, "rounds", len(log), "packed", sum(map(_is_packed, log)))
+    print(kind, C, scalar, "chains with a large V_aff of which few rows move:", late)
+    assert late > 0 or kind == "sbm", "the case is meant to have chains that are left to ordinary rounds"
