@@ -152,7 +152,9 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  * How the rows of one propagation round see each other (Eq. (1) is written with iteration indices,
  * Alg. 2 Step 3 updates F_u inside a parallel loop over V_aff).
  *   DYNLP_UPDATE_SYNCHRONOUS  (default) every row of a round is computed from the labels the round
- *       started with (Jacobi); for a given edge order results are reproducible round by round.
+ *       started with (Jacobi); for a given edge order results are reproducible round by round.  (Sums of rounds
+ *       over nearly all rows of large graphs may be taken in another order than those of small rounds, with errors of
+ *       the same size.)
  *   DYNLP_UPDATE_IN_PLACE     a new row replaces the old one at once and later rows of the same round
  *       may already read it, as in the parallel loop of Alg. 2 executed literally.  Same fixed point
  *       and same stop rule (a row leaves V_aff when it moves by <= tol), about 1.5x fewer rounds, no
@@ -160,9 +162,9 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  *       scheduling, so two runs agree only within the convergence tolerance, not bit for bit.
  *       On graphs of 32,768 updatable vertices or more with 2e-7 <= tol <= 1e-5, rounds while V_aff holds nearly
  *       every vertex update all rows from the round-start labels and relax them (new = omega * weighted mean +
- *       (1 - omega) * row of the round before, kept in [0, 1]): same fixed point, several times fewer rounds.  An
- *       ordinary round over all rows follows, decides V_aff and starts the rounds described above, so that the stop
- *       rule is the same.
+ *       (1 - omega) * row of the round before, kept a distribution): same fixed point, several times fewer rounds.
+ *       An ordinary round over all rows always follows (at max_iter too), decides V_aff and starts the rounds described
+ *       above, so that the stop rule is the same.
  * Applies to dynlp_static_solve and dynlp_apply_batch calls that follow.
  */
 typedef enum dynlp_update_mode { DYNLP_UPDATE_SYNCHRONOUS = 0, DYNLP_UPDATE_IN_PLACE = 1 } dynlp_update_mode;

@@ -1536,6 +1536,10 @@ void read_slots_start(dynlp_ctx* c) {
 //   50K kNN, 6 classes              12.4    1.75    1.71    1.92    2.01    2.15    2.36    2.50    2.77
 //   50M scalar, one batch            371     204     197     187     188     178     176     186     187
 // (50M: fastest of five; allocating its arrays takes 5 to 1,700 ms once the process has used all device memory before.)
+// With 0.9 the phase can end a chain earlier and further off; three inputs, 0.8 / 0.85 / 0.9: 300K planted blocks from cold
+// 4.9 / 4.8 / 4.6 ms at 1.0e-6 / 7e-7 / 1.0e-5, 600K 5.1 / 5.1 / 4.7 ms at 5e-7 / 1.3e-6 / 8e-6, 1M 11.2 / 11.1 / 10.6 ms at
+// 1.1e-6 / 4.7e-6 / 9e-6, 100K kNN 2.65 / 2.70 / 2.79 ms at 6e-6 / 7e-6 / 7e-6, 1M power law 103 / 110 / 118 ms at 4.6e-5 /
+// 9e-6 / 3.1e-5.
 // kRelaxLeave, the share of moved rows below which the phase ends: 0.05 ... 0.25 within 12% of each other on these graphs;
 // 0.5: 100K kNN 2.85 -> 2.48 ms, but 50K kNN 1.84 -> 3.96 ms (201 rounds); 0.75: 5.5 and 5.4 ms.
 // kRelaxMinGap keeps omega from 2 where labels are scarce.  300K planted blocks, 0.1% labelled: 67 ms without relaxation,
@@ -1554,7 +1558,7 @@ void read_slots_start(dynlp_ctx* c) {
 constexpr unsigned int kRelaxMinRows = 32768;
 constexpr float kRelaxMinTol = 2e-7f, kRelaxNowTol = 4e-6f, kRelaxMaxTol = 1e-5f;
 constexpr double kRelaxStuck = 0.99;
-constexpr double kRelaxGap = 0.9, kRelaxMinGap = 2e-3, kRelaxEnter = 0.90, kRelaxLeave = 0.25;
+constexpr double kRelaxGap = 0.85, kRelaxMinGap = 2e-3, kRelaxEnter = 0.90, kRelaxLeave = 0.25;
 
 bool relaxed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, float tol) {
     return c->update_mode == DYNLP_UPDATE_IN_PLACE && c->persist <= 0 && universe.size() >= kRelaxMinRows && tol >= kRelaxMinTol &&
