@@ -1173,7 +1173,8 @@ constexpr unsigned int kPackedMinRows = 32768;
 // kPackedShare: see packed_rounds_pay; kPackedUneven: a part with more than this many times the mean entries would keep
 // the round waiting for one CU (us per round, row update / packed, largest part 1 / 2 / 3 / 4 times the mean: 150,000 vertices
 // of degree 20 with 10 columns 61 / 37, 61 / 56, 63 / 77, 64 / 93; with 29 columns 73 / 49, 73 / 75, 72 / 102, 74 / 128;
-// 400,000 with 10 columns 152 / 78, 151 / 133, 152 / 183, 155 / 235).  kPackedMaxRow: longer rows would show the unit of the packed sums (see dynlp_packed.h).
+// 400,000 with 10 columns 152 / 78, 151 / 133, 152 / 183, 155 / 235).  kPackedMaxRow: longer rows would show the unit of the
+// packed sums (see dynlp_packed.h).
 constexpr unsigned int kPackedMaxRow = 8192;
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
 // Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk

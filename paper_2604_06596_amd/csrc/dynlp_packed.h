@@ -32,7 +32,7 @@
 //
 // Bound: the vector memory path of the CUs (a line of 128 bytes per gather through the L1; leaving out the LDS atomics
 // changes nothing, leaving out the gathers takes away half).  One round over all rows, row update -> packed round, us:
-//   1,000,000 vertices, degree 20, 10 columns (64 MB of label rows)   400 -> 178   (TCC misses 18.3M -> 6.3M)
+//   1,000,000 vertices, degree 20, 10 columns (64 MB of label rows)   400 -> 178   (lines read from memory 21.6M -> 6.3M)
 //     400,000 vertices, degree 20, 10 columns                         147 ->  77
 //     150,000 vertices, power law, degree 30, 20 columns              90 ->  62
 //     300,000 vertices, degree 16, 29 columns                        109 ->  71
