@@ -161,8 +161,10 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  *       second label buffer traffic; which mix of old and new neighbour rows a row reads depends on
  *       scheduling, so two runs agree only within the convergence tolerance, not bit for bit.
  *       On graphs of 32,768 updatable vertices or more with 2e-7 <= tol <= 1e-5, rounds while V_aff holds nearly
- *       every vertex update all rows from the round-start labels and relax them (new = omega * weighted mean +
- *       (1 - omega) * row of the round before, kept a distribution): same fixed point, several times fewer rounds.
+ *       every vertex are steps of a conjugate-gradient iteration for the same fixed point: up to ten times fewer rounds
+ *       (a round counts as one: one product of the graph with the label matrix).  Where max_iter leaves fewer than 64
+ *       rounds, or there is no memory for two more label matrices, all rows are relaxed instead (new = omega * weighted
+ *       mean + (1 - omega) * row of the round before).  Rows stay distributions.
  *       An ordinary round over all rows always follows (at max_iter too), decides V_aff and starts the rounds described
  *       above, so that the stop rule is the same.
  * Applies to dynlp_static_solve and dynlp_apply_batch calls that follow.

@@ -7,16 +7,19 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <unordered_map>
 #include <unordered_set>
 #include <vector>
 
 #include "dynlp.h"
 #include "dynlp_kernels.h"
+#include "dynlp_conjugate.h"
 #include "dynlp_frontier.h"
 #include "dynlp_components.h"
 #include "dynlp_binned.h"
@@ -196,6 +199,11 @@ struct dynlp_ctx {
     float* pk_deg = nullptr;         // degrees the weights are divided by
     unsigned int* pk_tab = nullptr;  // per part: its first entry; all entries; the largest part; the longest row
     int64_t pk_tab_cap = 0;
+    // conjugate rounds (dynlp_conjugate.h)
+    float *cg_z = nullptr, *cg_p = nullptr;
+    int64_t cg_cap = 0;             // floats in each
+    CgSlot* cg_ring = nullptr;      // kCgRing slots
+    CgSlot* h_cg = nullptr;         // pinned, kChain slots
     // label initialisation of inserted vertices (dynlp_components.h)
     int init_mode = DYNLP_INIT_UNIFORM;
     float tau = 0.f;
@@ -258,15 +266,18 @@ void* dev_try_alloc(dynlp_ctx* c, size_t bytes) {
 
 void free_binned(dynlp_ctx* c);
 void free_packed(dynlp_ctx* c);
+void free_conjugate(dynlp_ctx* c);
 
-// As dev_try_alloc, for an array that a call cannot do without: the arrays of the binned and packed rounds, which only
-// save time and are laid out again by the next solve or batch that wants them, give way to it.  (Called outside of rounds.)
+// As dev_try_alloc, for an array that a call cannot do without: the arrays of the binned, packed and conjugate rounds, which
+// only save time and are laid out again by the next solve or batch that wants them, give way to it.  (Called outside of
+// rounds.)
 void* dev_alloc_or_reclaim(dynlp_ctx* c, size_t bytes) {
     void* p = dev_try_alloc(c, bytes);
-    if (p || (!c->pk_ent && !c->pb_src)) return p;
+    if (p || (!c->pk_ent && !c->pb_src && !c->cg_z)) return p;
     (void)hipStreamSynchronize(c->stream);
     free_packed(c);
     free_binned(c);
+    free_conjugate(c);
     return dev_try_alloc(c, bytes);
 }
 
@@ -1234,28 +1245,33 @@ void free_packed(dynlp_ctx* c) {
 
 size_t packed_lds(const dynlp_ctx* c) { return (size_t)c->pk_rows * packed_stride(c) * 4 + (size_t)c->pk_rows / 32 * 8; }
 
-// Calls fn with the instantiation of the packed round for the context's columns.
+template <int CP, int LANES>
+struct PackedShape {
+    static constexpr int cp = CP, lanes = LANES;
+};
+
+// Calls fn with the columns and lanes of the context's packed rounds.
 template <typename Fn>
 auto packed_kernel(const dynlp_ctx* c, Fn fn) {
     switch (c->CP > 4 ? (c->Cs + 3) / 4 : c->CP == 4 ? 1 : -c->CP) {
-        case -1: return fn(k_pk_round<1, 1>);
-        case -2: return fn(k_pk_round<2, 1>);
-        case 1: return fn(k_pk_round<4, 1>);
-        case 2: return fn(k_pk_round<8, 2>);
-        case 3: return fn(k_pk_round<16, 3>);
-        case 4: return fn(k_pk_round<16, 4>);
-        case 5: return fn(k_pk_round<32, 5>);
-        case 6: return fn(k_pk_round<32, 6>);
-        case 7: return fn(k_pk_round<32, 7>);
-        case 8: return fn(k_pk_round<32, 8>);
-        case 9: return fn(k_pk_round<64, 9>);
-        case 10: return fn(k_pk_round<64, 10>);
-        case 11: return fn(k_pk_round<64, 11>);
-        case 12: return fn(k_pk_round<64, 12>);
-        case 13: return fn(k_pk_round<64, 13>);
-        case 14: return fn(k_pk_round<64, 14>);
-        case 15: return fn(k_pk_round<64, 15>);
-        default: return fn(k_pk_round<64, 16>);
+        case -1: return fn(PackedShape<1, 1>{});
+        case -2: return fn(PackedShape<2, 1>{});
+        case 1: return fn(PackedShape<4, 1>{});
+        case 2: return fn(PackedShape<8, 2>{});
+        case 3: return fn(PackedShape<16, 3>{});
+        case 4: return fn(PackedShape<16, 4>{});
+        case 5: return fn(PackedShape<32, 5>{});
+        case 6: return fn(PackedShape<32, 6>{});
+        case 7: return fn(PackedShape<32, 7>{});
+        case 8: return fn(PackedShape<32, 8>{});
+        case 9: return fn(PackedShape<64, 9>{});
+        case 10: return fn(PackedShape<64, 10>{});
+        case 11: return fn(PackedShape<64, 11>{});
+        case 12: return fn(PackedShape<64, 12>{});
+        case 13: return fn(PackedShape<64, 13>{});
+        case 14: return fn(PackedShape<64, 14>{});
+        case 15: return fn(PackedShape<64, 15>{});
+        default: return fn(PackedShape<64, 16>{});
     }
 }
 
@@ -1286,9 +1302,16 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
     c->pk_bits = plan.col_bits;
     if (ok) {
         // always the same value: the attribute belongs to the kernel, not to this context
-        hipError_t e = packed_kernel(c, [&](auto kernel) {
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kPkLds - kPkFixedLds);
+        hipError_t e = packed_kernel(c, [&](auto shape) {
+            using S = decltype(shape);
+            const void* kernels[] = {reinterpret_cast<const void*>(&k_pk_round<S::cp, S::lanes>),
+                                     reinterpret_cast<const void*>(&k_pk_product<S::cp, S::lanes>)};
+            hipError_t worst = hipSuccess;
+            for (const void* k : kernels) {
+                const hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kPkLds - kPkFixedLds);
+                if (r != hipSuccess) worst = r;
+            }
+            return worst;
         });
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pk_place), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1342,7 +1365,10 @@ void launch_packed_round(dynlp_ctx* c, const PullRoundArgs& a, int round) {
                     c->pk_len, c->meta, c->pool, a.F_in, a.F_out, a.moved_prev, a.moved_cur, a.moved_clear,
                     (unsigned int)c->moved_words, a.tol, a.flags, a.omega};
     const dim3 grid((unsigned int)c->pk_parts), block(kPkThreads);
-    packed_kernel(c, [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, packed_lds(c), c->stream, r); });
+    packed_kernel(c, [&](auto shape) {
+        using S = decltype(shape);
+        hipLaunchKernelGGL((k_pk_round<S::cp, S::lanes>), grid, block, packed_lds(c), c->stream, r);
+    });
     HIPCHK(c, hipGetLastError());
     close_timed_span(c, e1);
 }
@@ -1566,7 +1592,9 @@ bool relaxed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, float tol)
            tol <= kRelaxMaxTol;
 }
 
-struct RelaxedRounds {
+// What rounds over all updatable rows did (accelerate, conjugate).
+struct DenseRounds {
+    bool settled = true;        // conjugate rounds: ended because the residual was small enough
     int rounds = 0;             // executed, the ordinary round at the end included
     float last = 0.f;           // max change of the last round
     unsigned int changed = 0;   // rows it moved
@@ -1577,8 +1605,8 @@ struct RelaxedRounds {
 // Rounds it, it + 1, ... (at most `budget`, which is not 0): relaxed rounds over `universe`, then one ordinary round over
 // all of it.  That one is always run: only its moves tell how far the rows are from their neighbours' means (a relaxed row
 // may stand still on its way past the fixed point).
-RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float tol, int it, int budget, bool binned, bool packed) {
-    RelaxedRounds out;
+DenseRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float tol, int it, int budget, bool binned, bool packed) {
+    DenseRounds out;
     sync_partner(c);
     for (unsigned int* mv : c->moved) HIPCHK(c, hipMemsetAsync(mv, 0, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
     // share of the updatable rows' edge weight that leads to labelled vertices, from a sample of rows
@@ -1645,6 +1673,256 @@ RelaxedRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float to
     return out;
 }
 
+// ---- conjugate rounds (in-place mode, dynlp_conjugate.h) -------------------------------------------------------
+// They take the place of the relaxed rounds where the call leaves them enough rounds and there is memory for two more arrays
+// of the size of the label matrix.  A call that is cut short by its round cap returns better labels from relaxed rounds (a
+// conjugate iterate on its way is further from the fixed point in single rows than the rows it started from), so budgets
+// below kCgMinBudget keep them: that many rounds are more than the iteration needs on the graphs it was measured on.
+constexpr int kCgMinBudget = 64;
+// The iteration ends when no row would move by more than kCgStop * tol (in the recurrence's own residual), or when the largest
+// move has not reached a new low (by 10%) in kCgPatience iterations; relaxed rounds then go on.
+constexpr float kCgStop = 0.5f;
+constexpr int kCgPatience = 96;
+
+void free_conjugate(dynlp_ctx* c) {
+    dev_free(c, c->cg_z);
+    dev_free(c, c->cg_p);
+    c->cg_z = c->cg_p = nullptr;
+    c->cg_cap = 0;
+}
+
+bool conjugate_arrays(dynlp_ctx* c, const Frontier& universe, float** z, float** p) {
+    if (!c->cg_ring) {
+        c->cg_ring = static_cast<CgSlot*>(dev_try_alloc(c, sizeof(CgSlot) * kCgRing));
+        if (!c->cg_ring) return false;
+    }
+    if (!c->h_cg) HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_cg), sizeof(CgSlot) * kChain, hipHostMallocDefault));
+    if (c->CP == 1) {  // one float per vertex: the two arrays of row lists that are idle meanwhile
+        float* idle[2];
+        int k = 0;
+        for (int32_t* q : c->queue)
+            if (q != universe.front && k < 2) idle[k++] = reinterpret_cast<float*>(q);
+        *z = idle[0];
+        *p = idle[1];
+        return true;
+    }
+    if (c->n * c->CP > c->cg_cap) {
+        free_conjugate(c);
+        if (!try_alloc_n(c, c->cg_z, c->n_cap * c->CP) || !try_alloc_n(c, c->cg_p, c->n_cap * c->CP)) {
+            free_conjugate(c);
+            return false;
+        }
+        c->cg_cap = c->n_cap * c->CP;
+    }
+    *z = c->cg_z;
+    *p = c->cg_p;
+    return true;
+}
+
+template <int CP, int G>
+void launch_row_product_inst(dynlp_ctx* c, const Frontier& universe, const CgRun& run, const float* p, float* v) {
+    const int64_t cap = (int64_t)c->num_cu * 32;
+    const unsigned int short_blocks =
+        (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div((int64_t)universe.ns, kBlock / G), cap));
+    const unsigned int long_blocks = (unsigned int)std::min<int64_t>((int64_t)universe.nl, cap / 2);
+    hipLaunchKernelGGL((k_row_product<CP, G>), dim3(short_blocks + long_blocks), dim3(kBlock), 0, c->stream, run, long_blocks,
+                       universe.front, universe.back, universe.ns, universe.nl, c->meta, c->pool, p, v);
+}
+
+template <int CP>
+void launch_row_product(dynlp_ctx* c, int G, const Frontier& universe, const CgRun& run, const float* p, float* v) {
+    constexpr int LPN = CP >= 4 ? CP / 4 : 1;
+#define DYNLP_CASE(GV)                                                   \
+    case GV:                                                             \
+        if constexpr (GV >= LPN) {                                       \
+            launch_row_product_inst<CP, GV>(c, universe, run, p, v);     \
+            return;                                                      \
+        }                                                                \
+        break;
+    switch (G) {
+        DYNLP_CASE(4)
+        DYNLP_CASE(8)
+        DYNLP_CASE(16)
+        DYNLP_CASE(32)
+        DYNLP_CASE(64)
+        default: break;
+    }
+#undef DYNLP_CASE
+    launch_row_product_inst<CP, 64>(c, universe, run, p, v);
+}
+
+// Calls fn with the padded number of columns.
+template <typename Fn>
+void with_columns(int CP, Fn fn) {
+    switch (CP) {
+        case 1: fn(std::integral_constant<int, 1>{}); break;
+        case 2: fn(std::integral_constant<int, 2>{}); break;
+        case 4: fn(std::integral_constant<int, 4>{}); break;
+        case 8: fn(std::integral_constant<int, 8>{}); break;
+        case 16: fn(std::integral_constant<int, 16>{}); break;
+        case 32: fn(std::integral_constant<int, 32>{}); break;
+        default: fn(std::integral_constant<int, 64>{}); break;
+    }
+}
+
+void launch_product(dynlp_ctx* c, int G, const Frontier& universe, const CgRun& run, const float* p, float* v, bool binned, bool packed) {
+    if (binned) {
+        const int lg = pb_run_lanes(c->pb_bins);
+        const dim3 grid(8 * (unsigned int)std::max<int64_t>(1, ceil_div(c->pb_chunks, 8)));
+        const unsigned int* bin_off = c->pb_bin + (kPbMaxBins + 1);
+#define DYNLP_SCATTER(NB, PACKED, SRC)                                                                                        \
+    hipLaunchKernelGGL((k_pb_scatter_product<NB, PACKED>), grid, dim3(kPbScatterThreads), 0, c->stream, run, c->pb_first + c->n, \
+                       (unsigned int)c->pb_chunks, c->pb_bins, lg, SRC, c->pb_row0, c->pb_lpos, c->pb_table, bin_off, p, c->pb_val)
+        if (c->pb_bins <= 2048 && c->pb_packed_ok) DYNLP_SCATTER(2048, true, c->pb_sp);
+        else if (c->pb_bins <= 2048) DYNLP_SCATTER(2048, false, c->pb_src);
+        else if (c->pb_packed_ok) DYNLP_SCATTER(kPbMaxBins, true, c->pb_sp);
+        else DYNLP_SCATTER(kPbMaxBins, false, c->pb_src);
+#undef DYNLP_SCATTER
+        hipLaunchKernelGGL(k_pb_product, dim3(c->pb_bins), dim3(kPbGatherThreads), 0, c->stream, run, c->n, c->pb_bits, bin_off,
+                           c->pb_dst, c->pb_wn, reinterpret_cast<const float*>(c->pb_val), c->pb_len, c->deg, p, v);
+    } else if (packed) {
+        const PkProduct r{run, c->n, c->pk_rows, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab, c->pk_len, c->deg, p, v};
+        packed_kernel(c, [&](auto shape) {
+            using S = decltype(shape);
+            hipLaunchKernelGGL((k_pk_product<S::cp, S::lanes>), dim3((unsigned int)c->pk_parts), dim3(kPkThreads), packed_lds(c),
+                               c->stream, r);
+        });
+    } else {
+        with_columns(c->CP, [&](auto cp) { launch_row_product<decltype(cp)::value>(c, G, universe, run, p, v); });
+    }
+    HIPCHK(c, hipGetLastError());
+}
+
+// One ordinary round over all updatable rows whatever moved before (F -> F2); the buffers are not swapped.
+void launch_full_round(dynlp_ctx* c, const Frontier& universe, int G, float tol, int t, int q, bool binned, bool packed) {
+    PullRoundArgs a{slot_of(c, t - 1), c->F, c->F2, c->moved[(q + 2) % 3], c->moved[q % 3], c->moved[(q + 1) % 3], tol,
+                    slot_of(c, t), slot_of(c, t + 1)};
+    a.flags = kRoundAll | kRoundForce;
+    if (binned) launch_binned_round(c, a, t, false);
+    else if (packed) launch_packed_round(c, a, t);
+    else launch_update_pull(c, G, universe, a, t);
+}
+
+// Rounds it, it + 1, ... (at most `budget` >= kCgMinBudget): an ordinary round over all rows, whose moves are the first
+// residual, conjugate rounds, and an ordinary round that decides what is in V_aff.
+DenseRounds conjugate(dynlp_ctx* c, const Frontier& universe, int G, float tol, int it, int budget, bool binned, bool packed,
+                      float* z, float* p) {
+    DenseRounds out;
+    sync_partner(c);
+    for (unsigned int* mv : c->moved) HIPCHK(c, hipMemsetAsync(mv, 0, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->cg_ring, 0, sizeof(CgSlot) * kCgRing, c->stream));
+    const unsigned int blocks =
+        (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(c->n * std::max(1, c->CP / 4), 2 * kBlock), (int64_t)c->num_cu * 8));
+    launch_full_round(c, universe, G, tol, it, 0, binned, packed);
+    with_columns(c->CP, [&](auto cp) {
+        hipLaunchKernelGGL(k_cg_begin<decltype(cp)::value>, dim3(blocks), dim3(kBlock), 0, c->stream, c->n, c->deg, c->F, c->F2, z, p,
+                           tol, c->cg_ring);
+    });
+    HIPCHK(c, hipGetLastError());
+    const float stop = kCgStop * tol;
+    auto log_round = [&](const RoundCtr& rc) {
+        out.changed = rc.changed;
+        std::memcpy(&out.last, &rc.resid_bits, sizeof(float));
+        const unsigned int nq = rc.rows_short + rc.rows_long;
+        if (nq) out.avg_len = (double)(rc.edges + rc.edges_long) / (double)nq;
+        c->log.push_back(round_info(rc, binned ? 3 : 2, packed ? 0 : G));
+    };
+    dynlp_round_info full{};
+    int k = 0;  // iterations executed
+    int best_at = 0;
+    float best = std::numeric_limits<float>::infinity();
+    for (bool more = true; more;) {
+        const int r = std::min(kChain, budget - 2 - k);
+        if (r <= 0) {
+            out.settled = false;
+            break;
+        }
+        if (k > 0)
+            for (int i = 1; i <= r;) {
+                const int at = (k + i) % kCgRing, run = std::min(r + 1 - i, kCgRing - at);
+                HIPCHK(c, hipMemsetAsync(c->cg_ring + at, 0, sizeof(CgSlot) * (size_t)run, c->stream));
+                i += run;
+            }
+        const size_t first_pair = c->events_used / 2;
+        for (int i = 1; i <= r; ++i) {
+            const CgRun run{c->cg_ring + (k + i - 1) % kCgRing, c->cg_ring + (k + i) % kCgRing, stop, tol};
+            c->ev_adjacent = i > 1;
+            hipEvent_t e1 = open_timed_span(c, it + k + i, 1);
+            launch_product(c, G, universe, run, p, c->F2, binned, packed);
+            with_columns(c->CP, [&](auto cp) {
+                hipLaunchKernelGGL(k_cg_step<decltype(cp)::value>, dim3(blocks), dim3(kBlock), 0, c->stream, run, c->n, c->deg, c->F, z,
+                                   p, c->F2);
+            });
+            HIPCHK(c, hipGetLastError());
+            close_timed_span(c, e1);
+        }
+        for (int i = 1; i <= r;) {
+            const int at = (k + i) % kCgRing, run = std::min(r + 1 - i, kCgRing - at);
+            HIPCHK(c, hipMemcpyAsync(c->h_cg + i - 1, c->cg_ring + at, sizeof(CgSlot) * (size_t)run, hipMemcpyDeviceToHost, c->stream));
+            i += run;
+        }
+        if (k == 0) {
+            read_slots(c, it, 1);  // (waits for everything above)
+            log_round(c->h_slot[0]);
+            full = c->log.back();
+            if (!(out.last > stop)) more = false;
+        } else {
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+        }
+        int executed = 0;
+        for (int i = 0; i < r && more; ++i) {
+            unsigned int zmax = 0, moved = 0;
+            for (const CgPart& part : c->h_cg[i].part) {
+                zmax = std::max(zmax, part.zmax);
+                moved += part.moved;
+            }
+            ++executed;
+            dynlp_round_info ri = full;
+            std::memcpy(&ri.max_delta, &zmax, sizeof(float));
+            ri.rows_moved = moved;
+            c->log.push_back(ri);
+            if (ri.max_delta < 0.9f * best) {
+                best = ri.max_delta;
+                best_at = k + executed;
+            }
+            if (!(ri.max_delta > stop)) more = false;
+        }
+        k += executed;
+        if (c->time_kernels) trim_timed_spans(c, first_pair, it + k + 1);
+        if (more && k - best_at >= kCgPatience) {
+            out.settled = false;
+            more = false;
+        }
+    }
+    with_columns(c->CP, [&](auto cp) {
+        hipLaunchKernelGGL(k_cg_end<decltype(cp)::value>, dim3(blocks), dim3(kBlock), 0, c->stream, c->n, c->Cs, c->deg, c->seed_class,
+                           c->F, c->F2);
+    });
+    HIPCHK(c, hipGetLastError());
+    const int t = it + k + 1;
+    for (int s : {t - 1, t}) HIPCHK(c, hipMemsetAsync(slot_of(c, s), 0, sizeof(RoundCtr), c->stream));
+    launch_full_round(c, universe, G, tol, t, 1, binned, packed);
+    read_slots(c, t, 1);
+    log_round(c->h_slot[0]);
+    std::swap(c->F, c->F2);
+    out.last_map = 1;
+    out.rounds = k + 2;
+    return out;
+}
+
+// The rounds over all rows of a call in in-place mode: conjugate ones where they can run, else (or where they do not settle)
+// relaxed ones.
+DenseRounds dense_rounds(dynlp_ctx* c, const Frontier& universe, int G, float tol, int it, int budget, bool binned, bool packed) {
+    float *z = nullptr, *p = nullptr;
+    if (budget < kCgMinBudget || !conjugate_arrays(c, universe, &z, &p)) return accelerate(c, universe, G, tol, it, budget, binned, packed);
+    DenseRounds out = conjugate(c, universe, G, tol, it, budget, binned, packed, z, p);
+    if (out.settled || out.last <= tol || out.rounds >= budget) return out;
+    const int before = out.rounds;
+    out = accelerate(c, universe, G, tol, it + before, budget - before, binned, packed);
+    out.rounds += before;
+    return out;
+}
+
 void fill_stats_zero(dynlp_stats* s) {
     if (s) std::memset(s, 0, sizeof *s);
 }
@@ -1697,7 +1975,8 @@ void destroy_ctx(dynlp_ctx* c) {
                     c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
                     c->pb_src, c->pb_sp, c->pb_row0, c->pb_lpos, c->pb_tmp, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, c->pb_upd,
-                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab};
+                    c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab,
+                    c->cg_z, c->cg_p, c->cg_ring};
     for (void* p : ptrs) dev_free(c, p);
     const std::vector<void*> left(c->live.begin(), c->live.end());  // arrays an interrupted call never got to free
     for (void* p : left) dev_free(c, p);
@@ -1715,6 +1994,7 @@ void destroy_ctx(dynlp_ctx* c) {
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
     if (c->h_slot) (void)hipHostFree(c->h_slot);
     if (c->h_bc) (void)hipHostFree(c->h_bc);
+    if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
         if (e) (void)hipEventDestroy(e);
@@ -2354,7 +2634,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
         bool packed = can_pack && relaxed && build_packed(c, all_rows, pk_plan);
         bool pack_tried = packed || !can_pack || relaxed;
         if (relaxed) {
-            const RelaxedRounds done = accelerate(c, all_rows, G, tol, 0, max_iter, binned, packed);
+            const DenseRounds done = dense_rounds(c, all_rows, G, tol, 0, max_iter, binned, packed);
             it = done.rounds;
             last = done.last;
             converged = last <= tol;
@@ -2699,7 +2979,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 const bool use_bins = binned_rounds_pay(c, universe) && (c->pb_built || build_binned(c));
                 const bool use_pack = !use_bins && packed_rounds_pay(c, universe, &pk_plan) && (c->pk_built || build_packed(c, universe, pk_plan));
                 const size_t logged = c->log.size();
-                const RelaxedRounds done = accelerate(c, universe, G, c->tol, it, c->max_iter - it, use_bins, use_pack);
+                const DenseRounds done = dense_rounds(c, universe, G, c->tol, it, c->max_iter - it, use_bins, use_pack);
                 it += done.rounds;
                 last = done.last;
                 if (done.avg_len > 0.0) avg_len = done.avg_len;

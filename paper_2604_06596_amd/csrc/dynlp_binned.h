@@ -27,6 +27,7 @@
 #pragma once
 
 #include "dynlp_device.h"
+#include "dynlp_conjugate.h"
 
 namespace dynlp {
 
@@ -389,50 +390,20 @@ __device__ inline bool pb_round_runs(const RoundCtr* __restrict__ prev, int flag
 constexpr int kPbScatterThreads = 1024;  // two workgroups of this size and 64 KB fill a CU (256 / 512 / 1024 threads:
                                          // 2.25 / 1.75 / 1.63 ms per round on 250M entries)
 
-template <int NB, bool PACKED>
-__global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr* __restrict__ prev,
-                                                      const unsigned int* __restrict__ num_entries, unsigned int chunk0,
-                                                      unsigned int chunks, int nbins, int lg_group,
-                                                      const unsigned int* __restrict__ src,
-                                                      const unsigned int* __restrict__ chunk_row0,
-                                                      const unsigned short* __restrict__ lpos,
-                                                      const unsigned int* __restrict__ table,
-                                                      const unsigned int* __restrict__ bin_off, const float* F_in,
-                                                      const unsigned int* __restrict__ moved_prev,
-                                                      const unsigned int* __restrict__ moved_also,
-                                                      unsigned int* __restrict__ moved_clear, unsigned int words,
-                                                      unsigned int* __restrict__ val, int flags,
-                                                      RoundCtr* __restrict__ ctr_zero) {
-    // chunks chunk0 .. chunk0 + chunks - 1; moved_prev (and moved_also, if not NULL): the bitmaps whose bits travel
-    // with the labels ("the sender moved"); moved_clear / ctr_zero may be NULL
+// The chunk of this workgroup out of chunk0 .. chunk0 + chunks - 1.  SIGNED: numbers of either sign without the flag.
+template <int NB, bool PACKED, bool SIGNED>
+__device__ inline void pb_scatter_chunk(const unsigned int* __restrict__ num_entries, unsigned int chunk0, unsigned int chunks,
+                                        int nbins, int lg_group, const unsigned int* __restrict__ src,
+                                        const unsigned int* __restrict__ chunk_row0, const unsigned short* __restrict__ lpos,
+                                        const unsigned int* __restrict__ table, const unsigned int* __restrict__ bin_off,
+                                        const float* F_in, const unsigned int* __restrict__ moved_prev,
+                                        const unsigned int* __restrict__ moved_also, unsigned int* __restrict__ val) {
     __shared__ unsigned int stage[kPbChunk];
     __shared__ unsigned int first_slot[NB];    // slot of the chunk's first entry of the bin
     __shared__ unsigned short loff[NB + 2];    // its position in the sorted chunk; loff[nbins] = entries with a slot
     constexpr int T = kPbScatterThreads;
     constexpr int NW = T / kWave;
     __shared__ unsigned int wave_tot[NW + 1];
-    if (ctr_zero && blockIdx.x == 0) {
-        if (threadIdx.x == 0) {
-            ctr_zero->next_count = 0;
-            ctr_zero->next_long = 0;
-            ctr_zero->executed = 0;
-            ctr_zero->rows_short = 0;
-            ctr_zero->rows_long = 0;
-            ctr_zero->any_moved = 0;
-        }
-        if (threadIdx.x < kCtrLanes) {
-            RoundPart* p = &ctr_zero->part[threadIdx.x];
-            p->resid_bits = 0;
-            p->changed = 0;
-            p->edges = 0;
-            p->edges_long = 0;
-            p->rows_short = 0;
-            p->rows_long = 0;
-        }
-    }
-    if (!pb_round_runs(prev, flags)) return;
-    if (moved_clear)
-        for (unsigned int w = blockIdx.x * T + threadIdx.x; w < words; w += gridDim.x * T) moved_clear[w] = 0u;
     const unsigned int per_xcd = (chunks + 7u) / 8u;
     const unsigned int local = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if ((blockIdx.x >> 3) >= per_xcd || local >= chunks) return;
@@ -456,8 +427,9 @@ __global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr
 #pragma unroll
         for (int q = 0; q < UN; ++q)
             if (u[q] != 0xffffffffu)
-                stage[p[q]] = __float_as_uint(F_in[u[q]]) |
-                              ((pb_bit(moved_prev, (int32_t)u[q]) || (moved_also && pb_bit(moved_also, (int32_t)u[q]))) ? 0x80000000u : 0u);
+                stage[p[q]] = SIGNED ? __float_as_uint(F_in[u[q]])
+                                     : __float_as_uint(F_in[u[q]]) |
+                                           ((pb_bit(moved_prev, (int32_t)u[q]) || (moved_also && pb_bit(moved_also, (int32_t)u[q]))) ? 0x80000000u : 0u);
     }
     __syncthreads();
     const int gl = (int)threadIdx.x & ((1 << lg_group) - 1);
@@ -467,6 +439,64 @@ __global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr
         const unsigned int s0 = first_slot[b];
         for (unsigned int p = lo + gl; p < hi; p += G) val[s0 + (p - lo)] = stage[p];
     }
+}
+
+template <int NB, bool PACKED>
+__global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter(const RoundCtr* __restrict__ prev,
+                                                      const unsigned int* __restrict__ num_entries, unsigned int chunk0,
+                                                      unsigned int chunks, int nbins, int lg_group,
+                                                      const unsigned int* __restrict__ src,
+                                                      const unsigned int* __restrict__ chunk_row0,
+                                                      const unsigned short* __restrict__ lpos,
+                                                      const unsigned int* __restrict__ table,
+                                                      const unsigned int* __restrict__ bin_off, const float* F_in,
+                                                      const unsigned int* __restrict__ moved_prev,
+                                                      const unsigned int* __restrict__ moved_also,
+                                                      unsigned int* __restrict__ moved_clear, unsigned int words,
+                                                      unsigned int* __restrict__ val, int flags,
+                                                      RoundCtr* __restrict__ ctr_zero) {
+    // moved_prev (and moved_also, if not NULL): the bitmaps whose bits travel with the labels ("the sender moved");
+    // moved_clear / ctr_zero may be NULL
+    constexpr int T = kPbScatterThreads;
+    if (ctr_zero && blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            ctr_zero->next_count = 0;
+            ctr_zero->next_long = 0;
+            ctr_zero->executed = 0;
+            ctr_zero->rows_short = 0;
+            ctr_zero->rows_long = 0;
+            ctr_zero->any_moved = 0;
+        }
+        if (threadIdx.x < kCtrLanes) {
+            RoundPart* p = &ctr_zero->part[threadIdx.x];
+            p->resid_bits = 0;
+            p->changed = 0;
+            p->edges = 0;
+            p->edges_long = 0;
+            p->rows_short = 0;
+            p->rows_long = 0;
+        }
+    }
+    if (!pb_round_runs(prev, flags)) return;
+    if (moved_clear)
+        for (unsigned int w = blockIdx.x * T + threadIdx.x; w < words; w += gridDim.x * T) moved_clear[w] = 0u;
+    pb_scatter_chunk<NB, PACKED, false>(num_entries, chunk0, chunks, nbins, lg_group, src, chunk_row0, lpos, table, bin_off, F_in,
+                                        moved_prev, moved_also, val);
+}
+
+// The same for a product of the conjugate rounds.
+template <int NB, bool PACKED>
+__global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter_product(CgRun run, const unsigned int* __restrict__ num_entries,
+                                                      unsigned int chunks, int nbins, int lg_group,
+                                                      const unsigned int* __restrict__ src,
+                                                      const unsigned int* __restrict__ chunk_row0,
+                                                      const unsigned short* __restrict__ lpos,
+                                                      const unsigned int* __restrict__ table,
+                                                      const unsigned int* __restrict__ bin_off,
+                                                      const float* __restrict__ p, unsigned int* __restrict__ val) {
+    if (cg_done(run)) return;
+    pb_scatter_chunk<NB, PACKED, true>(num_entries, 0u, chunks, nbins, lg_group, src, chunk_row0, lpos, table, bin_off, p, nullptr,
+                                       nullptr, val);
 }
 
 // Gather pass: one workgroup of kPbGatherThreads per bin (the accumulators take most of a CU's LDS, so the
@@ -606,6 +636,71 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
         }
         if (nrows) atomicAdd(&p->rows_short, nrows);
     }
+}
+
+// Gather pass of a product of the conjugate rounds: v = p - (weighted mean of the neighbours' p) for the receivers of the
+// bin, and the sums (p, v), (v, v).  The sums are signed, the largest |p| takes half of their range.
+__global__ void __launch_bounds__(kPbGatherThreads) k_pb_product(CgRun run, int64_t n, int bin_bits,
+                                                                const unsigned int* __restrict__ bin_off,
+                                                                const unsigned short* __restrict__ dst,
+                                                                const float* __restrict__ wn, const float* __restrict__ val,
+                                                                const int32_t* __restrict__ len, const float* __restrict__ deg,
+                                                                const float* __restrict__ p, float* __restrict__ v) {
+    constexpr int T = kPbGatherThreads;
+    constexpr float kUnits = 2.f * kPbUnit;
+    __shared__ int acc[1 << kPbMaxBinBits];
+    if (cg_done(run)) return;
+    const float scale = cg_scale(run);
+    const int size = 1 << bin_bits;
+    const int64_t first = (int64_t)blockIdx.x << bin_bits;
+    for (int d = threadIdx.x; d < size; d += T) acc[d] = 0;
+    __syncthreads();
+    const unsigned int lo = bin_off[blockIdx.x], hi = bin_off[blockIdx.x + 1];
+    const float units = scale * kUnits;
+    constexpr int UN = 4;
+    for (unsigned int i0 = lo; i0 < hi; i0 += UN * T) {
+        unsigned int d[UN];
+        float x[UN], w[UN];
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const unsigned int i = i0 + q * T + threadIdx.x;
+            const bool ok = i < hi;
+            d[q] = ok ? dst[i] : 0u;
+            x[q] = ok ? val[i] : 0.f;
+            w[q] = ok ? wn[i] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const int t = (int)__builtin_rintf(w[q] * (x[q] * units));
+            if (t) atomicAdd(&acc[d[q]], t);
+        }
+    }
+    __syncthreads();
+    const float unit = 1.f / units;
+    float pv = 0.f, vv = 0.f;
+    constexpr int UF = 4;
+    for (int d0 = 0; d0 < size; d0 += UF * T) {
+        int l[UF];
+        float own[UF], dg[UF];
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            const int d = d0 + q * T + (int)threadIdx.x;
+            const bool ok = d < size && first + d < n;
+            l[q] = ok ? len[first + d] : 0;
+            own[q] = ok ? p[first + d] : 0.f;
+            dg[q] = ok ? deg[first + d] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            if (l[q] == 0) continue;
+            const int d = d0 + q * T + (int)threadIdx.x;
+            const float r = own[q] - (float)acc[d] * unit;
+            v[first + d] = r;
+            pv += dg[q] * own[q] * r;
+            vv += dg[q] * r * r;
+        }
+    }
+    cg_add_product<T>(run, pv, vv);
 }
 
 }  // namespace dynlp

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "dynlp_device.h"
+#include "dynlp_conjugate.h"
 
 namespace dynlp {
 
@@ -769,6 +770,111 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
     else
         row_update_short<CP, G, false, true, false, RELAX>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool,
                                              F_in, F_out, 1, nullptr, moved_cur, tol, ctr, moved_prev, omega);
+}
+
+// =================================================================================================
+// One product of the conjugate rounds (dynlp_conjugate.h), row by row
+// =================================================================================================
+// v[u] = p[u] - (weighted mean of the neighbours' rows of p) for every updatable row, and the sums (p, v), (v, v).  Rows are
+// walked as in k_row_update (workgroups [0, long_blocks) take the long ones).
+template <int CP, int G>
+__device__ inline void row_product_short(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ front,
+                                         unsigned int ns, const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                         const float* __restrict__ p, float* __restrict__ v, float& pv, float& vv) {
+    constexpr int VEC = RowShape<CP>::VEC;
+    constexpr int LPN = RowShape<CP>::LPN;
+    constexpr int GPB = kBlock / G;
+    const int gl = threadIdx.x % G;
+    for (unsigned int g = bid * GPB + threadIdx.x / G; g < ns; g += nblocks * GPB) {
+        const int32_t u = front[g];
+        const RowMeta m = meta[u];
+        Vec<VEC> acc;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
+        float s = 0.f;
+        Edge e;
+        e.col = u;
+        e.w = 0.f;
+        accumulate_row<CP, G>(pool + m.off, m.len, 0, 1, u, p, gl, acc, s, e);
+        if (gl >= LPN) continue;
+        const size_t at = (size_t)u * CP + gl * VEC;
+        const Vec<VEC> own = load_vec<VEC>(p + at);
+        Vec<VEC> r;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            r.v[k] = own.v[k] - acc.v[k] / s;
+            pv += s * own.v[k] * r.v[k];
+            vv += s * r.v[k] * r.v[k];
+        }
+        store_vec<VEC>(v + at, r);
+    }
+}
+
+template <int CP>
+__device__ inline void row_product_long(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ back,
+                                        unsigned int nl, const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                        const float* __restrict__ p, float* __restrict__ v, float& pv, float& vv) {
+    constexpr int VEC = RowShape<CP>::VEC;
+    constexpr int LPN = RowShape<CP>::LPN;
+    constexpr int G = LPN > 16 ? LPN : 16;
+    constexpr int NG = kBlock / G;
+    __shared__ float part[NG][CP + 1];
+    __shared__ float part_s[NG];
+    const int gi = threadIdx.x / G;
+    const int gl = threadIdx.x % G;
+    for (unsigned int j = bid; j < nl; j += nblocks) {
+        const int32_t u = back[-(long long)j];
+        const RowMeta m = meta[u];
+        Vec<VEC> acc;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
+        float s = 0.f;
+        Edge e;
+        e.col = u;
+        e.w = 0.f;
+        accumulate_row<CP, G>(pool + m.off, m.len, gi, NG, u, p, gl, acc, s, e);
+        if (gl < LPN) {
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) part[gi][gl * VEC + k] = acc.v[k];
+            if (gl == 0) part_s[gi] = s;
+        }
+        __syncthreads();
+        if (threadIdx.x < LPN) {
+            Vec<VEC> tot;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) tot.v[k] = 0.f;
+            float st = 0.f;
+#pragma unroll 4
+            for (int q = 0; q < NG; ++q) {
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) tot.v[k] += part[q][gl * VEC + k];
+                st += part_s[q];
+            }
+            const size_t at = (size_t)u * CP + gl * VEC;
+            const Vec<VEC> own = load_vec<VEC>(p + at);
+            Vec<VEC> r;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                r.v[k] = own.v[k] - tot.v[k] / st;
+                pv += st * own.v[k] * r.v[k];
+                vv += st * r.v[k] * r.v[k];
+            }
+            store_vec<VEC>(v + at, r);
+        }
+        __syncthreads();
+    }
+}
+
+template <int CP, int G>
+__global__ void __launch_bounds__(kBlock) k_row_product(CgRun run, unsigned int long_blocks, const int32_t* __restrict__ front,
+                                                       const int32_t* __restrict__ back, unsigned int ns, unsigned int nl,
+                                                       const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
+                                                       const float* __restrict__ p, float* __restrict__ v) {
+    if (cg_done(run)) return;
+    float pv = 0.f, vv = 0.f;
+    if (blockIdx.x < long_blocks) row_product_long<CP>(blockIdx.x, long_blocks, back, nl, meta, pool, p, v, pv, vv);
+    else row_product_short<CP, G>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool, p, v, pv, vv);
+    cg_add_product<kBlock>(run, pv, vv);
 }
 
 // =================================================================================================

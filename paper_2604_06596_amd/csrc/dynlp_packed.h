@@ -43,6 +43,7 @@
 #pragma once
 
 #include "dynlp_device.h"
+#include "dynlp_conjugate.h"
 
 namespace dynlp {
 
@@ -324,6 +325,115 @@ struct PkRound {
     float omega;  // relaxation; 1: none, else F_out holds the rows of the round before the last
 };
 
+// The entries of one part on their way through a workgroup of kPkThreads: SLOTS neighbour rows per gather, LANES lanes each.
+// SIGNED: the table holds numbers of either sign of at most 1 / (2 * scale) (k_pk_product); else labels, scale = 1.
+template <int CP, int LANES, bool SIGNED>
+struct PkStream {
+    static constexpr int NW = kPkThreads / kWave;
+    static constexpr int VEC = CP >= 4 ? 4 : CP;
+    static constexpr int SLOTS = kWave / LANES;  // neighbour rows per gather
+    static constexpr int GATHERS = kWave / SLOTS;
+    static constexpr int TILE = SLOTS * GATHERS;  // entries a wave reads at once, one per lane
+    static constexpr int TILES = GATHERS >= 3 ? 1 : 4 / GATHERS;
+    static constexpr unsigned int kStep = NW * TILES * TILE;  // entries the workgroup takes at a time
+    int mslot, mchunk, C, col_bits;
+    unsigned int lane_part, mask, stride, piece, count, own;
+    __amdgpu_buffer_rsrc_t ent, rows;
+    PkEntry e[TILES];
+
+    // asks for the first entries
+    __device__ inline PkStream(int wave, int64_t n, int columns, int lds_stride, int bits, const PkEntry* entries,
+                               const unsigned int* start, const float* table) {
+        mslot = lane_id() / LANES;
+        mchunk = lane_id() % LANES;
+        C = columns;
+        col_bits = bits;
+        lane_part = (unsigned int)mchunk * 2779933u;
+        mask = (1u << col_bits) - 1u;
+        stride = (unsigned int)lds_stride * 4u;  // bytes of a row's sums
+        piece = (unsigned int)mchunk * VEC * 4u;
+        const unsigned int first = __builtin_amdgcn_readfirstlane(start[blockIdx.x]);
+        count = __builtin_amdgcn_readfirstlane(start[blockIdx.x + 1]) - first;
+        // buffer reads: one address register, and reads past the part's last entry return an entry of weight 0
+        ent = pk_buffer(entries + first, count * (unsigned int)sizeof(PkEntry));
+        rows = pk_buffer(table, (unsigned int)n * (unsigned int)(CP * 4));
+        own = (unsigned int)(wave * TILES * TILE + (lane_id() < TILE ? lane_id() : TILE - 1)) * (unsigned int)sizeof(PkEntry);
+#pragma unroll
+        for (int q = 0; q < TILES; ++q) e[q] = pk_load_entry(ent, own + q * TILE * (unsigned int)sizeof(PkEntry));
+    }
+
+    // adds all entries to the sums in LDS
+    __device__ inline void add(unsigned int* lds, float scale) {
+        char* const sums = reinterpret_cast<char*>(lds) + piece;
+        const bool second = mchunk * VEC + 2 < C;  // the upper two columns of a piece of four are in use
+        unsigned int since = 0;
+#pragma unroll 1
+        for (unsigned int i0 = 0; i0 < count; i0 += kStep) {  // uniform in the workgroup
+            since += kStep;
+            if (since > kPkWindow) {  // keeps the waves of the workgroup within kPkWindow entries of each other
+                __syncthreads();
+                since = kStep;
+            }
+            PkEntry cur[TILES];
+#pragma unroll
+            for (int q = 0; q < TILES; ++q) {
+                cur[q] = e[q];
+                if constexpr (SIGNED) cur[q].wn *= scale;
+                e[q] = pk_load_entry(ent, own + (i0 + kStep + q * TILE) * (unsigned int)sizeof(PkEntry));
+            }
+            constexpr int ALL = TILES * GATHERS;
+            constexpr int UN = ALL <= 8 ? ALL : ALL % 8 == 0 ? 8 : ALL % 6 == 0 ? 6 : ALL % 5 == 0 ? 5 : ALL;
+            static_assert(ALL % UN == 0, "whole groups of gathers");
+#pragma unroll
+            for (int g0 = 0; g0 < ALL; g0 += UN) {
+                Vec<VEC> f[UN];
+                unsigned int to[UN];
+                float wn[UN], dither[UN];
+#pragma unroll
+                for (int t = 0; t < UN; ++t) {
+                    const int q = (g0 + t) / GATHERS, src = (g0 + t) % GATHERS * SLOTS + mslot;
+                    unsigned int at = cur[q].at;
+                    wn[t] = cur[q].wn;
+                    if constexpr (LANES > 1) {
+                        at = __shfl(at, src);
+                        wn[t] = __shfl(wn[t], src);
+                    }
+                    f[t] = pk_load_piece<VEC>(rows, (at & mask) * (unsigned int)(CP * 4) + piece);
+                    to[t] = at >> col_bits;
+                    dither[t] = pk_dither(at, lane_part);
+                }
+                if (mslot >= SLOTS) continue;  // the lanes left over
+#pragma unroll
+                for (int t = 0; t < UN; ++t) {
+                    unsigned int byte = __umul24(to[t], stride);
+                    asm("" : "+v"(byte));  // computed once, outside the masked half below
+                    char* const dst = sums + byte;
+                    unsigned int x[VEC];
+#pragma unroll
+                    for (int k = 0; k < VEC; ++k) {
+                        const float r = __builtin_rintf(__builtin_fmaf(wn[t], f[t].v[k], dither[t]));
+                        x[k] = SIGNED ? (unsigned int)(int)r : (unsigned int)r;
+                    }
+                    if constexpr (VEC == 1) {
+                        atomicAdd(reinterpret_cast<unsigned int*>(dst), x[0]);
+                    } else {
+                        // two columns per atomic.  Labels: sums stay below 2^32, nothing carries over.  Signed: the sum of
+                        // the two as one 64-bit number (pk_signed_sum takes it apart)
+                        auto pair = [](unsigned int lo, unsigned int hi) {
+                            if constexpr (SIGNED) hi += (unsigned int)((int)lo >> 31);
+                            return lo | ((unsigned long long)hi << 32);
+                        };
+                        atomicAdd(reinterpret_cast<unsigned long long*>(dst), pair(x[0], x[1]));
+                        if constexpr (VEC == 4)
+                            if (second) atomicAdd(reinterpret_cast<unsigned long long*>(dst) + 1, pair(x[2], x[3]));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+};
+
 // One round.  V_aff is decided per row as in k_row_update_pull: u is in it iff u or a neighbour moved in the previous
 // round; rows outside it are copied to F_out.  Does nothing if the previous round did not run or moved no row.
 // LANES: lanes that read one neighbour row (those of its CP columns that are in use).
@@ -344,27 +454,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
     }
     // the first entries are asked for before anything that has to be waited for
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    constexpr int SLOTS = kWave / LANES;  // neighbour rows per gather
-    constexpr int GATHERS = kWave / SLOTS;
-    constexpr int TILE = SLOTS * GATHERS;  // entries a wave reads at once, one per lane
-    constexpr int TILES = GATHERS >= 3 ? 1 : 4 / GATHERS;
-    constexpr unsigned int kStep = NW * TILES * TILE;  // entries the workgroup takes at a time
-    const int mslot = lane_id() / LANES, mchunk = lane_id() % LANES;
-    const unsigned int lane_part = (unsigned int)mchunk * 2779933u;
-    const unsigned int mask = (1u << a.col_bits) - 1u;
-    const unsigned int stride = (unsigned int)a.stride * 4u;  // bytes of a row's sums
-    const unsigned int piece = (unsigned int)mchunk * VEC * 4u;
-    char* const sums = reinterpret_cast<char*>(pk_lds) + piece;
-    const bool second = mchunk * VEC + 2 < a.C;  // the upper two columns of a piece of four are in use
-    const unsigned int first = __builtin_amdgcn_readfirstlane(a.start[blockIdx.x]);
-    const unsigned int count = __builtin_amdgcn_readfirstlane(a.start[blockIdx.x + 1]) - first;
-    // buffer reads: one address register, and reads past the part's last entry return an entry of weight 0
-    const __amdgpu_buffer_rsrc_t ent = pk_buffer(a.ent + first, count * (unsigned int)sizeof(PkEntry));
-    const __amdgpu_buffer_rsrc_t rows = pk_buffer(a.F_in, (unsigned int)a.n * (unsigned int)(CP * 4));
-    const unsigned int own = (unsigned int)(wave * TILES * TILE + (lane_id() < TILE ? lane_id() : TILE - 1)) * (unsigned int)sizeof(PkEntry);
-    PkEntry e[TILES];
-#pragma unroll
-    for (int q = 0; q < TILES; ++q) e[q] = pk_load_entry(ent, own + q * TILE * (unsigned int)sizeof(PkEntry));
+    PkStream<CP, LANES, false> stream(wave, a.n, a.C, a.stride, a.col_bits, a.ent, a.start, a.F_in);
     if (!(a.flags & kRoundForce) && (!a.prev->executed || a.prev->any_moved == 0u)) return;
 #pragma unroll 1
     for (unsigned int w = blockIdx.x * T + threadIdx.x; w < a.words; w += gridDim.x * T) a.moved_clear[w] = 0u;
@@ -405,62 +495,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
             if (hit && gl == 0) atomicOr(&in[r >> 5], 1u << (r & 31));
         }
     }
-    unsigned int since = 0;
-#pragma unroll 1
-    for (unsigned int i0 = 0; i0 < count; i0 += kStep) {  // uniform in the workgroup
-        since += kStep;
-        if (since > kPkWindow) {  // keeps the waves of the workgroup within kPkWindow entries of each other
-            __syncthreads();
-            since = kStep;
-        }
-        PkEntry cur[TILES];
-#pragma unroll
-        for (int q = 0; q < TILES; ++q) {
-            cur[q] = e[q];
-            e[q] = pk_load_entry(ent, own + (i0 + kStep + q * TILE) * (unsigned int)sizeof(PkEntry));
-        }
-        constexpr int ALL = TILES * GATHERS;
-        constexpr int UN = ALL <= 8 ? ALL : ALL % 8 == 0 ? 8 : ALL % 6 == 0 ? 6 : ALL % 5 == 0 ? 5 : ALL;
-        static_assert(ALL % UN == 0, "whole groups of gathers");
-#pragma unroll
-        for (int g0 = 0; g0 < ALL; g0 += UN) {
-            Vec<VEC> f[UN];
-            unsigned int to[UN];
-            float wn[UN], dither[UN];
-#pragma unroll
-            for (int t = 0; t < UN; ++t) {
-                const int q = (g0 + t) / GATHERS, src = (g0 + t) % GATHERS * SLOTS + mslot;
-                unsigned int at = cur[q].at;
-                wn[t] = cur[q].wn;
-                if constexpr (LANES > 1) {
-                    at = __shfl(at, src);
-                    wn[t] = __shfl(wn[t], src);
-                }
-                f[t] = pk_load_piece<VEC>(rows, (at & mask) * (unsigned int)(CP * 4) + piece);
-                to[t] = at >> a.col_bits;
-                dither[t] = pk_dither(at, lane_part);
-            }
-            if (mslot >= SLOTS) continue;  // the lanes left over
-#pragma unroll
-            for (int t = 0; t < UN; ++t) {
-                unsigned int byte = __umul24(to[t], stride);
-                asm("" : "+v"(byte));  // computed once, outside the masked half below
-                char* const dst = sums + byte;
-                unsigned int x[VEC];
-#pragma unroll
-                for (int k = 0; k < VEC; ++k) x[k] = (unsigned int)__builtin_rintf(__builtin_fmaf(wn[t], f[t].v[k], dither[t]));
-                if constexpr (VEC == 1) {
-                    atomicAdd(reinterpret_cast<unsigned int*>(dst), x[0]);
-                } else {
-                    // two columns per atomic: sums stay below 2^32, nothing carries over
-                    atomicAdd(reinterpret_cast<unsigned long long*>(dst), x[0] | ((unsigned long long)x[1] << 32));
-                    if constexpr (VEC == 4)
-                        if (second) atomicAdd(reinterpret_cast<unsigned long long*>(dst) + 1, x[2] | ((unsigned long long)x[3] << 32));
-                }
-            }
-        }
-    }
-    __syncthreads();
+    stream.add(pk_lds, 1.f);
     const int cols = a.C - chunk * VEC;  // columns of this lane's piece of a row that are in use (may be <= 0)
     float rmax = 0.f;
     unsigned int edges = 0, edges_long = 0;
@@ -554,6 +589,100 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
         if (nrows) atomicAdd(&p->rows_short, nrows);
         if (nrows_long) atomicAdd(&p->rows_long, nrows_long);
     }
+}
+
+// ---- one product of the conjugate rounds (dynlp_conjugate.h): v = p - (weighted mean of the neighbours' p) -------------
+// The rows of p are numbers of either sign; they are scaled so that the largest in the whole table takes half of a sum's
+// range.  Sums of one row: at most 2^30 units and half a unit per entry, either sign.
+__device__ inline Vec<2> pk_signed_sum(unsigned long long s, float unit) {
+    const int lo = (int)(unsigned int)s;
+    const int hi = (int)(unsigned int)(s >> 32) - (lo >> 31);
+    Vec<2> r;
+    r.v[0] = (float)lo * unit;
+    r.v[1] = (float)hi * unit;
+    return r;
+}
+
+struct PkProduct {
+    CgRun run;
+    int64_t n;
+    int rows, C, stride, col_bits;
+    const PkEntry* ent;
+    const unsigned int* start;
+    const int32_t* len;
+    const float* deg;
+    const float* p;
+    float* v;  // 0 in rows that are not updated
+};
+
+template <int CP, int LANES>
+__global__ void __launch_bounds__(kPkThreads, 4) k_pk_product(PkProduct a) {
+    constexpr int T = kPkThreads;
+    constexpr int VEC = CP >= 4 ? 4 : CP;
+    constexpr int LPN = CP / VEC;
+    extern __shared__ __align__(16) unsigned int pk_lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    PkStream<CP, LANES, true> stream(wave, a.n, a.C, a.stride, a.col_bits, a.ent, a.start, a.p);
+    if (cg_done(a.run)) return;
+    const float scale = cg_scale(a.run);
+    const int chunk = threadIdx.x % LPN;
+    const int64_t base = (int64_t)blockIdx.x * a.rows;
+    const int nr = (int)(a.n - base < a.rows ? a.n - base : a.rows);
+#pragma unroll 1
+    for (int i = threadIdx.x; i < a.rows * a.stride; i += T) pk_lds[i] = 0u;
+    __syncthreads();
+    stream.add(pk_lds, scale);
+    const int cols = a.C - chunk * VEC;
+    const float unit = 1.0f / (scale * kPkUnit);
+    float pv = 0.f, vv = 0.f;
+    constexpr int RPP = T / LPN;
+    constexpr int UF = 4;
+#pragma unroll 1
+    for (int r0 = 0; r0 < nr; r0 += UF * RPP) {
+        int l[UF];
+        float d[UF];
+        Vec<VEC> own[UF];
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            const int r = r0 + q * RPP + (int)threadIdx.x / LPN;
+            l[q] = r < nr ? a.len[base + r] : 0;
+            d[q] = 0.f;
+            if (l[q] > 0) {
+                own[q] = load_vec<VEC>(a.p + (size_t)(base + r) * CP + chunk * VEC);
+                d[q] = a.deg[base + r];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < UF; ++q) {
+            const int r = r0 + q * RPP + (int)threadIdx.x / LPN;
+            if (l[q] == 0) continue;
+            Vec<VEC> v;
+            const unsigned int* const sum = pk_lds + r * a.stride + chunk * VEC;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) v.v[k] = 0.f;
+            if constexpr (VEC == 1) {
+                v.v[0] = own[q].v[0] - (float)(int)sum[0] * unit;
+            } else {
+#pragma unroll
+                for (int k = 0; k < VEC; k += 2) {
+                    if (k >= cols) continue;
+                    const Vec<2> m = pk_signed_sum(*reinterpret_cast<const unsigned long long*>(sum + k), unit);
+                    v.v[k] = own[q].v[k] - m.v[0];
+                    v.v[k + 1] = k + 1 < cols ? own[q].v[k + 1] - m.v[1] : 0.f;
+                }
+            }
+            float a1 = 0.f, a2 = 0.f;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                a1 += own[q].v[k] * v.v[k];
+                a2 += v.v[k] * v.v[k];
+            }
+            pv += d[q] * a1;
+            vv += d[q] * a2;
+            store_vec<VEC>(a.v + (size_t)(base + r) * CP + chunk * VEC, v);
+        }
+    }
+    cg_add_product<T>(a.run, pv, vv);
 }
 
 }  // namespace dynlp
