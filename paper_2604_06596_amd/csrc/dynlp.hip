@@ -197,7 +197,8 @@ struct dynlp_ctx {
     int32_t* pk_len = nullptr;
     int64_t pk_vcap = 0;
     float* pk_deg = nullptr;         // degrees the weights are divided by
-    unsigned int* pk_tab = nullptr;  // per part: its first entry; all entries; the largest part; the longest row
+    unsigned int* pk_tab = nullptr;  // per part its first entry, and all entries; most entries and rows of a part, the
+                                     // longest row; per part its first row / 32, and the last; build scratch
     int64_t pk_tab_cap = 0;
     // conjugate rounds (dynlp_conjugate.h)
     float *cg_z = nullptr, *cg_p = nullptr;
@@ -1188,13 +1189,15 @@ constexpr unsigned int kPackedMinRows = 32768;
 // packed sums (see dynlp_packed.h).
 constexpr unsigned int kPackedMaxRow = 8192;
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
+// A row's share of a part's time, in entries: its sums are cleared, its old row read and its new one written.
+constexpr unsigned int kPackedRowCost = 4;
 // Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk
 // to a labelled vertex) that the last bits of a row decide visibly where: a row that moves by the threshold to within
 // rounding enters V_aff or not and takes its neighbours along.  With tol = 1e-4 on 1,000,000 vertices two solves that
 // agree to 7e-8 are 1.4e-4 apart after a batch (2-norm, relative).  Such runs keep the sums of the row update.
 constexpr float kPackedMaxTol = 1e-5f;
 struct PackedPlan {
-    int rows, parts, col_bits, bucket_bits;
+    int rows, parts, col_bits, bucket_bits;  // rows: as many as a part may have
 };
 
 int packed_stride(const dynlp_ctx* c) { return c->Cs == 1 ? 1 : (c->Cs + 1) / 2 * 2; }
@@ -1226,7 +1229,7 @@ bool packed_rounds_pay(const dynlp_ctx* c, const Frontier& universe, PackedPlan*
     const double packed = 8.0 * (double)gens * (double)c->n * c->CP * 4.0;
     const double ordinary = (double)c->entries * std::max(128.0, c->CP * 4.0);
     if (packed > kPackedShare * ordinary) return false;
-    *plan = PackedPlan{(int)rows, (int)ceil_div(c->n, rows), col_bits, bucket_bits};
+    *plan = PackedPlan{(int)std::min<int64_t>(rows_max, (int64_t)1 << (32 - col_bits)), (int)ceil_div(c->n, rows), col_bits, bucket_bits};
     return true;
 }
 
@@ -1279,7 +1282,8 @@ auto packed_kernel(const dynlp_ctx* c, Fn fn) {
 // memory, parts so uneven that the largest would keep a round waiting, or a row that is too long (no array of entries is
 // kept); the caller then runs ordinary rounds.
 bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan) {
-    const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), tab = parts + 3;
+    const int64_t parts = plan.parts, ent = std::max<int64_t>(c->entries, 1), granules = ceil_div(c->n, 32);
+    const int64_t tab = 2 * (parts + 1) + 3 + granules;
     bool ok = true;
     if (c->n > c->pk_vcap) {
         dev_free(c, c->pk_len);
@@ -1297,7 +1301,6 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
         ok = try_alloc_n(c, c->pk_tab, tab + tab / 8);
         if (ok) c->pk_tab_cap = tab + tab / 8;
     }
-    c->pk_rows = plan.rows;
     c->pk_parts = plan.parts;
     c->pk_bits = plan.col_bits;
     if (ok) {
@@ -1327,16 +1330,20 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
     }
     unsigned int* start = c->pk_tab;
     unsigned int* largest = start + parts + 1;
-    HIPCHK(c, hipMemsetAsync(start + parts, 0, 3 * sizeof(unsigned int), c->stream));
+    unsigned int* bound = largest + 3;
+    unsigned int* gran = bound + parts + 1;
+    HIPCHK(c, hipMemsetAsync(largest + 2, 0, sizeof(unsigned int), c->stream));
     hipLaunchKernelGGL(k_pk_receivers, dim3(grid_for(c->n)), dim3(kBlock), 0, c->stream, c->n, c->meta, c->seed_class, c->deg,
-                       c->pk_len, c->pk_deg);
-    hipLaunchKernelGGL(k_pk_totals, dim3(plan.parts), dim3(kBlock), 0, c->stream, c->n, plan.rows, c->pk_len, start, largest);
-    hipLaunchKernelGGL(k_pb_scan_blocks, dim3(1), dim3(kBlock), 0, c->stream, parts + 1, start);
+                       c->pk_len, c->pk_deg, gran, largest + 2);
+    hipLaunchKernelGGL(k_pk_bounds, dim3(1), dim3(kPkThreads), 0, c->stream, c->n, (int)granules, plan.parts, kPackedRowCost,
+                       (unsigned int)plan.rows, gran, bound, start, largest);
     HIPCHK(c, hipGetLastError());
-    unsigned int most[2] = {0, 0};
+    unsigned int most[3] = {0, 0, 0};  // entries and rows of a part, longest row
     HIPCHK(c, hipMemcpyAsync(most, largest, sizeof most, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const bool refused = (double)most[0] > kPackedUneven * (double)ent / (double)parts || most[1] > kPackedMaxRow;
+    const bool refused = (double)most[0] > kPackedUneven * (double)ent / (double)parts || most[2] > kPackedMaxRow ||
+                         most[1] > (unsigned int)plan.rows;
+    c->pk_rows = (int)most[1];
     if (refused || ent > c->pk_ent_cap) {
         dev_free(c, c->pk_ent);
         c->pk_ent = nullptr;
@@ -1351,7 +1358,7 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
     if (universe.nl)
         hipLaunchKernelGGL(k_pk_long_degrees, dim3(std::min<unsigned int>(universe.nl, (unsigned int)c->num_cu * 8)), dim3(kBlock), 0,
                            c->stream, universe.nl, universe.back, c->meta, c->pool, c->pk_deg);
-    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), (size_t)(plan.rows + 1) * 4, c->stream, c->n, plan.rows, plan.col_bits,
+    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), (size_t)(c->pk_rows + 1) * 4, c->stream, c->n, bound, plan.col_bits,
                        plan.bucket_bits, c->meta, c->pool, c->pk_len, c->pk_deg, start, c->pk_ent);
     HIPCHK(c, hipGetLastError());
     c->pk_built = true;
@@ -1361,7 +1368,7 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
 // One packed round (arguments as for the fused round).
 void launch_packed_round(dynlp_ctx* c, const PullRoundArgs& a, int round) {
     hipEvent_t e1 = open_timed_span(c, round, 1);
-    const PkRound r{a.prev, a.ctr, a.ctr_zero, c->n, c->pk_rows, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab,
+    const PkRound r{a.prev, a.ctr, a.ctr_zero, c->n, c->pk_rows, c->pk_tab + c->pk_parts + 4, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab,
                     c->pk_len, c->meta, c->pool, a.F_in, a.F_out, a.moved_prev, a.moved_cur, a.moved_clear,
                     (unsigned int)c->moved_words, a.tol, a.flags, a.omega};
     const dim3 grid((unsigned int)c->pk_parts), block(kPkThreads);
@@ -1781,7 +1788,7 @@ void launch_product(dynlp_ctx* c, int G, const Frontier& universe, const CgRun& 
         hipLaunchKernelGGL(k_pb_product, dim3(c->pb_bins), dim3(kPbGatherThreads), 0, c->stream, run, c->n, c->pb_bits, bin_off,
                            c->pb_dst, c->pb_wn, reinterpret_cast<const float*>(c->pb_val), c->pb_len, c->deg, p, v);
     } else if (packed) {
-        const PkProduct r{run, c->n, c->pk_rows, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab, c->pk_len, c->deg, p, v};
+        const PkProduct r{run, c->n, c->pk_rows, c->pk_tab + c->pk_parts + 4, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab, c->pk_len, c->deg, p, v};
         packed_kernel(c, [&](auto shape) {
             using S = decltype(shape);
             hipLaunchKernelGGL((k_pk_product<S::cp, S::lanes>), dim3((unsigned int)c->pk_parts), dim3(kPkThreads), packed_lds(c),

@@ -9,7 +9,7 @@
 //
 // While the graph does not change (all rounds of a batch, all sweeps of a static solve) the entries are laid out once
 // for the order the chip wants to read them in:
-//   parts    ranges of consecutive vertices, one workgroup each; the sums of all its rows stay in the workgroup's LDS
+//   parts    ranges of consecutive vertices with about the same number of entries, one workgroup each; the sums of all its rows stay in the workgroup's LDS
 //            from the first entry to the last (256 CUs x 160 KB hold 1,000,000 rows of 10 columns);
 //   buckets  a part's entries are in ascending order of neighbour id (512 ranges of ids).  Every workgroup goes through
 //            the ids in the same order, and since all parts hold about the same number of entries per range, the
@@ -120,15 +120,36 @@ __device__ inline void clear_round_slot(RoundCtr* slot) {  // called by one work
     }
 }
 
-// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0; pk_deg[v] = its degree.
+// len[v] = row length of an updatable vertex (unlabelled, at least one entry), else 0; pk_deg[v] = its degree;
+// gran[g] = the entries of such rows among 32 g .. 32 g + 31; *longest = the longest of all (0 at launch).
 __global__ void __launch_bounds__(kBlock) k_pk_receivers(int64_t n, const RowMeta* __restrict__ meta,
                                                         const int32_t* __restrict__ seed_class,
                                                         const float* __restrict__ deg, int32_t* __restrict__ len,
-                                                        float* __restrict__ pk_deg) {
+                                                        float* __restrict__ pk_deg, unsigned int* __restrict__ gran,
+                                                        unsigned int* longest) {
+    __shared__ unsigned int sm[kBlock / kWave];
     const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (v >= n) return;
-    len[v] = seed_class[v] < 0 ? meta[v].len : 0;
-    pk_deg[v] = deg[v];
+    unsigned int l = 0;
+    if (v < n) {
+        l = seed_class[v] < 0 ? (unsigned int)meta[v].len : 0u;
+        len[v] = (int32_t)l;
+        pk_deg[v] = deg[v];
+    }
+    unsigned int sum = l, most = l;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        if (d < 32) sum += __shfl_xor(sum, d);
+        const unsigned int o = __shfl_xor(most, d);
+        most = most > o ? most : o;
+    }
+    if ((threadIdx.x & 31) == 0 && v < n) gran[v >> 5] = sum;
+    if (lane_id() == 0) sm[threadIdx.x / kWave] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / kWave; ++w) most = most > sm[w] ? most : sm[w];
+        // (atomics on one address run at 1e8 per second: most workgroups find a longer row listed already)
+        if (most > __atomic_load_n(longest, __ATOMIC_RELAXED)) atomicMax(longest, most);
+    }
 }
 
 // Degrees of the long rows (listed backwards from `back`), summed in 64 bits; one workgroup per row.
@@ -153,31 +174,86 @@ __global__ void __launch_bounds__(kBlock) k_pk_long_degrees(unsigned int nl, con
     }
 }
 
-// part_total[p] = the entries of the updatable rows of part p; largest[0] = the largest part, largest[1] = the longest row.
-__global__ void __launch_bounds__(kBlock) k_pk_totals(int64_t n, int rows, const int32_t* __restrict__ len,
-                                                     unsigned int* __restrict__ part_total,
-                                                     unsigned int* __restrict__ largest) {
-    __shared__ unsigned int smem[kBlock / kWave + 1];
-    const int64_t base = (int64_t)blockIdx.x * rows;
-    const int64_t end = base + rows < n ? base + rows : n;
-    unsigned int v = 0, longest = 0;
-    for (int64_t u = base + threadIdx.x; u < end; u += kBlock) {
-        const unsigned int l = (unsigned int)len[u];
-        v += l;
-        longest = longest > l ? longest : l;
+// Cuts the granules into `parts` runs of about the same cost, row_cost entries per row and one per entry (a workgroup sums
+// its entries, then finishes its rows): part p is granules bound[p] .. bound[p + 1] - 1 (maybe none) and the entries
+// start[p] .. start[p + 1] - 1 of the stream.  Where that gives a part more than max_rows rows, cut by rows alone.
+// largest[0], largest[1]: the most entries and rows of a part.
+// With as many rows in every part a power law's hubs fall where they fall, and a round waits for the part that has most
+// entries: 150,000 vertices, power law of mean degree 30, 20 columns: 1.46 times the mean and 60.6 us per round, cut by cost
+// 1.11 times and 52.2 us; planted blocks 1.02 times either way.  One workgroup.
+__global__ void __launch_bounds__(kPkThreads) k_pk_bounds(int64_t n, int granules, int parts, unsigned int row_cost,
+                                                         unsigned int max_rows, const unsigned int* __restrict__ gran,
+                                                         unsigned int* bound, unsigned int* start, unsigned int* __restrict__ largest) {
+    constexpr int NW = kPkThreads / kWave;
+    __shared__ unsigned long long sm_cost[NW];
+    __shared__ unsigned int sm_ent[NW];
+    __shared__ unsigned int most[2];
+    const int per = (granules + kPkThreads - 1) / kPkThreads;
+    const int g0 = (int)threadIdx.x * per < granules ? (int)threadIdx.x * per : granules;
+    const int g1 = g0 + per < granules ? g0 + per : granules;
+    for (unsigned int entry_cost = 1u;; entry_cost = 0u) {  // uniform in the workgroup
+        auto cost_of = [&](int g, unsigned int ent) {
+            const int64_t rows = n - (int64_t)g * 32 < 32 ? n - (int64_t)g * 32 : 32;
+            return (unsigned long long)ent * entry_cost + (unsigned long long)rows * row_cost;
+        };
+        unsigned long long cost = 0;
+        unsigned int ent = 0;
+        for (int g = g0; g < g1; ++g) {
+            const unsigned int e = gran[g];
+            ent += e;
+            cost += cost_of(g, e);
+        }
+        const unsigned long long cost_in = wave_inclusive_scan(cost);
+        const unsigned int ent_in = wave_inclusive_scan(ent);
+        if (lane_id() == kWave - 1) {
+            sm_cost[threadIdx.x / kWave] = cost_in;
+            sm_ent[threadIdx.x / kWave] = ent_in;
+        }
+        if (threadIdx.x < 2) most[threadIdx.x] = 0u;
+        __syncthreads();
+        unsigned long long c = cost_in - cost, total = 0;
+        unsigned int e0 = ent_in - ent;
+        for (int w = 0; w < NW; ++w) {
+            if (w < (int)threadIdx.x / kWave) {
+                c += sm_cost[w];
+                e0 += sm_ent[w];
+            }
+            total += sm_cost[w];
+        }
+        auto part_of = [&](unsigned long long middle) {
+            const unsigned long long p = middle * (unsigned long long)parts / total;
+            return (int)(p < (unsigned long long)parts ? p : (unsigned long long)(parts - 1));
+        };
+        if (g0 < g1) {
+            int before = g0 > 0 ? part_of(c - (cost_of(g0 - 1, gran[g0 - 1]) + 1) / 2) : -1;
+            for (int g = g0; g < g1; ++g) {
+                const unsigned int e = gran[g];
+                const unsigned long long w = cost_of(g, e);
+                const int p = part_of(c + w - (w + 1) / 2);
+                for (int q = before + 1; q <= p; ++q) {
+                    bound[q] = (unsigned int)g;
+                    start[q] = e0;
+                }
+                before = p;
+                c += w;
+                e0 += e;
+            }
+            if (g1 == granules)
+                for (int q = before + 1; q <= parts; ++q) {
+                    bound[q] = (unsigned int)granules;
+                    start[q] = e0;
+                }
+        }
+        __syncthreads();
+        for (int p = threadIdx.x; p < parts; p += kPkThreads) {
+            atomicMax(&most[0], start[p + 1] - start[p]);
+            atomicMax(&most[1], (bound[p + 1] - bound[p]) * 32u);
+        }
+        __syncthreads();
+        if (most[1] <= max_rows || entry_cost == 0u) break;
+        __syncthreads();
     }
-    unsigned int total;
-    (void)block_exclusive_scan<unsigned int>(v, smem, &total);
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        const unsigned int o = (unsigned int)__shfl_xor((int)longest, d);
-        longest = longest > o ? longest : o;
-    }
-    if (lane_id() == 0) atomicMax(&largest[1], longest);
-    if (threadIdx.x == 0) {
-        part_total[blockIdx.x] = total;
-        atomicMax(&largest[0], total);
-    }
+    if (threadIdx.x < 2) largest[threadIdx.x] = most[threadIdx.x];
 }
 
 // Place of the i-th entry of a bucket of L: entries of one row arrive one after the other and would meet at the row's
@@ -194,14 +270,20 @@ __device__ inline unsigned int pk_spread(unsigned int L) {
     }
 }
 
-// The entries of part p to its stretch of the stream, start[p] .. start[p + 1] - 1 (exclusive scan of part_total), in
+// The entries of part p to its stretch of the stream, start[p] .. start[p + 1] - 1, in
 // ascending order of neighbour >> bucket_bits.  Which of a bucket's places an entry gets depends on timing and has no
 // influence on results.  One workgroup per part, one lane per entry (running row lengths in LDS tell its row): the reads
 // of eight entries per lane are in flight together and a hub row is as quick as any other (1,000,000 vertices of degree
 // 20, 16 lanes per row: 667 us).
 constexpr int kPkMaxRows = 32768;  // their running lengths fit the LDS
 
-__global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, int rows, int col_bits, int bucket_bits,
+// Rows of the workgroup's part (0: an empty part).
+__device__ inline int pk_part_rows(int64_t n, const unsigned int* __restrict__ bound) {
+    const int64_t base = (int64_t)bound[blockIdx.x] * 32, end = (int64_t)bound[blockIdx.x + 1] * 32;
+    return (int)((end < n ? end : n) - (base < n ? base : n));
+}
+
+__global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, const unsigned int* __restrict__ bound, int col_bits, int bucket_bits,
                                                         const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
                                                         const int32_t* __restrict__ len, const float* __restrict__ deg,
                                                         const unsigned int* __restrict__ start,
@@ -215,8 +297,8 @@ __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, int rows, in
     __shared__ unsigned int wave_tot[NW];
     static_assert(kPkBuckets <= T, "one thread per bucket");
     unsigned int* const pre = pk_lds;
-    const int64_t base = (int64_t)blockIdx.x * rows;
-    const int nr = (int)(n - base < rows ? n - base : rows);
+    const int64_t base = (int64_t)bound[blockIdx.x] * 32;
+    const int nr = pk_part_rows(n, bound);
     if (threadIdx.x < kPkBuckets) cur[threadIdx.x] = 0u;
     // running row lengths: every thread sums a run of rows, the runs are scanned
     const int per = (nr + T - 1) / T;
@@ -305,7 +387,8 @@ struct PkRound {
     RoundCtr* ctr;
     RoundCtr* ctr_zero;
     int64_t n;
-    int rows;  // per part, a multiple of 32
+    int rows;  // of the largest part, a multiple of 32
+    const unsigned int* bound;  // per part: its first row / 32
     int C;     // stored columns that are in use
     int stride;  // sums per row in LDS: C, rounded up to even where a row has several columns
     int col_bits;
@@ -461,8 +544,8 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_round(PkRound a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->executed = 1;
 
     const int chunk = threadIdx.x % LPN;
-    const int64_t base = (int64_t)blockIdx.x * a.rows;
-    const int nr = (int)(a.n - base < a.rows ? a.n - base : a.rows);  // the host launches no part without rows
+    const int64_t base = (int64_t)a.bound[blockIdx.x] * 32;
+    const int nr = pk_part_rows(a.n, a.bound);
     const int nwords = (nr + 31) / 32;
     unsigned int* const acc = pk_lds;
     unsigned int* const in = pk_lds + a.rows * a.stride;  // rows in V_aff
@@ -606,7 +689,9 @@ __device__ inline Vec<2> pk_signed_sum(unsigned long long s, float unit) {
 struct PkProduct {
     CgRun run;
     int64_t n;
-    int rows, C, stride, col_bits;
+    int rows;
+    const unsigned int* bound;
+    int C, stride, col_bits;
     const PkEntry* ent;
     const unsigned int* start;
     const int32_t* len;
@@ -626,8 +711,8 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_product(PkProduct a) {
     if (cg_done(a.run)) return;
     const float scale = cg_scale(a.run);
     const int chunk = threadIdx.x % LPN;
-    const int64_t base = (int64_t)blockIdx.x * a.rows;
-    const int nr = (int)(a.n - base < a.rows ? a.n - base : a.rows);
+    const int64_t base = (int64_t)a.bound[blockIdx.x] * 32;
+    const int nr = pk_part_rows(a.n, a.bound);
 #pragma unroll 1
     for (int i = threadIdx.x; i < a.rows * a.stride; i += T) pk_lds[i] = 0u;
     __syncthreads();

@@ -222,3 +222,34 @@ def test_packed_stretches_begin_while_nearly_all_rows_move(kind, C, scalar):
         print(kind, C, scalar, tol, "rounds", len(log), "packed", sum(map(_is_packed, log)))
     print(kind, C, scalar, "chains with a large V_aff of which few rows move:", late)
     assert late > 0 or kind == "sbm", "the case is meant to have chains that are left to ordinary rounds"
+
+
+@pytest.mark.parametrize("C,heavy,isolated", [(20, 3000, 9001), (29, 2000, 0), (3, 500, 20000), (64, 37, 1)])
+def test_parts_of_unequal_numbers_of_rows(C, heavy, isolated):
+    """Parts are cut by their entries: the first `heavy` vertices have several times the mean (few rows per part, for 37
+    vertices parts without any row), the last `isolated` none (many rows per part; with 64 columns as many as fit, so that
+    the cut is by rows).  Sweeps and the rounds of a batch against the oracle."""
+    rng = np.random.default_rng(17)
+    n = 36000 + isolated
+    m = 6 * 36000
+    eu = np.concatenate([rng.integers(0, 36000, m), rng.integers(0, heavy, min(m, 60 * heavy))])
+    ev = rng.integers(0, 36000, eu.size)
+    keep = eu != ev
+    rp, col, w = W.edges_to_csr(n, eu[keep], ev[keep], rng.uniform(0.1, 1, int(keep.sum())).astype(np.float32))
+    sv = rng.permutation(36000)[:900].astype(np.int32)
+    sc = rng.integers(0, C, 900).astype(np.int32)
+    g = R.Graph(n, rp, col, w, C, sv, sc)
+    F = R.initial_labels(g.seed_class, C)
+    for _ in range(13):
+        F, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), F, g.seed_class)
+    with P.DynLP(n, rp, col, w, C, sv, sc) as d:
+        d.static_solve(1e-9, 13)
+        assert [_is_packed(r) for r in d.round_log_full()] == [False] * 8 + [True] * 5
+        assert np.max(np.abs(d.get_labels()[0] - F)) <= ROUNDS_ATOL
+        log = d.round_log_full()
+        assert len({(r.rows_short + r.rows_long, r.entries_short + r.entries_long) for r in log}) == 1
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        assert d.static_solve(TOL, 20000)[0] == 0
+        soft = d.get_labels()[0]
+    mean, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), soft.astype(np.float64), g.seed_class)
+    assert np.max(np.abs(mean - soft)) <= 2 * TOL
