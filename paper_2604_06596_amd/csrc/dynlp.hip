@@ -2897,14 +2897,16 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
                                c->meta, c->pool, rank);
             // the batch's entries of every row in a fixed order, then degree, scratch and V_aff flag of the row (the
-            // relocation offsets are no longer needed: their array holds the list of rows with long appended segments)
+            // relocation offsets are no longer needed: their array holds the lists of rows with long appended segments and
+            // of hubs)
             int32_t* long_list = reinterpret_cast<int32_t*>(c->reloc_off);
+            int32_t* hub_list = long_list + c->touched_cap;
             hipLaunchKernelGGL(k_sort_finish, dim3(grid_for((int64_t)nt * 16)), dim3(kBlock), 0, c->stream, nt, c->touched,
-                               c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, c->bc, c->deg, c->flag);
+                               c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc, c->deg, c->flag);
             hipLaunchKernelGGL(k_sort_long_segments, dim3(std::min<unsigned int>(nt, 512u)), dim3(kSortThreads), 0, c->stream,
                                long_list, c->meta, c->pool, c->add_cnt, c->bc);
-            hipLaunchKernelGGL(k_finish_rows, dim3(std::min<unsigned int>(grid_for((int64_t)nt * 16), 512u)), dim3(kBlock), 0,
-                               c->stream, long_list, c->bc, c->meta, c->pool, c->add_cnt, c->deg, c->flag);
+            hipLaunchKernelGGL(k_finish_rows, dim3(std::min<unsigned int>(nt, 1024u)), dim3(kBlock), 0,
+                               c->stream, long_list, hub_list, c->bc, c->meta, c->pool, c->add_cnt, c->deg, c->flag);
             HIPCHK(c, hipGetLastError());
         }
         c->n = n1;

@@ -80,7 +80,7 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned int upd_long;           //                                              long rows
     unsigned long long removed;      // CSR entries removed by the deletion step
     unsigned int sort_long;          // touched rows whose appended segment is sorted by a whole workgroup
-    unsigned int sort_pad;
+    unsigned int finish_hubs;        // hubs whose degree is summed by a whole workgroup
 };
 
 // Rounds over all updatable rows (see accelerate in dynlp.hip).  kRoundAll: every updatable row is updated, whatever moved

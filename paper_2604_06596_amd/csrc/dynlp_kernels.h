@@ -393,6 +393,37 @@ __global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int
     }
 }
 
+// d(u) of a row by a whole workgroup, added in the order in which a 16-lane group adds it (lane j mod 16 takes entry j, then
+// the lanes' sums by halves): the weights pass through LDS in tiles, so that the 16 chains of additions wait for nothing.  A
+// hub of 50,000 entries: 390 dependent trips to memory of 16 lanes took 100 to 200 us.  Thread 0 has the sum.
+constexpr int kHubRow = 1024;    // rows longer than this are handled by a workgroup in the passes of a batch
+constexpr int kDegTile = 4096;   // weights per tile, a multiple of 16
+
+__device__ inline float block_row_degree(const Edge* __restrict__ row, int len, float* tile) {
+    constexpr int G = 16, UN = 8;
+    float s = 0.f;
+    for (int t0 = 0; t0 < len; t0 += kDegTile) {
+        const int m = len - t0 < kDegTile ? len - t0 : kDegTile;
+        for (int i = threadIdx.x; i < m; i += kBlock) tile[i] = row[t0 + i].w;
+        __syncthreads();
+        if (threadIdx.x < G)
+            for (int j0 = threadIdx.x; j0 < m; j0 += UN * G) {
+                float wv[UN];
+#pragma unroll
+                for (int q = 0; q < UN; ++q) wv[q] = j0 + q * G < m ? tile[j0 + q * G] : 0.f;
+#pragma unroll
+                for (int q = 0; q < UN; ++q)
+                    if (j0 + q * G < m) s += wv[q];
+            }
+        __syncthreads();
+    }
+    if (threadIdx.x < G) {
+#pragma unroll
+        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
+    }
+    return s;
+}
+
 // The entries one batch appends to a row land in the order their atomics happened to take.  Sorting
 // the appended segment by (neighbour id, weight bits) makes the stored row, and with it every sum
 // over the row, a function of the batch alone.  16 lanes per touched row; segments of up to
@@ -413,11 +444,13 @@ __device__ inline Edge key_edge(unsigned long long k) {
 // order, lane j mod 16 takes entry j), the counting scratch cleared, the row put into V_aff (both endpoints of every
 // inserted edge are affected).  The sorted weights go through LDS so that the sum needs no second pass over the row.
 // len_is_old: the rows' lengths do not yet include the appended entries (k_write_halfedges with ranks); the kernel
-// then stores the new length.  Rows with long appended segments only get their length and are listed.
+// then stores the new length.  Rows with long appended segments only get their length and are listed (long_list), hubs that
+// received a few entries are sorted and listed for k_finish_rows (hub_list).
 __global__ void __launch_bounds__(kBlock) k_sort_finish(unsigned int nt, const int32_t* __restrict__ touched,
                                                        RowMeta* __restrict__ meta, Edge* __restrict__ pool,
                                                        int32_t* __restrict__ add_cnt, int len_is_old,
-                                                       int32_t* __restrict__ long_list, BatchCtr* bc,
+                                                       int32_t* __restrict__ long_list,
+                                                       int32_t* __restrict__ hub_list, BatchCtr* bc,
                                                        float* __restrict__ deg, uint8_t* __restrict__ flag) {
     constexpr int G = 16;
     __shared__ float sorted_w[kBlock / G][G * kSortRegs];
@@ -491,9 +524,15 @@ __global__ void __launch_bounds__(kBlock) k_sort_finish(unsigned int nt, const i
         return;
     }
     const int len_new = len_old + a;
+    if (len_new > kHubRow) {
+        if (gl == 0) {
+            if (len_is_old) meta[u].len = len_new;
+            hub_list[atomicAdd(&bc->finish_hubs, 1u)] = u;
+        }
+        return;
+    }
     float s = 0.f;
-    // (a row may be a hub of tens of thousands of entries that received a few: several loads in flight, added in order)
-    constexpr int UN = 4;
+    constexpr int UN = 4;  // loads in flight, added in order
     for (int j0 = gl; j0 < len_new; j0 += UN * G) {
         float wv[UN];
 #pragma unroll
@@ -613,32 +652,21 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(const int32
     }
 }
 
-// The rows k_sort_long_segments has sorted (their number is bc->sort_long): recompute d(u) from the stored row in
-// the same order as k_sort_finish, clear the counting scratch, and put the row into V_aff.
-__global__ void __launch_bounds__(kBlock) k_finish_rows(const int32_t* __restrict__ list, const BatchCtr* bc,
+// The rows k_sort_long_segments has sorted (bc->sort_long of them) and the hubs that k_sort_finish listed
+// (bc->finish_hubs): recompute d(u) from the stored row in the same order as k_sort_finish, clear the counting scratch, and
+// put the row into V_aff.  One workgroup per row.
+__global__ void __launch_bounds__(kBlock) k_finish_rows(const int32_t* __restrict__ long_list,
+                                                       const int32_t* __restrict__ hub_list, const BatchCtr* bc,
                                                        const RowMeta* __restrict__ meta,
                                                        const Edge* __restrict__ pool, int32_t* __restrict__ add_cnt,
                                                        float* __restrict__ deg, uint8_t* __restrict__ flag) {
-    constexpr int G = 16;
-    const unsigned int count = bc->sort_long;
-    const int gl = threadIdx.x % G;
-    for (unsigned int t = (blockIdx.x * kBlock + threadIdx.x) / G; t < count; t += gridDim.x * (kBlock / G)) {
-        const int32_t u = list[t];
+    __shared__ float tile[kDegTile];
+    const unsigned int nl = bc->sort_long, count = nl + bc->finish_hubs;
+    for (unsigned int t = blockIdx.x; t < count; t += gridDim.x) {
+        const int32_t u = t < nl ? long_list[t] : hub_list[t - nl];
         const RowMeta m = meta[u];
-        float s = 0.f;
-        // these are hub rows of up to tens of thousands of entries: 8 loads in flight per lane, added in order
-        constexpr int UN = 8;
-        for (int j0 = gl; j0 < m.len; j0 += UN * G) {
-            float wv[UN];
-#pragma unroll
-            for (int q = 0; q < UN; ++q) wv[q] = j0 + q * G < m.len ? pool[m.off + j0 + q * G].w : 0.f;
-#pragma unroll
-            for (int q = 0; q < UN; ++q)
-                if (j0 + q * G < m.len) s += wv[q];
-        }
-#pragma unroll
-        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
-        if (gl == 0) {
+        const float s = block_row_degree(pool + m.off, m.len, tile);
+        if (threadIdx.x == 0) {
             deg[u] = s;
             add_cnt[u] = 0;
             if (flag) flag[u] = 1;
@@ -677,6 +705,11 @@ __global__ void __launch_bounds__(kBlock) k_mark_deleted(int64_t nd, const int32
 // first touch, into the list of rows that must drop their entries towards deleted vertices.  The
 // deleted row keeps its place and capacity in the pool (a later batch may give the id edges again);
 // its label row becomes the neutral 1/C.
+// Rows of up to kLongRow entries are held in registers, and a workgroup appends what its 16 rows touch first with one
+// atomic (atomics on one address run at 1e8 per second; one per 64 entries: 30,000 vertices of degree 32 took 190 us);
+// longer rows are left to the whole workgroup (a hub of 50,000 entries walked by 16 lanes took 1.2 ms).
+constexpr int kDeleteRegs = 8;  // entries per lane: rows of up to 128
+
 __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_t* __restrict__ del, int C, int Cs, int CP,
                                                        RowMeta* meta, const Edge* __restrict__ pool,
                                                        const int32_t* __restrict__ seed_class,
@@ -684,101 +717,174 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
                                                        int32_t* __restrict__ touched, float* __restrict__ deg,
                                                        float* __restrict__ F, BatchCtr* bc) {
     constexpr int G = 16;
+    __shared__ unsigned int smem[kBlock / kWave + 1];
+    __shared__ int64_t long_off[kBlock / G];
+    __shared__ int long_len[kBlock / G];
+    __shared__ unsigned int nlong;
+    if (threadIdx.x == 0) nlong = 0u;
+    __syncthreads();
     const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
     const int gl = threadIdx.x % G;
     int len = 0;
-    int32_t u = 0;
     int64_t off = 0;
     if (i < nd) {
-        u = del[i];
+        const int32_t u = del[i];
         if (gl == 0) len = atomicExch(&meta[u].len, 0);
         len = __shfl(len, 0, G);
         off = meta[u].off;
-    }
-    // all 64 lanes of the wave walk together (wave_reserve needs every lane)
-    int maxlen = len;
-#pragma unroll
-    for (int d = G; d < kWave; d <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, d, kWave));
-    unsigned long long removed = 0;
-    for (int base = 0; base < maxlen; base += G) {
-        const int j = base + gl;
-        bool first = false;
-        int32_t v = -1;
-        if (j < len) {
-            v = pool[off + j].col;
-            removed += 1;
-            if (seed_class[v] != kDeletedMark) {
-                flag[v] = 1;
-                removed += 1;  // the entry v -> u goes as well
-                first = atomicAdd(&add_cnt[v], 1) == 0;
-            }
-        }
-        const unsigned int slot = wave_reserve(&bc->touched, first);
-        if (first) touched[slot] = v;
-    }
-    removed = wave_sum(removed);
-    if (lane_id() == 0 && removed) atomicAdd(&bc->removed, removed);
-    if (i < nd) {  // also for a vertex that had no edges, or is listed twice: the same values again
+        // also for a vertex that had no edges, or is listed twice: the same values again
         if (gl == 0) deg[u] = 0.f;
         for (int c = gl; c < CP; c += G) F[(size_t)u * CP + c] = c < Cs ? 1.0f / (float)C : 0.f;
+        if (len > G * kDeleteRegs) {
+            if (gl == 0) {
+                const unsigned int k = atomicAdd(&nlong, 1u);
+                long_off[k] = off;
+                long_len[k] = len;
+            }
+            len = 0;
+        }
     }
+    unsigned long long removed = 0;
+    int32_t v[kDeleteRegs];
+    // the entries of one step: item q of this thread is entry at + q * stride (below end)
+    auto take = [&](int64_t row, int at, int stride, int end) {
+        unsigned int first = 0;
+#pragma unroll
+        for (int q = 0; q < kDeleteRegs; ++q) v[q] = at + q * stride < end ? pool[row + at + q * stride].col : -1;
+#pragma unroll
+        for (int q = 0; q < kDeleteRegs; ++q) {
+            if (v[q] < 0) continue;
+            removed += 1;
+            if (seed_class[v[q]] == kDeletedMark) continue;
+            flag[v[q]] = 1;
+            removed += 1;  // the entry v -> u goes as well
+            if (atomicAdd(&add_cnt[v[q]], 1) == 0) first |= 1u << q;
+        }
+        unsigned int slot = block_reserve(&bc->touched, (unsigned int)__popc(first), smem);
+#pragma unroll
+        for (int q = 0; q < kDeleteRegs; ++q)
+            if ((first >> q) & 1u) touched[slot++] = v[q];
+    };
+    take(off, gl, G, len);
+    for (unsigned int k = 0; k < nlong; ++k)  // uniform in the workgroup (block_reserve has barriers)
+        for (int base = 0; base < long_len[k]; base += kDeleteRegs * kBlock) take(long_off[k], base + (int)threadIdx.x, kBlock, long_len[k]);
+    removed = wave_sum(removed);
+    __shared__ unsigned long long block_removed;
+    if (threadIdx.x == 0) block_removed = 0ull;
+    __syncthreads();
+    if (lane_id() == 0) atomicAdd(&block_removed, removed);
+    __syncthreads();
+    if (threadIdx.x == 0 && block_removed) atomicAdd(&bc->removed, block_removed);
 }
 
 // Touched rows: drop the entries that point at deleted vertices, keeping the order of the others,
-// then recompute d(v) from the stored row (same summation order as k_finish_rows) and clear the
+// then recompute d(v) from the stored row (same summation order as k_sort_finish) and clear the
 // counting scratch.  16 lanes per row; a chunk is loaded completely before any of it is written
-// back, and the write position never passes the read position.
+// back, and the write position never passes the read position.  Hubs are left to the whole workgroup.
 __global__ void __launch_bounds__(kBlock) k_drop_deleted_entries(unsigned int nt, const int32_t* __restrict__ touched,
                                                                 RowMeta* __restrict__ meta, Edge* __restrict__ pool,
                                                                 const int32_t* __restrict__ seed_class,
                                                                 int32_t* __restrict__ add_cnt,
                                                                 float* __restrict__ deg) {
     constexpr int G = 16;
+    __shared__ float tile[kDegTile];
+    __shared__ unsigned int smem[kBlock / kWave + 1];
+    __shared__ int32_t hub[kBlock / G];
+    __shared__ unsigned int nhubs;
+    if (threadIdx.x == 0) nhubs = 0u;
+    __syncthreads();
     const unsigned int t = (blockIdx.x * kBlock + threadIdx.x) / G;
     const int gl = threadIdx.x % G;
     const int gshift = (lane_id() / G) * G;
-    if (t >= nt) return;
-    const int32_t v = touched[t];
-    const RowMeta m = meta[v];
-    int out = 0;
-    // UN chunks of G entries per step (the row may be a hub of tens of thousands of entries): their loads and the
-    // lookups of their neighbours are in flight together; the kept ones are written in order, always to positions
-    // that lie before everything the step has read
-    constexpr int UN = 4;
-    for (int base = 0; base < m.len; base += UN * G) {
-        Edge e[UN];
-        bool keep[UN];
-#pragma unroll
-        for (int q = 0; q < UN; ++q) {
-            const int j = base + q * G + gl;
-            e[q].col = 0;
-            e[q].w = 0.f;
-            if (j < m.len) e[q] = pool[m.off + j];
-        }
-#pragma unroll
-        for (int q = 0; q < UN; ++q) keep[q] = base + q * G + gl < m.len && seed_class[e[q].col] != kDeletedMark;
-#pragma unroll
-        for (int q = 0; q < UN; ++q) {
-            const unsigned int mask = (unsigned int)((__ballot(keep[q]) >> gshift) & 0xffffull);
-            if (keep[q]) pool[m.off + out + __popc(mask & ((1u << gl) - 1u))] = e[q];
-            out += __popc(mask);
+    int32_t v = 0;
+    RowMeta m;
+    m.off = 0;
+    m.len = 0;
+    m.cap = 0;
+    bool own = t < nt;
+    if (own) {
+        v = touched[t];
+        m = meta[v];
+        if (m.len > kHubRow) {
+            if (gl == 0) hub[atomicAdd(&nhubs, 1u)] = v;
+            own = false;
         }
     }
-    float s = 0.f;
-    for (int j0 = gl; j0 < out; j0 += 8 * G) {  // the same order of additions as k_sort_finish / k_finish_rows
-        float wv[8];
+    if (own) {
+        int out = 0;
+        // UN chunks of G entries per step: their loads and the lookups of their neighbours are in flight together; the
+        // kept ones are written in order, always to positions that lie before everything the step has read
+        constexpr int UN = 4;
+        for (int base = 0; base < m.len; base += UN * G) {
+            Edge e[UN];
+            bool keep[UN];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) wv[q] = j0 + q * G < out ? pool[m.off + j0 + q * G].w : 0.f;
+            for (int q = 0; q < UN; ++q) {
+                const int j = base + q * G + gl;
+                e[q].col = 0;
+                e[q].w = 0.f;
+                if (j < m.len) e[q] = pool[m.off + j];
+            }
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (j0 + q * G < out) s += wv[q];
+            for (int q = 0; q < UN; ++q) keep[q] = base + q * G + gl < m.len && seed_class[e[q].col] != kDeletedMark;
+#pragma unroll
+            for (int q = 0; q < UN; ++q) {
+                const unsigned int mask = (unsigned int)((__ballot(keep[q]) >> gshift) & 0xffffull);
+                if (keep[q]) pool[m.off + out + __popc(mask & ((1u << gl) - 1u))] = e[q];
+                out += __popc(mask);
+            }
+        }
+        float s = 0.f;
+        for (int j0 = gl; j0 < out; j0 += 8 * G) {  // the same order of additions as k_sort_finish
+            float wv[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) wv[q] = j0 + q * G < out ? pool[m.off + j0 + q * G].w : 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (j0 + q * G < out) s += wv[q];
+        }
+#pragma unroll
+        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
+        if (gl == 0) {
+            meta[v].len = out;
+            deg[v] = s;
+            add_cnt[v] = 0;
+        }
     }
+    __syncthreads();
+    for (unsigned int k = 0; k < nhubs; ++k) {  // uniform in the workgroup
+        const int32_t h = hub[k];
+        const RowMeta r = meta[h];
+        constexpr int UN = 8;  // neighbouring entries per thread
+        unsigned int out = 0;
+        for (int base = 0; base < r.len; base += UN * kBlock) {
+            const int j0 = base + (int)threadIdx.x * UN;
+            Edge e[UN];
+            unsigned int keep = 0;
 #pragma unroll
-    for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
-    if (gl == 0) {
-        meta[v].len = out;
-        deg[v] = s;
-        add_cnt[v] = 0;
+            for (int q = 0; q < UN; ++q) {
+                e[q].col = -1;
+                e[q].w = 0.f;
+                if (j0 + q < r.len) e[q] = pool[r.off + j0 + q];
+            }
+#pragma unroll
+            for (int q = 0; q < UN; ++q)
+                if (e[q].col >= 0 && seed_class[e[q].col] != kDeletedMark) keep |= 1u << q;
+            // (the barriers of the scan: the whole step has been read before any of it is written)
+            unsigned int total;
+            unsigned int at = out + block_exclusive_scan<unsigned int>((unsigned int)__popc(keep), smem, &total);
+#pragma unroll
+            for (int q = 0; q < UN; ++q)
+                if ((keep >> q) & 1u) pool[r.off + at++] = e[q];
+            out += total;
+        }
+        __syncthreads();
+        const float s = block_row_degree(pool + r.off, (int)out, tile);
+        if (threadIdx.x == 0) {
+            meta[h].len = (int)out;
+            deg[h] = s;
+            add_cnt[h] = 0;
+        }
     }
 }
 

@@ -224,15 +224,14 @@ def test_packed_stretches_begin_while_nearly_all_rows_move(kind, C, scalar):
     assert late > 0 or kind == "sbm", "the case is meant to have chains that are left to ordinary rounds"
 
 
-@pytest.mark.parametrize("C,heavy,isolated", [(20, 3000, 9001), (29, 2000, 0), (3, 500, 20000), (64, 37, 1)])
-def test_parts_of_unequal_numbers_of_rows(C, heavy, isolated):
-    """Parts are cut by their entries: the first `heavy` vertices have several times the mean (few rows per part, for 37
-    vertices parts without any row), the last `isolated` none (many rows per part; with 64 columns as many as fit, so that
+@pytest.mark.parametrize("C,heavy,extra,isolated", [(20, 3000, 60, 9001), (29, 2000, 60, 0), (3, 500, 20, 20000), (64, 37, 60, 1)])
+def test_parts_of_unequal_numbers_of_rows(C, heavy, extra, isolated):
+    """Parts are cut by their entries: the first `heavy` vertices have several times the mean (few rows per part), the last `isolated` none (many rows per part; with 64 columns as many as fit, so that
     the cut is by rows).  Sweeps and the rounds of a batch against the oracle."""
     rng = np.random.default_rng(17)
     n = 36000 + isolated
-    m = 6 * 36000
-    eu = np.concatenate([rng.integers(0, 36000, m), rng.integers(0, heavy, min(m, 60 * heavy))])
+    m = 8 * 36000
+    eu = np.concatenate([rng.integers(0, 36000, m), rng.integers(0, heavy, extra * heavy)])
     ev = rng.integers(0, 36000, eu.size)
     keep = eu != ev
     rp, col, w = W.edges_to_csr(n, eu[keep], ev[keep], rng.uniform(0.1, 1, int(keep.sum())).astype(np.float32))
