@@ -134,6 +134,8 @@ struct dynlp_ctx {
     int32_t *b_eu = nullptr, *b_ev = nullptr, *b_sv = nullptr, *b_sc = nullptr;
     float* b_ew = nullptr;
     int64_t b_edge_cap = 0, b_seed_cap = 0;
+    int32_t* b_del = nullptr;
+    int64_t b_del_cap = 0;
 
     // pipelined ingest of host-resident batches (see ingest_edges)
     int64_t ingest_chunk = 0;            // edges per chunk
@@ -147,7 +149,11 @@ struct dynlp_ctx {
     BatchCtr* bc = nullptr;
     RoundCtr* h_slot = nullptr;  // pinned, kRing slots
     unsigned int h_slot_start_long = 0;  // long rows among the updatable vertices of the running static solve
-    BatchCtr* h_bc = nullptr;    // pinned
+    struct HostStart {
+        RoundCtr start;
+        BatchCtr bc;
+    }* h_start = nullptr;        // pinned: the start slot and the batch counters, which lie behind it on the device too
+    BatchCtr* h_bc = nullptr;    // (in h_start)
 
     int update_mode = DYNLP_UPDATE_SYNCHRONOUS;
     bool final_check = false;  // dynlp_set_final_check
@@ -441,14 +447,16 @@ void grow_pool(dynlp_ctx* c, int64_t min_cap) {
     c->pool_cap = new_cap;
 }
 
-void ensure_batch_scratch(dynlp_ctx* c, int64_t m, int64_t s) {
-    const int64_t need_t = std::max<int64_t>(1, std::min<int64_t>(2 * m, c->n_cap));
+void ensure_batch_scratch(dynlp_ctx* c, int64_t nd, int64_t m, int64_t s) {
+    // (with deletions any vertex may lose an entry)
+    const int64_t need_t = nd > 0 ? c->n_cap : std::max<int64_t>(1, std::min<int64_t>(2 * m, c->n_cap));
     if (need_t > c->touched_cap) {
         dev_free(c, c->touched);
         dev_free(c, c->reloc_off);
         c->touched = nullptr;
         c->reloc_off = nullptr;
-        const int64_t cap = need_t + need_t / 2;
+        const int64_t cap = nd > 0 ? need_t : need_t + need_t / 2;
+        c->touched_cap = 0;
         c->touched = dev_alloc_n<int32_t>(c, cap);
         c->reloc_off = dev_alloc_n<int64_t>(c, cap);
         c->touched_cap = cap;
@@ -461,6 +469,13 @@ void ensure_batch_scratch(dynlp_ctx* c, int64_t m, int64_t s) {
         if (c->he_rank) c->he_rank_cap = 3 * m;
     }
     if (!c->dev_ptrs) {
+        if (nd > c->b_del_cap) {
+            dev_free(c, c->b_del);
+            c->b_del = nullptr;
+            c->b_del_cap = 0;
+            c->b_del = dev_alloc_n<int32_t>(c, nd + nd / 2);
+            c->b_del_cap = nd + nd / 2;
+        }
         if (m > c->b_edge_cap) {
             dev_free(c, c->b_eu);
             dev_free(c, c->b_ev);
@@ -569,7 +584,8 @@ void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, c
                            c->b_ev + off, c->b_ew + off, c->bc, off);
         hipLaunchKernelGGL(k_count_halfedges, dim3(grid_for(ceil_div(2 * mc, kAppendItems))), dim3(kBlock), 0, c->stream, mc,
                            n_total, c->b_eu + off, c->b_ev + off, c->add_cnt, c->touched, c->bc,
-                           c->he_rank ? c->he_rank + off : nullptr, c->he_rank ? c->he_rank + m + off : nullptr);
+                           c->he_rank ? c->he_rank + off : nullptr, c->he_rank ? c->he_rank + m + off : nullptr,
+                           grid_for(ceil_div(2 * mc, kAppendItems)), (int64_t)0, (const int32_t*)nullptr, (int32_t*)nullptr);
         HIPCHK(c, hipGetLastError());
     }
     c->ingest_chunks_last = chunks;
@@ -1427,6 +1443,15 @@ void launch_compact(dynlp_ctx* c, const Frontier& out, unsigned int* count_short
     HIPCHK(c, hipGetLastError());
 }
 
+// The first frontier of a batch (its size goes to the start slot) and the list of all updatable vertices.
+void launch_compact_start(dynlp_ctx* c, const Frontier& out, const Frontier& universe, const BatchGate& gate) {
+    const int seg = c->n >= (16 << 20) ? 4 : 1;
+    const unsigned int blocks = (unsigned int)ceil_div(std::max<int64_t>(c->n, 1), seg * kFlagsPerBlock);
+    auto kernel = seg == 4 ? k_compact_start<4> : k_compact_start<1>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, c->stream, (unsigned int)c->n, c->flag, c->seed_class, c->meta, out.front,
+                       out.back, c->ring + kRing, universe.front, universe.back, c->bc, gate);
+}
+
 void launch_commit(dynlp_ctx* c, const Frontier& f, const RoundCtr* prev, int64_t rows_bound) {
     const int64_t items = rows_bound * (c->CP >= 4 ? c->CP / 4 : c->CP);
     const unsigned int blocks = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(items, kBlock), (int64_t)c->num_cu * 8));
@@ -1534,6 +1559,12 @@ void read_slots(dynlp_ctx* c, int t0, int count) {
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (int i = 0; i < count; ++i) fold_slot(c->h_slot[i]);
+}
+
+// The start slot and the batch counters, in one copy.
+void read_start(dynlp_ctx* c) {
+    HIPCHK(c, hipMemcpyAsync(c->h_start, c->ring + kRing, sizeof(dynlp_ctx::HostStart), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
 }
 
 void read_slots_start(dynlp_ctx* c) {
@@ -1979,7 +2010,7 @@ void destroy_ctx(dynlp_ctx* c) {
     (void)hipSetDevice(c->device);
     if (c->stream || c->meta) (void)hipStreamSynchronize(c->stream);
     void* ptrs[] = {c->meta, c->pool, c->F, c->F2, c->seed_class, c->flag, c->queue[0], c->queue[1], c->queue[2], c->moved[0], c->moved[1], c->moved[2], c->add_cnt,
-                    c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc,
+                    c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
                     c->pb_src, c->pb_sp, c->pb_row0, c->pb_lpos, c->pb_tmp, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, c->pb_upd,
                     c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab,
@@ -1992,7 +2023,6 @@ void destroy_ctx(dynlp_ctx* c) {
     for (hipEvent_t e : c->init_ev)
         if (e) (void)hipEventDestroy(e);
     dev_free(c, c->ring);
-    dev_free(c, c->bc);
     dev_free(c, c->persist_ctl);
     for (void* b : c->bounce)
         if (b) (void)hipHostFree(b);
@@ -2000,7 +2030,7 @@ void destroy_ctx(dynlp_ctx* c) {
         if (e) (void)hipEventDestroy(e);
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
     if (c->h_slot) (void)hipHostFree(c->h_slot);
-    if (c->h_bc) (void)hipHostFree(c->h_bc);
+    if (c->h_start) (void)hipHostFree(c->h_start);
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
@@ -2234,10 +2264,11 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         HIPCHK(c, hipGetDeviceProperties(&prop, c->device));
         c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
         c->persist_ctl = static_cast<unsigned int*>(dev_alloc(c, kBarWords * sizeof(unsigned int)));
-        c->ring = static_cast<RoundCtr*>(dev_alloc(c, sizeof(RoundCtr) * (kRing + 1)));
-        c->bc = static_cast<BatchCtr*>(dev_alloc(c, sizeof(BatchCtr)));
+        c->ring = static_cast<RoundCtr*>(dev_alloc(c, sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)));
+        c->bc = reinterpret_cast<BatchCtr*>(c->ring + kRing + 1);
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_slot), sizeof(RoundCtr) * kRing, hipHostMallocDefault));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_bc), sizeof(BatchCtr), hipHostMallocDefault));
+        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_start), sizeof(dynlp_ctx::HostStart), hipHostMallocDefault));
+        c->h_bc = &c->h_start->bc;
         for (auto& e : c->phase_ev) HIPCHK(c, hipEventCreate(&e));
         std::memset(c->h_bc, 0, sizeof(BatchCtr));
         write_bc(c);
@@ -2779,159 +2810,123 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         reset_timed_spans(c);
         // ---- capacity for new vertices; their rows start empty, unlabelled, uniform ----
         if (n1 > c->n_cap) alloc_vertex_arrays(c, n1 + std::max<int64_t>(n1 / 2, 1024));
-        ensure_batch_scratch(c, m, s);
+        ensure_batch_scratch(c, nd, m, s);
         const bool use_rank = c->he_rank != nullptr;
-        const int32_t *d_eu = eu, *d_ev = ev, *d_sv = sv, *d_sc = sc;
+        const int32_t *d_eu = eu, *d_ev = ev, *d_sv = sv, *d_sc = sc, *d_del = del;
         const float* d_ew = ew;
         c->ingest_chunks_last = 0;
         if (!c->dev_ptrs) {
-            if (m > 0 && !pipelined) {
-                HIPCHK(c, hipMemcpyAsync(c->b_eu, eu, (size_t)m * 4, hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipMemcpyAsync(c->b_ev, ev, (size_t)m * 4, hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipMemcpyAsync(c->b_ew, ew, (size_t)m * 4, hipMemcpyHostToDevice, c->stream));
+            auto send = [&](void* to, const void* from, int64_t count) {
+                if (count > 0) HIPCHK(c, hipMemcpyAsync(to, from, (size_t)count * 4, hipMemcpyHostToDevice, c->stream));
+            };
+            if (!pipelined) {
+                send(c->b_eu, eu, m);
+                send(c->b_ev, ev, m);
+                send(c->b_ew, ew, m);
             }
-            if (s > 0) {
-                HIPCHK(c, hipMemcpyAsync(c->b_sv, sv, (size_t)s * 4, hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipMemcpyAsync(c->b_sc, sc, (size_t)s * 4, hipMemcpyHostToDevice, c->stream));
-            }
+            send(c->b_sv, sv, s);
+            send(c->b_sc, sc, s);
+            send(c->b_del, del, nd);
             d_eu = c->b_eu;
             d_ev = c->b_ev;
             d_ew = c->b_ew;
             d_sv = c->b_sv;
             d_sc = c->b_sc;
+            d_del = c->b_del;
         }
         HIPCHK(c, hipEventRecord(c->phase_ev[0], c->stream));
 
-        // ---- deletions come first (Alg. 2 Step 1): the whole batch is validated before anything changes ----
+        // ---- Alg. 2 Step 1.  Everything up to the first list of rows is queued without a wait: the kernels that change the
+        // graph look at the result of the checks and at the planned size of the pool themselves (BatchGate).  Deletions come
+        // first; the whole batch is checked before anything changes ----
+        const unsigned int zero_words = (unsigned int)((sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)) / sizeof(unsigned int));
+        hipLaunchKernelGGL(k_batch_begin, dim3(64), dim3(kBlock), 0, c->stream, reinterpret_cast<unsigned int*>(c->ring), zero_words,
+                           c->bc, (unsigned long long)c->pool_tail);
+        const int64_t checked = nd + (pipelined ? 0 : m) + s;
+        if (checked > 0)
+            hipLaunchKernelGGL(k_validate_batch, dim3(grid_for(checked)), dim3(kBlock), 0, c->stream, nd, d_del, pipelined ? 0 : m, d_eu,
+                               d_ev, d_ew, s, d_sv, d_sc, n1, n0, c->C, c->seed_class, c->add_cnt, c->bc);
+        if (nd + s + k > 0)
+            hipLaunchKernelGGL(k_batch_prepare, dim3(grid_for(nd + s + k)), dim3(kBlock), 0, c->stream, c->bc, nd, d_del, s, d_sv, n1,
+                               c->add_cnt, n0, k, c->meta, c->deg, c->seed_class);
+        const unsigned int most_blocks = (unsigned int)c->num_cu * 32;  // of kernels that find the number of their rows on the device
         if (nd > 0) {
-            DevIn<int32_t> d_del(c, del, nd);
-            if (c->n_cap > c->touched_cap) {  // any vertex may lose an entry
-                dev_free(c, c->touched);
-                dev_free(c, c->reloc_off);
-                c->touched = nullptr;
-                c->reloc_off = nullptr;
-                c->touched_cap = 0;
-                c->touched = dev_alloc_n<int32_t>(c, c->n_cap);
-                c->reloc_off = dev_alloc_n<int64_t>(c, c->n_cap);
-                c->touched_cap = c->n_cap;
-            }
-            std::memset(c->h_bc, 0, sizeof(BatchCtr));
-            c->h_bc->pool_tail = (unsigned long long)c->pool_tail;
-            HIPCHK(c, hipMemcpyAsync(c->bc, c->h_bc, sizeof(BatchCtr), hipMemcpyHostToDevice, c->stream));
-            hipLaunchKernelGGL(k_validate_deleted, dim3(grid_for(nd)), dim3(kBlock), 0, c->stream, nd, n0, d_del.ptr, c->bc);
-            if (m > 0)
-                hipLaunchKernelGGL(k_validate_edges, dim3(grid_for(m)), dim3(kBlock), 0, c->stream, m, n1, d_eu, d_ev, d_ew,
-                                   c->bc);
-            if (s > 0) {
-                hipLaunchKernelGGL(k_validate_seeds, dim3(grid_for(s)), dim3(kBlock), 0, c->stream, s, n1, n0, c->C, d_sv,
-                                   d_sc, c->seed_class, c->add_cnt, c->bc);
-                hipLaunchKernelGGL(k_clear_seed_tmp, dim3(grid_for(s)), dim3(kBlock), 0, c->stream, s, n1, d_sv, c->add_cnt);
-            }
-            HIPCHK(c, hipGetLastError());
-            read_bc(c);
-            if (c->h_bc->err_code) return bad(format_validation(c->h_bc->err_code, c->h_bc->err_index));
             mutated = true;
-            hipLaunchKernelGGL(k_mark_deleted, dim3(grid_for(nd)), dim3(kBlock), 0, c->stream, nd, d_del.ptr, c->seed_class,
-                               kDeletedMark);
-            hipLaunchKernelGGL(k_delete_rows, dim3(grid_for(nd * 16)), dim3(kBlock), 0, c->stream, nd, d_del.ptr, c->C, c->Cs, c->CP,
-                               c->meta, c->pool, c->seed_class, c->flag, c->add_cnt, c->touched, c->deg, c->F, c->bc);
-            HIPCHK(c, hipGetLastError());
-            read_bc(c);
-            const unsigned int nt_del = c->h_bc->touched;
-            if (nt_del)
-                hipLaunchKernelGGL(k_drop_deleted_entries, dim3(grid_for((int64_t)nt_del * 16)), dim3(kBlock), 0, c->stream,
-                                   nt_del, c->touched, c->meta, c->pool, c->seed_class, c->add_cnt, c->deg);
-            hipLaunchKernelGGL(k_mark_deleted, dim3(grid_for(nd)), dim3(kBlock), 0, c->stream, nd, d_del.ptr, c->seed_class, -1);
-            HIPCHK(c, hipGetLastError());
-            c->entries -= (int64_t)c->h_bc->removed;
+            int32_t* dropping = reinterpret_cast<int32_t*>(c->reloc_off);  // (not in use before the plan)
+            hipLaunchKernelGGL(k_delete_rows, dim3(grid_for(nd * 16)), dim3(kBlock), 0, c->stream, nd, d_del, c->C, c->Cs, c->CP,
+                               c->meta, c->pool, c->seed_class, c->flag, c->add_cnt, dropping, c->deg, c->F, c->bc);
+            // (rows that lose entries: as many as the deleted rows have entries, which the host does not know; the mean tells)
+            const double guess = 16.0 * (double)nd * std::max(1.0, (double)c->entries / (double)std::max<int64_t>(1, c->n));
+            hipLaunchKernelGGL(k_drop_deleted_entries, dim3(std::min<unsigned int>(grid_for((int64_t)std::min(guess, 1e9)), most_blocks)),
+                               dim3(kBlock), 0, c->stream, c->bc, dropping, c->meta, c->pool, c->seed_class, c->add_cnt, c->deg);
         }
-
-        // ---- validate, count entries per row, plan relocations: one read-back for all three ----
-        std::memset(c->h_bc, 0, sizeof(BatchCtr));
-        c->h_bc->pool_tail = (unsigned long long)c->pool_tail;
-        HIPCHK(c, hipMemcpyAsync(c->bc, c->h_bc, sizeof(BatchCtr), hipMemcpyHostToDevice, c->stream));
-        if (m > 0 && !pipelined)
-            hipLaunchKernelGGL(k_validate_edges, dim3(grid_for(m)), dim3(kBlock), 0, c->stream, m, n1, d_eu, d_ev, d_ew, c->bc);
-        if (s > 0) {
-            hipLaunchKernelGGL(k_validate_seeds, dim3(grid_for(s)), dim3(kBlock), 0, c->stream, s, n1, n0, c->C, d_sv,
-                               d_sc, c->seed_class, c->add_cnt, c->bc);
-            hipLaunchKernelGGL(k_clear_seed_tmp, dim3(grid_for(s)), dim3(kBlock), 0, c->stream, s, n1, d_sv, c->add_cnt);
-        }
-        if (k > 0) {  // empty rows for the new ids (scratch state only until n is advanced)
-            hipLaunchKernelGGL(k_init_meta, dim3(grid_for(k)), dim3(kBlock), 0, c->stream, n0, n1, c->meta, c->deg);
-            hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(k)), dim3(kBlock), 0, c->stream, n0, n1, c->seed_class, -1);
-        }
-        if (pipelined)
+        if (pipelined) {
             ingest_edges(c, m, n1, eu, ev, ew);
-        else if (m > 0)
-            hipLaunchKernelGGL(k_count_halfedges, dim3(grid_for(ceil_div(2 * m, kAppendItems))), dim3(kBlock), 0, c->stream, m, n1, d_eu, d_ev,
-                               c->add_cnt, c->touched, c->bc, use_rank ? c->he_rank : nullptr,
-                               use_rank ? c->he_rank + m : nullptr);
+        } else if (m + nd > 0) {
+            const unsigned int count_blocks = m > 0 ? grid_for(ceil_div(2 * m, kAppendItems)) : 0u;
+            hipLaunchKernelGGL(k_count_halfedges, dim3(count_blocks + (nd > 0 ? grid_for(nd) : 0u)), dim3(kBlock), 0, c->stream, m, n1,
+                               d_eu, d_ev, c->add_cnt, c->touched, c->bc, use_rank ? c->he_rank : nullptr,
+                               use_rank ? c->he_rank + m : nullptr, count_blocks, nd, d_del, c->seed_class);
+        }
+        // room at the pool tail for the rows whose slack is too small
+        const int64_t most_touched = std::min<int64_t>(2 * m, n1);
+        if (m > 0)
+            hipLaunchKernelGGL(k_plan_reserve, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0, c->stream,
+                               c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->bc);
         HIPCHK(c, hipGetLastError());
-        read_bc(c);
-        unsigned int nt = c->h_bc->touched;
+        c->last_init = dynlp_init_info{};
+        Frontier universe = frontier_of(c, 2);
+        mutated = true;
+        c->n = n1;
+        for (;;) {
+            const BatchGate gate{c->bc, (unsigned long long)c->pool_cap};
+            if (k > 0)
+                hipLaunchKernelGGL(k_init_labels, dim3(grid_for(k * c->CP)), dim3(kBlock), 0, c->stream, n0, n1, c->C, c->Cs, c->coff,
+                                   c->CP, c->seed_class, c->F);
+            if (m > 0) {
+                hipLaunchKernelGGL(k_relocate, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0, c->stream,
+                                   c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->pool, gate);
+                hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
+                                   c->meta, c->pool, use_rank ? c->he_rank : nullptr, gate);
+                // the batch's entries of every row in a fixed order, then degree, scratch and V_aff flag of the row (the
+                // relocation offsets are no longer needed: their array holds the lists of rows with long appended segments
+                // and of hubs)
+                int32_t* long_list = reinterpret_cast<int32_t*>(c->reloc_off);
+                int32_t* hub_list = long_list + c->touched_cap;
+                hipLaunchKernelGGL(k_sort_finish, dim3(std::min<unsigned int>(grid_for(most_touched * 16), 2 * most_blocks)), dim3(kBlock), 0,
+                                   c->stream, c->touched, c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc,
+                                   c->deg, c->flag, gate);
+                hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::min<int64_t>(most_touched, 512)), dim3(kSortThreads), 0,
+                                   c->stream, long_list, hub_list, c->meta, c->pool, c->add_cnt, c->bc, c->deg, c->flag);
+            }
+            HIPCHK(c, hipEventRecord(c->phase_ev[1], c->stream));
+            // seeds: clamp one-hot, their neighbours join V_aff; first frontier from the flags (its size goes to the start
+            // slot), and the list of all updatable vertices
+            if (s > 0)
+                hipLaunchKernelGGL(k_apply_seeds, dim3(grid_for(s * 16)), dim3(kBlock), 0, c->stream, s, d_sv, d_sc, c->Cs, c->coff, c->CP,
+                                   c->seed_class, c->F, c->meta, c->pool, c->flag, gate);
+            launch_compact_start(c, frontier_of(c, 0), universe, gate);
+            HIPCHK(c, hipGetLastError());
+            read_start(c);
+            if (c->h_bc->err_code || (int64_t)c->h_bc->pool_tail <= c->pool_cap) break;
+            // the pool is too small for the plan and nothing has been inserted yet
+            const int64_t tail = (int64_t)c->h_bc->pool_tail;
+            grow_pool(c, tail + (tail - c->pool_tail) / 2);
+        }
         if (c->h_bc->err_code) {
+            c->n = n0;
+            const unsigned int nt = c->h_bc->touched;
             if (nt) hipLaunchKernelGGL(k_clear_counts, dim3(grid_for(nt)), dim3(kBlock), 0, c->stream, nt, c->touched, c->add_cnt);
             HIPCHK(c, hipStreamSynchronize(c->stream));
             return bad(format_validation(c->h_bc->err_code, c->h_bc->err_index));
         }
-        if (nt) {
-            // room at the pool tail for the rows whose slack is too small: planned on the device (no row is touched
-            // yet), then the pool is made large enough for the plan
-            hipLaunchKernelGGL(k_plan_reserve, dim3(grid_for(nt)), dim3(kBlock), 0, c->stream, nt, c->touched, c->meta,
-                               c->add_cnt, c->slack, c->reloc_off, c->bc);
-            HIPCHK(c, hipGetLastError());
-            read_bc(c);
-            const int64_t tail = (int64_t)c->h_bc->pool_tail;
-            if (tail > c->pool_cap) grow_pool(c, tail + (tail - c->pool_tail) / 2);
-        }
-        // ---- from here on the graph changes ----
-        mutated = true;
-        if (k > 0)
-            hipLaunchKernelGGL(k_init_labels, dim3(grid_for(k * c->CP)), dim3(kBlock), 0, c->stream, n0, n1, c->C, c->Cs, c->coff,
-                               c->CP, c->seed_class, c->F);
-        if (nt) {
-            hipLaunchKernelGGL(k_relocate, dim3(grid_for(nt)), dim3(kBlock), 0, c->stream, nt, c->touched, c->meta, c->add_cnt,
-                               c->slack, c->reloc_off, c->pool);
-            const int32_t* rank = use_rank ? c->he_rank : nullptr;
-            hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
-                               c->meta, c->pool, rank);
-            // the batch's entries of every row in a fixed order, then degree, scratch and V_aff flag of the row (the
-            // relocation offsets are no longer needed: their array holds the lists of rows with long appended segments and
-            // of hubs)
-            int32_t* long_list = reinterpret_cast<int32_t*>(c->reloc_off);
-            int32_t* hub_list = long_list + c->touched_cap;
-            hipLaunchKernelGGL(k_sort_finish, dim3(grid_for((int64_t)nt * 16)), dim3(kBlock), 0, c->stream, nt, c->touched,
-                               c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc, c->deg, c->flag);
-            hipLaunchKernelGGL(k_sort_long_segments, dim3(std::min<unsigned int>(nt, 512u)), dim3(kSortThreads), 0, c->stream,
-                               long_list, c->meta, c->pool, c->add_cnt, c->bc);
-            hipLaunchKernelGGL(k_finish_rows, dim3(std::min<unsigned int>(nt, 1024u)), dim3(kBlock), 0,
-                               c->stream, long_list, hub_list, c->bc, c->meta, c->pool, c->add_cnt, c->deg, c->flag);
-            HIPCHK(c, hipGetLastError());
-        }
-        c->n = n1;
-        c->entries += 2 * m;
-        HIPCHK(c, hipEventRecord(c->phase_ev[1], c->stream));
-        // ---- seeds: clamp one-hot, their neighbours join V_aff; first compaction ----
-        if (s > 0)
-            hipLaunchKernelGGL(k_apply_seeds, dim3(grid_for(s * 16)), dim3(kBlock), 0, c->stream, s, d_sv, d_sc, c->Cs, c->coff, c->CP,
-                               c->seed_class, c->F, c->meta, c->pool, c->flag);
-        c->last_init = dynlp_init_info{};
-        if (c->init_mode == DYNLP_INIT_SUPERNODE && k > 0) run_supernode_init(c, n0, k, m, d_eu, d_ev, d_ew);
-        zero_ring(c);
-        // first frontier from the flags (its size goes to the start slot), and the list of all updatable
-        // vertices
-        RoundCtr* start = slot_of(c, -1);
-        launch_compact(c, frontier_of(c, 0), &start->next_count, &start->next_long, 0);
-        Frontier universe = frontier_of(c, 2);
-        launch_compact(c, universe, &c->bc->upd_short, &c->bc->upd_long, 1);
-        read_bc(c);
-        read_slots_start(c);
+        c->entries += 2 * m - (int64_t)c->h_bc->removed;
         c->pool_tail = (int64_t)c->h_bc->pool_tail;
         const int64_t relocated = c->h_bc->relocated;
+        if (c->init_mode == DYNLP_INIT_SUPERNODE && k > 0) run_supernode_init(c, n0, k, m, d_eu, d_ev, d_ew);
         universe.ns = c->h_bc->upd_short;
         universe.nl = c->h_bc->upd_long;
-        unsigned int known = c->h_slot[0].next_count + c->h_slot[0].next_long;  // |V_aff| the host knows of
+        unsigned int known = c->h_start->start.next_count + c->h_start->start.next_long;  // |V_aff| the host knows of
         HIPCHK(c, hipEventRecord(c->phase_ev[2], c->stream));
 
         // ---- Step 3: rounds over V_aff, queued in chains of kChain rounds per host round trip ----

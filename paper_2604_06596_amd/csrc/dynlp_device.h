@@ -69,9 +69,9 @@ struct __attribute__((aligned(64))) RoundCtr {
 struct __attribute__((aligned(64))) BatchCtr {
     unsigned long long pool_tail;    // first free pool entry
     unsigned int touched;            // rows that receive at least one new entry
+    unsigned int dropping;           // rows that lose entries to deleted vertices
     unsigned int relocated;          // rows moved by the last insertion
     int err_code;                    // 0 = none; first validation error wins
-    int err_pad;
     long long err_index;             // index of the offending item
     unsigned int init_count;         // first frontier: short rows
     unsigned int init_long;          //                 long rows
@@ -114,6 +114,14 @@ enum ValidationError : int {
 __device__ inline void report_error(BatchCtr* bc, int code, long long index) {
     if (atomicCAS(&bc->err_code, 0, code) == 0) bc->err_index = index;
 }
+
+// The kernels of a batch are queued without waiting for the checks of its arguments or for the plan of its relocations; those
+// that change the graph look first whether the checks have passed and the plan fits the pool.
+struct BatchGate {
+    const BatchCtr* bc;
+    unsigned long long pool_cap;
+    __device__ inline bool closed() const { return bc->err_code != 0 || bc->pool_tail > pool_cap; }
+};
 
 __device__ inline int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 

@@ -106,6 +106,80 @@ __global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __r
     }
 }
 
+// The first frontier of a batch from the flags (cleared) and the list of all updatable vertices, in one pass.
+template <int SEG>
+__global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_t* __restrict__ flag,
+                                                         const int32_t* __restrict__ seed_class,
+                                                         const RowMeta* __restrict__ meta, int32_t* __restrict__ front,
+                                                         int32_t* __restrict__ back, RoundCtr* __restrict__ start,
+                                                         int32_t* __restrict__ ufront, int32_t* __restrict__ uback, BatchCtr* bc,
+                                                         BatchGate gate) {
+    __shared__ unsigned long long sm[kBlock / kWave + 1];
+    __shared__ unsigned int sbase[4];
+    static_assert(SEG * kFlagsPerBlock < 65536, "four counts in one 64-bit scan");
+    if (gate.closed()) return;
+    unsigned int listed[SEG], keep[SEG], is_long[SEG];  // bit k: vertex v0+k is updatable / also flagged / a long row
+    unsigned long long cnt = 0;                         // frontier short, long, updatable short, long
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+        const unsigned int v0 = (blockIdx.x * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
+        listed[q] = keep[q] = is_long[q] = 0;
+        if (v0 < n) {
+            unsigned int cand = 0;
+            const uint4 f = *reinterpret_cast<const uint4*>(flag + v0);
+            if ((f.x | f.y | f.z | f.w) != 0) {
+                const unsigned int wds[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+                for (int k = 0; k < kFlagsPerThread; ++k)
+                    if ((wds[k >> 2] >> ((k & 3) * 8)) & 0xffu) cand |= 1u << k;
+                *reinterpret_cast<uint4*>(flag + v0) = make_uint4(0, 0, 0, 0);
+            }
+            for (int k = 0; k < kFlagsPerThread; ++k) {
+                const unsigned int v = v0 + k;
+                if (v >= n || seed_class[v] >= 0) continue;
+                const int len = meta[v].len;
+                if (len > 0) listed[q] |= 1u << k;
+                if (len > kLongRow) is_long[q] |= 1u << k;
+            }
+            keep[q] = listed[q] & cand;
+        }
+        cnt += (unsigned long long)__popc(keep[q] & ~is_long[q]) | ((unsigned long long)__popc(keep[q] & is_long[q]) << 16) |
+               ((unsigned long long)__popc(listed[q] & ~is_long[q]) << 32) | ((unsigned long long)__popc(listed[q] & is_long[q]) << 48);
+    }
+    unsigned long long total;
+    const unsigned long long ex = block_exclusive_scan<unsigned long long>(cnt, sm, &total);
+    if (threadIdx.x < 4) {
+        const unsigned int t = (unsigned int)(total >> (16 * threadIdx.x)) & 0xffffu;
+        unsigned int* const counter = threadIdx.x == 0   ? &start->next_count
+                                      : threadIdx.x == 1 ? &start->next_long
+                                      : threadIdx.x == 2 ? &bc->upd_short
+                                                         : &bc->upd_long;
+        sbase[threadIdx.x] = t ? atomicAdd(counter, t) : 0u;
+    }
+    __syncthreads();
+    unsigned int at[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) at[k] = sbase[k] + ((unsigned int)(ex >> (16 * k)) & 0xffffu);
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+        const unsigned int v0 = (blockIdx.x * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
+        unsigned int todo = listed[q];
+        while (todo) {
+            const int k = __ffs(todo) - 1;
+            todo &= todo - 1;
+            const int32_t v = (int32_t)(v0 + k);
+            const bool f = (keep[q] >> k) & 1u;
+            if ((is_long[q] >> k) & 1u) {
+                uback[-(long long)(at[3]++)] = v;
+                if (f) back[-(long long)(at[1]++)] = v;
+            } else {
+                ufront[at[2]++] = v;
+                if (f) front[at[0]++] = v;
+            }
+        }
+    }
+}
+
 // =================================================================================================
 // Commit of staged rows (staged rounds) and the next frontier after a ping-pong round
 // =================================================================================================

@@ -135,34 +135,26 @@ __global__ void __launch_bounds__(kBlock) k_fill_i32(int64_t u0, int64_t u1, int
     if (i < u1) a[i] = v;
 }
 
-__global__ void __launch_bounds__(kBlock) k_init_meta(int64_t u0, int64_t u1, RowMeta* __restrict__ meta,
-                                                     float* __restrict__ deg) {
-    const int64_t i = u0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < u1) {
-        RowMeta m;
-        m.off = 0;
-        m.len = 0;
-        m.cap = 0;
-        meta[i] = m;
-        deg[i] = 0.f;
-    }
-}
-
-// Seeds: range checks, clash with an existing label, two classes for one vertex in this list.
-// tmp is an all-zero int32 scratch (n_total entries) that k_clear_seed_tmp restores afterwards.
-__global__ void __launch_bounds__(kBlock) k_validate_seeds(int64_t s, int64_t n_total, int64_t n_existing, int C,
-                                                          const int32_t* __restrict__ sv,
-                                                          const int32_t* __restrict__ sc,
-                                                          const int32_t* __restrict__ seed_class,
-                                                          int32_t* __restrict__ tmp, BatchCtr* bc) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= s) return;
+// Seed i: range checks, clash with an existing label, two classes for one vertex in this list.
+// tmp is an all-zero int32 scratch (n_total entries) that k_clear_seed_tmp or k_batch_prepare restores afterwards.
+__device__ inline void validate_seed(int64_t i, int64_t n_total, int64_t n_existing, int C, const int32_t* __restrict__ sv,
+                                     const int32_t* __restrict__ sc, const int32_t* __restrict__ seed_class,
+                                     int32_t* __restrict__ tmp, BatchCtr* bc) {
     const int32_t v = sv[i], c = sc[i];
     if (v < 0 || v >= n_total) { report_error(bc, kErrSeedVertex, i); return; }
     if (c < 0 || c >= C) { report_error(bc, kErrSeedClass, i); return; }
     if (v < n_existing && seed_class[v] >= 0 && seed_class[v] != c) { report_error(bc, kErrRelabel, i); return; }
     const int32_t old = atomicCAS(&tmp[v], 0, c + 1);
     if (old != 0 && old != c + 1) report_error(bc, kErrSeedConflict, i);
+}
+
+__global__ void __launch_bounds__(kBlock) k_validate_seeds(int64_t s, int64_t n_total, int64_t n_existing, int C,
+                                                          const int32_t* __restrict__ sv,
+                                                          const int32_t* __restrict__ sc,
+                                                          const int32_t* __restrict__ seed_class,
+                                                          int32_t* __restrict__ tmp, BatchCtr* bc) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < s) validate_seed(i, n_total, n_existing, C, sv, sc, seed_class, tmp, bc);
 }
 
 __global__ void __launch_bounds__(kBlock) k_clear_seed_tmp(int64_t s, int64_t n_total, const int32_t* __restrict__ sv,
@@ -186,8 +178,10 @@ __global__ void __launch_bounds__(kBlock) k_apply_seeds(int64_t s, const int32_t
                                                        const int32_t* __restrict__ sc, int Cs, int coff, int CP,
                                                        int32_t* __restrict__ seed_class, float* __restrict__ F,
                                                        const RowMeta* __restrict__ meta,
-                                                       const Edge* __restrict__ pool, uint8_t* __restrict__ flag) {
+                                                       const Edge* __restrict__ pool, uint8_t* __restrict__ flag,
+                                                       BatchGate gate) {
     constexpr int G = 16;
+    if (gate.closed()) return;
     const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
     const int gl = threadIdx.x % G;
     if (i >= s) return;
@@ -259,18 +253,86 @@ __global__ void __launch_bounds__(kBlock) k_scalar_soft(int64_t n, const float* 
 // =================================================================================================
 // Edge insertion (Alg. 2 Step 1 for insertions) into the slack CSR
 // =================================================================================================
+__device__ inline void validate_edge(int64_t i, int64_t n_total, const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                     const float* __restrict__ ew, BatchCtr* bc, int64_t index_base) {
+    const int32_t a = eu[i], b = ev[i];
+    const float ww = ew[i];
+    if (a < 0 || a >= n_total || b < 0 || b >= n_total) { report_error(bc, kErrEndpoint, index_base + i); return; }
+    if (a == b) { report_error(bc, kErrSelfLoop, index_base + i); return; }
+    if (!(ww > 0.f) || !isfinite(ww)) report_error(bc, kErrWeight, index_base + i);
+}
+
 // index_base: position of eu[0] in the caller's batch (the arrays may be one chunk of it), for the error report.
 __global__ void __launch_bounds__(kBlock) k_validate_edges(int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
                                                           const int32_t* __restrict__ ev,
                                                           const float* __restrict__ ew, BatchCtr* bc,
                                                           int64_t index_base = 0) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= m) return;
-    const int32_t a = eu[i], b = ev[i];
-    const float ww = ew[i];
-    if (a < 0 || a >= n_total || b < 0 || b >= n_total) { report_error(bc, kErrEndpoint, index_base + i); return; }
-    if (a == b) { report_error(bc, kErrSelfLoop, index_base + i); return; }
-    if (!(ww > 0.f) || !isfinite(ww)) report_error(bc, kErrWeight, index_base + i);
+    if (i < m) validate_edge(i, n_total, eu, ev, ew, bc, index_base);
+}
+
+// ---- the steps of a batch that come before its edges are inserted -----------------------------------------------------
+// All counters a batch uses: `words` 32-bit words from `zero` on are cleared, then the pool's tail is set.
+__global__ void __launch_bounds__(kBlock) k_batch_begin(unsigned int* __restrict__ zero, unsigned int words,
+                                                       BatchCtr* bc, unsigned long long pool_tail) {
+    for (unsigned int i = blockIdx.x * kBlock + threadIdx.x; i < words; i += gridDim.x * kBlock) {
+        const unsigned int* tail = reinterpret_cast<const unsigned int*>(&bc->pool_tail);
+        zero[i] = zero + i == tail ? (unsigned int)pool_tail : zero + i == tail + 1 ? (unsigned int)(pool_tail >> 32) : 0u;
+    }
+}
+
+// Every argument of a batch: nd deleted vertices, then m edges, then s seeds.
+__global__ void __launch_bounds__(kBlock) k_validate_batch(int64_t nd, const int32_t* __restrict__ del, int64_t m,
+                                                          const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                                          const float* __restrict__ ew, int64_t s,
+                                                          const int32_t* __restrict__ sv, const int32_t* __restrict__ sc,
+                                                          int64_t n_total, int64_t n_existing, int C,
+                                                          const int32_t* __restrict__ seed_class, int32_t* __restrict__ tmp,
+                                                          BatchCtr* bc) {
+    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < nd) {
+        if (del[i] < 0 || del[i] >= n_existing) report_error(bc, kErrDeleted, i);
+        return;
+    }
+    i -= nd;
+    if (i < m) {
+        validate_edge(i, n_total, eu, ev, ew, bc, 0);
+        return;
+    }
+    i -= m;
+    if (i < s) validate_seed(i, n_total, n_existing, C, sv, sc, seed_class, tmp, bc);
+}
+
+constexpr int32_t kDeletedMark = -2;  // seed_class value of a vertex while its batch deletes it
+
+// Deleted vertices marked (nd of them, if the checks have passed), the seeds' scratch cleared (s), empty rows for the new ids
+// n0 .. n0 + k - 1 (they are nobody's until the batch is done).
+__global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, int64_t nd, const int32_t* __restrict__ del,
+                                                         int64_t s, const int32_t* __restrict__ sv, int64_t n_total,
+                                                         int32_t* __restrict__ tmp, int64_t n0, int64_t k,
+                                                         RowMeta* __restrict__ meta, float* __restrict__ deg,
+                                                         int32_t* __restrict__ seed_class) {
+    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < nd) {
+        if (bc->err_code == 0) seed_class[del[i]] = kDeletedMark;
+        return;
+    }
+    i -= nd;
+    if (i < s) {
+        const int32_t v = sv[i];
+        if (v >= 0 && v < n_total) tmp[v] = 0;
+        return;
+    }
+    i -= s;
+    if (i < k) {
+        RowMeta m;
+        m.off = 0;
+        m.len = 0;
+        m.cap = 0;
+        meta[n0 + i] = m;
+        deg[n0 + i] = 0.f;
+        seed_class[n0 + i] = -1;
+    }
 }
 
 // Half-edge i < m has source eu[i]; half-edge m + i has source ev[i].  Count the entries each row
@@ -279,12 +341,20 @@ __global__ void __launch_bounds__(kBlock) k_validate_edges(int64_t m, int64_t n_
 // and appends its first-touched rows with one counter atomic.
 // rank_u / rank_v (both or neither): what the counting atomic returned for half-edge i / m + i, i.e. the
 // half-edge's place among the entries this batch appends to its row; k_write_halfedges then needs no second atomic.
+// Workgroups from count_blocks on take the marks from the nd deleted vertices again (if the checks have passed).
 __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
                                                            const int32_t* __restrict__ ev,
                                                            int32_t* __restrict__ add_cnt,
                                                            int32_t* __restrict__ touched, BatchCtr* bc,
-                                                           int32_t* __restrict__ rank_u, int32_t* __restrict__ rank_v) {
+                                                           int32_t* __restrict__ rank_u, int32_t* __restrict__ rank_v,
+                                                           unsigned int count_blocks, int64_t nd,
+                                                           const int32_t* __restrict__ del, int32_t* __restrict__ seed_class) {
     __shared__ unsigned int smem[kBlock / kWave + 1];
+    if (blockIdx.x >= count_blocks) {
+        const int64_t i = (int64_t)(blockIdx.x - count_blocks) * kBlock + threadIdx.x;
+        if (i < nd && bc->err_code == 0) seed_class[del[i]] = -1;
+        return;
+    }
     const int64_t base = (int64_t)blockIdx.x * kBlock * kAppendItems;
     int32_t srcs[kAppendItems];
     unsigned int firstmask = 0;
@@ -311,60 +381,69 @@ __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n
 // Rows whose slack cannot take the new entries get room at the pool tail (one tail atomic per workgroup: atomics
 // on one address run at about 1e8 per second); reloc_off[t] is the new offset or -1.  Touches no row: bc->pool_tail
 // afterwards tells the host how large the pool has to be before k_relocate may run.
-__global__ void __launch_bounds__(kBlock) k_plan_reserve(unsigned int nt, const int32_t* __restrict__ touched,
+__global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restrict__ touched,
                                                         const RowMeta* __restrict__ meta,
                                                         const int32_t* __restrict__ add_cnt, float slack,
                                                         int64_t* __restrict__ reloc_off, BatchCtr* bc) {
     __shared__ unsigned long long smem[kBlock / kWave + 1];
     __shared__ unsigned long long sbase;
-    const unsigned int t = blockIdx.x * kBlock + threadIdx.x;
-    unsigned long long cap = 0;
-    if (t < nt) {
-        const int32_t u = touched[t];
-        const RowMeta m = meta[u];
-        const int64_t need = (int64_t)m.len + add_cnt[u];
-        if (need > m.cap) cap = (unsigned long long)row_capacity(need, slack);
+    if (bc->err_code) return;
+    const unsigned int nt = bc->touched;
+    for (unsigned int t0 = blockIdx.x * kBlock; t0 < nt; t0 += gridDim.x * kBlock) {  // uniform in the workgroup
+        const unsigned int t = t0 + threadIdx.x;
+        unsigned long long cap = 0;
+        if (t < nt) {
+            const int32_t u = touched[t];
+            const RowMeta m = meta[u];
+            const int64_t need = (int64_t)m.len + add_cnt[u];
+            if (need > m.cap) cap = (unsigned long long)row_capacity(need, slack);
+        }
+        unsigned long long total;
+        const unsigned long long ex = block_exclusive_scan<unsigned long long>(cap, smem, &total);
+        const int nrel = __syncthreads_count(cap != 0);
+        if (threadIdx.x == 0) {
+            sbase = total ? atomicAdd(&bc->pool_tail, total) : 0ull;
+            if (nrel) atomicAdd(&bc->relocated, (unsigned int)nrel);
+        }
+        __syncthreads();
+        if (t < nt) reloc_off[t] = cap ? (int64_t)(sbase + ex) : -1;
+        __syncthreads();
     }
-    unsigned long long total;
-    const unsigned long long ex = block_exclusive_scan<unsigned long long>(cap, smem, &total);
-    const int nrel = __syncthreads_count(cap != 0);
-    if (threadIdx.x == 0) {
-        sbase = total ? atomicAdd(&bc->pool_tail, total) : 0ull;
-        if (nrel) atomicAdd(&bc->relocated, (unsigned int)nrel);
-    }
-    __syncthreads();
-    if (t < nt) reloc_off[t] = cap ? (int64_t)(sbase + ex) : -1;
 }
 
 // Give every relocated row its new place.  One lane per touched row; rows that already hold entries (few, but
 // hubs among them) are copied by the whole wave, one row after the other.
-__global__ void __launch_bounds__(kBlock) k_relocate(unsigned int nt, const int32_t* __restrict__ touched,
+__global__ void __launch_bounds__(kBlock) k_relocate(const int32_t* __restrict__ touched,
                                                     RowMeta* __restrict__ meta, const int32_t* __restrict__ add_cnt,
                                                     float slack, const int64_t* __restrict__ reloc_off,
-                                                    Edge* __restrict__ pool) {
-    const unsigned int t = blockIdx.x * kBlock + threadIdx.x;
-    const int64_t noff = t < nt ? reloc_off[t] : -1;
-    int64_t ooff = 0;
-    int len = 0;
-    if (noff >= 0) {
-        const int32_t u = touched[t];
-        const RowMeta m = meta[u];
-        ooff = m.off;
-        len = m.len;
-        RowMeta r;
-        r.off = noff;
-        r.len = m.len;
-        r.cap = row_capacity((int64_t)m.len + add_cnt[u], slack);
-        meta[u] = r;
-    }
-    unsigned long long todo = __ballot(len > 0);
+                                                    Edge* __restrict__ pool, BatchGate gate) {
+    if (gate.closed()) return;
+    const unsigned int nt = gate.bc->touched;
     const int lane = lane_id();
-    while (todo) {
-        const int l = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        const int64_t from = __shfl(ooff, l), to = __shfl(noff, l);
-        const int n = __shfl(len, l);
-        for (int j = lane; j < n; j += kWave) pool[to + j] = pool[from + j];
+    for (unsigned int t0 = blockIdx.x * kBlock; t0 < nt; t0 += gridDim.x * kBlock) {
+        const unsigned int t = t0 + threadIdx.x;
+        const int64_t noff = t < nt ? reloc_off[t] : -1;
+        int64_t ooff = 0;
+        int len = 0;
+        if (noff >= 0) {
+            const int32_t u = touched[t];
+            const RowMeta m = meta[u];
+            ooff = m.off;
+            len = m.len;
+            RowMeta r;
+            r.off = noff;
+            r.len = m.len;
+            r.cap = row_capacity((int64_t)m.len + add_cnt[u], slack);
+            meta[u] = r;
+        }
+        unsigned long long todo = __ballot(len > 0);
+        while (todo) {
+            const int l = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int64_t from = __shfl(ooff, l), to = __shfl(noff, l);
+            const int n = __shfl(len, l);
+            for (int j = lane; j < n; j += kWave) pool[to + j] = pool[from + j];
+        }
     }
 }
 
@@ -375,9 +454,10 @@ __global__ void __launch_bounds__(kBlock) k_relocate(unsigned int nt, const int3
 __global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int32_t* __restrict__ eu,
                                                            const int32_t* __restrict__ ev,
                                                            const float* __restrict__ ew, RowMeta* __restrict__ meta,
-                                                           Edge* __restrict__ pool, const int32_t* __restrict__ rank) {
+                                                           Edge* __restrict__ pool, const int32_t* __restrict__ rank,
+                                                           BatchGate gate) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 2 * m) return;
+    if (i >= 2 * m || gate.closed()) return;
     const int64_t k = i < m ? i : i - m;
     const int32_t src = i < m ? eu[k] : ev[k];
     const int32_t dst = i < m ? ev[k] : eu[k];
@@ -399,12 +479,13 @@ __global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int
 constexpr int kHubRow = 1024;    // rows longer than this are handled by a workgroup in the passes of a batch
 constexpr int kDegTile = 4096;   // weights per tile, a multiple of 16
 
-__device__ inline float block_row_degree(const Edge* __restrict__ row, int len, float* tile) {
+template <int T>
+__device__ inline float block_row_degree(const Edge* row, int len, float* tile) {
     constexpr int G = 16, UN = 8;
     float s = 0.f;
     for (int t0 = 0; t0 < len; t0 += kDegTile) {
         const int m = len - t0 < kDegTile ? len - t0 : kDegTile;
-        for (int i = threadIdx.x; i < m; i += kBlock) tile[i] = row[t0 + i].w;
+        for (int i = threadIdx.x; i < m; i += T) tile[i] = row[t0 + i].w;
         __syncthreads();
         if (threadIdx.x < G)
             for (int j0 = threadIdx.x; j0 < m; j0 += UN * G) {
@@ -428,7 +509,7 @@ __device__ inline float block_row_degree(const Edge* __restrict__ row, int len, 
 // the appended segment by (neighbour id, weight bits) makes the stored row, and with it every sum
 // over the row, a function of the batch alone.  16 lanes per touched row; segments of up to
 // 16 * kSortRegs entries are rank-sorted in registers (every key is broadcast to the group once),
-// longer ones are queued for k_sort_long_segments (and finished by k_finish_rows afterwards).
+// longer ones are queued for k_sort_long_segments.
 __device__ inline unsigned long long edge_key(const Edge& e) {
     return ((unsigned long long)(unsigned int)e.col << 32) | (unsigned long long)__float_as_uint(e.w);
 }
@@ -445,112 +526,117 @@ __device__ inline Edge key_edge(unsigned long long k) {
 // inserted edge are affected).  The sorted weights go through LDS so that the sum needs no second pass over the row.
 // len_is_old: the rows' lengths do not yet include the appended entries (k_write_halfedges with ranks); the kernel
 // then stores the new length.  Rows with long appended segments only get their length and are listed (long_list), hubs that
-// received a few entries are sorted and listed for k_finish_rows (hub_list).
-__global__ void __launch_bounds__(kBlock) k_sort_finish(unsigned int nt, const int32_t* __restrict__ touched,
+// received a few entries are sorted and listed for k_sort_long_segments (hub_list), which ends Step 1 for both.
+__global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restrict__ touched,
                                                        RowMeta* __restrict__ meta, Edge* __restrict__ pool,
                                                        int32_t* __restrict__ add_cnt, int len_is_old,
                                                        int32_t* __restrict__ long_list,
                                                        int32_t* __restrict__ hub_list, BatchCtr* bc,
-                                                       float* __restrict__ deg, uint8_t* __restrict__ flag) {
+                                                       float* __restrict__ deg, uint8_t* __restrict__ flag, BatchGate gate) {
     constexpr int G = 16;
     __shared__ float sorted_w[kBlock / G][G * kSortRegs];
-    const unsigned int t = (blockIdx.x * kBlock + threadIdx.x) / G;
+    if (gate.closed()) return;
+    const unsigned int nt = bc->touched;
     const int grp = threadIdx.x / G;
     const int gl = threadIdx.x % G;
-    int32_t u = 0;
-    int a = 0, len_old = 0;
-    RowMeta m;
-    m.off = 0;
-    m.len = 0;
-    m.cap = 0;
-    bool is_long = false;
-    if (t < nt) {
-        u = touched[t];
-        a = add_cnt[u];
-        m = meta[u];
-        len_old = len_is_old ? m.len : m.len - a;
-        is_long = a > G * kSortRegs;
-    }
-    const bool sorts = t < nt && !is_long;
-    Edge* seg = pool + m.off + len_old;
-    if (sorts) {
-        const int slots = (a + G - 1) / G;  // uniform in the group
-        unsigned long long key[kSortRegs];
-#pragma unroll
-        for (int r = 0; r < kSortRegs; ++r) {
-            const int j = r * G + gl;
-            key[r] = (r < slots && j < a) ? edge_key(seg[j]) : ~0ull;
+    for (unsigned int t0 = blockIdx.x * (kBlock / G); t0 < nt; t0 += gridDim.x * (kBlock / G)) {  // uniform in the workgroup
+        // (a group's weights stay with its wave: nobody else reads sorted_w[grp])
+        const unsigned int t = t0 + threadIdx.x / G;
+        int32_t u = 0;
+        int a = 0, len_old = 0;
+        RowMeta m;
+        m.off = 0;
+        m.len = 0;
+        m.cap = 0;
+        bool is_long = false;
+        if (t < nt) {
+            u = touched[t];
+            a = add_cnt[u];
+            m = meta[u];
+            len_old = len_is_old ? m.len : m.len - a;
+            is_long = a > G * kSortRegs;
         }
-        int rank[kSortRegs];
+        const bool sorts = t < nt && !is_long;
+        Edge* seg = pool + m.off + len_old;
+        if (sorts) {
+            const int slots = (a + G - 1) / G;  // uniform in the group
+            unsigned long long key[kSortRegs];
 #pragma unroll
-        for (int r = 0; r < kSortRegs; ++r) rank[r] = r * G + gl;
-        if (a > 1) {
+            for (int r = 0; r < kSortRegs; ++r) {
+                const int j = r * G + gl;
+                key[r] = (r < slots && j < a) ? edge_key(seg[j]) : ~0ull;
+            }
+            int rank[kSortRegs];
 #pragma unroll
-            for (int r = 0; r < kSortRegs; ++r) rank[r] = 0;
+            for (int r = 0; r < kSortRegs; ++r) rank[r] = r * G + gl;
+            if (a > 1) {
 #pragma unroll
-            for (int r2 = 0; r2 < kSortRegs; ++r2) {
-                if (r2 < slots) {
-                    for (int l = 0; l < G; ++l) {
-                        const unsigned int hi = __shfl((unsigned int)(key[r2] >> 32), l, G);
-                        const unsigned int lo = __shfl((unsigned int)(key[r2] & 0xffffffffull), l, G);
-                        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
-                        const int oj = r2 * G + l;
+                for (int r = 0; r < kSortRegs; ++r) rank[r] = 0;
 #pragma unroll
-                        for (int r = 0; r < kSortRegs; ++r) {
-                            const int j = r * G + gl;
-                            rank[r] += (other < key[r] || (other == key[r] && oj < j)) ? 1 : 0;
+                for (int r2 = 0; r2 < kSortRegs; ++r2) {
+                    if (r2 < slots) {
+                        for (int l = 0; l < G; ++l) {
+                            const unsigned int hi = __shfl((unsigned int)(key[r2] >> 32), l, G);
+                            const unsigned int lo = __shfl((unsigned int)(key[r2] & 0xffffffffull), l, G);
+                            const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+                            const int oj = r2 * G + l;
+#pragma unroll
+                            for (int r = 0; r < kSortRegs; ++r) {
+                                const int j = r * G + gl;
+                                rank[r] += (other < key[r] || (other == key[r] && oj < j)) ? 1 : 0;
+                            }
                         }
                     }
                 }
             }
-        }
 #pragma unroll
-        for (int r = 0; r < kSortRegs; ++r) {
-            const int j = r * G + gl;
-            if (r < slots && j < a) {
-                const Edge e = key_edge(key[r]);
-                if (a > 1) seg[rank[r]] = e;
-                sorted_w[grp][rank[r]] = e.w;
+            for (int r = 0; r < kSortRegs; ++r) {
+                const int j = r * G + gl;
+                if (r < slots && j < a) {
+                    const Edge e = key_edge(key[r]);
+                    if (a > 1) seg[rank[r]] = e;
+                    sorted_w[grp][rank[r]] = e.w;
+                }
             }
         }
-    }
-    __syncthreads();
-    if (t >= nt) return;
-    if (is_long) {
-        if (gl == 0) {
-            if (len_is_old) meta[u].len = len_old + a;
-            long_list[atomicAdd(&bc->sort_long, 1u)] = u;
+        __syncthreads();
+        if (t >= nt) continue;
+        if (is_long) {
+            if (gl == 0) {
+                if (len_is_old) meta[u].len = len_old + a;
+                long_list[atomicAdd(&bc->sort_long, 1u)] = u;
+            }
+            continue;
         }
-        return;
-    }
-    const int len_new = len_old + a;
-    if (len_new > kHubRow) {
+        const int len_new = len_old + a;
+        if (len_new > kHubRow) {
+            if (gl == 0) {
+                if (len_is_old) meta[u].len = len_new;
+                hub_list[atomicAdd(&bc->finish_hubs, 1u)] = u;
+            }
+            continue;
+        }
+        float s = 0.f;
+        constexpr int UN = 4;  // loads in flight, added in order
+        for (int j0 = gl; j0 < len_new; j0 += UN * G) {
+            float wv[UN];
+#pragma unroll
+            for (int q = 0; q < UN; ++q) {
+                const int j = j0 + q * G;
+                wv[q] = j < len_old ? pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
+            }
+#pragma unroll
+            for (int q = 0; q < UN; ++q)
+                if (j0 + q * G < len_new) s += wv[q];
+        }
+#pragma unroll
+        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
         if (gl == 0) {
             if (len_is_old) meta[u].len = len_new;
-            hub_list[atomicAdd(&bc->finish_hubs, 1u)] = u;
+            deg[u] = s;
+            add_cnt[u] = 0;
+            if (flag) flag[u] = 1;
         }
-        return;
-    }
-    float s = 0.f;
-    constexpr int UN = 4;  // loads in flight, added in order
-    for (int j0 = gl; j0 < len_new; j0 += UN * G) {
-        float wv[UN];
-#pragma unroll
-        for (int q = 0; q < UN; ++q) {
-            const int j = j0 + q * G;
-            wv[q] = j < len_old ? pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
-        }
-#pragma unroll
-        for (int q = 0; q < UN; ++q)
-            if (j0 + q * G < len_new) s += wv[q];
-    }
-#pragma unroll
-    for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
-    if (gl == 0) {
-        if (len_is_old) meta[u].len = len_new;
-        deg[u] = s;
-        add_cnt[u] = 0;
-        if (flag) flag[u] = 1;
     }
 }
 
@@ -584,16 +670,32 @@ __device__ inline void sort_tile_steps(unsigned long long* keys, unsigned int le
 }
 
 __global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(const int32_t* __restrict__ long_list,
+                                                                    const int32_t* __restrict__ hub_list,
                                                                     const RowMeta* __restrict__ meta, Edge* pool,
-                                                                    const int32_t* __restrict__ add_cnt,
-                                                                    const BatchCtr* bc) {
+                                                                    int32_t* __restrict__ add_cnt,
+                                                                    const BatchCtr* bc, float* __restrict__ deg,
+                                                                    uint8_t* __restrict__ flag) {
     __shared__ unsigned long long keys[kSortTile];
     constexpr unsigned int T = kSortTile;
-    const unsigned int count = bc->sort_long;
-    for (unsigned int q = blockIdx.x; q < count; q += gridDim.x) {  // uniform per workgroup
-        const int32_t u = long_list[q];
-        const unsigned int a = (unsigned int)add_cnt[u];
+    const unsigned int count = bc->sort_long, hubs = bc->finish_hubs;
+    // ... and then, as k_sort_finish does for the others: d(u) from the stored row, the counting scratch cleared, the row
+    // put into V_aff
+    auto finish = [&](int32_t u, const RowMeta& m) {
+        const float d = block_row_degree<kSortThreads>(pool + m.off, m.len, reinterpret_cast<float*>(keys));
+        if (threadIdx.x == 0) {
+            deg[u] = d;
+            add_cnt[u] = 0;
+            if (flag) flag[u] = 1;
+        }
+    };
+    for (unsigned int q = blockIdx.x; q < count + hubs; q += gridDim.x) {  // uniform per workgroup
+        const int32_t u = q < count ? long_list[q] : hub_list[q - count];
         const RowMeta m = meta[u];
+        if (q >= count) {
+            finish(u, m);
+            continue;
+        }
+        const unsigned int a = (unsigned int)add_cnt[u];
         Edge* seg = pool + m.off + (m.len - (int)a);
         unsigned int P = 2;
         while (P < a) P <<= 1;
@@ -649,28 +751,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(const int32
                 store_tile(t);
             }
         }
-    }
-}
-
-// The rows k_sort_long_segments has sorted (bc->sort_long of them) and the hubs that k_sort_finish listed
-// (bc->finish_hubs): recompute d(u) from the stored row in the same order as k_sort_finish, clear the counting scratch, and
-// put the row into V_aff.  One workgroup per row.
-__global__ void __launch_bounds__(kBlock) k_finish_rows(const int32_t* __restrict__ long_list,
-                                                       const int32_t* __restrict__ hub_list, const BatchCtr* bc,
-                                                       const RowMeta* __restrict__ meta,
-                                                       const Edge* __restrict__ pool, int32_t* __restrict__ add_cnt,
-                                                       float* __restrict__ deg, uint8_t* __restrict__ flag) {
-    __shared__ float tile[kDegTile];
-    const unsigned int nl = bc->sort_long, count = nl + bc->finish_hubs;
-    for (unsigned int t = blockIdx.x; t < count; t += gridDim.x) {
-        const int32_t u = t < nl ? long_list[t] : hub_list[t - nl];
-        const RowMeta m = meta[u];
-        const float s = block_row_degree(pool + m.off, m.len, tile);
-        if (threadIdx.x == 0) {
-            deg[u] = s;
-            add_cnt[u] = 0;
-            if (flag) flag[u] = 1;
-        }
+        finish(u, m);
     }
 }
 
@@ -684,22 +765,6 @@ __global__ void __launch_bounds__(kBlock) k_clear_counts(unsigned int nt, const 
 // =================================================================================================
 // Vertex deletion (Alg. 2 Step 1 for Delta^Del): V_aff <- V_aff U N(u), then u and its edges go
 // =================================================================================================
-constexpr int32_t kDeletedMark = -2;  // seed_class value of a vertex while its batch deletes it
-
-__global__ void __launch_bounds__(kBlock) k_validate_deleted(int64_t nd, int64_t n, const int32_t* __restrict__ del,
-                                                            BatchCtr* bc) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nd) return;
-    const int32_t u = del[i];
-    if (u < 0 || u >= n) report_error(bc, kErrDeleted, i);
-}
-
-__global__ void __launch_bounds__(kBlock) k_mark_deleted(int64_t nd, const int32_t* __restrict__ del,
-                                                        int32_t* __restrict__ seed_class, int32_t value) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < nd) seed_class[del[i]] = value;
-}
-
 // One 16-lane group per listed vertex.  The group that swaps the row length to 0 owns the row (a
 // vertex listed twice is handled once): every surviving neighbour v is put into V_aff (flag) and, on
 // first touch, into the list of rows that must drop their entries towards deleted vertices.  The
@@ -714,9 +779,10 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
                                                        RowMeta* meta, const Edge* __restrict__ pool,
                                                        const int32_t* __restrict__ seed_class,
                                                        uint8_t* __restrict__ flag, int32_t* __restrict__ add_cnt,
-                                                       int32_t* __restrict__ touched, float* __restrict__ deg,
+                                                       int32_t* __restrict__ dropping, float* __restrict__ deg,
                                                        float* __restrict__ F, BatchCtr* bc) {
     constexpr int G = 16;
+    if (bc->err_code) return;
     __shared__ unsigned int smem[kBlock / kWave + 1];
     __shared__ int64_t long_off[kBlock / G];
     __shared__ int long_len[kBlock / G];
@@ -760,10 +826,10 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
             removed += 1;  // the entry v -> u goes as well
             if (atomicAdd(&add_cnt[v[q]], 1) == 0) first |= 1u << q;
         }
-        unsigned int slot = block_reserve(&bc->touched, (unsigned int)__popc(first), smem);
+        unsigned int slot = block_reserve(&bc->dropping, (unsigned int)__popc(first), smem);
 #pragma unroll
         for (int q = 0; q < kDeleteRegs; ++q)
-            if ((first >> q) & 1u) touched[slot++] = v[q];
+            if ((first >> q) & 1u) dropping[slot++] = v[q];
     };
     take(off, gl, G, len);
     for (unsigned int k = 0; k < nlong; ++k)  // uniform in the workgroup (block_reserve has barriers)
@@ -777,11 +843,11 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
     if (threadIdx.x == 0 && block_removed) atomicAdd(&bc->removed, block_removed);
 }
 
-// Touched rows: drop the entries that point at deleted vertices, keeping the order of the others,
+// Rows that lose entries (listed by k_delete_rows): drop the entries that point at deleted vertices, keeping the order of the others,
 // then recompute d(v) from the stored row (same summation order as k_sort_finish) and clear the
 // counting scratch.  16 lanes per row; a chunk is loaded completely before any of it is written
 // back, and the write position never passes the read position.  Hubs are left to the whole workgroup.
-__global__ void __launch_bounds__(kBlock) k_drop_deleted_entries(unsigned int nt, const int32_t* __restrict__ touched,
+__global__ void __launch_bounds__(kBlock) k_drop_deleted_entries(const BatchCtr* bc, const int32_t* __restrict__ dropping,
                                                                 RowMeta* __restrict__ meta, Edge* __restrict__ pool,
                                                                 const int32_t* __restrict__ seed_class,
                                                                 int32_t* __restrict__ add_cnt,
@@ -791,100 +857,104 @@ __global__ void __launch_bounds__(kBlock) k_drop_deleted_entries(unsigned int nt
     __shared__ unsigned int smem[kBlock / kWave + 1];
     __shared__ int32_t hub[kBlock / G];
     __shared__ unsigned int nhubs;
-    if (threadIdx.x == 0) nhubs = 0u;
-    __syncthreads();
-    const unsigned int t = (blockIdx.x * kBlock + threadIdx.x) / G;
+    const unsigned int nt = bc->dropping;
     const int gl = threadIdx.x % G;
     const int gshift = (lane_id() / G) * G;
-    int32_t v = 0;
-    RowMeta m;
-    m.off = 0;
-    m.len = 0;
-    m.cap = 0;
-    bool own = t < nt;
-    if (own) {
-        v = touched[t];
-        m = meta[v];
-        if (m.len > kHubRow) {
-            if (gl == 0) hub[atomicAdd(&nhubs, 1u)] = v;
-            own = false;
-        }
-    }
-    if (own) {
-        int out = 0;
-        // UN chunks of G entries per step: their loads and the lookups of their neighbours are in flight together; the
-        // kept ones are written in order, always to positions that lie before everything the step has read
-        constexpr int UN = 4;
-        for (int base = 0; base < m.len; base += UN * G) {
-            Edge e[UN];
-            bool keep[UN];
-#pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                const int j = base + q * G + gl;
-                e[q].col = 0;
-                e[q].w = 0.f;
-                if (j < m.len) e[q] = pool[m.off + j];
-            }
-#pragma unroll
-            for (int q = 0; q < UN; ++q) keep[q] = base + q * G + gl < m.len && seed_class[e[q].col] != kDeletedMark;
-#pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                const unsigned int mask = (unsigned int)((__ballot(keep[q]) >> gshift) & 0xffffull);
-                if (keep[q]) pool[m.off + out + __popc(mask & ((1u << gl) - 1u))] = e[q];
-                out += __popc(mask);
+    for (unsigned int t0 = blockIdx.x * (kBlock / G); t0 < nt; t0 += gridDim.x * (kBlock / G)) {  // uniform in the workgroup
+        if (threadIdx.x == 0) nhubs = 0u;
+        __syncthreads();
+        const unsigned int t = t0 + threadIdx.x / G;
+        int32_t v = 0;
+        RowMeta m;
+        m.off = 0;
+        m.len = 0;
+        m.cap = 0;
+        bool own = t < nt;
+        if (own) {
+            v = dropping[t];
+            m = meta[v];
+            if (m.len > kHubRow) {
+                if (gl == 0) hub[atomicAdd(&nhubs, 1u)] = v;
+                own = false;
             }
         }
-        float s = 0.f;
-        for (int j0 = gl; j0 < out; j0 += 8 * G) {  // the same order of additions as k_sort_finish
-            float wv[8];
+        if (own) {
+            int out = 0;
+            // UN chunks of G entries per step: their loads and the lookups of their neighbours are in flight together; the
+            // kept ones are written in order, always to positions that lie before everything the step has read
+            constexpr int UN = 4;
+            for (int base = 0; base < m.len; base += UN * G) {
+                Edge e[UN];
+                bool keep[UN];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) wv[q] = j0 + q * G < out ? pool[m.off + j0 + q * G].w : 0.f;
+                for (int q = 0; q < UN; ++q) {
+                    const int j = base + q * G + gl;
+                    e[q].col = 0;
+                    e[q].w = 0.f;
+                    if (j < m.len) e[q] = pool[m.off + j];
+                }
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (j0 + q * G < out) s += wv[q];
-        }
+                for (int q = 0; q < UN; ++q) keep[q] = base + q * G + gl < m.len && seed_class[e[q].col] != kDeletedMark;
 #pragma unroll
-        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
-        if (gl == 0) {
-            meta[v].len = out;
-            deg[v] = s;
-            add_cnt[v] = 0;
-        }
-    }
-    __syncthreads();
-    for (unsigned int k = 0; k < nhubs; ++k) {  // uniform in the workgroup
-        const int32_t h = hub[k];
-        const RowMeta r = meta[h];
-        constexpr int UN = 8;  // neighbouring entries per thread
-        unsigned int out = 0;
-        for (int base = 0; base < r.len; base += UN * kBlock) {
-            const int j0 = base + (int)threadIdx.x * UN;
-            Edge e[UN];
-            unsigned int keep = 0;
+                for (int q = 0; q < UN; ++q) {
+                    const unsigned int mask = (unsigned int)((__ballot(keep[q]) >> gshift) & 0xffffull);
+                    if (keep[q]) pool[m.off + out + __popc(mask & ((1u << gl) - 1u))] = e[q];
+                    out += __popc(mask);
+                }
+            }
+            float s = 0.f;
+            for (int j0 = gl; j0 < out; j0 += 8 * G) {  // the same order of additions as k_sort_finish
+                float wv[8];
 #pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                e[q].col = -1;
-                e[q].w = 0.f;
-                if (j0 + q < r.len) e[q] = pool[r.off + j0 + q];
+                for (int q = 0; q < 8; ++q) wv[q] = j0 + q * G < out ? pool[m.off + j0 + q * G].w : 0.f;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (j0 + q * G < out) s += wv[q];
             }
 #pragma unroll
-            for (int q = 0; q < UN; ++q)
-                if (e[q].col >= 0 && seed_class[e[q].col] != kDeletedMark) keep |= 1u << q;
-            // (the barriers of the scan: the whole step has been read before any of it is written)
-            unsigned int total;
-            unsigned int at = out + block_exclusive_scan<unsigned int>((unsigned int)__popc(keep), smem, &total);
-#pragma unroll
-            for (int q = 0; q < UN; ++q)
-                if ((keep >> q) & 1u) pool[r.off + at++] = e[q];
-            out += total;
+            for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
+            if (gl == 0) {
+                meta[v].len = out;
+                deg[v] = s;
+                add_cnt[v] = 0;
+            }
         }
         __syncthreads();
-        const float s = block_row_degree(pool + r.off, (int)out, tile);
-        if (threadIdx.x == 0) {
-            meta[h].len = (int)out;
-            deg[h] = s;
-            add_cnt[h] = 0;
+        for (unsigned int k = 0; k < nhubs; ++k) {  // uniform in the workgroup
+            const int32_t h = hub[k];
+            const RowMeta r = meta[h];
+            constexpr int UN = 8;  // neighbouring entries per thread
+            unsigned int out = 0;
+            for (int base = 0; base < r.len; base += UN * kBlock) {
+                const int j0 = base + (int)threadIdx.x * UN;
+                Edge e[UN];
+                unsigned int keep = 0;
+#pragma unroll
+                for (int q = 0; q < UN; ++q) {
+                    e[q].col = -1;
+                    e[q].w = 0.f;
+                    if (j0 + q < r.len) e[q] = pool[r.off + j0 + q];
+                }
+#pragma unroll
+                for (int q = 0; q < UN; ++q)
+                    if (e[q].col >= 0 && seed_class[e[q].col] != kDeletedMark) keep |= 1u << q;
+                // (the barriers of the scan: the whole step has been read before any of it is written)
+                unsigned int total;
+                unsigned int at = out + block_exclusive_scan<unsigned int>((unsigned int)__popc(keep), smem, &total);
+#pragma unroll
+                for (int q = 0; q < UN; ++q)
+                    if ((keep >> q) & 1u) pool[r.off + at++] = e[q];
+                out += total;
+            }
+            __syncthreads();
+            const float s = block_row_degree<kBlock>(pool + r.off, (int)out, tile);
+            if (threadIdx.x == 0) {
+                meta[h].len = (int)out;
+                deg[h] = s;
+                add_cnt[h] = 0;
+            }
         }
+        __syncthreads();  // hub, nhubs
     }
 }
 
