@@ -136,6 +136,10 @@ struct dynlp_ctx {
     int64_t b_edge_cap = 0, b_seed_cap = 0;
     int32_t* b_del = nullptr;
     int64_t b_del_cap = 0;
+    // small calls with host arrays: pinned memory that all inputs are gathered in for one copy (to d_io), and that the label
+    // kernel writes to over the bus
+    unsigned char *h_io = nullptr, *d_io = nullptr;
+    int64_t h_io_cap = 0, d_io_cap = 0;
 
     // pipelined ingest of host-resident batches (see ingest_edges)
     int64_t ingest_chunk = 0;            // edges per chunk
@@ -445,6 +449,27 @@ void grow_pool(dynlp_ctx* c, int64_t min_cap) {
     dev_free(c, c->pool);
     c->pool = p;
     c->pool_cap = new_cap;
+}
+
+// Pinned memory for `bytes` of a small call with host arrays; false: too large a call, or no memory (nothing is lost but time).
+// Up to kIoBytes: beyond, the copies themselves take longer than what they cost to start.
+constexpr int64_t kIoBytes = (int64_t)1 << 20;
+constexpr int64_t kIoOutBytes = (int64_t)128 << 10;  // labels that the kernel writes over the bus
+
+bool ensure_pinned(dynlp_ctx* c, int64_t bytes) {
+    if (bytes > kIoBytes) return false;
+    if (bytes <= c->h_io_cap) return true;
+    if (c->h_io) (void)hipHostFree(c->h_io);  // (no copy from or to it is under way: every call ends with a wait)
+    c->h_io = nullptr;
+    c->h_io_cap = 0;
+    const int64_t cap = std::min<int64_t>(kIoBytes, round_up(std::max<int64_t>(bytes + bytes / 2, 64 << 10), 4096));
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_io), (size_t)cap, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        c->h_io = nullptr;
+        return false;
+    }
+    c->h_io_cap = cap;
+    return true;
 }
 
 void ensure_batch_scratch(dynlp_ctx* c, int64_t nd, int64_t m, int64_t s) {
@@ -2010,7 +2035,7 @@ void destroy_ctx(dynlp_ctx* c) {
     (void)hipSetDevice(c->device);
     if (c->stream || c->meta) (void)hipStreamSynchronize(c->stream);
     void* ptrs[] = {c->meta, c->pool, c->F, c->F2, c->seed_class, c->flag, c->queue[0], c->queue[1], c->queue[2], c->moved[0], c->moved[1], c->moved[2], c->add_cnt,
-                    c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del,
+                    c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del, c->d_io,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
                     c->pb_src, c->pb_sp, c->pb_row0, c->pb_lpos, c->pb_tmp, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, c->pb_upd,
                     c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab,
@@ -2031,6 +2056,7 @@ void destroy_ctx(dynlp_ctx* c) {
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
     if (c->h_slot) (void)hipHostFree(c->h_slot);
     if (c->h_start) (void)hipHostFree(c->h_start);
+    if (c->h_io) (void)hipHostFree(c->h_io);
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
@@ -2144,18 +2170,12 @@ int64_t scan_block_sums(dynlp_ctx* c, int64_t nb, int64_t* sums) {
 // device buffers.  Every row is overwritten, so the buffers need no clearing.
 void launch_label_output(dynlp_ctx* c, float* d_soft, int32_t* d_hard) {
     const int64_t n = c->n;
-    if (d_soft) {
-        if (c->coff)
-            hipLaunchKernelGGL(k_scalar_soft, dim3(grid_for(2 * n)), dim3(kBlock), 0, c->stream, n, c->F, d_soft);
-        else
-            hipLaunchKernelGGL(k_pack_soft, dim3(grid_for(n * c->C)), dim3(kBlock), 0, c->stream, n, c->C, c->CP, c->F, d_soft);
-    }
-    if (d_hard) {
-        if (c->coff)
-            hipLaunchKernelGGL(k_scalar_hard, dim3(grid_for(n)), dim3(kBlock), 0, c->stream, n, c->F, d_hard);
-        else
-            hipLaunchKernelGGL(k_argmax, dim3(grid_for(n * (c->CP >= 4 ? c->CP / 4 : 1))), dim3(kBlock), 0, c->stream, n, c->C, c->CP, c->F, d_hard);
-    }
+    if (!d_soft && !d_hard) return;
+    if (c->coff)
+        hipLaunchKernelGGL(k_scalar_labels, dim3(grid_for(n)), dim3(kBlock), 0, c->stream, n, c->F, d_soft, d_hard);
+    else
+        hipLaunchKernelGGL(k_labels, dim3(grid_for(n * (c->CP >= 4 ? c->CP / 4 : 1))), dim3(kBlock), 0, c->stream, n, c->C, c->CP, c->F,
+                           d_soft, d_hard);
     HIPCHK(c, hipGetLastError());
 }
 
@@ -2816,23 +2836,38 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         const float* d_ew = ew;
         c->ingest_chunks_last = 0;
         if (!c->dev_ptrs) {
-            auto send = [&](void* to, const void* from, int64_t count) {
-                if (count > 0) HIPCHK(c, hipMemcpyAsync(to, from, (size_t)count * 4, hipMemcpyHostToDevice, c->stream));
-            };
-            if (!pipelined) {
-                send(c->b_eu, eu, m);
-                send(c->b_ev, ev, m);
-                send(c->b_ew, ew, m);
+            // one copy of everything where it is little (six copies of a few hundred bytes cost 5 us each), else one per array
+            const void* from[6] = {pipelined ? nullptr : eu, pipelined ? nullptr : ev, pipelined ? nullptr : ew, sv, sc, del};
+            const int64_t count[6] = {pipelined ? 0 : m, pipelined ? 0 : m, pipelined ? 0 : m, s, s, nd};
+            int64_t at[6], bytes = 0;
+            for (int i = 0; i < 6; ++i) {
+                at[i] = bytes;
+                bytes += round_up(count[i] * 4, 64);
             }
-            send(c->b_sv, sv, s);
-            send(c->b_sc, sc, s);
-            send(c->b_del, del, nd);
-            d_eu = c->b_eu;
-            d_ev = c->b_ev;
-            d_ew = c->b_ew;
-            d_sv = c->b_sv;
-            d_sc = c->b_sc;
-            d_del = c->b_del;
+            bool together = bytes > 0 && ensure_pinned(c, bytes);
+            if (together && bytes > c->d_io_cap) {
+                dev_free(c, c->d_io);
+                c->d_io_cap = 0;
+                c->d_io = static_cast<unsigned char*>(dev_try_alloc(c, (size_t)c->h_io_cap));
+                if (c->d_io) c->d_io_cap = c->h_io_cap;
+                else together = false;
+            }
+            if (together) {
+                for (int i = 0; i < 6; ++i)
+                    if (count[i] > 0) std::memcpy(c->h_io + at[i], from[i], (size_t)count[i] * 4);
+                HIPCHK(c, hipMemcpyAsync(c->d_io, c->h_io, (size_t)bytes, hipMemcpyHostToDevice, c->stream));
+            } else {
+                void* const to[6] = {c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del};
+                for (int i = 0; i < 6; ++i)
+                    if (count[i] > 0) HIPCHK(c, hipMemcpyAsync(to[i], from[i], (size_t)count[i] * 4, hipMemcpyHostToDevice, c->stream));
+            }
+            auto where = [&](int i, void* own) { return together ? static_cast<void*>(c->d_io + at[i]) : own; };
+            d_eu = static_cast<int32_t*>(pipelined ? c->b_eu : where(0, c->b_eu));
+            d_ev = static_cast<int32_t*>(pipelined ? c->b_ev : where(1, c->b_ev));
+            d_ew = static_cast<float*>(pipelined ? c->b_ew : where(2, c->b_ew));
+            d_sv = static_cast<int32_t*>(where(3, c->b_sv));
+            d_sc = static_cast<int32_t*>(where(4, c->b_sc));
+            d_del = static_cast<int32_t*>(where(5, c->b_del));
         }
         HIPCHK(c, hipEventRecord(c->phase_ev[0], c->stream));
 
@@ -3267,6 +3302,17 @@ dynlp_status dynlp_get_labels(dynlp_ctx* c, float* soft, int32_t* hard) {
     dynlp_status st = DYNLP_OK;
     try {
         HIPCHK(c, hipSetDevice(c->device));
+        const int64_t soft_bytes = soft ? n * c->C * (int64_t)sizeof(float) : 0, hard_off = round_up(soft_bytes, 64);
+        const int64_t out_bytes = hard_off + (hard ? n * (int64_t)sizeof(int32_t) : 0);
+        if (!c->dev_ptrs && out_bytes <= kIoOutBytes && ensure_pinned(c, out_bytes)) {
+            // few labels: written by the kernel straight into pinned host memory
+            launch_label_output(c, soft ? reinterpret_cast<float*>(c->h_io) : nullptr,
+                                hard ? reinterpret_cast<int32_t*>(c->h_io + hard_off) : nullptr);
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+            if (soft) std::memcpy(soft, c->h_io, (size_t)soft_bytes);
+            if (hard) std::memcpy(hard, c->h_io + hard_off, (size_t)n * sizeof(int32_t));
+            return DYNLP_OK;
+        }
         // staging of the packed outputs in host-pointer mode; without memory for it the call fails and the context
         // stays usable
         if (soft && !c->dev_ptrs) d_soft = Temp<float>(c, n * c->C).release();

@@ -192,11 +192,12 @@ __global__ void __launch_bounds__(kBlock) k_apply_seeds(int64_t s, const int32_t
     for (int j = gl; j < m.len; j += G) flag[pool[m.off + j].col] = 1;
 }
 
-// hard[u] = argmax_c F[u][c], lowest index on ties.  A row of CP >= 4 floats is read by CP/4 adjacent
-// lanes as one float4 each (a coalesced 16*L-byte segment per row); the lanes' (value, index) pairs
-// are then merged with xor shuffles.  CP < 4 rows are read by one lane.
-__global__ void __launch_bounds__(kBlock) k_argmax(int64_t n, int C, int CP, const float* __restrict__ F,
-                                                  int32_t* __restrict__ hard) {
+// Labels in the caller's format from one pass over the rows (either output may be NULL): soft without the padding columns, and
+// hard[u] = argmax_c F[u][c], lowest index on ties.  A row of CP >= 4 floats is read by CP/4 adjacent lanes as one float4
+// each (a coalesced 16*L-byte segment per row); the lanes' (value, index) pairs are merged with xor shuffles.  CP < 4 rows
+// are read by one lane.  (1,000,000 rows of 10 columns: 25 + 13 us as two kernels.)
+__global__ void __launch_bounds__(kBlock) k_labels(int64_t n, int C, int CP, const float* __restrict__ F,
+                                                  float* __restrict__ soft, int32_t* __restrict__ hard) {
     const int L = CP >= 4 ? CP / 4 : 1;  // lanes per row: 1, 2, 4, 8 or 16
     const int64_t u = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / L;
     const int sub = threadIdx.x & (L - 1);
@@ -205,20 +206,27 @@ __global__ void __launch_bounds__(kBlock) k_argmax(int64_t n, int C, int CP, con
     int best = 0;
     if (live) {
         const float* row = F + u * CP;
+        float* const out = soft ? soft + u * C : nullptr;
         if (CP >= 4) {
             const float4 q = *reinterpret_cast<const float4*>(row + 4 * sub);
             const float v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int c = 4 * sub + k;
-                if (c < C && v[k] > bv) { bv = v[k]; best = c; }
+                if (c >= C) continue;
+                if (v[k] > bv) { bv = v[k]; best = c; }
+                if (out) out[c] = v[k];
             }
         } else {
             bv = row[0];
-            for (int c = 1; c < C; ++c)
-                if (row[c] > bv) { bv = row[c]; best = c; }
+            for (int c = 0; c < C; ++c) {
+                const float x = row[c];
+                if (x > bv) { bv = x; best = c; }
+                if (out) out[c] = x;
+            }
         }
     }
+    if (!hard) return;
     for (int d = L >> 1; d > 0; d >>= 1) {
         const float ov = __shfl_xor(bv, d);
         const int ob = __shfl_xor(best, d);
@@ -227,27 +235,18 @@ __global__ void __launch_bounds__(kBlock) k_argmax(int64_t n, int C, int CP, con
     if (live && sub == 0) hard[u] = best;
 }
 
-__global__ void __launch_bounds__(kBlock) k_pack_soft(int64_t n, int C, int CP, const float* __restrict__ F,
-                                                     float* __restrict__ soft) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n * C) return;
-    soft[i] = F[(i / C) * CP + (i % C)];
-}
-
 // Binary scalar layout: hard label = the paper's 0.5 cut-off (class 1 iff F_u > 0.5, i.e. iff class 1
 // beats class 0; a tie goes to class 0 like the argmax), soft row = (1 - F_u, F_u).
-__global__ void __launch_bounds__(kBlock) k_scalar_hard(int64_t n, const float* __restrict__ F,
-                                                       int32_t* __restrict__ hard) {
+__global__ void __launch_bounds__(kBlock) k_scalar_labels(int64_t n, const float* __restrict__ F, float* __restrict__ soft,
+                                                         int32_t* __restrict__ hard) {
     const int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (u < n) hard[u] = F[u] > 0.5f ? 1 : 0;
-}
-
-__global__ void __launch_bounds__(kBlock) k_scalar_soft(int64_t n, const float* __restrict__ F,
-                                                       float* __restrict__ soft) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 2 * n) return;
-    const float f = F[i >> 1];
-    soft[i] = (i & 1) ? f : 1.0f - f;
+    if (u >= n) return;
+    const float f = F[u];
+    if (soft) {  // (two stores: the caller's array need not be aligned to 8 bytes)
+        soft[2 * u] = 1.0f - f;
+        soft[2 * u + 1] = f;
+    }
+    if (hard) hard[u] = f > 0.5f ? 1 : 0;
 }
 
 // =================================================================================================
