@@ -866,15 +866,32 @@ bool tail_rounds_pay(const dynlp_ctx* c, unsigned int known, unsigned int before
     return before >= known || (double)known * avg_len <= (double)rows;
 }
 
+// LDS that a launch with the labels on the CU may ask for: what one workgroup can have, less the kernel's own arrays.
+constexpr unsigned int kTailLds = 120 << 10;
+
+template <int CP, int G>
+void launch_tail_inst(dynlp_ctx* c, const TailArgs& a) {
+    const unsigned int lds = c->n < 65536 ? tail_resident_bytes((unsigned int)c->n, CP, a.max_rows) : 0xffffffffu;
+    bool resident = lds <= kTailLds && c->pool_cap < ((int64_t)1 << 32);
+    if (resident) {
+        // always the same value: the attribute belongs to the kernel, not to this context
+        resident = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tail_rounds<CP, G, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kTailLds) == hipSuccess;
+        if (!resident) (void)hipGetLastError();
+    }
+    if (resident) hipLaunchKernelGGL((k_tail_rounds<CP, G, true>), dim3(1), dim3(kTailThreads), lds, c->stream, a);
+    else hipLaunchKernelGGL((k_tail_rounds<CP, G, false>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
+}
+
 template <int CP>
 void launch_tail_cp(dynlp_ctx* c, int G, const TailArgs& a) {
     if constexpr (CP <= 4) {
         if (G == 4) {
-            hipLaunchKernelGGL((k_tail_rounds<CP, 4>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
+            launch_tail_inst<CP, 4>(c, a);
             return;
         }
     }
-    hipLaunchKernelGGL((k_tail_rounds<CP, 16>), dim3(1), dim3(kTailThreads), 0, c->stream, a);
+    launch_tail_inst<CP, 16>(c, a);
 }
 
 // Rounds [round, round + count) at most; the list of the first one is that of parity `cur`.  chain_off: rounds of the
@@ -905,6 +922,7 @@ void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vert
     a.by_vertex = by_vertex;
     a.flag = c->flag;
     a.tol = c->tol;
+    a.n = (unsigned int)c->n;
     tail_limits(c, &a.max_rows, &a.max_entries);
     hipEvent_t e1 = open_timed_span(c, round, count);
     switch (c->CP) {

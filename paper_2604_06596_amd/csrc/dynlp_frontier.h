@@ -5,6 +5,8 @@
 #include "dynlp_device.h"
 #include "dynlp_conjugate.h"
 
+#include <type_traits>
+
 namespace dynlp {
 
 constexpr int kFlagsPerThread = 16;
@@ -967,6 +969,10 @@ __global__ void __launch_bounds__(kBlock) k_row_product(CgRun run, unsigned int 
 // list of the next round is then where an ordinary round expects it.
 constexpr int kTailThreads = 1024;
 
+// On a graph whose labels, row records and lists fit the LDS of the CU beside the rest, they are brought there at the start of
+// the launch (RES): a round is a chain of a dozen dependent accesses, and all but the entries' then stay on the CU.  3,001
+// vertices with one label column, rounds of up to 850 rows: 14 -> 8 us per round, whole call 322 -> 244 us.
+//
 // A row's entries, cut where they are beyond every limit: the sum over all rows a round may list fits 32 bits.
 __device__ inline unsigned int tail_entries(int len) { return len < 65536 ? (unsigned int)len : 65536u; }
 
@@ -988,14 +994,23 @@ struct TailArgs {
     unsigned int len_lo, len_hi;  // mean row lengths [len_lo, len_hi) keep the lanes per row of this launch
     int same_run, same_max;       // rounds that repeated themselves before this launch, and how many make the rows averaged
     unsigned int sig[3];          // rows, rows moved, max change of the round before
+    unsigned int n;               // RES: vertices, below 65,536; the pool's entries are numbered with 32 bits
 };
 
-template <int CP, int G>
+// LDS of a RES launch, in bytes: row records (offset; length, top bit: labelled), label rows, staged rows, marks, two lists.
+// (Records and rows of n rounded up to a multiple of four vertices, so that everything is aligned.)
+__host__ __device__ inline unsigned int tail_resident_bytes(unsigned int n, int CP, unsigned int max_rows) {
+    const unsigned int n4 = (n + 3u) & ~3u;
+    return n4 * 8u + n4 * (unsigned int)CP * 4u + max_rows * (unsigned int)CP * 4u + (n + 31u) / 32u * 4u + 2u * n4 * 2u;
+}
+
+template <int CP, int G, bool RES>
 __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int GL = LPN > 16 ? LPN : 16, NG = kBlock / GL;  // long rows: as in row_update_long
     constexpr int TEAMS = kTailThreads / kBlock;
+    extern __shared__ __align__(16) unsigned int tail_lds[];
     __shared__ float part[TEAMS][NG][CP + 1];
     __shared__ float part_s[TEAMS][NG];
     __shared__ unsigned int big[TEAMS];
@@ -1007,6 +1022,28 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
     int same_run = a.same_run;              // (thread 0)
     bool repeats = false;
     unsigned int sig[3] = {a.sig[0], a.sig[1], a.sig[2]};
+    // RES: the graph's label rows etc. in LDS (see tail_resident_bytes)
+    const unsigned int lstride = (a.n + 3u) & ~3u;
+    uint2* const lrow = reinterpret_cast<uint2*>(tail_lds);
+    float* const lF = reinterpret_cast<float*>(lrow + lstride);
+    float* const lstaged = lF + lstride * CP;
+    unsigned int* const lmark = reinterpret_cast<unsigned int*>(lstaged + a.max_rows * CP);
+    unsigned short* const llist = reinterpret_cast<unsigned short*>(lmark + (a.n + 31u) / 32u);
+    auto listed = [&](int parity, unsigned int ns, unsigned int pos) -> int32_t {
+        if constexpr (RES) return (int32_t)llist[parity * lstride + (pos < ns ? pos : a.n - 1u - (pos - ns))];
+        else return frontier_vertex(a.front[parity], a.back[parity], ns, pos);
+    };
+    auto record = [&](int32_t u, int64_t* off, int* len) {
+        if constexpr (RES) {
+            const uint2 q = lrow[u];
+            *off = (int64_t)q.x;
+            *len = (int)(q.y & 0x7fffffffu);
+        } else {
+            const RowMeta m = a.meta[u];
+            *off = m.off;
+            *len = m.len;
+        }
+    };
     {
         // the slots of all rounds this launch may run, and of the round after
         constexpr int kWords = sizeof(RoundCtr) / 4;
@@ -1019,19 +1056,55 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             next[2] = 0u;
             leave = false;
         }
+        if constexpr (RES) {
+            constexpr unsigned int UN = 4;  // loads in flight
+            for (unsigned int i0 = threadIdx.x; i0 < a.n * CP / VEC; i0 += UN * kTailThreads) {
+                Vec<VEC> x[UN];
+#pragma unroll
+                for (unsigned int q = 0; q < UN; ++q)
+                    if (i0 + q * kTailThreads < a.n * CP / VEC) x[q] = load_vec<VEC>(a.F + (size_t)(i0 + q * kTailThreads) * VEC);
+#pragma unroll
+                for (unsigned int q = 0; q < UN; ++q)
+                    if (i0 + q * kTailThreads < a.n * CP / VEC) store_vec<VEC>(lF + (i0 + q * kTailThreads) * VEC, x[q]);
+            }
+            for (unsigned int v0 = threadIdx.x; v0 < a.n; v0 += UN * kTailThreads) {
+                RowMeta m[UN];
+                int32_t sc[UN];
+#pragma unroll
+                for (unsigned int q = 0; q < UN; ++q) {
+                    const unsigned int v = v0 + q * kTailThreads < a.n ? v0 + q * kTailThreads : a.n - 1u;
+                    m[q] = a.meta[v];
+                    sc[q] = a.seed_class[v];
+                }
+#pragma unroll
+                for (unsigned int q = 0; q < UN; ++q)
+                    if (v0 + q * kTailThreads < a.n)
+                        lrow[v0 + q * kTailThreads] = make_uint2((unsigned int)m[q].off, (unsigned int)m[q].len | (sc[q] >= 0 ? 0x80000000u : 0u));
+            }
+            for (unsigned int w = threadIdx.x; w < (a.n + 31u) / 32u; w += kTailThreads) lmark[w] = 0u;
+        }
     }
     __syncthreads();
-    if (count[0] + count[1] <= a.max_rows) {  // the entries of the first round (the host knows their number of rows)
+    // (the host knows the number of rows of the first round, not that a few of them are hubs)
+    const bool fits = count[0] + count[1] <= a.max_rows;
+    if (fits) {
         unsigned int e = 0;
-        for (unsigned int i = threadIdx.x; i < count[0] + count[1]; i += kTailThreads)
-            e += tail_entries(a.meta[frontier_vertex(a.front[0], a.back[0], count[0], i)].len);
+        for (unsigned int i = threadIdx.x; i < count[0] + count[1]; i += kTailThreads) {
+            const int32_t u = frontier_vertex(a.front[0], a.back[0], count[0], i);
+            if constexpr (RES) llist[i < count[0] ? i : a.n - 1u - (i - count[0])] = (unsigned short)u;
+            int64_t off;
+            int len;
+            record(u, &off, &len);
+            e += tail_entries(len);
+        }
         e = wave_sum(e);
         if (lane_id() == 0) atomicAdd(&next[2], e);
     }
     __syncthreads();
-    for (int r = 0; r < a.rounds; ++r) {
+    int r = 0;
+    for (; r < a.rounds; ++r) {
         const unsigned int ns = count[0], nl = count[1];  // uniform from here on
-        if (ns + nl == 0u || leave || ns + nl > a.max_rows || next[2] > a.max_entries) return;
+        if (ns + nl == 0u || leave || ns + nl > a.max_rows || next[2] > a.max_entries) break;
         __syncthreads();
         if (threadIdx.x == 0) {
             next[0] = next[1] = next[2] = 0u;
@@ -1039,20 +1112,43 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             entries[0] = entries[1] = 0u;
         }
         __syncthreads();
-        const int32_t* front = a.front[r & 1];
-        const int32_t* back = a.back[r & 1];
-        int32_t* nfront = a.front[(r + 1) & 1];
-        int32_t* nback = a.back[(r + 1) & 1];
+        const int cur = r & 1, nxt = cur ^ 1;
         float rmax = 0.f;
         unsigned int nmoved = 0, nent[2] = {0u, 0u};
         auto mark = [&](int32_t v) {  // v joins the next V_aff, once
-            if (a.seed_class[v] >= 0) return;
-            const unsigned int bit = 1u << (((unsigned int)v & 3u) * 8u);
-            if (atomicOr(reinterpret_cast<unsigned int*>(a.flag) + ((unsigned int)v >> 2), bit) & bit) return;
-            const int len = a.meta[v].len;
+            int len;
+            if constexpr (RES) {
+                const unsigned int q = lrow[v].y;
+                if (q >> 31) return;
+                len = (int)q;
+                const unsigned int bit = 1u << ((unsigned int)v & 31u);
+                if (atomicOr(&lmark[(unsigned int)v >> 5], bit) & bit) return;
+            } else {
+                // (both reads on their way together)
+                const int32_t sc = a.seed_class[v];
+                len = a.meta[v].len;
+                if (sc >= 0) return;
+                const unsigned int bit = 1u << (((unsigned int)v & 3u) * 8u);
+                if (atomicOr(reinterpret_cast<unsigned int*>(a.flag) + ((unsigned int)v >> 2), bit) & bit) return;
+            }
             atomicAdd(&next[2], tail_entries(len));
-            if (len > kLongRow) nback[-(long long)atomicAdd(&next[1], 1u)] = v;
-            else nfront[atomicAdd(&next[0], 1u)] = v;
+            if (len > kLongRow) {
+                const unsigned int at = atomicAdd(&next[1], 1u);
+                if constexpr (RES) llist[nxt * lstride + a.n - 1u - at] = (unsigned short)v;
+                else a.back[nxt][-(long long)at] = v;
+            } else {
+                const unsigned int at = atomicAdd(&next[0], 1u);
+                if constexpr (RES) llist[nxt * lstride + at] = (unsigned short)v;
+                else a.front[nxt][at] = v;
+            }
+        };
+        auto old_row = [&](int32_t u, int chunk) {
+            if constexpr (RES) return load_vec<VEC>(lF + (unsigned int)u * CP + chunk * VEC);
+            else return load_vec<VEC>(a.F + (size_t)u * CP + chunk * VEC);
+        };
+        auto accumulate = [&](auto lanes, const Edge* row, int len, int first, int step, int32_t u, int gl, Vec<VEC>& acc, float& s, Edge& e) {
+            if constexpr (RES) accumulate_row<CP, decltype(lanes)::value>(row, len, first, step, u, lF, gl, acc, s, e);
+            else accumulate_row<CP, decltype(lanes)::value>(row, len, first, step, u, a.F, gl, acc, s, e);
         };
         // the new row from the sums of its entries (the lanes of slot 0 hold acc and s), by the LPN lanes of one slot
         auto finish = [&](unsigned int pos, int32_t u, int chunk, const Vec<VEC>& acc, float s, const Vec<VEC>& old) {
@@ -1066,8 +1162,12 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             }
 #pragma unroll
             for (int k = 1; k < LPN; k <<= 1) d = fmaxf(d, __shfl_xor(d, k, LPN));
-            float* const out = a.by_vertex & kRowByVertex ? a.F + (size_t)u * CP : a.staged + (size_t)pos * CP;
-            store_vec<VEC>(out + chunk * VEC, fn);
+            if constexpr (RES) {
+                store_vec<VEC>((a.by_vertex & kRowByVertex ? lF + (unsigned int)u * CP : lstaged + pos * CP) + chunk * VEC, fn);
+            } else {
+                float* const out = a.by_vertex & kRowByVertex ? a.F + (size_t)u * CP : a.staged + (size_t)pos * CP;
+                store_vec<VEC>(out + chunk * VEC, fn);
+            }
             return d;
         };
         // long rows: four at a time, 256 threads each, summed in the order k_row_update sums them
@@ -1075,10 +1175,12 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             const int team = threadIdx.x / kBlock, tid = threadIdx.x % kBlock;
             const unsigned int j = j0 + team;
             const int gi = tid / GL, gl = tid % GL, slot = gl / LPN, chunk = gl % LPN;
-            const int32_t u = j < nl ? back[-(long long)j] : 0;
-            const RowMeta m = a.meta[u];
-            const int len = j < nl ? m.len : 0;
-            const Edge* __restrict__ row = a.pool + m.off;
+            const int32_t u = j < nl ? listed(cur, ns, ns + j) : 0;
+            int64_t off;
+            int len;
+            record(u, &off, &len);
+            if (j >= nl) len = 0;
+            const Edge* __restrict__ row = a.pool + off;
             Vec<VEC> acc;
 #pragma unroll
             for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
@@ -1086,7 +1188,7 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             Edge e;
             e.col = u;
             e.w = 0.f;
-            accumulate_row<CP, GL>(row, len, gi, NG, u, a.F, gl, acc, s, e);
+            accumulate(std::integral_constant<int, GL>{}, row, len, gi, NG, u, gl, acc, s, e);
             if (slot == 0) {
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) part[team][gi][chunk * VEC + k] = acc.v[k];
@@ -1104,7 +1206,7 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
                     for (int k = 0; k < VEC; ++k) tot.v[k] += part[team][q][chunk * VEC + k];
                     st += part_s[team][q];
                 }
-                const float d = finish(ns + j, u, chunk, tot, st, load_vec<VEC>(a.F + (size_t)u * CP + chunk * VEC));
+                const float d = finish(ns + j, u, chunk, tot, st, old_row(u, chunk));
                 if (gl == 0) {
                     rmax = fmaxf(rmax, d);
                     nent[1] += (unsigned int)len;
@@ -1120,10 +1222,12 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             __syncthreads();
         }
         for (unsigned int i = threadIdx.x / G; i < ns; i += kTailThreads / G) {
-            const int32_t u = front[i];
+            const int32_t u = listed(cur, ns, i);
             const int gl = threadIdx.x % G, slot = gl / LPN, chunk = gl % LPN;
-            const RowMeta m = a.meta[u];
-            const Edge* __restrict__ row = a.pool + m.off;
+            int64_t off;
+            int len;
+            record(u, &off, &len);
+            const Edge* __restrict__ row = a.pool + off;
             Vec<VEC> acc;
 #pragma unroll
             for (int k = 0; k < VEC; ++k) acc.v[k] = 0.f;
@@ -1131,19 +1235,21 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             Edge e;
             e.col = u;
             e.w = 0.f;
-            const Vec<VEC> old = load_vec<VEC>(a.F + (size_t)u * CP + chunk * VEC);
-            accumulate_row<CP, G>(row, m.len, 0, 1, u, a.F, gl, acc, s, e);
+            const Vec<VEC> old = old_row(u, chunk);
+            accumulate(std::integral_constant<int, G>{}, row, len, 0, 1, u, gl, acc, s, e);
             float d = 0.f;
             if (slot == 0) d = finish(i, u, chunk, acc, s, old);
             d = __shfl(d, 0, G);
             if (gl == 0) {
                 rmax = fmaxf(rmax, d);
-                nent[0] += (unsigned int)m.len;
+                nent[0] += (unsigned int)len;
                 nmoved += d > a.tol ? 1u : 0u;
             }
-            if (d > a.tol) {
+            if (d > a.tol) {  // the last chunk of the row is still in registers
                 if (gl == 0) mark(u);
-                for (int j = gl; j < m.len; j += G) mark(row[j].col);
+                if (e.w != 0.f) mark(e.col);
+                const int last = ((len - 1) / G) * G;
+                for (int j = gl; j < last; j += G) mark(row[j].col);
             }
         }
         rmax = wave_max(rmax);
@@ -1161,12 +1267,18 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             constexpr unsigned int PER = CP / VEC;
             for (unsigned int i = threadIdx.x; i < (ns + nl) * PER; i += kTailThreads) {
                 const unsigned int pos = i / PER;
-                store_vec<VEC>(a.F + (size_t)frontier_vertex(front, back, ns, pos) * CP + (i % PER) * VEC,
-                               load_vec<VEC>(a.staged + (size_t)pos * CP + (i % PER) * VEC));
+                const unsigned int to = (unsigned int)listed(cur, ns, pos) * CP + (i % PER) * VEC;
+                if constexpr (RES) store_vec<VEC>(lF + to, load_vec<VEC>(lstaged + pos * CP + (i % PER) * VEC));
+                else
+                    store_vec<VEC>(a.F + (size_t)listed(cur, ns, pos) * CP + (i % PER) * VEC,
+                                   load_vec<VEC>(a.staged + (size_t)pos * CP + (i % PER) * VEC));
             }
         }
-        for (unsigned int i = threadIdx.x; i < next[0] + next[1]; i += kTailThreads)
-            a.flag[frontier_vertex(nfront, nback, next[0], i)] = 0;
+        if constexpr (RES) {
+            for (unsigned int w = threadIdx.x; w < (a.n + 31u) / 32u; w += kTailThreads) lmark[w] = 0u;
+        } else {
+            for (unsigned int i = threadIdx.x; i < next[0] + next[1]; i += kTailThreads) a.flag[listed(nxt, next[0], i)] = 0;
+        }
         if (threadIdx.x == 0) {
             RoundCtr* slot = a.ring + (a.t0 + r) % kRing;
             slot->next_count = next[0];
@@ -1191,6 +1303,17 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_rounds(TailArgs a) {
             leave = (a.chain_off + r + 1) % a.chain == 0 && (repeats || e < n * a.len_lo || e >= n * a.len_hi);
         }
         __syncthreads();
+    }
+    if constexpr (RES) {
+        if (r == 0) return;  // nothing has run: list and labels are as they were
+        for (unsigned int i = threadIdx.x; i < a.n * CP / VEC; i += kTailThreads)
+            store_vec<VEC>(a.F + (size_t)i * VEC, load_vec<VEC>(lF + i * VEC));
+        const unsigned int ns = count[0], nl = count[1];
+        for (unsigned int i = threadIdx.x; i < ns + nl; i += kTailThreads) {
+            const int32_t u = listed(r & 1, ns, i);
+            if (i < ns) a.front[r & 1][i] = u;
+            else a.back[r & 1][-(long long)(i - ns)] = u;
+        }
     }
 }
 
