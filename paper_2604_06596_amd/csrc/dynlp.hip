@@ -1495,10 +1495,16 @@ void launch_compact_start(dynlp_ctx* c, const Frontier& out, const Frontier& uni
                        out.back, c->ring + kRing, universe.front, universe.back, c->bc, gate);
 }
 
-void launch_commit(dynlp_ctx* c, const Frontier& f, const RoundCtr* prev, int64_t rows_bound) {
+// After a staged round over `f`: commit and next list (`out`; its counts as for launch_compact).
+void launch_commit_compact(dynlp_ctx* c, const Frontier& f, const RoundCtr* prev, int64_t rows_bound, const Frontier& out,
+                           unsigned int* count_short, unsigned int* count_long) {
     const int64_t items = rows_bound * (c->CP >= 4 ? c->CP / 4 : c->CP);
-    const unsigned int blocks = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(items, kBlock), (int64_t)c->num_cu * 8));
-    hipLaunchKernelGGL(k_commit, dim3(blocks), dim3(kBlock), 0, c->stream, prev, f.front, f.back, c->F2, c->F, c->CP);
+    const unsigned int commit = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(items, kBlock), (int64_t)c->num_cu * 8));
+    const int seg = c->n >= (16 << 20) ? 4 : 1;
+    const unsigned int compact = (unsigned int)ceil_div(std::max<int64_t>(c->n, 1), seg * kFlagsPerBlock);
+    auto kernel = seg == 4 ? k_commit_compact<4> : k_commit_compact<1>;
+    hipLaunchKernelGGL(kernel, dim3(compact + commit), dim3(kBlock), 0, c->stream, compact, (unsigned int)c->n, c->flag, c->seed_class,
+                       c->meta, out.front, out.back, count_short, count_long, prev, f.front, f.back, c->F2, c->F, c->CP);
     HIPCHK(c, hipGetLastError());
 }
 
@@ -3201,8 +3207,11 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                                        slot, slot_of(c, t + 1), (int64_t)universe.size(), (int64_t)universe.nl,
                                        (in_place ? kRowByVertex : 0) | (lazy ? kRowLazy : 0)};
                     launch_update<true>(c, G, f, a, t);
-                    if (!in_place) launch_commit(c, f, slot_of(c, t - 1), (int64_t)universe.size());
-                    launch_compact(c, frontier_of(c, cur ^ 1), &slot->next_count, &slot->next_long, 0);
+                    if (in_place)
+                        launch_compact(c, frontier_of(c, cur ^ 1), &slot->next_count, &slot->next_long, 0);
+                    else
+                        launch_commit_compact(c, f, slot_of(c, t - 1), (int64_t)universe.size(), frontier_of(c, cur ^ 1),
+                                              &slot->next_count, &slot->next_long);
                     cur ^= 1;
                 }
             }

@@ -37,21 +37,19 @@ __device__ inline int32_t frontier_vertex(const int32_t* front, const int32_t* b
 // per second, so the 12,000 workgroups of a 50M-vertex graph at SEG = 1 spend 0.12 ms queueing for the counter;
 // the host picks SEG = 4 from 16M vertices on and SEG = 1 (more workgroups) below.
 // all_rows != 0 ignores the flags and lists every updatable vertex (static solve, and the count of
-// updatable vertices).
+// updatable vertices).  bid: number of the workgroup among those that compact.
 template <int SEG>
-__global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __restrict__ flag,
-                                                   const int32_t* __restrict__ seed_class,
-                                                   const RowMeta* __restrict__ meta, int all_rows,
-                                                   int32_t* __restrict__ front, int32_t* __restrict__ back,
-                                                   unsigned int* __restrict__ count_short,
-                                                   unsigned int* __restrict__ count_long) {
+__device__ inline void compact_flags(unsigned int bid, unsigned int n, uint8_t* __restrict__ flag,
+                                     const int32_t* __restrict__ seed_class, const RowMeta* __restrict__ meta, int all_rows,
+                                     int32_t* __restrict__ front, int32_t* __restrict__ back,
+                                     unsigned int* __restrict__ count_short, unsigned int* __restrict__ count_long) {
     __shared__ unsigned long long sm[kBlock / kWave + 1];
     __shared__ unsigned int sbase[2];
     unsigned int keep[SEG], is_long[SEG];  // bit k: vertex v0+k enters the frontier / as a long row
     unsigned int n_short = 0, n_long = 0;
 #pragma unroll
     for (int q = 0; q < SEG; ++q) {
-        const unsigned int v0 = (blockIdx.x * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
+        const unsigned int v0 = (bid * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
         keep[q] = 0;
         is_long[q] = 0;
         if (v0 < n) {
@@ -97,7 +95,7 @@ __global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __r
     unsigned int pl = sbase[1] + (unsigned int)(ex >> 32);
 #pragma unroll
     for (int q = 0; q < SEG; ++q) {
-        const unsigned int v0 = (blockIdx.x * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
+        const unsigned int v0 = (bid * SEG + q) * kFlagsPerBlock + threadIdx.x * kFlagsPerThread;
         unsigned int kp = keep[q];
         while (kp) {
             const int k = __ffs(kp) - 1;
@@ -106,6 +104,16 @@ __global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __r
             else front[ps++] = (int32_t)(v0 + k);
         }
     }
+}
+
+template <int SEG>
+__global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __restrict__ flag,
+                                                   const int32_t* __restrict__ seed_class,
+                                                   const RowMeta* __restrict__ meta, int all_rows,
+                                                   int32_t* __restrict__ front, int32_t* __restrict__ back,
+                                                   unsigned int* __restrict__ count_short,
+                                                   unsigned int* __restrict__ count_long) {
+    compact_flags<SEG>(blockIdx.x, n, flag, seed_class, meta, all_rows, front, back, count_short, count_long);
 }
 
 // The first frontier of a batch from the flags (cleared) and the list of all updatable vertices, in one pass.
@@ -183,13 +191,12 @@ __global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_
 }
 
 // =================================================================================================
-// Commit of staged rows (staged rounds) and the next frontier after a ping-pong round
+// Commit of staged rows (staged rounds) and the next frontier after a round
 // =================================================================================================
-// F[vertex at position i] = Fq[i] for all positions: the Jacobi commit of a staged round.
-__global__ void __launch_bounds__(kBlock) k_commit(const RoundCtr* __restrict__ prev,
-                                                  const int32_t* __restrict__ front,
-                                                  const int32_t* __restrict__ back,
-                                                  const float* __restrict__ Fq, float* __restrict__ F, int CP) {
+// F[vertex at position i] = Fq[i] for all positions: the Jacobi commit of a staged round, by nblocks workgroups.
+__device__ inline void commit_rows(unsigned int bid, unsigned int nblocks, const RoundCtr* __restrict__ prev,
+                                   const int32_t* __restrict__ front, const int32_t* __restrict__ back,
+                                   const float* __restrict__ Fq, float* __restrict__ F, int CP) {
     const unsigned int ns = prev->next_count, nl = prev->next_long;
     const unsigned int nq = ns + nl;
     if (CP >= 4) {
@@ -197,20 +204,37 @@ __global__ void __launch_bounds__(kBlock) k_commit(const RoundCtr* __restrict__ 
         const unsigned long long total = (unsigned long long)nq * vpr;
         const float4* src = reinterpret_cast<const float4*>(Fq);
         float4* dst = reinterpret_cast<float4*>(F);
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kBlock + threadIdx.x; i < total;
-             i += (unsigned long long)gridDim.x * kBlock) {
+        for (unsigned long long i = (unsigned long long)bid * kBlock + threadIdx.x; i < total;
+             i += (unsigned long long)nblocks * kBlock) {
             const unsigned int pos = (unsigned int)(i / vpr);
             const unsigned int ch = (unsigned int)(i % vpr);
             dst[(unsigned long long)frontier_vertex(front, back, ns, pos) * vpr + ch] = src[i];
         }
     } else {
         const unsigned long long total = (unsigned long long)nq * CP;
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kBlock + threadIdx.x; i < total;
-             i += (unsigned long long)gridDim.x * kBlock) {
+        for (unsigned long long i = (unsigned long long)bid * kBlock + threadIdx.x; i < total;
+             i += (unsigned long long)nblocks * kBlock) {
             const unsigned int pos = (unsigned int)(i / CP);
             F[(unsigned long long)frontier_vertex(front, back, ns, pos) * CP + (i % CP)] = Fq[i];
         }
     }
+}
+
+// What follows a staged round, in one launch: its rows are committed (workgroups from compact_blocks on) and the next list of
+// rows is made from the marks.  (Two launches: a round over a few thousand rows spent 2 us in the commit, 5 in the
+// compaction and 3 between them.)
+template <int SEG>
+__global__ void __launch_bounds__(kBlock) k_commit_compact(unsigned int compact_blocks, unsigned int n,
+                                                          uint8_t* __restrict__ flag, const int32_t* __restrict__ seed_class,
+                                                          const RowMeta* __restrict__ meta, int32_t* __restrict__ next_front,
+                                                          int32_t* __restrict__ next_back, unsigned int* __restrict__ count_short,
+                                                          unsigned int* __restrict__ count_long, const RoundCtr* __restrict__ prev,
+                                                          const int32_t* __restrict__ front, const int32_t* __restrict__ back,
+                                                          const float* __restrict__ Fq, float* __restrict__ F, int CP) {
+    if (blockIdx.x < compact_blocks)
+        compact_flags<SEG>(blockIdx.x, n, flag, seed_class, meta, 0, next_front, next_back, count_short, count_long);
+    else
+        commit_rows(blockIdx.x - compact_blocks, gridDim.x - compact_blocks, prev, front, back, Fq, F, CP);
 }
 
 __device__ inline void mark(uint8_t* __restrict__ flag, int32_t v) {
