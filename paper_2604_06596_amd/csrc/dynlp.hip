@@ -562,7 +562,7 @@ void parallel_copy(void* dst, const void* src, size_t bytes) {
 
 // Copies eu / ev / ew (host) into c->b_eu / b_ev / b_ew and, per chunk, launches validation and counting on the
 // main stream.  bc must have been reset on the main stream before the call.
-void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, const int32_t* ev, const float* ew) {
+void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, const int32_t* ev, const float* ew, int32_t* touched) {
     const int64_t chunk = c->ingest_chunk;
     if (!c->copy_stream) {
         HIPCHK(c, hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
@@ -608,7 +608,7 @@ void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, c
         hipLaunchKernelGGL(k_validate_edges, dim3(grid_for(mc)), dim3(kBlock), 0, c->stream, mc, n_total, c->b_eu + off,
                            c->b_ev + off, c->b_ew + off, c->bc, off);
         hipLaunchKernelGGL(k_count_halfedges, dim3(grid_for(ceil_div(2 * mc, kAppendItems))), dim3(kBlock), 0, c->stream, mc,
-                           n_total, c->b_eu + off, c->b_ev + off, c->add_cnt, c->touched, c->bc,
+                           n_total, c->b_eu + off, c->b_ev + off, c->add_cnt, touched, c->bc,
                            c->he_rank ? c->he_rank + off : nullptr, c->he_rank ? c->he_rank + m + off : nullptr,
                            grid_for(ceil_div(2 * mc, kAppendItems)), (int64_t)0, (const int32_t*)nullptr, (int32_t*)nullptr);
         HIPCHK(c, hipGetLastError());
@@ -843,6 +843,9 @@ void launch_update_pull(dynlp_ctx* c, int G, const Frontier& universe, const Pul
 
 // Rounds queued per host round trip.
 constexpr int kChain = 8;
+// A batch of more half-edges than one per kInOrderShare vertices lists the rows it touches by a pass over all vertices.
+constexpr int64_t kInOrderShare = 8;
+constexpr int64_t kPlanItems = (int64_t)2 << 20;  // touched rows from which the plan takes several per thread (k_plan_reserve)
 // Rounds in a row that repeat themselves exactly before the rows are averaged (see dynlp_apply_update).
 constexpr int kSameRounds = 16;
 
@@ -2919,19 +2922,25 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             hipLaunchKernelGGL(k_drop_deleted_entries, dim3(std::min<unsigned int>(grid_for((int64_t)std::min(guess, 1e9)), most_blocks)),
                                dim3(kBlock), 0, c->stream, c->bc, dropping, c->meta, c->pool, c->seed_class, c->add_cnt, c->deg);
         }
+        // where many of the rows are touched, they are listed in the order of their ids after the counting
+        const bool in_order = m > 0 && 2 * m >= n1 / kInOrderShare;
+        int32_t* const as_touched = in_order ? nullptr : c->touched;
         if (pipelined) {
-            ingest_edges(c, m, n1, eu, ev, ew);
+            ingest_edges(c, m, n1, eu, ev, ew, as_touched);
         } else if (m + nd > 0) {
             const unsigned int count_blocks = m > 0 ? grid_for(ceil_div(2 * m, kAppendItems)) : 0u;
             hipLaunchKernelGGL(k_count_halfedges, dim3(count_blocks + (nd > 0 ? grid_for(nd) : 0u)), dim3(kBlock), 0, c->stream, m, n1,
-                               d_eu, d_ev, c->add_cnt, c->touched, c->bc, use_rank ? c->he_rank : nullptr,
+                               d_eu, d_ev, c->add_cnt, as_touched, c->bc, use_rank ? c->he_rank : nullptr,
                                use_rank ? c->he_rank + m : nullptr, count_blocks, nd, d_del, c->seed_class);
         }
+        if (in_order)
+            hipLaunchKernelGGL(k_list_touched, dim3(grid_for(ceil_div(n1, 16))), dim3(kBlock), 0, c->stream, n1, c->add_cnt, c->touched, c->bc);
         // room at the pool tail for the rows whose slack is too small
         const int64_t most_touched = std::min<int64_t>(2 * m, n1);
         if (m > 0)
-            hipLaunchKernelGGL(k_plan_reserve, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0, c->stream,
-                               c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->bc);
+            hipLaunchKernelGGL((most_touched >= kPlanItems ? k_plan_reserve<kAppendItems> : k_plan_reserve<1>),
+                               dim3(std::min<unsigned int>(grid_for(ceil_div(most_touched, most_touched >= kPlanItems ? kAppendItems : 1)), most_blocks)),
+                               dim3(kBlock), 0, c->stream, c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->bc);
         HIPCHK(c, hipGetLastError());
         c->last_init = dynlp_init_info{};
         Frontier universe = frontier_of(c, 2);

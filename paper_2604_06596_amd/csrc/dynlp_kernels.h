@@ -340,6 +340,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, in
 // and appends its first-touched rows with one counter atomic.
 // rank_u / rank_v (both or neither): what the counting atomic returned for half-edge i / m + i, i.e. the
 // half-edge's place among the entries this batch appends to its row; k_write_halfedges then needs no second atomic.
+// touched NULL: only counted, the rows are listed afterwards (k_list_touched).
 // Workgroups from count_blocks on take the marks from the nd deleted vertices again (if the checks have passed).
 __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
                                                            const int32_t* __restrict__ ev,
@@ -365,21 +366,51 @@ __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n
             src = i < m ? eu[i] : ev[i - m];
             if (src >= 0 && src < n_total) {
                 const int32_t r = atomicAdd(&add_cnt[src], 1);
-                if (r == 0) firstmask |= 1u << k;
+                if (r == 0 && touched) firstmask |= 1u << k;
                 if (rank_u) (i < m ? rank_u[i] : rank_v[i - m]) = r;
             }
         }
         srcs[k] = src;
     }
+    if (!touched) return;
     unsigned int slot = block_reserve(&bc->touched, (unsigned int)__popc(firstmask), smem);
 #pragma unroll
     for (int k = 0; k < kAppendItems; ++k)
         if ((firstmask >> k) & 1u) touched[slot++] = srcs[k];
 }
 
+// The rows that receive entries, in runs of ascending ids: rows that move to the pool's tail then lie there in the order of
+// their vertices, and everything that goes through the list or through the rows finds neighbours next to each other (listed
+// as they were touched first, 50M vertices and 250M half-edges lay in random order).  A workgroup lists 4,096 vertices.
+__global__ void __launch_bounds__(kBlock) k_list_touched(int64_t n, const int32_t* __restrict__ add_cnt,
+                                                        int32_t* __restrict__ touched, BatchCtr* bc) {
+    __shared__ unsigned int smem[kBlock / kWave + 1];
+    constexpr int PER = 16;
+    const int64_t v0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * PER;
+    unsigned int mask = 0;
+    if (v0 + PER <= n) {
+        int4 c[PER / 4];
+#pragma unroll
+        for (int q = 0; q < PER / 4; ++q) c[q] = reinterpret_cast<const int4*>(add_cnt + v0)[q];
+#pragma unroll
+        for (int q = 0; q < PER / 4; ++q)
+            mask |= ((c[q].x ? 1u : 0u) | (c[q].y ? 2u : 0u) | (c[q].z ? 4u : 0u) | (c[q].w ? 8u : 0u)) << (4 * q);
+    } else {
+        for (int k = 0; k < PER && v0 + k < n; ++k)
+            if (add_cnt[v0 + k]) mask |= 1u << k;
+    }
+    unsigned int slot = block_reserve(&bc->touched, (unsigned int)__popc(mask), smem);
+    while (mask) {
+        const int k = __ffs(mask) - 1;
+        mask &= mask - 1;
+        touched[slot++] = (int32_t)(v0 + k);
+    }
+}
+
 // Rows whose slack cannot take the new entries get room at the pool tail (one tail atomic per workgroup: atomics
 // on one address run at about 1e8 per second); reloc_off[t] is the new offset or -1.  Touches no row: bc->pool_tail
 // afterwards tells the host how large the pool has to be before k_relocate may run.
+template <int ITEMS>
 __global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restrict__ touched,
                                                         const RowMeta* __restrict__ meta,
                                                         const int32_t* __restrict__ add_cnt, float slack,
@@ -388,24 +419,40 @@ __global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restri
     __shared__ unsigned long long sbase;
     if (bc->err_code) return;
     const unsigned int nt = bc->touched;
-    for (unsigned int t0 = blockIdx.x * kBlock; t0 < nt; t0 += gridDim.x * kBlock) {  // uniform in the workgroup
-        const unsigned int t = t0 + threadIdx.x;
+    // ITEMS rows per thread: with one, 195,000 workgroups queue for the tail when 50M rows are touched (4.6 ms, with 8 1.4);
+    // with 8, a few hundred thousand rows keep too few lanes busy (400,000: 6 us with one, 14 with 8)
+    for (unsigned int t0 = blockIdx.x * kBlock * ITEMS; t0 < nt; t0 += gridDim.x * kBlock * ITEMS) {  // uniform in the workgroup
+        unsigned int caps[ITEMS];
         unsigned long long cap = 0;
-        if (t < nt) {
-            const int32_t u = touched[t];
-            const RowMeta m = meta[u];
-            const int64_t need = (int64_t)m.len + add_cnt[u];
-            if (need > m.cap) cap = (unsigned long long)row_capacity(need, slack);
+        unsigned int moved = 0;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const unsigned int t = t0 + threadIdx.x * ITEMS + k;
+            caps[k] = 0;
+            if (t < nt) {
+                const int32_t u = touched[t];
+                const RowMeta m = meta[u];
+                const int64_t need = (int64_t)m.len + add_cnt[u];
+                if (need > m.cap) caps[k] = (unsigned int)row_capacity(need, slack);
+            }
+            cap += caps[k];
+            moved += caps[k] ? 1u : 0u;
         }
-        unsigned long long total;
-        const unsigned long long ex = block_exclusive_scan<unsigned long long>(cap, smem, &total);
-        const int nrel = __syncthreads_count(cap != 0);
+        unsigned long long total, rows;
+        unsigned long long at = block_exclusive_scan<unsigned long long>(cap, smem, &total);
+        (void)block_exclusive_scan<unsigned long long>(moved, smem, &rows);
         if (threadIdx.x == 0) {
             sbase = total ? atomicAdd(&bc->pool_tail, total) : 0ull;
-            if (nrel) atomicAdd(&bc->relocated, (unsigned int)nrel);
+            if (rows) atomicAdd(&bc->relocated, (unsigned int)rows);
         }
         __syncthreads();
-        if (t < nt) reloc_off[t] = cap ? (int64_t)(sbase + ex) : -1;
+        at += sbase;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const unsigned int t = t0 + threadIdx.x * ITEMS + k;
+            if (t < nt) reloc_off[t] = caps[k] ? (int64_t)at : -1;
+            at += caps[k];
+        }
         __syncthreads();
     }
 }
