@@ -845,6 +845,9 @@ void launch_update_pull(dynlp_ctx* c, int G, const Frontier& universe, const Pul
 constexpr int kChain = 8;
 // A batch of more half-edges than one per kInOrderShare vertices lists the rows it touches by a pass over all vertices.
 constexpr int64_t kInOrderShare = 8;
+// Such a batch sorts what a row receives with 8 lanes instead of 16 where it holds fewer half-edges than this per vertex and
+// the chip is full either way (20,000 rows: 11 us with 16 lanes, 14 with 8).
+constexpr int64_t kSortLanes8 = 8, kSortRows8 = 131072;
 constexpr int64_t kPlanItems = (int64_t)2 << 20;  // touched rows from which the plan takes several per thread (k_plan_reserve)
 // Rounds in a row that repeat themselves exactly before the rows are averaged (see dynlp_apply_update).
 constexpr int kSameRounds = 16;
@@ -2961,7 +2964,10 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 // and of hubs)
                 int32_t* long_list = reinterpret_cast<int32_t*>(c->reloc_off);
                 int32_t* hub_list = long_list + c->touched_cap;
-                hipLaunchKernelGGL(k_sort_finish, dim3(std::min<unsigned int>(grid_for(most_touched * 16), 2 * most_blocks)), dim3(kBlock), 0,
+                // (the mean number of half-edges per touched row, if all rows are touched: the least it can be)
+                const int lanes = in_order && most_touched >= kSortRows8 && 2 * m < kSortLanes8 * n1 ? 8 : 16;
+                auto sort_finish = lanes == 8 ? k_sort_finish<8> : k_sort_finish<16>;
+                hipLaunchKernelGGL(sort_finish, dim3(std::min<unsigned int>(grid_for(most_touched * lanes), 2 * most_blocks)), dim3(kBlock), 0,
                                    c->stream, c->touched, c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc,
                                    c->deg, c->flag, gate);
                 hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::min<int64_t>(most_touched, 512)), dim3(kSortThreads), 0,

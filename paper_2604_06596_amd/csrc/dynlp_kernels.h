@@ -553,8 +553,9 @@ __device__ inline float block_row_degree(const Edge* row, int len, float* tile) 
 
 // The entries one batch appends to a row land in the order their atomics happened to take.  Sorting
 // the appended segment by (neighbour id, weight bits) makes the stored row, and with it every sum
-// over the row, a function of the batch alone.  16 lanes per touched row; segments of up to
-// 16 * kSortRegs entries are rank-sorted in registers (every key is broadcast to the group once),
+// over the row, a function of the batch alone.  G lanes per touched row (16; 8 where rows receive a few entries each, whose
+// other lanes would have nothing to do: 50M rows of 5, 9.8 -> 5.5 ms; 330,000 of 1 to 20, 45 -> 30 us); segments of up to
+// G * kSortRegs entries are rank-sorted in registers (every key is broadcast to the group once),
 // longer ones are queued for k_sort_long_segments.
 __device__ inline unsigned long long edge_key(const Edge& e) {
     return ((unsigned long long)(unsigned int)e.col << 32) | (unsigned long long)__float_as_uint(e.w);
@@ -573,13 +574,14 @@ __device__ inline Edge key_edge(unsigned long long k) {
 // len_is_old: the rows' lengths do not yet include the appended entries (k_write_halfedges with ranks); the kernel
 // then stores the new length.  Rows with long appended segments only get their length and are listed (long_list), hubs that
 // received a few entries are sorted and listed for k_sort_long_segments (hub_list), which ends Step 1 for both.
+template <int G>
 __global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restrict__ touched,
                                                        RowMeta* __restrict__ meta, Edge* __restrict__ pool,
                                                        int32_t* __restrict__ add_cnt, int len_is_old,
                                                        int32_t* __restrict__ long_list,
                                                        int32_t* __restrict__ hub_list, BatchCtr* bc,
                                                        float* __restrict__ deg, uint8_t* __restrict__ flag, BatchGate gate) {
-    constexpr int G = 16;
+    constexpr int L = 16, P = L / G;  // sums: entry j goes to sum j mod L, P sums per lane
     __shared__ float sorted_w[kBlock / G][G * kSortRegs];
     if (gate.closed()) return;
     const unsigned int nt = bc->touched;
@@ -662,19 +664,28 @@ __global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restric
             }
             continue;
         }
-        float s = 0.f;
-        constexpr int UN = 4;  // loads in flight, added in order
-        for (int j0 = gl; j0 < len_new; j0 += UN * G) {
-            float wv[UN];
+        float sum[P];
 #pragma unroll
-            for (int q = 0; q < UN; ++q) {
-                const int j = j0 + q * G;
-                wv[q] = j < len_old ? pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
-            }
+        for (int p = 0; p < P; ++p) sum[p] = 0.f;
+        constexpr int UN = 4;  // rounds of L entries whose loads are in flight, added in order
+        for (int j0 = gl; j0 < len_new; j0 += UN * L) {
+            float wv[UN][P];
 #pragma unroll
             for (int q = 0; q < UN; ++q)
-                if (j0 + q * G < len_new) s += wv[q];
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    const int j = j0 + q * L + p * G;
+                    wv[q][p] = j < len_old ? pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
+                }
+#pragma unroll
+            for (int q = 0; q < UN; ++q)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    if (j0 + q * L + p * G < len_new) sum[p] += wv[q][p];
         }
+        // the sums by halves: l and l + 8, l and l + 4, ...
+        float s = sum[0];
+        if constexpr (P == 2) s += sum[1];
 #pragma unroll
         for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
         if (gl == 0) {

@@ -118,3 +118,36 @@ def test_rows_about_the_lengths_that_change_hands(hub):
         assert d.apply_update(np.array([0, 0], np.int32))[0] == 0
         g.delete(np.array([0]))
         _check_graph(d, g, ordered=False)
+
+
+@pytest.mark.parametrize("n,per_row,hub", [(140001, 2, 63), (140001, 2, 64), (140001, 2, 65), (140001, 1, 129), (140001, 6, 3000), (9001, 2, 65)])
+def test_rows_of_a_batch_that_touches_many(n, per_row, hub):
+    """Where a batch touches many rows they are listed by a pass over the vertices, and from 131,072 rows on segments are
+    sorted with 8 lanes: up to 64 entries per row, more are sorted by a workgroup.  Entries in order of id and weight, and
+    degrees summed in the order of a fresh context, bit for bit."""
+    rng = np.random.default_rng(hub)
+    m = per_row * n // 2
+    eu = np.concatenate([rng.integers(0, n, m), np.full(hub, 7)]).astype(np.int32)
+    ev = np.concatenate([rng.integers(0, n, m), 8 + np.arange(hub)]).astype(np.int32)
+    keep = (eu != ev) & ((eu != 7) & (ev != 7) | (np.arange(eu.size) >= m))
+    eu, ev = eu[keep], ev[keep]
+    ew = rng.uniform(0.1, 1, eu.size).astype(np.float32)
+    base = np.arange(n - 1)
+    rp0, col0, w0 = W.edges_to_csr(n, base[base % 3 == 0], base[base % 3 == 0] + 1, np.full(int(np.sum(base % 3 == 0)), 0.5, np.float32))
+    sv, sc = np.arange(5, dtype=np.int32), np.array([0, 1, 0, 1, 0], np.int32)
+    with P.DynLP(n, rp0, col0, w0, 2, sv, sc, slack_factor=1.01) as d:
+        d.set_params(1e-3, 1)
+        assert d.apply_batch(0, eu, ev, ew)[0] in (0, 1)
+        rp, col, w, deg, _ = d.export_graph()
+    src, dst = np.concatenate([eu, ev]), np.concatenate([ev, eu])
+    ww = np.concatenate([ew, ew])
+    order = np.lexsort((ww.view(np.uint32), dst, src))
+    counts = np.bincount(src, minlength=n)
+    old = np.diff(rp0)
+    assert np.array_equal(np.diff(rp), old + counts)
+    start = np.concatenate([[0], np.cumsum(counts)])[:-1]
+    at = np.repeat(rp[:-1] + old - start, counts) + np.arange(src.size)  # where the appended entries belong
+    assert np.array_equal(col[at], dst[order]) and np.array_equal(w[at], ww[order])
+    with P.DynLP(n, rp, col, w, 2, sv, sc) as fresh:
+        deg2 = fresh.export_graph()[3]
+    assert np.array_equal(deg, deg2)
