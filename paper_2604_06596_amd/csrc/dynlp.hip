@@ -3339,41 +3339,36 @@ dynlp_status dynlp_get_labels(dynlp_ctx* c, float* soft, int32_t* hard) {
     }
     const int64_t n = c->n;
     if (n == 0 || (!soft && !hard)) return DYNLP_OK;
-    float* d_soft = nullptr;
-    int32_t* d_hard = nullptr;
+    unsigned char* d_out = nullptr;
     dynlp_status st = DYNLP_OK;
     try {
         HIPCHK(c, hipSetDevice(c->device));
         const int64_t soft_bytes = soft ? n * c->C * (int64_t)sizeof(float) : 0, hard_off = round_up(soft_bytes, 64);
         const int64_t out_bytes = hard_off + (hard ? n * (int64_t)sizeof(int32_t) : 0);
-        if (!c->dev_ptrs && out_bytes <= kIoOutBytes && ensure_pinned(c, out_bytes)) {
-            // few labels: written by the kernel straight into pinned host memory
-            launch_label_output(c, soft ? reinterpret_cast<float*>(c->h_io) : nullptr,
-                                hard ? reinterpret_cast<int32_t*>(c->h_io + hard_off) : nullptr);
+        if (c->dev_ptrs) {
+            launch_label_output(c, soft, hard);
             HIPCHK(c, hipStreamSynchronize(c->stream));
-            if (soft) std::memcpy(soft, c->h_io, (size_t)soft_bytes);
-            if (hard) std::memcpy(hard, c->h_io + hard_off, (size_t)n * sizeof(int32_t));
             return DYNLP_OK;
         }
-        // staging of the packed outputs in host-pointer mode; without memory for it the call fails and the context
-        // stays usable
-        if (soft && !c->dev_ptrs) d_soft = Temp<float>(c, n * c->C).release();
-        if (hard && !c->dev_ptrs) d_hard = Temp<int32_t>(c, n).release();
-        float* dst_soft = !soft ? nullptr : c->dev_ptrs ? soft : d_soft;
-        int32_t* dst_hard = !hard ? nullptr : c->dev_ptrs ? hard : d_hard;
-        launch_label_output(c, dst_soft, dst_hard);
-        if (!c->dev_ptrs) {
-            if (soft) HIPCHK(c, hipMemcpyAsync(soft, dst_soft, (size_t)n * c->C * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-            if (hard) HIPCHK(c, hipMemcpyAsync(hard, dst_hard, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-        }
+        // few labels: written by the kernel straight into pinned host memory; else staged in device memory (one array; without
+        // memory for it the call fails and the context stays usable) and, up to kIoBytes, copied by way of the pinned memory
+        const bool pinned = ensure_pinned(c, out_bytes);
+        const bool direct = pinned && out_bytes <= kIoOutBytes;
+        if (!direct) d_out = Temp<unsigned char>(c, out_bytes).release();
+        unsigned char* const to = direct ? c->h_io : d_out;
+        launch_label_output(c, soft ? reinterpret_cast<float*>(to) : nullptr, hard ? reinterpret_cast<int32_t*>(to + hard_off) : nullptr);
+        if (pinned && !direct) HIPCHK(c, hipMemcpyAsync(c->h_io, d_out, (size_t)out_bytes, hipMemcpyDeviceToHost, c->stream));
+        if (!pinned && soft) HIPCHK(c, hipMemcpyAsync(soft, d_out, (size_t)soft_bytes, hipMemcpyDeviceToHost, c->stream));
+        if (!pinned && hard) HIPCHK(c, hipMemcpyAsync(hard, d_out + hard_off, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (pinned && soft) std::memcpy(soft, c->h_io, (size_t)soft_bytes);
+        if (pinned && hard) std::memcpy(hard, c->h_io + hard_off, (size_t)n * sizeof(int32_t));
     } catch (const SoftOom&) {
         st = DYNLP_ERR_OOM;
     } catch (const Fail& f) {
         st = f.st;
     }
-    dev_free(c, d_soft);
-    dev_free(c, d_hard);
+    dev_free(c, d_out);
     return st;
 }
 
