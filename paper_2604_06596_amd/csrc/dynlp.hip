@@ -158,6 +158,8 @@ struct dynlp_ctx {
         BatchCtr bc;
     }* h_start = nullptr;        // pinned: the start slot and the batch counters, which lie behind it on the device too
     BatchCtr* h_bc = nullptr;    // (in h_start)
+    unsigned int* h_flag = nullptr;  // pinned: number of the last k_to_host that has arrived
+    unsigned int h_sent = 0;         // ... that was launched
 
     int update_mode = DYNLP_UPDATE_SYNCHRONOUS;
     bool final_check = false;  // dynlp_set_final_check
@@ -373,6 +375,34 @@ void read_bc(dynlp_ctx* c) {
 void write_bc(dynlp_ctx* c) {
     HIPCHK(c, hipMemcpyAsync(c->bc, c->h_bc, sizeof(BatchCtr), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+}
+
+constexpr float kPollMs = 20.f;
+
+// Device records (whole multiples of 16 bytes, in up to two runs) to pinned host memory; waits for them, and with that for
+// everything the stream holds.
+void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const void* b = nullptr, size_t bytes_b = 0) {
+    const unsigned int value = ++c->h_sent;
+    hipLaunchKernelGGL(k_to_host, dim3(1), dim3(kBlock), 0, c->stream, static_cast<const uint4*>(a), (unsigned int)(bytes_a / 16),
+                       static_cast<const uint4*>(b), (unsigned int)(bytes_b / 16), static_cast<uint4*>(to), c->h_flag, value);
+    HIPCHK(c, hipGetLastError());
+    // the flag comes with the last work of the stream, so the wait ends when that does; an error of the device, after which
+    // the flag may never come, shows in the state of the stream
+    auto arrived = [&]() { return __atomic_load_n(c->h_flag, __ATOMIC_ACQUIRE) == value; };
+    const auto t0 = Clock::now();
+    for (unsigned int polls = 0; !arrived(); ++polls) {
+        if (polls % 64 != 63 || ms_since(t0) < kPollMs) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        // (not a chain of rounds of a graph that waits show on: let the runtime wait)
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (!arrived()) {
+            c->err = "internal error: the counters did not arrive";
+            c->poisoned = true;
+            throw Fail{DYNLP_ERR_DEVICE};
+        }
+    }
 }
 
 std::string format_validation(int code, long long index) {
@@ -1606,20 +1636,14 @@ void fold_slot(RoundCtr& r) {
 
 // Copy the slots of rounds [t0, t0 + count) to the host (count <= kRing) and wait for them.
 void read_slots(dynlp_ctx* c, int t0, int count) {
-    for (int i = 0; i < count;) {
-        const int idx = (t0 + i) % kRing;
-        const int run = std::min(count - i, kRing - idx);
-        HIPCHK(c, hipMemcpyAsync(c->h_slot + i, c->ring + idx, sizeof(RoundCtr) * (size_t)run, hipMemcpyDeviceToHost, c->stream));
-        i += run;
-    }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    const int at = t0 % kRing, run = std::min(count, kRing - at);
+    read_to_host(c, c->h_slot, c->ring + at, sizeof(RoundCtr) * (size_t)run, c->ring, sizeof(RoundCtr) * (size_t)(count - run));
     for (int i = 0; i < count; ++i) fold_slot(c->h_slot[i]);
 }
 
 // The start slot and the batch counters, in one copy.
 void read_start(dynlp_ctx* c) {
-    HIPCHK(c, hipMemcpyAsync(c->h_start, c->ring + kRing, sizeof(dynlp_ctx::HostStart), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    read_to_host(c, c->h_start, c->ring + kRing, sizeof(dynlp_ctx::HostStart));
 }
 
 void read_slots_start(dynlp_ctx* c) {
@@ -1949,18 +1973,13 @@ DenseRounds conjugate(dynlp_ctx* c, const Frontier& universe, int G, float tol, 
             HIPCHK(c, hipGetLastError());
             close_timed_span(c, e1);
         }
-        for (int i = 1; i <= r;) {
-            const int at = (k + i) % kCgRing, run = std::min(r + 1 - i, kCgRing - at);
-            HIPCHK(c, hipMemcpyAsync(c->h_cg + i - 1, c->cg_ring + at, sizeof(CgSlot) * (size_t)run, hipMemcpyDeviceToHost, c->stream));
-            i += run;
-        }
+        const int at = (k + 1) % kCgRing, run = std::min(r, kCgRing - at);
+        read_to_host(c, c->h_cg, c->cg_ring + at, sizeof(CgSlot) * (size_t)run, c->cg_ring, sizeof(CgSlot) * (size_t)(r - run));
         if (k == 0) {
-            read_slots(c, it, 1);  // (waits for everything above)
+            read_slots(c, it, 1);
             log_round(c->h_slot[0]);
             full = c->log.back();
             if (!(out.last > stop)) more = false;
-        } else {
-            HIPCHK(c, hipStreamSynchronize(c->stream));
         }
         int executed = 0;
         for (int i = 0; i < r && more; ++i) {
@@ -2087,6 +2106,7 @@ void destroy_ctx(dynlp_ctx* c) {
     if (c->h_slot) (void)hipHostFree(c->h_slot);
     if (c->h_start) (void)hipHostFree(c->h_start);
     if (c->h_io) (void)hipHostFree(c->h_io);
+    if (c->h_flag) (void)hipHostFree(c->h_flag);
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
@@ -2319,6 +2339,8 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_slot), sizeof(RoundCtr) * kRing, hipHostMallocDefault));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_start), sizeof(dynlp_ctx::HostStart), hipHostMallocDefault));
         c->h_bc = &c->h_start->bc;
+        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_flag), sizeof(unsigned int), hipHostMallocDefault));
+        *c->h_flag = 0u;
         for (auto& e : c->phase_ev) HIPCHK(c, hipEventCreate(&e));
         std::memset(c->h_bc, 0, sizeof(BatchCtr));
         write_bc(c);
