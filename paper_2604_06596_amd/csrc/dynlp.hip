@@ -1286,6 +1286,8 @@ constexpr unsigned int kPackedMaxRow = 8192;
 constexpr double kPackedShare = 0.6, kPackedUneven = 2.0;
 // A row's share of a part's time, in entries: its sums are cleared, its old row read and its new one written.
 constexpr unsigned int kPackedRowCost = 4;
+// A longest row of more than one in kPackedSpread of a part's entries: its entries are spread over their buckets (k_pk_place).
+constexpr double kPackedSpread = 16.0;
 // Above kPackedMaxTol a synchronous run stops so far from the fixed point (the threshold times the steps of a random walk
 // to a labelled vertex) that the last bits of a row decide visibly where: a row that moves by the threshold to within
 // rounding enters V_aff or not and takes its neighbours along.  With tol = 1e-4 on 1,000,000 vertices two solves that
@@ -1413,7 +1415,7 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
         });
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pk_place), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (kPkMaxRows + 1) * (int)sizeof(unsigned int));
+                                    kPkPlaceLds);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             ok = false;
@@ -1453,8 +1455,13 @@ bool build_packed(dynlp_ctx* c, const Frontier& universe, const PackedPlan& plan
     if (universe.nl)
         hipLaunchKernelGGL(k_pk_long_degrees, dim3(std::min<unsigned int>(universe.nl, (unsigned int)c->num_cu * 8)), dim3(kBlock), 0,
                            c->stream, universe.nl, universe.back, c->meta, c->pool, c->pk_deg);
-    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), (size_t)(c->pk_rows + 1) * 4, c->stream, c->n, bound, plan.col_bits,
-                       plan.bucket_bits, c->meta, c->pool, c->pk_len, c->pk_deg, start, c->pk_ent);
+    const int spread = (double)most[2] * kPackedSpread > (double)ent / (double)parts ? 1 : 0;
+    // tiles as large as the running row lengths leave room for
+    const size_t lengths = (size_t)(c->pk_rows + 1) * sizeof(unsigned int);
+    unsigned int tile = kPkTile;
+    while (tile * sizeof(PkEntry) + lengths > (size_t)kPkPlaceLds) tile /= 2;
+    hipLaunchKernelGGL(k_pk_place, dim3(plan.parts), dim3(kPkThreads), tile * sizeof(PkEntry) + lengths, c->stream, c->n, bound, plan.col_bits,
+                       plan.bucket_bits, tile, spread, c->meta, c->pool, c->pk_len, c->pk_deg, start, c->pk_ent);
     HIPCHK(c, hipGetLastError());
     c->pk_built = true;
     return true;

@@ -275,7 +275,17 @@ __device__ inline unsigned int pk_spread(unsigned int L) {
 // influence on results.  One workgroup per part, one lane per entry (running row lengths in LDS tell its row): the reads
 // of eight entries per lane are in flight together and a hub row is as quick as any other (1,000,000 vertices of degree
 // 20, 16 lanes per row: 667 us).
-constexpr int kPkMaxRows = 32768;  // their running lengths fit the LDS
+// The entries go through LDS in tiles, where they are ordered by bucket, and leave as one run of neighbouring places per tile
+// and bucket (us, placed one by one, 8 bytes each at 512 places at a time, and now: 1,000,000 vertices of degree 20 588, 282;
+// 400,000 177, 100; 300,000 of degree 16 136, 77).  Tile t of T takes every T-th group of 16 entries, in steps of 0.618 of the
+// tile's groups, so that entries of one row that fall into one bucket do not come one after the other.
+// spread: a row holds so much of a part that several of its entries are added at once wherever they lie; they then go to the
+// places that pk_spread gives, each on its own (150,000 vertices, a power law whose longest row is a sixth of a part: rounds
+// of 52.0 us, 52.8 to 54.2 with runs).
+constexpr int kPkMaxRows = 32768;  // their running lengths fit the LDS beside a tile of 1,024 entries
+constexpr unsigned int kPkTile = 8192;
+constexpr int kPkPlaceLds = 146 * 1024;  // dynamic LDS of k_pk_place
+static_assert((kPkMaxRows + 1) * 4 + 1024 * sizeof(PkEntry) <= kPkPlaceLds, "the smallest tile");
 
 // Rows of the workgroup's part (0: an empty part).
 __device__ inline int pk_part_rows(int64_t n, const unsigned int* __restrict__ bound) {
@@ -284,22 +294,25 @@ __device__ inline int pk_part_rows(int64_t n, const unsigned int* __restrict__ b
 }
 
 __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, const unsigned int* __restrict__ bound, int col_bits, int bucket_bits,
-                                                        const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
-                                                        const int32_t* __restrict__ len, const float* __restrict__ deg,
-                                                        const unsigned int* __restrict__ start,
+                                                        unsigned int tile, int spread, const RowMeta* __restrict__ meta,
+                                                        const Edge* __restrict__ pool, const int32_t* __restrict__ len,
+                                                        const float* __restrict__ deg, const unsigned int* __restrict__ start,
                                                         PkEntry* __restrict__ ent) {
     constexpr int T = kPkThreads;
     constexpr int NW = T / kWave;
     constexpr int UN = 4;
-    extern __shared__ __align__(16) unsigned int pk_lds[];  // rows + 1 words: entries in the part's rows before
-    __shared__ unsigned int cur[kPkBuckets];  // entries per bucket, then entries placed
-    __shared__ unsigned int seg0[kPkBuckets], seg_len[kPkBuckets], step[kPkBuckets];
+    extern __shared__ __align__(16) unsigned int pk_lds[];  // a tile of entries; rows + 1 words: entries in the part's rows before
+    __shared__ unsigned int next[kPkBuckets];               // entries per bucket, then the next place of the bucket
+    __shared__ unsigned int cnt[kPkBuckets], off[kPkBuckets];  // of the tile: entries per bucket, their first place in the tile
+    __shared__ unsigned int seg0[kPkBuckets], seg_len[kPkBuckets], step[kPkBuckets];  // spread: of the bucket
     __shared__ unsigned int wave_tot[NW];
-    static_assert(kPkBuckets <= T, "one thread per bucket");
-    unsigned int* const pre = pk_lds;
+    static_assert(kPkBuckets <= T && kPkBuckets % kWave == 0, "one thread per bucket");
+    PkEntry* const sorted = reinterpret_cast<PkEntry*>(pk_lds);
+    unsigned int* const pre = pk_lds + 2 * tile;
     const int64_t base = (int64_t)bound[blockIdx.x] * 32;
     const int nr = pk_part_rows(n, bound);
-    if (threadIdx.x < kPkBuckets) cur[threadIdx.x] = 0u;
+    const unsigned int mask = (1u << col_bits) - 1u;
+    if (threadIdx.x < kPkBuckets) next[threadIdx.x] = 0u;
     // running row lengths: every thread sums a run of rows, the runs are scanned
     const int per = (nr + T - 1) / T;
     const int r0 = (int)threadIdx.x * per < nr ? (int)threadIdx.x * per : nr;
@@ -318,6 +331,7 @@ __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, const unsign
     const unsigned int count = start[blockIdx.x + 1] - start[blockIdx.x];
     if (threadIdx.x == 0) pre[nr] = count;
     __syncthreads();
+    if (count == 0) return;
     auto row_of = [&](unsigned int i) {  // the last row r with pre[r] <= i (rows without entries share their start with the next)
         int lo = 0, hi = nr;             // pre[lo] <= i < pre[hi]
         while (hi - lo > 1) {
@@ -328,57 +342,100 @@ __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, const unsign
         return lo;
     };
     for (unsigned int i0 = threadIdx.x; i0 < count; i0 += UN * T) {
-        int r[UN];
-        Edge e[UN];
+        unsigned int b[UN];
 #pragma unroll
         for (int t = 0; t < UN; ++t) {
             const unsigned int i = i0 + t * T < count ? i0 + t * T : count - 1;
-            r[t] = row_of(i);
-            e[t] = pool[meta[base + r[t]].off + (i - pre[r[t]])];
+            const int r = row_of(i);
+            b[t] = (unsigned int)pool[meta[base + r].off + (i - pre[r])].col >> bucket_bits;
         }
 #pragma unroll
         for (int t = 0; t < UN; ++t)
-            if (i0 + t * T < count) atomicAdd(&cur[(unsigned int)e[t].col >> bucket_bits], 1u);
+            if (i0 + t * T < count) atomicAdd(&next[b[t]], 1u);
     }
     __syncthreads();
-    unsigned int v = 0, inc = 0;
-    if (threadIdx.x < kPkBuckets) {
-        v = cur[threadIdx.x];
-        inc = wave_inclusive_scan(v);
-        if (lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = inc;
-        seg_len[threadIdx.x] = v;
-        step[threadIdx.x] = v > 0u ? pk_spread(v) : 1u;
-    }
-    __syncthreads();
-    if (threadIdx.x < kPkBuckets) {
-        unsigned int at = start[blockIdx.x];
-        for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) at += wave_tot[w];
-        seg0[threadIdx.x] = at + inc - v;
-        cur[threadIdx.x] = 0u;
-    }
-    __syncthreads();
-    for (unsigned int i0 = threadIdx.x; i0 < count; i0 += UN * T) {
-        int r[UN];
-        Edge e[UN];
-        float d[UN];
-#pragma unroll
-        for (int t = 0; t < UN; ++t) {
-            const unsigned int i = i0 + t * T < count ? i0 + t * T : count - 1;
-            r[t] = row_of(i);
-            e[t] = pool[meta[base + r[t]].off + (i - pre[r[t]])];
-            d[t] = deg[base + r[t]];
+    // exclusive scan over the buckets: every thread of the first kPkBuckets gives its value and takes its prefix
+    auto scan_buckets = [&](unsigned int v) {
+        unsigned int inc = 0;
+        if (threadIdx.x < kPkBuckets) {
+            inc = wave_inclusive_scan(v);
+            if (lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = inc;
         }
-#pragma unroll
-        for (int t = 0; t < UN; ++t) {
-            if (i0 + t * T >= count) continue;
-            const unsigned int b = (unsigned int)e[t].col >> bucket_bits;
-            PkEntry x;
-            x.at = ((unsigned int)r[t] << col_bits) | (unsigned int)e[t].col;
-            x.wn = e[t].w / d[t] * kPkUnit;
-            const unsigned int k = atomicAdd(&cur[b], 1u), L = seg_len[b];
-            const unsigned int place = L < 65536u ? k * step[b] % L : (unsigned int)((unsigned long long)k * step[b] % L);
-            ent[seg0[b] + place] = x;
+        __syncthreads();
+        unsigned int at = inc - v;
+        if (threadIdx.x < kPkBuckets)
+            for (unsigned int w = 0; w < threadIdx.x / kWave; ++w) at += wave_tot[w];
+        __syncthreads();
+        return at;
+    };
+    {
+        const unsigned int at = scan_buckets(threadIdx.x < kPkBuckets ? next[threadIdx.x] : 0u);
+        if (threadIdx.x < kPkBuckets) {
+            if (spread) {
+                const unsigned int v = next[threadIdx.x];
+                seg0[threadIdx.x] = start[blockIdx.x] + at;
+                seg_len[threadIdx.x] = v;
+                step[threadIdx.x] = v > 0u ? pk_spread(v) : 1u;
+            }
+            next[threadIdx.x] = start[blockIdx.x] + at;
         }
+    }
+    constexpr unsigned int GRP = 16;
+    constexpr int MOST = 8;  // entries per thread and tile: a tile holds at most MOST * T
+    const unsigned int groups = (count + GRP - 1) / GRP, tiles = (groups + tile / GRP - 1) / (tile / GRP);
+    for (unsigned int q = 0; q < tiles; ++q) {
+        if (threadIdx.x < kPkBuckets) cnt[threadIdx.x] = 0u;
+        __syncthreads();
+        PkEntry x[MOST];
+        unsigned int place[MOST];  // bucket << 16 | rank; ~0: none
+#pragma unroll
+        for (int k0 = 0; k0 < MOST; k0 += UN) {
+            int r[UN];
+            Edge e[UN];
+            float d[UN];
+            bool ok[UN];
+#pragma unroll
+            for (int t = 0; t < UN; ++t) {
+                const unsigned int j = (unsigned int)(k0 + t) * T + threadIdx.x;
+                const unsigned int g = (j / GRP) * 317u % (tile / GRP);
+                const unsigned int i = GRP * (q + tiles * g) + j % GRP;
+                ok[t] = j < tile && i < count;
+                const unsigned int from = ok[t] ? i : count - 1;
+                r[t] = row_of(from);
+                e[t] = pool[meta[base + r[t]].off + (from - pre[r[t]])];
+                d[t] = deg[base + r[t]];
+            }
+#pragma unroll
+            for (int t = 0; t < UN; ++t) {
+                place[k0 + t] = ~0u;
+                if (!ok[t]) continue;
+                x[k0 + t].at = ((unsigned int)r[t] << col_bits) | (unsigned int)e[t].col;
+                x[k0 + t].wn = e[t].w / d[t] * kPkUnit;
+                const unsigned int b = (unsigned int)e[t].col >> bucket_bits;
+                place[k0 + t] = (b << 16) | atomicAdd(&cnt[b], 1u);
+            }
+        }
+        __syncthreads();
+        const unsigned int at = scan_buckets(threadIdx.x < kPkBuckets ? cnt[threadIdx.x] : 0u);
+        if (threadIdx.x < kPkBuckets) off[threadIdx.x] = at;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < MOST; ++k)
+            if (place[k] != ~0u) sorted[off[place[k] >> 16] + (place[k] & 0xffffu)] = x[k];
+        __syncthreads();
+        const unsigned int held = off[kPkBuckets - 1] + cnt[kPkBuckets - 1];
+        for (unsigned int p = threadIdx.x; p < held; p += T) {
+            const PkEntry e = sorted[p];
+            const unsigned int b = (e.at & mask) >> bucket_bits;
+            unsigned int to = next[b] + (p - off[b]);
+            if (spread) {
+                const unsigned int k = to - seg0[b], L = seg_len[b];
+                to = seg0[b] + (L < 65536u ? k * step[b] % L : (unsigned int)((unsigned long long)k * step[b] % L));
+            }
+            ent[to] = e;
+        }
+        __syncthreads();
+        if (threadIdx.x < kPkBuckets) next[threadIdx.x] += cnt[threadIdx.x];
     }
 }
 
