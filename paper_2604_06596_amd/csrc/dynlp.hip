@@ -2014,8 +2014,8 @@ DenseRounds conjugate(dynlp_ctx* c, const Frontier& universe, int G, float tol, 
         }
     }
     with_columns(c->CP, [&](auto cp) {
-        hipLaunchKernelGGL(k_cg_end<decltype(cp)::value>, dim3(blocks), dim3(kBlock), 0, c->stream, c->n, c->Cs, c->deg, c->seed_class,
-                           c->F, c->F2);
+        hipLaunchKernelGGL(k_cg_end<decltype(cp)::value>, dim3(blocks), dim3(kBlock), 0, c->stream, c->cg_ring + k % kCgRing, c->n, c->Cs,
+                           c->deg, c->seed_class, z, p, c->F, c->F2);
     });
     HIPCHK(c, hipGetLastError());
     const int t = it + k + 1;

@@ -17,7 +17,9 @@
 // z' is: (z', z') = alpha^2 (v, v) - (z, z) by conjugacy (Meurant 1987).  alpha itself uses the (z, z) that was summed, which
 // keeps the recurrence from drifting.  An iteration is then two launches:
 //   product   k_pk_product, k_pb_product or k_row_product: v, and the sums (p, v) and (v, v)
-//   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|
+//   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|.  The step is
+//             bound by its seven streams; x, which nothing reads in between, is updated in every second step only, by the
+//             sum of two (1M rows of 16 floats 94 -> 68 us per step, of 64 floats 371 -> 297).
 // and needs no other wait.  Measured, whole calls at tol = 1e-6, relaxed / conjugate rounds (error against 64 bits): 1M planted
 // blocks, 10 classes 10.6 / 5.5 ms (1.2e-5 / 1e-7); 300K, 29 classes 7.6 / 3.2 ms (7e-7 / 1.5e-7); 100K kNN 2.70 / 1.50 ms (1.4e-5 /
 // 6e-7); 1M power law, 50 classes 95 / 40.5 ms (5e-5 / 2e-7).  Four arrays of the size of the label matrix: x in the labels themselves, v in their partner
@@ -39,9 +41,15 @@ struct __attribute__((aligned(64))) CgPart {
     unsigned int pad[3];
 };
 
-struct CgSlot {
+// pending: the iteration's step left its alpha p out of x; with its beta the next step finds that p again, as (p - z) / beta.
+struct __attribute__((aligned(64))) CgSlot {
     CgPart part[kCgLanes];
+    float alpha, beta;
+    unsigned int pending;
+    unsigned int pad[13];
 };
+// A step with a smaller beta leaves nothing out: the quotient's rounding, 2^-24 |z| / beta, would show.
+constexpr float kCgMinBeta = 5e-2f;
 
 // Iteration k: prev holds what iteration k - 1 (or k_cg_begin) left.  Nothing is done once its largest |z| is <= stop.
 struct CgRun {
@@ -188,19 +196,32 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(CgRun run, int64_t n, const 
             beta = next > 0.0 ? (float)(next / zz) : 0.f;
         }
     }
+    const bool owed = run.prev->pending != 0u, later = !owed && beta >= kCgMinBeta;
+    // x += alpha p, and what the step before left out: its alpha (p - z) / beta with p and z as they are now
+    const float owed_p = owed ? run.prev->alpha / run.prev->beta : 0.f;
+    const float from_p = alpha + owed_p, from_z = -owed_p;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        run.cur->alpha = alpha;
+        run.cur->beta = beta;
+        run.cur->pending = later ? 1u : 0u;
+    }
     CgTally t;
     const int64_t items = n * LPN, step = (int64_t)gridDim.x * kBlock;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < items; i += step) {
-        Vec<VEC> zi = load_vec<VEC>(z + i * VEC), pi = load_vec<VEC>(p + i * VEC), xi = load_vec<VEC>(x + i * VEC);
+        Vec<VEC> zi = load_vec<VEC>(z + i * VEC), pi = load_vec<VEC>(p + i * VEC);
         const Vec<VEC> vi = load_vec<VEC>(v + i * VEC);
         const float d = deg[i / LPN];
+        if (!later) {  // uniform in the launch
+            Vec<VEC> xi = load_vec<VEC>(x + i * VEC);
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) xi.v[k] = fmaf(from_p, pi.v[k], fmaf(from_z, zi.v[k], xi.v[k]));
+            store_vec<VEC>(x + i * VEC, xi);
+        }
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
-            xi.v[k] = fmaf(alpha, pi.v[k], xi.v[k]);
             zi.v[k] = fmaf(-alpha, vi.v[k], zi.v[k]);
             pi.v[k] = fmaf(beta, pi.v[k], zi.v[k]);
         }
-        store_vec<VEC>(x + i * VEC, xi);
         store_vec<VEC>(z + i * VEC, zi);
         store_vec<VEC>(p + i * VEC, pi);
         cg_tally<CP>(t, zi, pi, d, run.tol);
@@ -208,12 +229,15 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(CgRun run, int64_t n, const 
     cg_add_tally(run.cur, t);
 }
 
-// The rows are distributions again (columns below 0 or above 1 by rounding, or by more where the iteration was cut), and the
+// What the last step (its slot: last) left out of x is added.  The rows are distributions again (columns below 0 or above 1 by rounding, or by more where the iteration was cut), and the
 // partner buffer holds the same rows.  Rows that no round updates stay as they are.
 template <int CP>
-__global__ void __launch_bounds__(kBlock) k_cg_end(int64_t n, int Cs, const float* __restrict__ deg,
-                                                  const int32_t* __restrict__ seed_class, float* __restrict__ x,
+__global__ void __launch_bounds__(kBlock) k_cg_end(const CgSlot* __restrict__ last, int64_t n, int Cs, const float* __restrict__ deg,
+                                                  const int32_t* __restrict__ seed_class, const float* __restrict__ z,
+                                                  const float* __restrict__ p, float* __restrict__ x,
                                                   float* __restrict__ partner) {
+    const bool owed = last->pending != 0u;
+    const float factor = owed ? last->alpha / last->beta : 0.f;
     constexpr int VEC = CgShape<CP>::VEC, LPN = CgShape<CP>::LPN;
     const int64_t items = n * LPN, step = (int64_t)gridDim.x * kBlock;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < items; i += step) {
@@ -222,6 +246,11 @@ __global__ void __launch_bounds__(kBlock) k_cg_end(int64_t n, int Cs, const floa
         Vec<VEC> f = load_vec<VEC>(x + i * VEC);
         if (seed_class[u] < 0 && deg[u] > 0.f) {  // the same for the lanes of a row
             float s = 0.f;
+            if (owed) {
+                const Vec<VEC> pi = load_vec<VEC>(p + i * VEC), zi = load_vec<VEC>(z + i * VEC);
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) f.v[k] = fmaf(factor, pi.v[k] - zi.v[k], f.v[k]);
+            }
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {
                 f.v[k] = fminf(fmaxf(f.v[k], 0.f), 1.f);
