@@ -1820,7 +1820,13 @@ bool conjugate_arrays(dynlp_ctx* c, const Frontier& universe, float** z, float**
         c->cg_ring = static_cast<CgSlot*>(dev_try_alloc(c, sizeof(CgSlot) * kCgRing));
         if (!c->cg_ring) return false;
     }
-    if (!c->h_cg) HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_cg), sizeof(CgSlot) * kChain, hipHostMallocDefault));
+    if (!c->h_cg) {
+        if (hipHostMalloc(reinterpret_cast<void**>(&c->h_cg), sizeof(CgSlot) * kChain, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->h_cg = nullptr;
+            return false;
+        }
+    }
     if (c->CP == 1) {  // one float per vertex: the two arrays of row lists that are idle meanwhile
         float* idle[2];
         int k = 0;

@@ -18,12 +18,13 @@
 // keeps the recurrence from drifting.  An iteration is then two launches:
 //   product   k_pk_product, k_pb_product or k_row_product: v, and the sums (p, v) and (v, v)
 //   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|.  The step is
-//             bound by its seven streams; x, which nothing reads in between, is updated in every second step only, by the
+//             bound by its streams (seven with x's); x, which nothing reads in between, is updated in every second step only, by the
 //             sum of two (1M rows of 16 floats 94 -> 68 us per step, of 64 floats 371 -> 297).
 // and needs no other wait.  Measured, whole calls at tol = 1e-6, relaxed / conjugate rounds (error against 64 bits): 1M planted
 // blocks, 10 classes 10.6 / 5.5 ms (1.2e-5 / 1e-7); 300K, 29 classes 7.6 / 3.2 ms (7e-7 / 1.5e-7); 100K kNN 2.70 / 1.50 ms (1.4e-5 /
-// 6e-7); 1M power law, 50 classes 95 / 40.5 ms (5e-5 / 2e-7).  Four arrays of the size of the label matrix: x in the labels themselves, v in their partner
-// buffer, z and p allocated by the first call that runs conjugate rounds and kept.
+// 6e-7); 1M power law, 50 classes 95 / 40.5 ms (5e-5 / 2e-7); since then, with the rest of the batch, 4.4, 2.6, 1.31 and 36 ms.
+// Four arrays of the size of the label matrix: x in the labels themselves, v in their partner buffer, z and p allocated by the
+// first call that runs conjugate rounds and kept.
 #pragma once
 
 #include "dynlp_device.h"
@@ -229,8 +230,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(CgRun run, int64_t n, const 
     cg_add_tally(run.cur, t);
 }
 
-// What the last step (its slot: last) left out of x is added.  The rows are distributions again (columns below 0 or above 1 by rounding, or by more where the iteration was cut), and the
-// partner buffer holds the same rows.  Rows that no round updates stay as they are.
+// What the last step (its slot: last) left out of x is added.  The rows are distributions again (columns below 0 or above 1 by
+// rounding, or by more where the iteration was cut), and the partner buffer holds the same rows.  Rows that no round updates stay
+// as they are.
 template <int CP>
 __global__ void __launch_bounds__(kBlock) k_cg_end(const CgSlot* __restrict__ last, int64_t n, int Cs, const float* __restrict__ deg,
                                                   const int32_t* __restrict__ seed_class, const float* __restrict__ z,
