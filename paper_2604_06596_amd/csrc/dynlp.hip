@@ -3005,7 +3005,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 hipLaunchKernelGGL(sort_finish, dim3(std::min<unsigned int>(grid_for(most_touched * lanes), 2 * most_blocks)), dim3(kBlock), 0,
                                    c->stream, c->touched, c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc,
                                    c->deg, c->flag, gate);
-                hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::min<int64_t>(most_touched, 512)), dim3(kSortThreads), 0,
+                // (a context without vertices has none to touch, whatever edges it is given: they are refused)
+                hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::max<int64_t>(1, std::min<int64_t>(most_touched, 512))), dim3(kSortThreads), 0,
                                    c->stream, long_list, hub_list, c->meta, c->pool, c->add_cnt, c->bc, c->deg, c->flag);
             }
             HIPCHK(c, hipEventRecord(c->phase_ev[1], c->stream));

@@ -151,3 +151,18 @@ def test_rows_of_a_batch_that_touches_many(n, per_row, hub):
     with P.DynLP(n, rp, col, w, 2, sv, sc) as fresh:
         deg2 = fresh.export_graph()[3]
     assert np.array_equal(deg, deg2)
+
+
+def test_edges_for_a_context_without_vertices_are_refused():
+    """No vertex can be touched, so no launch may take its size from their number; the context is as good as before."""
+    cu = lambda a, t: torch.as_tensor(np.asarray(a, t), device="cuda")
+    none = (cu([], np.int32), cu([], np.int32))
+    edge = (cu([0], np.int32), cu([1], np.int32), cu([0.5], np.float32))
+    with P.DynLP(0, cu([0], np.int64), cu([0], np.int32), cu([1], np.float32), 2, *none, device_ptrs=True) as d:
+        for seeds in ((None, None), (cu([0], np.int32), cu([1], np.int32))):
+            with pytest.raises(P.DynLPError) as ei:
+                d.apply_batch(0, *edge, *seeds)
+            assert ei.value.status == -1 and d.num_vertices == 0 and d.num_entries == 0
+        st, _ = d.apply_batch(2, *edge, cu([0], np.int32), cu([1], np.int32))
+        assert st == 0
+        assert d.get_labels()[1].cpu().tolist() == [1, 1]
