@@ -1804,7 +1804,8 @@ DenseRounds accelerate(dynlp_ctx* c, const Frontier& universe, int G, float tol,
 // below kCgMinBudget keep them: that many rounds are more than the iteration needs on the graphs it was measured on.
 constexpr int kCgMinBudget = 64;
 // The iteration ends when no row would move by more than kCgStop * tol (in the recurrence's own residual), or when the largest
-// move has not reached a new low (by 10%) in kCgPatience iterations; relaxed rounds then go on.
+// move has not reached a new low (by 10%) in kCgPatience iterations, or when its coefficients are no numbers; relaxed rounds then
+// go on.
 constexpr float kCgStop = 0.5f;
 constexpr int kCgPatience = 96;
 
@@ -1996,6 +1997,10 @@ DenseRounds conjugate(dynlp_ctx* c, const Frontier& universe, int G, float tol, 
         }
         int executed = 0;
         for (int i = 0; i < r && more; ++i) {
+            if (c->h_cg[i].broken) {  // not a round
+                out.settled = more = false;
+                break;
+            }
             unsigned int zmax = 0, moved = 0;
             for (const CgPart& part : c->h_cg[i].part) {
                 zmax = std::max(zmax, part.zmax);

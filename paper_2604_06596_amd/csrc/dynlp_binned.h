@@ -677,7 +677,7 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_product(CgRun run, int6
     }
     __syncthreads();
     const float unit = 1.f / units;
-    float pv = 0.f, vv = 0.f;
+    double pv = 0.0, vv = 0.0;
     constexpr int UF = 4;
     for (int d0 = 0; d0 < size; d0 += UF * T) {
         int l[UF];
@@ -696,8 +696,8 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_product(CgRun run, int6
             const int d = d0 + q * T + (int)threadIdx.x;
             const float r = own[q] - (float)acc[d] * unit;
             v[first + d] = r;
-            pv += dg[q] * own[q] * r;
-            vv += dg[q] * r * r;
+            pv += (double)dg[q] * (double)(own[q] * r);
+            vv += (double)dg[q] * (double)(r * r);
         }
     }
     cg_add_product<T>(run, pv, vv);

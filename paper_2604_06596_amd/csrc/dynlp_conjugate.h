@@ -15,7 +15,9 @@
 // that a row's columns keep the sum they have.  The step needs (p, v), (v, v) and (z, z), weighted by D: the product kernel
 // leaves the first two and the step before it the third, so that the second coefficient, (z', z') / (z, z), is known before
 // z' is: (z', z') = alpha^2 (v, v) - (z, z) by conjugacy (Meurant 1987).  alpha itself uses the (z, z) that was summed, which
-// keeps the recurrence from drifting.  An iteration is then two launches:
+// keeps the recurrence from drifting.  The sums are formed in 64 bits from the first product with a degree on: weights may be
+// as large or as small as float32 has them, and a sum of products of degrees and squares leaves its range at both ends (labels
+// lost for weights of 1e36, no step taken for 1e-28).  An iteration is then two launches:
 //   product   k_pk_product, k_pb_product or k_row_product: v, and the sums (p, v) and (v, v)
 //   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|.  The step is
 //             bound by its streams (seven with x's); x, which nothing reads in between, is updated in every second step only, by the
@@ -43,16 +45,19 @@ struct __attribute__((aligned(64))) CgPart {
 };
 
 // pending: the iteration's step left its alpha p out of x; with its beta the next step finds that p again, as (p - z) / beta.
+// broken: its coefficients are no numbers (a degree that overflowed), it changed nothing.  All words are 0 before.
 struct __attribute__((aligned(64))) CgSlot {
     CgPart part[kCgLanes];
     float alpha, beta;
     unsigned int pending;
-    unsigned int pad[13];
+    unsigned int broken;
+    unsigned int pad[12];
 };
 // A step with a smaller beta leaves nothing out: the quotient's rounding, 2^-24 |z| / beta, would show.
 constexpr float kCgMinBeta = 5e-2f;
 
-// Iteration k: prev holds what iteration k - 1 (or k_cg_begin) left.  Nothing is done once its largest |z| is <= stop.
+// Iteration k: prev holds what iteration k - 1 (or k_cg_begin) left.  Nothing is done once its largest |z| is <= stop (a NaN
+// among the residuals counts as infinitely large, see cg_add_tally).
 struct CgRun {
     const CgSlot* prev;
     CgSlot* cur;
@@ -67,7 +72,6 @@ __device__ inline float cg_prev_max(const CgSlot* s, bool of_p) {
     return wave_max(__uint_as_float(m));
 }
 
-// (written so that a NaN ends the iteration)
 __device__ inline bool cg_done(const CgRun& r) { return !(cg_prev_max(r.prev, false) > r.stop); }
 
 // Power of two by which the rows of p are multiplied for sums in fixed point: the largest |p| becomes at most 1/2.
@@ -80,9 +84,9 @@ __device__ inline float cg_scale(const CgRun& r) {
 
 // Adds the sums of a workgroup of T threads to one of the iteration's partial records.
 template <int T>
-__device__ inline void cg_add_product(const CgRun& r, float pv, float vv) {
+__device__ inline void cg_add_product(const CgRun& r, double pv, double vv) {
     __shared__ double sm[2][T / kWave];
-    const double a = wave_sum((double)pv), b = wave_sum((double)vv);
+    const double a = wave_sum(pv), b = wave_sum(vv);
     if (lane_id() == 0) {
         sm[0][threadIdx.x / kWave] = a;
         sm[1][threadIdx.x / kWave] = b;
@@ -98,7 +102,8 @@ __device__ inline void cg_add_product(const CgRun& r, float pv, float vv) {
 
 // What a row piece contributes to the records of the next iteration.
 struct CgTally {
-    float zz = 0.f, zmax = 0.f, pmax = 0.f;
+    double zz = 0.0;
+    float zmax = 0.f, pmax = 0.f;
     unsigned int moved = 0;
 };
 
@@ -117,7 +122,7 @@ __device__ inline void cg_tally(CgTally& t, const Vec<CgShape<CP>::VEC>& z, cons
         m = fmaxf(m, fabsf(z.v[k]));
         t.pmax = fmaxf(t.pmax, fabsf(p.v[k]));
     }
-    t.zz += d * s;
+    t.zz += (double)d * (double)s;
     t.zmax = fmaxf(t.zmax, m);
 #pragma unroll
     for (int q = 1; q < CgShape<CP>::LPN; q <<= 1) m = fmaxf(m, __shfl_xor(m, q, CgShape<CP>::LPN));
@@ -128,7 +133,7 @@ __device__ inline void cg_add_tally(CgSlot* slot, const CgTally& t) {
     __shared__ double sm_z[kBlock / kWave];
     __shared__ float sm_m[2][kBlock / kWave];
     __shared__ unsigned int sm_n[kBlock / kWave];
-    const double zz = wave_sum((double)t.zz);
+    const double zz = wave_sum(t.zz);
     const float zmax = wave_max(t.zmax), pmax = wave_max(t.pmax);
     const unsigned int moved = wave_sum(t.moved);
     if (lane_id() == 0) {
@@ -144,6 +149,7 @@ __device__ inline void cg_add_tally(CgSlot* slot, const CgTally& t) {
         double s = 0.0;
         for (int w = 0; w < kBlock / kWave; ++w) s += sm_z[w];
         if (s != 0.0) unsafeAtomicAdd(&part->zz, s);
+        if (!isfinite(s)) atomicMax(&part->zmax, __float_as_uint(INFINITY));  // (a NaN gets past every maximum)
     } else if (threadIdx.x < 3) {
         float m = 0.f;
         for (int w = 0; w < kBlock / kWave; ++w) m = fmaxf(m, sm_m[threadIdx.x - 1][w]);
@@ -186,6 +192,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(CgRun run, int64_t n, const 
     constexpr int VEC = CgShape<CP>::VEC, LPN = CgShape<CP>::LPN;
     if (cg_done(run)) return;
     float alpha = 0.f, beta = 0.f;
+    bool broken = false;
     {
         const int lane = lane_id();
         const bool ok = lane < kCgLanes;
@@ -196,6 +203,11 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(CgRun run, int64_t n, const 
             alpha = (float)a;
             beta = next > 0.0 ? (float)(next / zz) : 0.f;
         }
+        broken = !isfinite(pv) || !isfinite(vv) || !isfinite(zz) || !isfinite(alpha) || !isfinite(beta);
+    }
+    if (broken) {  // the same in all workgroups; the iterations queued behind this one find a largest |z| of 0 and end
+        if (blockIdx.x == 0 && threadIdx.x == 0) run.cur->broken = 1u;
+        return;
     }
     const bool owed = run.prev->pending != 0u, later = !owed && beta >= kCgMinBeta;
     // x += alpha p, and what the step before left out: its alpha (p - z) / beta with p and z as they are now
@@ -251,7 +263,10 @@ __global__ void __launch_bounds__(kBlock) k_cg_end(const CgSlot* __restrict__ la
             if (owed) {
                 const Vec<VEC> pi = load_vec<VEC>(p + i * VEC), zi = load_vec<VEC>(z + i * VEC);
 #pragma unroll
-                for (int k = 0; k < VEC; ++k) f.v[k] = fmaf(factor, pi.v[k] - zi.v[k], f.v[k]);
+                for (int k = 0; k < VEC; ++k) {
+                    const float sum = fmaf(factor, pi.v[k] - zi.v[k], f.v[k]);
+                    f.v[k] = isfinite(sum) ? sum : f.v[k];
+                }
             }
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {

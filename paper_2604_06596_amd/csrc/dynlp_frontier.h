@@ -880,7 +880,7 @@ __global__ void __launch_bounds__(kBlock) k_row_update_pull(const RoundCtr* __re
 template <int CP, int G>
 __device__ inline void row_product_short(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ front,
                                          unsigned int ns, const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
-                                         const float* __restrict__ p, float* __restrict__ v, float& pv, float& vv) {
+                                         const float* __restrict__ p, float* __restrict__ v, double& pv, double& vv) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int GPB = kBlock / G;
@@ -900,12 +900,15 @@ __device__ inline void row_product_short(unsigned int bid, unsigned int nblocks,
         const size_t at = (size_t)u * CP + gl * VEC;
         const Vec<VEC> own = load_vec<VEC>(p + at);
         Vec<VEC> r;
+        float a1 = 0.f, a2 = 0.f;
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
             r.v[k] = own.v[k] - acc.v[k] / s;
-            pv += s * own.v[k] * r.v[k];
-            vv += s * r.v[k] * r.v[k];
+            a1 += own.v[k] * r.v[k];
+            a2 += r.v[k] * r.v[k];
         }
+        pv += (double)s * (double)a1;
+        vv += (double)s * (double)a2;
         store_vec<VEC>(v + at, r);
     }
 }
@@ -913,7 +916,7 @@ __device__ inline void row_product_short(unsigned int bid, unsigned int nblocks,
 template <int CP>
 __device__ inline void row_product_long(unsigned int bid, unsigned int nblocks, const int32_t* __restrict__ back,
                                         unsigned int nl, const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
-                                        const float* __restrict__ p, float* __restrict__ v, float& pv, float& vv) {
+                                        const float* __restrict__ p, float* __restrict__ v, double& pv, double& vv) {
     constexpr int VEC = RowShape<CP>::VEC;
     constexpr int LPN = RowShape<CP>::LPN;
     constexpr int G = LPN > 16 ? LPN : 16;
@@ -953,12 +956,15 @@ __device__ inline void row_product_long(unsigned int bid, unsigned int nblocks, 
             const size_t at = (size_t)u * CP + gl * VEC;
             const Vec<VEC> own = load_vec<VEC>(p + at);
             Vec<VEC> r;
+            float a1 = 0.f, a2 = 0.f;
 #pragma unroll
             for (int k = 0; k < VEC; ++k) {
                 r.v[k] = own.v[k] - tot.v[k] / st;
-                pv += st * own.v[k] * r.v[k];
-                vv += st * r.v[k] * r.v[k];
+                a1 += own.v[k] * r.v[k];
+                a2 += r.v[k] * r.v[k];
             }
+            pv += (double)st * (double)a1;
+            vv += (double)st * (double)a2;
             store_vec<VEC>(v + at, r);
         }
         __syncthreads();
@@ -971,7 +977,7 @@ __global__ void __launch_bounds__(kBlock) k_row_product(CgRun run, unsigned int 
                                                        const RowMeta* __restrict__ meta, const Edge* __restrict__ pool,
                                                        const float* __restrict__ p, float* __restrict__ v) {
     if (cg_done(run)) return;
-    float pv = 0.f, vv = 0.f;
+    double pv = 0.0, vv = 0.0;
     if (blockIdx.x < long_blocks) row_product_long<CP>(blockIdx.x, long_blocks, back, nl, meta, pool, p, v, pv, vv);
     else row_product_short<CP, G>(blockIdx.x - long_blocks, gridDim.x - long_blocks, front, ns, meta, pool, p, v, pv, vv);
     cg_add_product<kBlock>(run, pv, vv);

@@ -776,7 +776,7 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_product(PkProduct a) {
     stream.add(pk_lds, scale);
     const int cols = a.C - chunk * VEC;
     const float unit = 1.0f / (scale * kPkUnit);
-    float pv = 0.f, vv = 0.f;
+    double pv = 0.0, vv = 0.0;
     constexpr int RPP = T / LPN;
     constexpr int UF = 4;
 #pragma unroll 1
@@ -819,8 +819,8 @@ __global__ void __launch_bounds__(kPkThreads, 4) k_pk_product(PkProduct a) {
                 a1 += own[q].v[k] * v.v[k];
                 a2 += v.v[k] * v.v[k];
             }
-            pv += d[q] * a1;
-            vv += d[q] * a2;
+            pv += (double)d[q] * (double)a1;
+            vv += (double)d[q] * (double)a2;
             store_vec<VEC>(a.v + (size_t)(base + r) * CP + chunk * VEC, v);
         }
     }

@@ -81,3 +81,57 @@ def test_scarce_labels_settle():
         soft, hard = d.get_labels()
     print("rounds", s.iterations)
     _check(soft, hard, _graph(p), Cf.stop_rule_residual(TOL), "scarce labels")
+
+
+@pytest.mark.parametrize("kind,C,kw,power", [
+    ("sbm", 10, {}, 122), ("sbm", 10, {}, -70), ("sbm", 3, {}, -119), ("sbm", 7, dict(group_lanes=16), 122), ("hub", 5, {}, -95),
+    ("hub", 20, dict(group_lanes=8), -110), ("sbm", 2, dict(binary_scalar=True, binned_rounds=8), 122),
+    ("sbm", 2, dict(binary_scalar=True, binned_rounds=8), -119), ("hub", 2, dict(binary_scalar=True), -100)])
+def test_the_scale_of_the_weights_does_not_matter(kind, C, kw, power):
+    """All weights times 2^power, with degrees that stay normal float32 numbers: every quotient is the same, so the labels are
+    and so is the number of rounds (but for the order in which the sums of an iteration are added)."""
+    p = _problem(kind, C)
+    g = _graph(p)
+    rounds = []
+    for scale in (1.0, 2.0 ** power):
+        w = p.w * np.float32(scale)
+        assert np.all(np.isfinite(w)) and w.min() >= np.finfo(np.float32).tiny
+        with P.DynLP(p.n, p.row_ptr, p.col, w, C, p.seed_vertex, p.seed_class, **kw) as d:
+            d.set_update_mode(P.UPDATE_IN_PLACE)
+            st, s = d.static_solve(TOL, 20000)
+            assert st == 0
+            rounds.append(s.iterations)
+            soft, hard = d.get_labels()
+        _check(soft, hard, g, Cf.stop_rule_residual(TOL), f"{kind} {C} {kw} {scale}")
+    print(kind, C, kw, power, "rounds", rounds)
+    assert rounds[1] < 45
+
+
+def test_a_part_with_light_weights_settles_too():
+    """Two graphs without an edge between them, the weights of one 2^-60 of the other's: what the light one adds to the sums of an
+    iteration is beneath their last bit."""
+    p = _problem("sbm", 6)
+    n, e = p.n, len(p.col)
+    w = np.concatenate([p.w, p.w * np.float32(2.0 ** -60)])
+    rp = np.concatenate([p.row_ptr, p.row_ptr[1:] + e])
+    col = np.concatenate([p.col, p.col + n]).astype(np.int32)
+    sv, sc = np.concatenate([p.seed_vertex, p.seed_vertex + n]).astype(np.int32), np.concatenate([p.seed_class, p.seed_class])
+    with P.DynLP(2 * n, rp, col, w, 6, sv, sc) as d:
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        st, s = d.static_solve(TOL, 20000)
+        assert st == 0
+        soft, hard = d.get_labels()
+    print("rounds", s.iterations)
+    for half in (slice(0, n), slice(n, 2 * n)):
+        _check(soft[half], hard[half], _graph(p), Cf.stop_rule_residual(TOL), "light and heavy")
+
+
+def test_degrees_beyond_float32_leave_numbers():
+    """Every weight is finite, the sums of most rows are not: no result is promised, but the iteration ends, and with labels."""
+    p = _problem("sbm", 4)
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w * np.float32(2.0 ** 126), 4, p.seed_vertex, p.seed_class) as d:
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        assert d.static_solve(TOL, 300)[0] in (0, 1)
+        soft, _ = d.get_labels()
+    assert np.all(np.isfinite(soft)) and soft.min() >= 0 and soft.max() <= 1
+    assert np.array_equal(soft[p.seed_vertex].argmax(1), p.seed_class) and np.all(soft[p.seed_vertex].max(1) == 1)
