@@ -7,7 +7,7 @@ frontier-restricted propagation loop to an empty frontier) followed by dynlp_get
 All inputs are resident in HBM before the timed region (device-pointer mode of the C ABI).
 
 Prints ONE JSON line: metric = inserted undirected edges per second over the timed steps, plus
-  "roofline"     algorithmic bytes of the frontier row-update kernel / its device time (HIP events
+  "roofline"     algorithmic bytes of the rounds that take most device time, by kernel / that time (HIP events
                  on the launch stream, collected inside the library), against the 8 TB/s HBM peak;
   "cpu_baseline" the CPU oracle (plain C, OpenMP over rows) timed on a bounded sample of the same
                  batch on this machine's host cores.
@@ -46,6 +46,13 @@ def algorithmic_bytes(rows: int, edges: int, C: int) -> int:
     """Per frontier row of length k: queue entry + row meta (20) + k (col, w) pairs (8k) + k gathered
     neighbour rows (4C each) + own old row and new row (8C).  Summed over rows: edges = sum of k."""
     return 8 * edges + 4 * C * (edges + 2 * rows) + 20 * rows
+
+
+def step_bytes(rows: int, C: int) -> int:
+    """What an iteration of the conjugate rounds moves besides its product (whose bytes are those of a round: the product
+    gathers rows of search directions and writes one row per row): residuals and directions read and written, the product
+    read, the labels read and written in every second iteration, and the degree."""
+    return 4 * C * 6 * rows + 4 * rows
 
 
 def compulsory_bytes(rows: int, edges: int, C: int, launches: int, vertices: int) -> int:
@@ -210,13 +217,21 @@ def residual_after(base, applied, F_last, tol, rounds_total):
                 implied_by_stop_rule=(rounds_total + len(applied)) * tol + 2e-6)
 
 
-def round_kernel(staged: int, lanes: int, shared: bool, CP: int) -> str:
-    """Name of the kernel that ran a round of the library's log (dynlp_round_info)."""
+def round_kind(r) -> tuple:
+    """What tells the kernels of a round of the library's log (dynlp_round_info) apart."""
+    return int(r.staged), int(r.group_lanes), "shared" if r.launch_rounds > 0 else "conjugate" if r.launch_rounds < 0 else "own"
+
+
+def round_kernel(staged: int, lanes: int, launch: str, CP: int) -> str:
+    """Names of the kernels that ran a round of the library's log."""
+    if launch == "conjugate":
+        product = "k_pb_scatter_product + k_pb_product" if staged == 3 else f"k_pk_product<{CP}>" if lanes == 0 else f"k_row_product<{CP}, {lanes}>"
+        return f"{product} + k_cg_step<{CP}>"
     if staged == 3:
         return "k_pb_scatter + k_pb_gather"
     if lanes == 0:
         return f"k_pk_round<{CP}>"
-    if shared:
+    if launch == "shared":
         return f"k_rounds_persistent<{CP}, {lanes}>" if staged == 4 else f"k_tail_rounds<{CP}, {lanes}>"
     if staged == 2:
         return f"k_row_update_pull<{CP}, {lanes}>"
@@ -402,7 +417,7 @@ def main():
                                       hook_steps=int(ii.hook_steps), ms=round(float(ii.ms), 3)))
             info = d.round_log_full()
             for r in info:  # per kernel instantiation: launches, rows, entries, device ms
-                b = buckets.setdefault((int(r.staged), int(r.group_lanes), r.launch_rounds > 0), [0, 0, 0, 0.0])
+                b = buckets.setdefault(round_kind(r), [0, 0, 0, 0.0])
                 b[0] += 1
                 b[1] += int(r.rows_short + r.rows_long)
                 b[2] += int(r.entries_short + r.entries_long)
@@ -457,7 +472,7 @@ def main():
             torch.cuda.synchronize()
             xs.append(dict(ms=(time.perf_counter() - t0) * 1e3, status=st, edges=b.num_edges, **s.as_dict()))
             for r in d.round_log_full():
-                q = xb.setdefault((int(r.staged), int(r.group_lanes), r.launch_rounds > 0), [0, 0, 0, 0.0])
+                q = xb.setdefault(round_kind(r), [0, 0, 0, 0.0])
                 q[0] += 1
                 q[1] += int(r.rows_short + r.rows_long)
                 q[2] += int(r.entries_short + r.entries_long)
@@ -465,10 +480,11 @@ def main():
         progress(f"{len(xs)} batches at delta = 1e-4: {[round(x['ms'], 1) for x in xs]} ms")
         CPx = next(c for c in (1, 2, 4, 8, 16, 32, 64) if c >= Cs)
         kx = {}
-        for (staged, glanes, shared), (cnt, rws, ent, ms) in xb.items():
-            name = round_kernel(staged, glanes, shared, CPx)
+        for (staged, glanes, launch), (cnt, rws, ent, ms) in xb.items():
+            name = round_kernel(staged, glanes, launch, CPx)
+            xbytes = algorithmic_bytes(rws, ent, Cs) + (step_bytes(rws, Cs) if launch == "conjugate" else 0)
             kx[name] = dict(launches=cnt, rows=rws, entries=ent, device_ms=round(ms, 3), avg_launch_us=round(ms * 1e3 / max(1, cnt), 1),
-                            algorithmic_GBs=round(algorithmic_bytes(rws, ent, Cs) / 1e6 / max(ms, 1e-9), 1))
+                            algorithmic_GBs=round(xbytes / 1e6 / max(ms, 1e-9), 1))
         delta_block = dict(tol=1e-4, batches=len(xs), ms_per_batch=[round(x["ms"], 2) for x in xs],
                            inserted_edges_per_s=sum(x["edges"] for x in xs) / max(1e-9, sum(x["ms"] for x in xs) / 1e3),
                            rounds=[x["iterations"] for x in xs], frontier_initial=[x["frontier_initial"] for x in xs],
@@ -482,15 +498,17 @@ def main():
     edges_inserted = sum(x["edges"] for x in per_step)
     rows = sum(x["rows_updated"] for x in per_step)
     trav = sum(x["edges_traversed"] for x in per_step)
-    # The roofline entry is for the kernel that takes the most device time in the timed region.
+    # The roofline entry is for the kernel that takes the most device time in the timed region (an iteration of the conjugate
+    # rounds is two or three launches, which are timed together and counted as one).
     CP = next(c for c in (1, 2, 4, 8, 16, 32, 64) if c >= Cs)
     kstats = {}
-    for (staged, glanes, shared), (cnt, rws, ent, ms) in buckets.items():
-        name = round_kernel(staged, glanes, shared, CP)
-        ab = algorithmic_bytes(rws, ent, Cs)
+    for (staged, glanes, launch), (cnt, rws, ent, ms) in buckets.items():
+        name = round_kernel(staged, glanes, launch, CP)
+        sb = step_bytes(rws, Cs) if launch == "conjugate" else 0
+        ab = algorithmic_bytes(rws, ent, Cs) + sb
         kstats[name] = dict(launches=cnt, rows=rws, entries=ent, device_ms=round(ms, 3),
                             avg_launch_us=round(ms * 1e3 / max(1, cnt), 1),
-                            algorithmic_GBs=round(ab / 1e6 / max(ms, 1e-9), 1), algorithmic_bytes=ab)
+                            algorithmic_GBs=round(ab / 1e6 / max(ms, 1e-9), 1), algorithmic_bytes=ab, step_bytes=sb)
     dom = max(kstats, key=lambda k: kstats[k]["device_ms"])
     launches = kstats[dom]["launches"]
     k_ms = kstats[dom]["device_ms"]
@@ -510,7 +528,7 @@ def main():
             if hit.group(2).endswith(dom):
                 traffic_ratio = float(hit.group(1))
                 traffic = traffic_ratio * alg_bytes / max(1, launches)
-    comp_bytes = compulsory_bytes(kstats[dom]["rows"], kstats[dom]["entries"], Cs, launches, d.num_vertices)
+    comp_bytes = compulsory_bytes(kstats[dom]["rows"], kstats[dom]["entries"], Cs, launches, d.num_vertices) + kstats[dom]["step_bytes"]
     out = {
         "metric": "dynlp_batch_update_inserted_edges_per_s",
         "value": edges_inserted / total_s,
@@ -535,7 +553,8 @@ def main():
                      # what the counters say the same launch moves on the HBM side, as a rate (context: `frac`
                      # above is the algorithmic one)
                      "stream_copy_GBs": copy_gbs, "stream_read_GBs": read_gbs, "frac_of_stream_read": achieved / read_gbs,
-                     # gathers per second: this kernel's CSR entries per second against random whole-row reads of the
+                     # gathers per second: this kernel's CSR entries per second (the vector step of a conjugate iteration
+                     # included in the time) against random whole-row reads of the
                      # same stored row size with no other traffic
                      "gather_yardstick": {"row_bytes": max(16, 4 * CP_), "table_rows": table_rows,
                                           "rows_per_s": gather_rows_per_s, "GBs": gather_gbs},
@@ -554,7 +573,7 @@ def main():
                    "ms_iterate": [round(x["ms_iterate"], 3) for x in per_step],
                    "ms_update_kernel": [round(x["ms_update_kernel"], 3) for x in per_step],
                    "status": [x["status"] for x in per_step],
-                   "row_update_kernels": {k: {kk: vv for kk, vv in v.items() if kk != "algorithmic_bytes"}
+                   "row_update_kernels": {k: {kk: vv for kk, vv in v.items() if kk not in ("algorithmic_bytes", "step_bytes")}
                                           for k, v in kstats.items()},
                    "row_update_all_kernels_algorithmic_GBs": round(all_bytes / 1e6 / max(all_ms, 1e-9), 1),
                    "round_profile_first_step": round_profile,

@@ -358,11 +358,17 @@ typedef struct dynlp_round_info {
     int64_t entries_short; /* CSR entries those rows hold */
     int64_t entries_long;
     int64_t rows_moved;    /* rows with max_c |F'_u - F_u| > tol */
-    float max_delta;       /* max_u max_c |F'_u - F_u| */
-    float ms_update;       /* device time of the round's row-update launch (0 unless time_kernels) */
+    float max_delta;       /* max_u max_c |F'_u - F_u| (both: see launch_rounds) */
+    float ms_update;       /* device time of the round's row-update launch or launches (0 unless time_kernels) */
     float launch_rounds;   /* 0: the round had launches of its own; else one launch ran this many rounds, this one among
                               them (staged 4, and staged 1 where V_aff is small enough for one workgroup; ms_update is
-                              then that launch's time divided by its rounds) */
+                              then that launch's time divided by its rounds); negative: an iteration of the conjugate
+                              rounds (see dynlp_set_update_mode), two launches or, with staged 3, three: the product of the
+                              graph with the search directions, then a pass over the vectors.  Rows and entries are the
+                              product's, staged and group_lanes tell its kernel as they do for a round over the same
+                              rows, ms_update is the time of all its launches, and rows_moved and max_delta are those of
+                              the iteration's residual: what an ordinary round on the labels it leaves would move, as the
+                              iteration's recurrence has it */
     int32_t staged;        /* 1: the round marked the next V_aff in per-vertex flags from inside the update
                               kernel (synchronous mode: rows staged by position and committed after the
                               kernel); 0: rows written by vertex and the next V_aff pulled from a bitmap of

@@ -2010,6 +2010,7 @@ DenseRounds conjugate(dynlp_ctx* c, const Frontier& universe, int G, float tol, 
             dynlp_round_info ri = full;
             std::memcpy(&ri.max_delta, &zmax, sizeof(float));
             ri.rows_moved = moved;
+            ri.launch_rounds = -1.f;
             c->log.push_back(ri);
             if (ri.max_delta < 0.9f * best) {
                 best = ri.max_delta;

@@ -135,3 +135,25 @@ def test_degrees_beyond_float32_leave_numbers():
         soft, _ = d.get_labels()
     assert np.all(np.isfinite(soft)) and soft.min() >= 0 and soft.max() <= 1
     assert np.array_equal(soft[p.seed_vertex].argmax(1), p.seed_class) and np.all(soft[p.seed_vertex].max(1) == 1)
+
+
+@pytest.mark.parametrize("C,kw,how", [(10, {}, (2, True)), (7, dict(group_lanes=16), (2, False)),
+                                      (2, dict(binary_scalar=True, binned_rounds=8), (3, False))])
+def test_the_round_log_tells_iterations_from_rounds(C, kw, how):
+    """An ordinary round, the iterations, an ordinary round: only those in between are marked as iterations; the last one's
+    residual is beneath the threshold by the recurrence, and by the round that follows within what float32 labels allow."""
+    p = _problem("sbm", C)
+    with _make(p, time_kernels=True, **kw) as d:
+        st, s = d.static_solve(TOL, 20000)
+        assert st == 0
+        log = d.round_log_full()
+    marked = [r.launch_rounds < 0 for r in log]
+    last = max(i for i, m in enumerate(marked) if m)
+    assert marked == [False] + [True] * last + [False] * (len(log) - 1 - last)
+    assert all((r.staged, r.group_lanes == 0) == how for r in log[:last + 2])
+    assert all(r.ms_update > 0 for r in log)
+    assert len({(r.rows_short, r.rows_long, r.entries_short, r.entries_long) for r in log[:last + 1]}) == 1
+    assert log[last].max_delta <= 0.5 * TOL < log[last - 1].max_delta and log[last].rows_moved == 0
+    # the labels differ from what the iteration holds in 64 bits by a rounding per iteration, and a mean by its own
+    assert log[last + 1].max_delta <= 0.5 * TOL + (len(log) + 2) * 2.0 ** -24
+    assert sum(r.ms_update for r in log) <= s.ms_update_kernel * (1 + 1e-5)  # (which has the launches that found the end reached)
