@@ -164,7 +164,9 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  *       every vertex are steps of a conjugate-gradient iteration for the same fixed point: up to ten times fewer rounds
  *       (a round counts as one: one product of the graph with the label matrix).  Where max_iter leaves fewer than 64
  *       rounds, or there is no memory for two more label matrices, all rows are relaxed instead (new = omega * weighted
- *       mean + (1 - omega) * row of the round before).  Rows stay distributions.
+ *       mean + (1 - omega) * row of the round before).  Rows stay distributions.  A call that max_iter cuts amid the
+ *       iteration returns the labels it has reached: nearer to the fixed point as a whole than as many relaxed rounds
+ *       leave them, but dynlp_stats.final_max_delta may be larger than after the rounds before.
  *       An ordinary round over all rows always follows (at max_iter too), decides V_aff and starts the rounds described
  *       above, so that the stop rule is the same.
  * Applies to dynlp_static_solve and dynlp_apply_batch calls that follow.

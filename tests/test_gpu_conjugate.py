@@ -1,8 +1,12 @@
 """GPU tests of the conjugate rounds of the in-place mode: every kernel that forms their product (packed, row by row, binned)
 at the column counts where its layout changes, hub rows among them, against the exact labels; where there is no memory for
-their arrays, and where the round cap leaves them too little room, the relaxed rounds run as before."""
+their arrays, and where the round cap leaves them too little room, the relaxed rounds run as before; iterations that the round
+cap cuts or that make no progress, on 2D grids, where they are slow."""
+import functools
+
 import numpy as np
 import pytest
+import scipy.sparse as sp
 
 import workloads as W
 from oracle import reference as R
@@ -157,3 +161,100 @@ def test_the_round_log_tells_iterations_from_rounds(C, kw, how):
     # the labels differ from what the iteration holds in 64 bits by a rounding per iteration, and a mean by its own
     assert log[last + 1].max_delta <= 0.5 * TOL + (len(log) + 2) * 2.0 ** -24
     assert sum(r.ms_update for r in log) <= s.ms_update_kernel * (1 + 1e-5)  # (which has the launches that found the end reached)
+
+
+SIDE, GRID_CLASSES = 200, 3
+
+
+@functools.lru_cache(maxsize=None)
+def _grid(labelled):
+    """A weighted 2D grid of 200 x 200 vertices, `labelled` of them labelled: CSR, labels, degrees."""
+    rng = np.random.default_rng(labelled)
+    i = np.arange(SIDE * SIDE).reshape(SIDE, SIDE)
+    eu, ev = np.concatenate([i[:, :-1].ravel(), i[:-1].ravel()]), np.concatenate([i[:, 1:].ravel(), i[1:].ravel()])
+    rp, col, w = W.edges_to_csr(i.size, eu, ev, rng.uniform(0.1, 1, eu.size).astype(np.float32))
+    sv = rng.permutation(i.size)[:labelled].astype(np.int32)
+    sc = (np.arange(labelled) % GRID_CLASSES).astype(np.int32)
+    return rp, col, w, sv, sc
+
+
+@functools.lru_cache(maxsize=None)
+def _iterates(labelled, C, most):
+    """{rounds: labels} of a call cut after so many rounds, up to `most`, and the fixed point: the definition in 64 bits.  An ordinary round
+    gives the first residual, conjugate iterations, rows made distributions, an ordinary round."""
+    rp, col, w, sv, sc = _grid(labelled)
+    n = len(rp) - 1
+    A = sp.csr_matrix((w.astype(np.float64), col, rp), shape=(n, n))
+    deg = np.asarray(A.sum(1)).ravel()
+    P = (sp.diags(1.0 / deg) @ A).tocsr()
+    free = np.ones((n, 1), bool)
+    free[sv] = False
+    x = np.full((n, C), 1.0 / C)
+    x[sv] = 0.0
+    x[sv, sc % C] = 1.0
+    d = np.where(free, deg[:, None], 0.0)
+    z = np.where(free, P @ x, x) - x
+    p, zz, out = z.copy(), float((d * z * z).sum()), {}
+    for rounds in range(3, 5000):
+        v = np.where(free, p - P @ p, 0.0)
+        alpha = zz / float((d * p * v).sum())
+        x = x + alpha * p
+        z = z - alpha * v
+        new = float((d * z * z).sum())
+        p, zz = z + new / zz * p, new
+        if rounds <= most:
+            y = np.clip(x, 0.0, 1.0)
+            y = np.where(free, y / y.sum(1, keepdims=True), y)
+            out[rounds] = np.where(free, P @ y, y)
+        if np.abs(z).max() < 1e-13:
+            break
+    return out, x
+
+
+def _solve_grid(labelled, C, cap, **kw):
+    rp, col, w, sv, sc = _grid(labelled)
+    with P.DynLP(len(rp) - 1, rp, col, w, C, sv, sc % C, **kw) as d:
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        st, s = d.static_solve(TOL, cap)
+        log = d.round_log_full()
+        assert s.iterations == len(log) and s.edges_traversed == sum(r.entries_short + r.entries_long for r in log)
+        soft, hard = d.get_labels()
+    assert soft.min() >= 0 and soft.max() <= 1 and np.max(np.abs(soft.sum(1) - 1)) < 2e-5
+    assert np.array_equal(hard[sv], sc % C)
+    return st, s, log, soft
+
+
+@pytest.mark.parametrize("C,kw", [(3, {}), (3, dict(group_lanes=16)), (2, dict(binary_scalar=True, binned_rounds=8))])
+@pytest.mark.parametrize("labelled", [400, 40])
+def test_a_round_cap_amid_the_iteration(labelled, C, kw):
+    """Caps next to each other end where a step still owes its share to the labels and where it does not.  The labels are those of as many
+    iterations in 64 bits: a model of them in float32 is 2e-6 away, the kernels up to 1.1e-5, a step more or less 3e-3 and more.  As
+    a whole they are nearer to the fixed point than the relaxed rounds of a smaller cap leave them."""
+    iterates, exact = _iterates(labelled, C, 67)
+    far = lambda f: float(np.linalg.norm(f - exact) / np.linalg.norm(exact))
+    st, s, log, soft = _solve_grid(labelled, C, 63, **kw)
+    assert st == 1 and s.iterations == 63 and not any(r.launch_rounds < 0 for r in log)
+    relaxed = far(soft)
+    for cap in (64, 65, 66, 67):
+        st, s, log, soft = _solve_grid(labelled, C, cap, **kw)
+        assert st == 1 and s.converged == 0 and s.iterations == cap
+        assert [r.launch_rounds < 0 for r in log] == [False] + [True] * (cap - 2) + [False]
+        off, step = np.max(np.abs(soft - iterates[cap])), np.max(np.abs(iterates[cap] - iterates[cap - 1]))
+        print(labelled, C, kw, cap, f"off {off:.1e}, a step {step:.1e}, from the fixed point {far(soft):.1e}, relaxed {relaxed:.1e}")
+        assert off < 5e-5 < 0.05 * step
+        assert far(soft) < relaxed
+
+
+def test_iterations_without_progress_give_way_to_relaxed_rounds():
+    """Four labelled vertices: the largest residual stays where it is for more than 96 iterations while the labels are on
+    their way; relaxed rounds go on from there, to the round cap."""
+    _, exact = _iterates(4, 3, 3)
+    far = lambda f: float(np.linalg.norm(f - exact) / np.linalg.norm(exact))
+    off = {cap: far(_solve_grid(4, 3, cap)[3]) for cap in (63, 200)}
+    st, s, log, soft = _solve_grid(4, 3, 900)
+    marked = [r.launch_rounds < 0 for r in log]
+    k = sum(marked)
+    print("iterations", k, "of", s.iterations, "distances", off, far(soft))
+    assert st == 1 and s.iterations == 900 and 96 < k < 800
+    assert marked == [False] + [True] * k + [False] * (len(log) - k - 1)
+    assert far(soft) < off[200] < off[63]
