@@ -1483,12 +1483,12 @@ void launch_packed_round(dynlp_ctx* c, const PullRoundArgs& a, int round) {
 }
 
 // Resolve the per-round events into the round log; returns the summed device time of all
-// row-update launches.
+// row-update launches.  (After a wait for the stream: that counters have arrived does not mean that events have.)
 float collect_kernel_ms(dynlp_ctx* c) {
     float total = 0.f;
     for (size_t k = 0; 2 * k + 1 < c->events_used; ++k) {
         float a = 0.f;
-        (void)hipEventElapsedTime(&a, c->events[c->ev_first[k]], c->events[c->ev_last[k]]);
+        HIPCHK(c, hipEventElapsedTime(&a, c->events[c->ev_first[k]], c->events[c->ev_last[k]]));
         total += a;
         const int first = c->ev_round[k];
         if (first < 0) continue;
@@ -2846,6 +2846,8 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             c->F = buf[it & 1];
             c->F2 = buf[(it + 1) & 1];
         }
+        // (the counters of the last sweep have arrived; the copy that ends the rounds over all rows and the events may not have)
+        if (relaxed || c->time_kernels) HIPCHK(c, hipStreamSynchronize(c->stream));
         const float kernel_ms_total = c->time_kernels ? collect_kernel_ms(c) : 0.f;
         if (stats) {
             stats->iterations = it;

@@ -258,3 +258,16 @@ def test_iterations_without_progress_give_way_to_relaxed_rounds():
     assert st == 1 and s.iterations == 900 and 96 < k < 800
     assert marked == [False] + [True] * k + [False] * (len(log) - k - 1)
     assert far(soft) < off[200] < off[63]
+
+
+@pytest.mark.parametrize("mode", [P.UPDATE_SYNCHRONOUS, P.UPDATE_IN_PLACE])
+def test_every_sweep_of_a_static_solve_is_timed(mode):
+    """The events of the last sweeps are read after the stream is done, not when their counters have arrived."""
+    p = _problem("sbm", 4)
+    for _ in range(20):
+        with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, time_kernels=True) as d:
+            d.set_update_mode(mode)
+            _, s = d.static_solve(TOL, 200)
+            log = d.round_log_full()
+        assert len(log) == s.iterations and all(r.ms_update > 0 for r in log)
+        assert s.ms_update_kernel >= sum(r.ms_update for r in log) * (1 - 1e-5)
