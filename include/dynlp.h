@@ -167,6 +167,11 @@ dynlp_status dynlp_set_params(dynlp_ctx* ctx, float tol, int32_t max_iter);
  *       mean + (1 - omega) * row of the round before).  Rows stay distributions.  A call that max_iter cuts amid the
  *       iteration returns the labels it has reached: nearer to the fixed point as a whole than as many relaxed rounds
  *       leave them, but dynlp_stats.final_max_delta may be larger than after the rounds before.
+ *       The two label matrices (n * the stored columns floats each; 1, 2, 4, 8, 16, 32 or 64 columns are stored; none with
+ *       binary_scalar) are allocated by the first call that runs such steps, which triples a context's label memory, and
+ *       kept.  They are given back after four solves or batches in a row that have no use for them (mode, tol, max_iter), by
+ *       dynlp_compact_storage, where an allocation of this context that it cannot do without fails, and with the context.
+ *       Nothing takes them from a context for the sake of another context or of the caller's own allocations.
  *       An ordinary round over all rows always follows (at max_iter too), decides V_aff and starts the rounds described
  *       above, so that the stop rule is the same.
  * Applies to dynlp_static_solve and dynlp_apply_batch calls that follow.
@@ -327,7 +332,8 @@ dynlp_status dynlp_export_graph(dynlp_ctx* ctx, int64_t* row_ptr, int32_t* col, 
  * entries of 8 bytes; either pointer may be NULL; host memory).  dynlp_compact_storage lays all rows
  * out again in id order, each with fresh slack, in a new pool of the size that needs (plus a quarter
  * for growth) and releases the old one; graph, labels and every later result are unchanged.  It needs
- * room for both pools at once.
+ * room for both pools at once.  The two label matrices of the conjugate steps are given back as well
+ * (see dynlp_set_update_mode).
  */
 dynlp_status dynlp_storage_info(const dynlp_ctx* ctx, int64_t* pool_used, int64_t* pool_capacity);
 dynlp_status dynlp_compact_storage(dynlp_ctx* ctx);

@@ -215,6 +215,7 @@ struct dynlp_ctx {
     // conjugate rounds (dynlp_conjugate.h)
     float *cg_z = nullptr, *cg_p = nullptr;
     int64_t cg_cap = 0;             // floats in each
+    int cg_idle = 0;                // calls in a row that had no use for them
     CgSlot* cg_ring = nullptr;      // kCgRing slots
     CgSlot* h_cg = nullptr;         // pinned, kChain slots
     // label initialisation of inserted vertices (dynlp_components.h)
@@ -1820,12 +1821,25 @@ constexpr int kCgMinBudget = 64;
 // go on.
 constexpr float kCgStop = 0.5f;
 constexpr int kCgPatience = 96;
+// Solves and batches in a row that cannot run them (mode, threshold, round cap) after which their arrays are given back: not the
+// first, since a program may alternate between two thresholds or modes, and to allocate and release is slow.
+constexpr int kCgIdleCalls = 4;
 
 void free_conjugate(dynlp_ctx* c) {
     dev_free(c, c->cg_z);
     dev_free(c, c->cg_p);
     c->cg_z = c->cg_p = nullptr;
     c->cg_cap = 0;
+    c->cg_idle = 0;
+}
+
+// At the beginning of a solve or batch, when the stream is done with the call before.
+void conjugate_idle(dynlp_ctx* c) {
+    if (!c->cg_z) return;
+    const bool usable = c->update_mode == DYNLP_UPDATE_IN_PLACE && c->tol >= kRelaxMinTol && c->tol <= kRelaxMaxTol &&
+                        c->max_iter >= kCgMinBudget;
+    c->cg_idle = usable ? 0 : c->cg_idle + 1;
+    if (c->cg_idle >= kCgIdleCalls) free_conjugate(c);
 }
 
 bool conjugate_arrays(dynlp_ctx* c, const Frontier& universe, float** z, float** p) {
@@ -2600,6 +2614,8 @@ dynlp_status dynlp_compact_storage(dynlp_ctx* c) {
         HIPCHK(c, hipSetDevice(c->device));
         const int64_t n = c->n;
         const int64_t nb = grid_for(n);
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        free_conjugate(c);
         // the new layout is built beside the old one; the context switches over only when all of it exists, so
         // running out of memory here leaves graph and labels as they were
         Temp<RowMeta> meta_new(c, c->n_cap);
@@ -2737,6 +2753,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
     const auto t0 = Clock::now();
     try {
         HIPCHK(c, hipSetDevice(c->device));
+        conjugate_idle(c);
         c->log.clear();
         reset_timed_spans(c);
         const bool in_place = c->update_mode == DYNLP_UPDATE_IN_PLACE;
@@ -2911,6 +2928,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
     bool mutated = false;
     try {
         HIPCHK(c, hipSetDevice(c->device));
+        conjugate_idle(c);
         c->log.clear();
         reset_timed_spans(c);
         // ---- capacity for new vertices; their rows start empty, unlabelled, uniform ----

@@ -271,3 +271,39 @@ def test_every_sweep_of_a_static_solve_is_timed(mode):
             log = d.round_log_full()
         assert len(log) == s.iterations and all(r.ms_update > 0 for r in log)
         assert s.ms_update_kernel >= sum(r.ms_update for r in log) * (1 - 1e-5)
+
+
+def test_their_arrays_are_given_back():
+    """After four calls in a row that cannot use them, not before, and by compact_storage; the next call that wants them gets
+    them again."""
+    p = _problem("sbm", 10)
+    a = TorchAllocator()
+    with _make(p, allocator=a) as d:
+        size = (d.num_vertices + max(1024, p.n // 8)) * 16 * 4
+        held = lambda: sum(t.numel() == size for t in a.live.values())
+        plain = held()
+        first = d.static_solve(TOL, 20000)[1].iterations
+        assert held() == plain + 2
+        rule_out = [lambda: d.set_update_mode(P.UPDATE_SYNCHRONOUS), lambda: d.set_params(1e-4, 20000), lambda: d.set_params(TOL, 40)]
+        for change in rule_out:
+            d.set_update_mode(P.UPDATE_IN_PLACE)
+            assert d.static_solve(TOL, 20000)[1].iterations <= first and held() == plain + 2
+            change()
+            for call in range(1, 5):
+                assert held() == plain + 2
+                d.apply_batch(0, np.array([call], np.int32), np.array([call + 100], np.int32), np.array([1e-3], np.float32))
+                if call == 2:  # one call in between that can use them
+                    d.set_update_mode(P.UPDATE_IN_PLACE)
+                    d.static_solve(TOL, 20000)
+                    change()
+            for call in range(2):
+                assert held() == plain + 2
+                d.apply_batch(0, np.array([call + 9], np.int32), np.array([call + 900], np.int32), np.array([1e-3], np.float32))
+            assert held() == plain
+        d.set_update_mode(P.UPDATE_IN_PLACE)
+        assert d.static_solve(TOL, 20000)[0] == 0 and held() == plain + 2
+        d.compact_storage()
+        assert held() == plain
+        assert d.static_solve(TOL, 20000)[0] == 0
+        soft, _ = d.get_labels()
+    assert not a.live and np.max(np.abs(soft.sum(1) - 1)) < 2e-5
