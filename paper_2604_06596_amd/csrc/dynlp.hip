@@ -2425,8 +2425,8 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         }
         HIPCHK(c, hipGetLastError());
         read_bc(c);
-        if (c->h_bc->err_code) {
-            c->err = format_validation(c->h_bc->err_code, c->h_bc->err_index);
+        if (c->h_bc->err) {
+            c->err = format_validation(error_code(*c->h_bc), error_index(*c->h_bc));
             throw Fail{DYNLP_ERR_INVALID_ARG};
         }
 
@@ -2446,7 +2446,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->pool_cap = 0;
         grow_pool(c, tail + extra);
         c->h_bc->pool_tail = (unsigned long long)tail;
-        c->h_bc->err_code = 0;
+        c->h_bc->err = 0;
         write_bc(c);
         if (nnz > 0) {
             hipLaunchKernelGGL(k_scatter_entries, dim3(grid_for(nnz)), dim3(kBlock), 0, c->stream, nnz, n, d_rp.ptr,
@@ -2454,8 +2454,8 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
             HIPCHK(c, hipGetLastError());
         }
         read_bc(c);
-        if (c->h_bc->err_code) {
-            c->err = format_validation(c->h_bc->err_code, c->h_bc->err_index);
+        if (c->h_bc->err) {
+            c->err = format_validation(error_code(*c->h_bc), error_index(*c->h_bc));
             throw Fail{DYNLP_ERR_INVALID_ARG};
         }
         c->entries = nnz;
@@ -3056,17 +3056,17 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             launch_compact_start(c, frontier_of(c, 0), universe, gate);
             HIPCHK(c, hipGetLastError());
             read_start(c);
-            if (c->h_bc->err_code || (int64_t)c->h_bc->pool_tail <= c->pool_cap) break;
+            if (c->h_bc->err || (int64_t)c->h_bc->pool_tail <= c->pool_cap) break;
             // the pool is too small for the plan and nothing has been inserted yet
             const int64_t tail = (int64_t)c->h_bc->pool_tail;
             grow_pool(c, tail + (tail - c->pool_tail) / 2);
         }
-        if (c->h_bc->err_code) {
+        if (c->h_bc->err) {
             c->n = n0;
             const unsigned int nt = c->h_bc->touched;
             if (nt) hipLaunchKernelGGL(k_clear_counts, dim3(grid_for(nt)), dim3(kBlock), 0, c->stream, nt, c->touched, c->add_cnt);
             HIPCHK(c, hipStreamSynchronize(c->stream));
-            return bad(format_validation(c->h_bc->err_code, c->h_bc->err_index));
+            return bad(format_validation(error_code(*c->h_bc), error_index(*c->h_bc)));
         }
         c->entries += 2 * m - (int64_t)c->h_bc->removed;
         c->pool_tail = (int64_t)c->h_bc->pool_tail;

@@ -71,8 +71,8 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned int touched;            // rows that receive at least one new entry
     unsigned int dropping;           // rows that lose entries to deleted vertices
     unsigned int relocated;          // rows moved by the last insertion
-    int err_code;                    // 0 = none; first validation error wins
-    long long err_index;             // index of the offending item
+    unsigned int pad;
+    unsigned long long err;          // 0 = all arguments are valid so far; else what report_error made of the worst
     unsigned int init_count;         // first frontier: short rows
     unsigned int init_long;          //                 long rows
     unsigned long long scan_total;   // grand total of the last block-sum scan
@@ -111,16 +111,24 @@ enum ValidationError : int {
     kErrDeleted = 10,
 };
 
+// Of several invalid items one is reported, whichever thread finds its own first: of the kind that is checked first (rows and
+// deleted vertices, then entries and edges, then seeds) the one with the lowest index.
 __device__ inline void report_error(BatchCtr* bc, int code, long long index) {
-    if (atomicCAS(&bc->err_code, 0, code) == 0) bc->err_index = index;
+    const unsigned long long kind = code == kErrRowPtr || code == kErrDeleted ? 0
+                                    : code == kErrSeedVertex || code == kErrSeedClass || code == kErrSeedConflict || code == kErrRelabel ? 2
+                                                                                                                                     : 1;
+    atomicMax(&bc->err, ~(kind << 60 | (unsigned long long)index << 8 | (unsigned long long)code));
 }
+
+inline int error_code(const BatchCtr& bc) { return bc.err ? (int)(~bc.err & 0xff) : kErrNone; }
+inline long long error_index(const BatchCtr& bc) { return (long long)((~bc.err & 0x0fffffffffffffffull) >> 8); }
 
 // The kernels of a batch are queued without waiting for the checks of its arguments or for the plan of its relocations; those
 // that change the graph look first whether the checks have passed and the plan fits the pool.
 struct BatchGate {
     const BatchCtr* bc;
     unsigned long long pool_cap;
-    __device__ inline bool closed() const { return bc->err_code != 0 || bc->pool_tail > pool_cap; }
+    __device__ inline bool closed() const { return bc->err != 0 || bc->pool_tail > pool_cap; }
 };
 
 __device__ inline int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }

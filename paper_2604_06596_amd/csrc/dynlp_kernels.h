@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, in
                                                          int32_t* __restrict__ seed_class) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < nd) {
-        if (bc->err_code == 0) seed_class[del[i]] = kDeletedMark;
+        if (bc->err == 0) seed_class[del[i]] = kDeletedMark;
         return;
     }
     i -= nd;
@@ -352,7 +352,7 @@ __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n
     __shared__ unsigned int smem[kBlock / kWave + 1];
     if (blockIdx.x >= count_blocks) {
         const int64_t i = (int64_t)(blockIdx.x - count_blocks) * kBlock + threadIdx.x;
-        if (i < nd && bc->err_code == 0) seed_class[del[i]] = -1;
+        if (i < nd && bc->err == 0) seed_class[del[i]] = -1;
         return;
     }
     const int64_t base = (int64_t)blockIdx.x * kBlock * kAppendItems;
@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restri
                                                         int64_t* __restrict__ reloc_off, BatchCtr* bc) {
     __shared__ unsigned long long smem[kBlock / kWave + 1];
     __shared__ unsigned long long sbase;
-    if (bc->err_code) return;
+    if (bc->err) return;
     const unsigned int nt = bc->touched;
     // ITEMS rows per thread: with one, 195,000 workgroups queue for the tail when 50M rows are touched (4.6 ms, with 8 1.4);
     // with 8, a few hundred thousand rows keep too few lanes busy (400,000: 6 us with one, 14 with 8)
@@ -839,7 +839,7 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
                                                        int32_t* __restrict__ dropping, float* __restrict__ deg,
                                                        float* __restrict__ F, BatchCtr* bc) {
     constexpr int G = 16;
-    if (bc->err_code) return;
+    if (bc->err) return;
     __shared__ unsigned int smem[kBlock / kWave + 1];
     __shared__ int64_t long_off[kBlock / G];
     __shared__ int long_len[kBlock / G];

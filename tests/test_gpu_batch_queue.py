@@ -166,3 +166,30 @@ def test_edges_for_a_context_without_vertices_are_refused():
         st, _ = d.apply_batch(2, *edge, cu([0], np.int32), cu([1], np.int32))
         assert st == 0
         assert d.get_labels()[1].cpu().tolist() == [1, 1]
+
+
+@pytest.mark.parametrize("kinds,message", [
+    (("deleted", "edge", "seed"), "deleted vertex out of range (item 3)"), (("edge", "seed"), "self loop (item 5)"),
+    (("weight", "seed"), "weight must be finite and > 0 (item 11)"), (("seed",), "seed class out of range (seed 2)")])
+def test_which_of_several_invalid_arguments_is_reported(kinds, message):
+    """Found in one launch by whichever thread comes first; reported is, as when each kind had a launch of its own, a deleted
+    vertex before an edge before a seed, and of one kind the first in the list."""
+    p = W.small_random(2000, 3, 8.0, 100, 903)
+    cu = lambda a, t: torch.as_tensor(np.asarray(a, t), device="cuda")
+    m = 40000
+    dead, sv, sc = np.arange(1000), np.arange(3000) % 2000, np.zeros(3000, np.int64)
+    eu, ev, ew = np.arange(m) % 1000, 1000 + np.arange(m) % 1000, np.full(m, 0.5)
+    if "deleted" in kinds:
+        dead[3:] = -1
+    if "edge" in kinds:
+        ev[5:] = eu[5:]
+        ev[6:] = 2000
+    if "weight" in kinds:
+        ew[11:] = np.nan
+    sc[2:] = 3
+    with P.DynLP(p.n, cu(p.row_ptr, np.int64), cu(p.col, np.int32), cu(p.w, np.float32), 3, cu([], np.int32), cu([], np.int32),
+                 device_ptrs=True) as d:
+        for _ in range(5):
+            with pytest.raises(P.DynLPError) as ei:
+                d.apply_update(cu(dead, np.int32), 0, cu(eu, np.int32), cu(ev, np.int32), cu(ew, np.float32), cu(sv, np.int32), cu(sc, np.int32))
+            assert ei.value.status == -1 and ei.value.message == message
