@@ -22,7 +22,9 @@
  *   - The caller owns every buffer it passes; the library copies what it needs and keeps no
  *     caller pointer after a call returns.
  *   - Work is enqueued on dynlp_options.stream (a hipStream_t; NULL = the default stream).  Each
- *     call returns after that work has completed, so outputs are readable on return.
+ *     call returns after that work has completed, so outputs are readable on return.  A call that waits for
+ *     counters of the GPU (once per eight rounds) polls for up to 20 ms before it sleeps, offering its core to
+ *     other threads every few microseconds.
  *   - No C++ exception crosses this boundary.  A failed call leaves the context as it was
  *     before the call (arguments are validated before anything is changed), except for
  *     DYNLP_ERR_OOM / DYNLP_ERR_DEVICE, after which the context may only be destroyed.

@@ -378,6 +378,8 @@ void write_bc(dynlp_ctx* c) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
 }
 
+// How long the counters are polled for before the runtime waits for the stream.  Every 64
+// polls, about 3 us, the thread offers its core to others: programs with more contexts than cores have use for it.
 constexpr float kPollMs = 20.f;
 
 // Device records (whole multiples of 16 bytes, in up to two runs) to pinned host memory; waits for them, and with that for
@@ -392,8 +394,12 @@ void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const v
     auto arrived = [&]() { return __atomic_load_n(c->h_flag, __ATOMIC_ACQUIRE) == value; };
     const auto t0 = Clock::now();
     for (unsigned int polls = 0; !arrived(); ++polls) {
-        if (polls % 64 != 63 || ms_since(t0) < kPollMs) {
+        if (polls % 64 != 63) {
             __builtin_ia32_pause();
+            continue;
+        }
+        if (ms_since(t0) < kPollMs) {
+            std::this_thread::yield();
             continue;
         }
         // (not a chain of rounds of a graph that waits show on: let the runtime wait)
