@@ -279,6 +279,9 @@ __device__ inline unsigned int pk_spread(unsigned int L) {
 // and bucket (us, placed one by one, 8 bytes each at 512 places at a time, and now: 1,000,000 vertices of degree 20 588, 282;
 // 400,000 177, 100; 300,000 of degree 16 136, 77).  Tile t of T takes every T-th group of 16 entries, in steps of 0.618 of the
 // tile's groups, so that entries of one row that fall into one bucket do not come one after the other.
+// A part of more than 20,991 rows leaves room for a smaller tile; its threads then read no more entries than it holds (30M
+// entries among 100,000 vertices beside 31,072 without edges, tiles of 2,048: 691 us reading MOST per thread, 472 now; placed one by
+// one 828).
 // spread: a row holds so much of a part that several of its entries are added at once wherever they lie; they then go to the
 // places that pk_spread gives, each on its own (150,000 vertices, a power law whose longest row is a sixth of a part: rounds
 // of 52.0 us, 52.8 to 54.2 with runs).
@@ -396,6 +399,8 @@ __global__ void __launch_bounds__(kPkThreads) k_pk_place(int64_t n, const unsign
             bool ok[UN];
 #pragma unroll
             for (int t = 0; t < UN; ++t) {
+                ok[t] = false;
+                if ((unsigned int)(k0 + t) * T >= tile) continue;  // (a small tile: nothing for any thread)
                 const unsigned int j = (unsigned int)(k0 + t) * T + threadIdx.x;
                 const unsigned int g = (j / GRP) * 317u % (tile / GRP);
                 const unsigned int i = GRP * (q + tiles * g) + j % GRP;

@@ -252,3 +252,33 @@ def test_parts_of_unequal_numbers_of_rows(C, heavy, extra, isolated):
         soft = d.get_labels()[0]
     mean, _ = ON.itlp_sweep(rp, col, w.astype(np.float64), soft.astype(np.float64), g.seed_class)
     assert np.max(np.abs(mean - soft)) <= 2 * TOL
+
+
+@pytest.mark.parametrize("live", [112000, 106000, 99000])
+def test_parts_of_so_many_rows_that_their_entries_pass_through_smaller_tiles(live):
+    """Heavy rows fill 255 parts, the vertices without edges the last: tiles of 8,192, 4,096 and 2,048 entries."""
+    import scipy.sparse as sp
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(live)
+    n, m = 131072, live * 150
+    u = torch.randint(live, (m,), device="cuda", generator=g)
+    v = torch.randint(live, (m,), device="cuda", generator=g)
+    v = torch.where(u == v, (v + 1) % live, v)
+    w = 0.1 + 0.9 * torch.rand(m, device="cuda", generator=g)
+    src, order = torch.sort(torch.cat([u, v]), stable=True)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), torch.bincount(src, minlength=n).cumsum(0)])
+    col, ww = torch.cat([v, u])[order].int(), torch.cat([w, w])[order]
+    sv = torch.arange(1000, device="cuda", dtype=torch.int32)
+    with P.DynLP(n, rp, col, ww, 2, sv, sv % 2, device_ptrs=True, binary_scalar=True) as d:
+        d.static_solve(1e-9, 11)
+        assert [_is_packed(r) for r in d.round_log_full()] == [False] * 8 + [True] * 3
+        soft = d.get_labels()[0].cpu().numpy()
+    A = sp.csr_matrix((ww.double().cpu().numpy(), col.cpu().numpy(), rp.cpu().numpy()), shape=(n, n))
+    deg = np.asarray(A.sum(1)).ravel()
+    f = np.full(n, 0.5)
+    f[:1000] = np.arange(1000) % 2
+    for _ in range(11):
+        f[1000:live] = (A @ f)[1000:live] / deg[1000:live]
+    assert np.max(np.abs(soft[:, 1] - f)) <= ROUNDS_ATOL
