@@ -10,7 +10,7 @@ constexpr int kWave = 64;
 constexpr int kBlock = 256;       // threads per workgroup for every kernel here
 constexpr int kRowAlign = 8;      // row capacities are multiples of 8 entries = 64 bytes
 constexpr int kRing = 64;         // per-round counter slots
-constexpr int kSortRegs = 8;      // appended entries per lane the in-register segment sort can hold (16 lanes per row)
+constexpr int kSortRegs = 8;      // appended entries per lane the in-register segment sort can hold (8 or 16 lanes per row: 64 or 128)
 constexpr int kAppendItems = 8;   // items per thread in kernels that append to a list (one counter atomic per 2,048 items)
 constexpr int kInitChain = 4;     // hook/jump steps of the component search queued per host round trip
 
@@ -183,17 +183,6 @@ __device__ inline T block_exclusive_scan(T v, T* smem, T* total) {
     *total = smem[nw];
     __syncthreads();
     return res;
-}
-
-// Append-slot reservation with one atomic per wave: lanes with pred get consecutive slots.
-__device__ inline unsigned int wave_reserve(unsigned int* counter, bool pred) {
-    const unsigned long long mask = __ballot(pred);
-    const int lane = lane_id();
-    unsigned int base = 0;
-    const int leader = __ffsll((long long)mask) - 1;
-    if (pred && lane == leader) base = atomicAdd(counter, (unsigned int)__popcll(mask));
-    base = __shfl(base, leader < 0 ? 0 : leader, kWave);
-    return base + (unsigned int)__popcll(mask & ((1ull << lane) - 1ull));
 }
 
 // Append-slot reservation with one atomic per workgroup: every thread asks for `count` consecutive
