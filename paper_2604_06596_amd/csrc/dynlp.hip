@@ -3046,12 +3046,12 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 // (the mean number of half-edges per touched row, if all rows are touched: the least it can be)
                 const int lanes = in_order && most_touched >= kSortRows8 && 2 * m < kSortLanes8 * n1 ? 8 : 16;
                 auto sort_finish = lanes == 8 ? k_sort_finish<8> : k_sort_finish<16>;
+                const SortFinish f{c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->touched_cap, c->bc, c->deg, c->flag};
                 hipLaunchKernelGGL(sort_finish, dim3(std::min<unsigned int>(grid_for(most_touched * lanes), 2 * most_blocks)), dim3(kBlock), 0,
-                                   c->stream, c->touched, c->meta, c->pool, c->add_cnt, use_rank ? 1 : 0, long_list, hub_list, c->bc,
-                                   c->deg, c->flag, gate);
+                                   c->stream, c->touched, f, gate);
                 // (a context without vertices has none to touch, whatever edges it is given: they are refused)
                 hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::max<int64_t>(1, std::min<int64_t>(most_touched, 512))), dim3(kSortThreads), 0,
-                                   c->stream, long_list, hub_list, c->meta, c->pool, c->add_cnt, c->bc, c->deg, c->flag);
+                                   c->stream, f);
             }
             HIPCHK(c, hipEventRecord(c->phase_ev[1], c->stream));
             // seeds: clamp one-hot, their neighbours join V_aff; first frontier from the flags (its size goes to the start

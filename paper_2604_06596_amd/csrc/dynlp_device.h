@@ -71,7 +71,7 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned int touched;            // rows that receive at least one new entry
     unsigned int dropping;           // rows that lose entries to deleted vertices
     unsigned int relocated;          // rows moved by the last insertion
-    unsigned int pad;
+    unsigned int sort_wide;          // touched rows sorted by 16 lanes where the others are by 8
     unsigned long long err;          // 0 = all arguments are valid so far; else what report_error made of the worst
     unsigned int init_count;         // first frontier: short rows
     unsigned int init_long;          //                 long rows

@@ -556,7 +556,7 @@ __device__ inline float block_row_degree(const Edge* row, int len, float* tile) 
 // over the row, a function of the batch alone.  G lanes per touched row (16; 8 where rows receive a few entries each, whose
 // other lanes would have nothing to do: 50M rows of 5, 9.8 -> 5.5 ms; 330,000 of 1 to 20, 45 -> 30 us); segments of up to
 // G * kSortRegs entries are rank-sorted in registers (every key is broadcast to the group once),
-// longer ones are queued for k_sort_long_segments.
+// longer ones than 16 lanes hold are queued for k_sort_long_segments.
 __device__ inline unsigned long long edge_key(const Edge& e) {
     return ((unsigned long long)(unsigned int)e.col << 32) | (unsigned long long)__float_as_uint(e.w);
 }
@@ -574,125 +574,157 @@ __device__ inline Edge key_edge(unsigned long long k) {
 // len_is_old: the rows' lengths do not yet include the appended entries (k_write_halfedges with ranks); the kernel
 // then stores the new length.  Rows with long appended segments only get their length and are listed (long_list), hubs that
 // received a few entries are sorted and listed for k_sort_long_segments (hub_list), which ends Step 1 for both.
+struct SortFinish {
+    RowMeta* meta;
+    Edge* pool;
+    int32_t* add_cnt;
+    int len_is_old;
+    int32_t *long_list, *hub_list;
+    int64_t list_cap;  // entries of long_list: at least the rows that are touched
+    BatchCtr* bc;
+    float* deg;
+    uint8_t* flag;
+};
+
+// One row per group of G lanes (own: the group has one), all threads of the workgroup take part.  sorted_w: kSortRegs floats
+// per thread; a group's part stays with its wave.  True in lane 0 of a group whose segment is too long for it.
 template <int G>
-__global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restrict__ touched,
-                                                       RowMeta* __restrict__ meta, Edge* __restrict__ pool,
-                                                       int32_t* __restrict__ add_cnt, int len_is_old,
-                                                       int32_t* __restrict__ long_list,
-                                                       int32_t* __restrict__ hub_list, BatchCtr* bc,
-                                                       float* __restrict__ deg, uint8_t* __restrict__ flag, BatchGate gate) {
+__device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u, float* sorted_w) {
     constexpr int L = 16, P = L / G;  // sums: entry j goes to sum j mod L, P sums per lane
-    __shared__ float sorted_w[kBlock / G][G * kSortRegs];
-    if (gate.closed()) return;
-    const unsigned int nt = bc->touched;
-    const int grp = threadIdx.x / G;
     const int gl = threadIdx.x % G;
-    for (unsigned int t0 = blockIdx.x * (kBlock / G); t0 < nt; t0 += gridDim.x * (kBlock / G)) {  // uniform in the workgroup
-        // (a group's weights stay with its wave: nobody else reads sorted_w[grp])
-        const unsigned int t = t0 + threadIdx.x / G;
-        int32_t u = 0;
-        int a = 0, len_old = 0;
-        RowMeta m;
-        m.off = 0;
-        m.len = 0;
-        m.cap = 0;
-        bool is_long = false;
-        if (t < nt) {
-            u = touched[t];
-            a = add_cnt[u];
-            m = meta[u];
-            len_old = len_is_old ? m.len : m.len - a;
-            is_long = a > G * kSortRegs;
+    float* const sw = sorted_w + threadIdx.x / G * (G * kSortRegs);
+    int a = 0, len_old = 0;
+    RowMeta m;
+    m.off = 0;
+    m.len = 0;
+    m.cap = 0;
+    bool is_long = false;
+    if (own) {
+        a = f.add_cnt[u];
+        m = f.meta[u];
+        len_old = f.len_is_old ? m.len : m.len - a;
+        is_long = a > G * kSortRegs;
+    }
+    Edge* seg = f.pool + m.off + len_old;
+    if (own && !is_long) {
+        const int slots = (a + G - 1) / G;  // uniform in the group
+        unsigned long long key[kSortRegs];
+#pragma unroll
+        for (int r = 0; r < kSortRegs; ++r) {
+            const int j = r * G + gl;
+            key[r] = (r < slots && j < a) ? edge_key(seg[j]) : ~0ull;
         }
-        const bool sorts = t < nt && !is_long;
-        Edge* seg = pool + m.off + len_old;
-        if (sorts) {
-            const int slots = (a + G - 1) / G;  // uniform in the group
-            unsigned long long key[kSortRegs];
+        int rank[kSortRegs];
 #pragma unroll
-            for (int r = 0; r < kSortRegs; ++r) {
-                const int j = r * G + gl;
-                key[r] = (r < slots && j < a) ? edge_key(seg[j]) : ~0ull;
-            }
-            int rank[kSortRegs];
+        for (int r = 0; r < kSortRegs; ++r) rank[r] = r * G + gl;
+        if (a > 1) {
 #pragma unroll
-            for (int r = 0; r < kSortRegs; ++r) rank[r] = r * G + gl;
-            if (a > 1) {
+            for (int r = 0; r < kSortRegs; ++r) rank[r] = 0;
 #pragma unroll
-                for (int r = 0; r < kSortRegs; ++r) rank[r] = 0;
+            for (int r2 = 0; r2 < kSortRegs; ++r2) {
+                if (r2 < slots) {
+                    for (int l = 0; l < G; ++l) {
+                        const unsigned int hi = __shfl((unsigned int)(key[r2] >> 32), l, G);
+                        const unsigned int lo = __shfl((unsigned int)(key[r2] & 0xffffffffull), l, G);
+                        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+                        const int oj = r2 * G + l;
 #pragma unroll
-                for (int r2 = 0; r2 < kSortRegs; ++r2) {
-                    if (r2 < slots) {
-                        for (int l = 0; l < G; ++l) {
-                            const unsigned int hi = __shfl((unsigned int)(key[r2] >> 32), l, G);
-                            const unsigned int lo = __shfl((unsigned int)(key[r2] & 0xffffffffull), l, G);
-                            const unsigned long long other = ((unsigned long long)hi << 32) | lo;
-                            const int oj = r2 * G + l;
-#pragma unroll
-                            for (int r = 0; r < kSortRegs; ++r) {
-                                const int j = r * G + gl;
-                                rank[r] += (other < key[r] || (other == key[r] && oj < j)) ? 1 : 0;
-                            }
+                        for (int r = 0; r < kSortRegs; ++r) {
+                            const int j = r * G + gl;
+                            rank[r] += (other < key[r] || (other == key[r] && oj < j)) ? 1 : 0;
                         }
                     }
                 }
             }
+        }
 #pragma unroll
-            for (int r = 0; r < kSortRegs; ++r) {
-                const int j = r * G + gl;
-                if (r < slots && j < a) {
-                    const Edge e = key_edge(key[r]);
-                    if (a > 1) seg[rank[r]] = e;
-                    sorted_w[grp][rank[r]] = e.w;
-                }
+        for (int r = 0; r < kSortRegs; ++r) {
+            const int j = r * G + gl;
+            if (r < slots && j < a) {
+                const Edge e = key_edge(key[r]);
+                if (a > 1) seg[rank[r]] = e;
+                sw[rank[r]] = e.w;
             }
         }
-        __syncthreads();
-        if (t >= nt) continue;
-        if (is_long) {
-            if (gl == 0) {
-                if (len_is_old) meta[u].len = len_old + a;
-                long_list[atomicAdd(&bc->sort_long, 1u)] = u;
-            }
-            continue;
-        }
-        const int len_new = len_old + a;
-        if (len_new > kHubRow) {
-            if (gl == 0) {
-                if (len_is_old) meta[u].len = len_new;
-                hub_list[atomicAdd(&bc->finish_hubs, 1u)] = u;
-            }
-            continue;
-        }
-        float sum[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) sum[p] = 0.f;
-        constexpr int UN = 4;  // rounds of L entries whose loads are in flight, added in order
-        for (int j0 = gl; j0 < len_new; j0 += UN * L) {
-            float wv[UN][P];
-#pragma unroll
-            for (int q = 0; q < UN; ++q)
-#pragma unroll
-                for (int p = 0; p < P; ++p) {
-                    const int j = j0 + q * L + p * G;
-                    wv[q][p] = j < len_old ? pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
-                }
-#pragma unroll
-            for (int q = 0; q < UN; ++q)
-#pragma unroll
-                for (int p = 0; p < P; ++p)
-                    if (j0 + q * L + p * G < len_new) sum[p] += wv[q][p];
-        }
-        // the sums by halves: l and l + 8, l and l + 4, ...
-        float s = sum[0];
-        if constexpr (P == 2) s += sum[1];
-#pragma unroll
-        for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
+    }
+    __syncthreads();
+    if (!own) return false;
+    if (is_long) return gl == 0;
+    const int len_new = len_old + a;
+    if (len_new > kHubRow) {
         if (gl == 0) {
-            if (len_is_old) meta[u].len = len_new;
-            deg[u] = s;
-            add_cnt[u] = 0;
-            if (flag) flag[u] = 1;
+            if (f.len_is_old) f.meta[u].len = len_new;
+            f.hub_list[atomicAdd(&f.bc->finish_hubs, 1u)] = u;
+        }
+        return false;
+    }
+    float sum[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) sum[p] = 0.f;
+    constexpr int UN = 4;  // rounds of L entries whose loads are in flight, added in order
+    for (int j0 = gl; j0 < len_new; j0 += UN * L) {
+        float wv[UN][P];
+#pragma unroll
+        for (int q = 0; q < UN; ++q)
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const int j = j0 + q * L + p * G;
+                wv[q][p] = j < len_old ? f.pool[m.off + j].w : (j < len_new ? sw[j - len_old] : 0.f);
+            }
+#pragma unroll
+        for (int q = 0; q < UN; ++q)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (j0 + q * L + p * G < len_new) sum[p] += wv[q][p];
+    }
+    // the sums by halves: l and l + 8, l and l + 4, ...
+    float s = sum[0];
+    if constexpr (P == 2) s += sum[1];
+#pragma unroll
+    for (int d = G / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, G);
+    if (gl == 0) {
+        if (f.len_is_old) f.meta[u].len = len_new;
+        f.deg[u] = s;
+        f.add_cnt[u] = 0;
+        if (f.flag) f.flag[u] = 1;
+    }
+    return false;
+}
+
+// With 8 lanes per row, rows of 65 to 128 appended entries are listed for 16 lanes of k_sort_long_segments (from the end of
+// long_list, with one atomic per workgroup and step), not for whole workgroups: a power law has many of them (1M vertices of
+// mean degree 38, 10,000 / 50,000 / 100,000 of them replaced; k_sort_finish + k_sort_long_segments, us: 16 lanes 84 + 369 /
+// 211 + 664 / 316 + 960, 8 lanes and workgroups 70 + 381 / 149 + 773 / 210 + 1196, 8 and 16 lanes 72 + 374 / 158 + 677 / 211 + 1061;
+// 200,000 of mean degree 30, 10,000 replaced: 47 + 76, 38 + 99, 38 + 80; 16 lanes in a second pass of this kernel take its registers
+// up: 90 + 380 / 213 + 717 / 314 + 907, 53 + 80, and planted blocks, 100,000 of 1M replaced, 119 -> 135).
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restrict__ touched, SortFinish f, BatchGate gate) {
+    __shared__ float sorted_w[kBlock * kSortRegs];
+    __shared__ int32_t wide[kBlock / G];
+    __shared__ unsigned int nwide, base;
+    if (gate.closed()) return;
+    const unsigned int nt = f.bc->touched;
+    for (unsigned int t0 = blockIdx.x * (kBlock / G); t0 < nt; t0 += gridDim.x * (kBlock / G)) {  // uniform in the workgroup
+        if (G < 16 && threadIdx.x == 0) nwide = 0u;
+        const unsigned int t = t0 + threadIdx.x / G;
+        const int32_t u = t < nt ? touched[t] : 0;
+        if (sort_finish_row<G>(f, t < nt, u, sorted_w)) {
+            const int a = f.add_cnt[u];
+            if (G < 16 && a <= 16 * kSortRegs && f.meta[u].len + (f.len_is_old ? a : 0) <= kHubRow) {
+                wide[atomicAdd(&nwide, 1u)] = u;
+            } else {
+                if (f.len_is_old) f.meta[u].len += a;
+                f.long_list[atomicAdd(&f.bc->sort_long, 1u)] = u;
+            }
+        }
+        if constexpr (G < 16) {
+            __syncthreads();
+            const unsigned int n = nwide;  // (if it is not 0, it is set to 0 only after the barrier below)
+            if (n) {
+                if (threadIdx.x == 0) base = atomicAdd(&f.bc->sort_wide, n);
+                __syncthreads();
+                if (threadIdx.x < n) f.long_list[f.list_cap - 1 - (int64_t)(base + threadIdx.x)] = wide[threadIdx.x];
+            }
         }
     }
 }
@@ -726,33 +758,29 @@ __device__ inline void sort_tile_steps(unsigned long long* keys, unsigned int le
     }
 }
 
-__global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(const int32_t* __restrict__ long_list,
-                                                                    const int32_t* __restrict__ hub_list,
-                                                                    const RowMeta* __restrict__ meta, Edge* pool,
-                                                                    int32_t* __restrict__ add_cnt,
-                                                                    const BatchCtr* bc, float* __restrict__ deg,
-                                                                    uint8_t* __restrict__ flag) {
+__global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(SortFinish f) {
     __shared__ unsigned long long keys[kSortTile];
     constexpr unsigned int T = kSortTile;
-    const unsigned int count = bc->sort_long, hubs = bc->finish_hubs;
+    const unsigned int count = f.bc->sort_long, hubs = f.bc->finish_hubs, wide = f.bc->sort_wide;
+    Edge* const pool = f.pool;
     // ... and then, as k_sort_finish does for the others: d(u) from the stored row, the counting scratch cleared, the row
     // put into V_aff
     auto finish = [&](int32_t u, const RowMeta& m) {
         const float d = block_row_degree<kSortThreads>(pool + m.off, m.len, reinterpret_cast<float*>(keys));
         if (threadIdx.x == 0) {
-            deg[u] = d;
-            add_cnt[u] = 0;
-            if (flag) flag[u] = 1;
+            f.deg[u] = d;
+            f.add_cnt[u] = 0;
+            if (f.flag) f.flag[u] = 1;
         }
     };
     for (unsigned int q = blockIdx.x; q < count + hubs; q += gridDim.x) {  // uniform per workgroup
-        const int32_t u = q < count ? long_list[q] : hub_list[q - count];
-        const RowMeta m = meta[u];
+        const int32_t u = q < count ? f.long_list[q] : f.hub_list[q - count];
+        const RowMeta m = f.meta[u];
         if (q >= count) {
             finish(u, m);
             continue;
         }
-        const unsigned int a = (unsigned int)add_cnt[u];
+        const unsigned int a = (unsigned int)f.add_cnt[u];
         Edge* seg = pool + m.off + (m.len - (int)a);
         unsigned int P = 2;
         while (P < a) P <<= 1;
@@ -809,6 +837,14 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(const int32
             }
         }
         finish(u, m);
+    }
+    __syncthreads();
+    // rows for 16 lanes, from the workgroups that have no long row on
+    constexpr unsigned int ROWS = kSortThreads / 16;
+    static_assert(kSortThreads * kSortRegs * sizeof(float) <= sizeof keys, "the weights of the rows");
+    for (unsigned int i0 = (gridDim.x - 1 - blockIdx.x) * ROWS; i0 < wide; i0 += gridDim.x * ROWS) {  // uniform in the workgroup
+        const unsigned int i = i0 + threadIdx.x / 16;
+        (void)sort_finish_row<16>(f, i < wide, i < wide ? f.long_list[f.list_cap - 1 - (int64_t)i] : 0, reinterpret_cast<float*>(keys));
     }
 }
 

@@ -193,3 +193,40 @@ def test_which_of_several_invalid_arguments_is_reported(kinds, message):
             with pytest.raises(P.DynLPError) as ei:
                 d.apply_update(cu(dead, np.int32), 0, cu(eu, np.int32), cu(ev, np.int32), cu(ew, np.float32), cu(sv, np.int32), cu(sc, np.int32))
             assert ei.value.status == -1 and ei.value.message == message
+
+
+@pytest.mark.parametrize("slack", [1.01, 3.0])
+def test_rows_that_receive_more_than_eight_lanes_hold(slack):
+    """A batch that touches more than 131,072 rows, 1,500 of which (runs of neighbours, so that many meet in one workgroup) receive 60
+    to 140 entries and a few of those already hold 1,100: sorted by 8 lanes, by 16 and by workgroups, each row alike."""
+    rng = np.random.default_rng(4)
+    n, far = 150000, 3000
+    heavy = np.arange(500, 2000)
+    count = rng.integers(60, 141, heavy.size)
+    hub = heavy[::50]
+    b0 = np.concatenate([np.repeat(hub, 1100), np.arange(n - 1)[::3]])
+    b1 = np.concatenate([far + (np.arange(1100 * hub.size) * 7) % (n - far), np.arange(n - 1)[::3] + 1])
+    rp0, col0, w0 = W.edges_to_csr(n, b0, b1, rng.uniform(0.1, 1, b0.size).astype(np.float32))
+    light = rng.integers(far, n, (2, 140000))
+    eu = np.concatenate([np.repeat(heavy, count), light[0]])
+    ev = np.concatenate([rng.integers(far, n, int(count.sum())), np.where(light[0] == light[1], far + (light[1] + 1 - far) % (n - far), light[1])])
+    order = rng.permutation(eu.size)
+    eu, ev = eu[order].astype(np.int32), ev[order].astype(np.int32)
+    ew = rng.uniform(0.1, 1, eu.size).astype(np.float32)
+    sv, sc = np.arange(5, dtype=np.int32), np.array([0, 1, 0, 1, 0], np.int32)
+    with P.DynLP(n, rp0, col0, w0, 2, sv, sc, slack_factor=slack) as d:
+        d.set_params(1e-3, 1)
+        assert d.apply_batch(0, eu, ev, ew)[0] in (0, 1)
+        rp, col, w, deg, _ = d.export_graph()
+    src, dst, ww = np.concatenate([eu, ev]), np.concatenate([ev, eu]), np.concatenate([ew, ew])
+    order = np.lexsort((ww.view(np.uint32), dst, src))
+    counts, old = np.bincount(src, minlength=n), np.diff(rp0)
+    assert 2 * eu.size < 8 * n and np.count_nonzero(counts) > 131072, "the case is meant to be sorted with 8 lanes"
+    assert np.array_equal(np.diff(rp), old + counts)
+    start = np.concatenate([[0], np.cumsum(counts)])[:-1]
+    at = np.repeat(rp[:-1] + old - start, counts) + np.arange(src.size)
+    assert np.array_equal(col[at], dst[order]) and np.array_equal(w[at], ww[order])
+    before = np.repeat(rp[:-1] - rp0[:-1], old) + np.arange(col0.size)
+    assert np.array_equal(col[before], col0) and np.array_equal(w[before], w0)
+    with P.DynLP(n, rp, col, w, 2, sv, sc) as fresh:
+        assert np.array_equal(deg, fresh.export_graph()[3])
