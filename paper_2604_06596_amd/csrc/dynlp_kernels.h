@@ -586,13 +586,14 @@ struct SortFinish {
     uint8_t* flag;
 };
 
-// One row per group of G lanes (own: the group has one), all threads of the workgroup take part.  sorted_w: kSortRegs floats
-// per thread; a group's part stays with its wave.  True in lane 0 of a group whose segment is too long for it.
+// One row per group of G lanes (own: the group has one, at *row), all threads of the workgroup take part.  sorted_w: a group's
+// part stays with its wave.
 template <int G>
-__device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u, float* sorted_w) {
+__device__ inline void sort_finish_row(const SortFinish& f, bool own, const int32_t* __restrict__ row, float (*sorted_w)[G * kSortRegs]) {
     constexpr int L = 16, P = L / G;  // sums: entry j goes to sum j mod L, P sums per lane
     const int gl = threadIdx.x % G;
-    float* const sw = sorted_w + threadIdx.x / G * (G * kSortRegs);
+    const int grp = threadIdx.x / G;
+    int32_t u = 0;
     int a = 0, len_old = 0;
     RowMeta m;
     m.off = 0;
@@ -600,6 +601,7 @@ __device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u,
     m.cap = 0;
     bool is_long = false;
     if (own) {
+        u = *row;
         a = f.add_cnt[u];
         m = f.meta[u];
         len_old = f.len_is_old ? m.len : m.len - a;
@@ -643,20 +645,30 @@ __device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u,
             if (r < slots && j < a) {
                 const Edge e = key_edge(key[r]);
                 if (a > 1) seg[rank[r]] = e;
-                sw[rank[r]] = e.w;
+                sorted_w[grp][rank[r]] = e.w;
             }
         }
     }
     __syncthreads();
-    if (!own) return false;
-    if (is_long) return gl == 0;
+    if (!own) return;
     const int len_new = len_old + a;
+    if (is_long) {
+        if (gl == 0) {
+            if (G < 16 && a <= 16 * kSortRegs && len_new <= kHubRow) {
+                f.long_list[f.list_cap - 1 - (int64_t)atomicAdd(&f.bc->sort_wide, 1u)] = u;
+            } else {
+                if (f.len_is_old) f.meta[u].len = len_new;
+                f.long_list[atomicAdd(&f.bc->sort_long, 1u)] = u;
+            }
+        }
+        return;
+    }
     if (len_new > kHubRow) {
         if (gl == 0) {
             if (f.len_is_old) f.meta[u].len = len_new;
             f.hub_list[atomicAdd(&f.bc->finish_hubs, 1u)] = u;
         }
-        return false;
+        return;
     }
     float sum[P];
 #pragma unroll
@@ -669,7 +681,7 @@ __device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u,
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 const int j = j0 + q * L + p * G;
-                wv[q][p] = j < len_old ? f.pool[m.off + j].w : (j < len_new ? sw[j - len_old] : 0.f);
+                wv[q][p] = j < len_old ? f.pool[m.off + j].w : (j < len_new ? sorted_w[grp][j - len_old] : 0.f);
             }
 #pragma unroll
         for (int q = 0; q < UN; ++q)
@@ -688,44 +700,22 @@ __device__ inline bool sort_finish_row(const SortFinish& f, bool own, int32_t u,
         f.add_cnt[u] = 0;
         if (f.flag) f.flag[u] = 1;
     }
-    return false;
 }
 
 // With 8 lanes per row, rows of 65 to 128 appended entries are listed for 16 lanes of k_sort_long_segments (from the end of
-// long_list, with one atomic per workgroup and step), not for whole workgroups: a power law has many of them (1M vertices of
-// mean degree 38, 10,000 / 50,000 / 100,000 of them replaced; k_sort_finish + k_sort_long_segments, us: 16 lanes 84 + 369 /
-// 211 + 664 / 316 + 960, 8 lanes and workgroups 70 + 381 / 149 + 773 / 210 + 1196, 8 and 16 lanes 72 + 374 / 158 + 677 / 211 + 1061;
-// 200,000 of mean degree 30, 10,000 replaced: 47 + 76, 38 + 99, 38 + 80; 16 lanes in a second pass of this kernel take its registers
-// up: 90 + 380 / 213 + 717 / 314 + 907, 53 + 80, and planted blocks, 100,000 of 1M replaced, 119 -> 135).
+// long_list), not for whole workgroups: a power law has many of them (1M vertices of mean degree 38, 10,000 / 50,000 / 100,000
+// of them replaced; k_sort_finish + k_sort_long_segments, us: all with 16 lanes 84 + 369 / 211 + 664 / 316 + 960, 8 lanes and
+// workgroups 69 + 402 / 147 + 777 / 209 + 1183, 8 and 16 lanes 66 + 372 / 146 + 697 / 197 + 1007; 200,000 of mean degree 30, 10,000
+// replaced: 47 + 76, 37 + 97, 36 + 88).  16 lanes in a second pass of this kernel take its registers up (planted blocks, 100,000
+// of 1M replaced, 116 -> 135).
 template <int G>
 __global__ void __launch_bounds__(kBlock) k_sort_finish(const int32_t* __restrict__ touched, SortFinish f, BatchGate gate) {
-    __shared__ float sorted_w[kBlock * kSortRegs];
-    __shared__ int32_t wide[kBlock / G];
-    __shared__ unsigned int nwide, base;
+    __shared__ float sorted_w[kBlock / G][G * kSortRegs];
     if (gate.closed()) return;
     const unsigned int nt = f.bc->touched;
     for (unsigned int t0 = blockIdx.x * (kBlock / G); t0 < nt; t0 += gridDim.x * (kBlock / G)) {  // uniform in the workgroup
-        if (G < 16 && threadIdx.x == 0) nwide = 0u;
         const unsigned int t = t0 + threadIdx.x / G;
-        const int32_t u = t < nt ? touched[t] : 0;
-        if (sort_finish_row<G>(f, t < nt, u, sorted_w)) {
-            const int a = f.add_cnt[u];
-            if (G < 16 && a <= 16 * kSortRegs && f.meta[u].len + (f.len_is_old ? a : 0) <= kHubRow) {
-                wide[atomicAdd(&nwide, 1u)] = u;
-            } else {
-                if (f.len_is_old) f.meta[u].len += a;
-                f.long_list[atomicAdd(&f.bc->sort_long, 1u)] = u;
-            }
-        }
-        if constexpr (G < 16) {
-            __syncthreads();
-            const unsigned int n = nwide;  // (if it is not 0, it is set to 0 only after the barrier below)
-            if (n) {
-                if (threadIdx.x == 0) base = atomicAdd(&f.bc->sort_wide, n);
-                __syncthreads();
-                if (threadIdx.x < n) f.long_list[f.list_cap - 1 - (int64_t)(base + threadIdx.x)] = wide[threadIdx.x];
-            }
-        }
+        sort_finish_row<G>(f, t < nt, touched + t, sorted_w);
     }
 }
 
@@ -844,7 +834,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_long_segments(SortFinish 
     static_assert(kSortThreads * kSortRegs * sizeof(float) <= sizeof keys, "the weights of the rows");
     for (unsigned int i0 = (gridDim.x - 1 - blockIdx.x) * ROWS; i0 < wide; i0 += gridDim.x * ROWS) {  // uniform in the workgroup
         const unsigned int i = i0 + threadIdx.x / 16;
-        (void)sort_finish_row<16>(f, i < wide, i < wide ? f.long_list[f.list_cap - 1 - (int64_t)i] : 0, reinterpret_cast<float*>(keys));
+        sort_finish_row<16>(f, i < wide, f.long_list + f.list_cap - 1 - (int64_t)i, reinterpret_cast<float(*)[16 * kSortRegs]>(keys));
     }
 }
 
