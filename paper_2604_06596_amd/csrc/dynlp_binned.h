@@ -677,29 +677,39 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_product(CgRun run, int6
     }
     __syncthreads();
     const float unit = 1.f / units;
-    double pv = 0.0, vv = 0.0;
-    constexpr int UF = 4;
-    for (int d0 = 0; d0 < size; d0 += UF * T) {
-        int l[UF];
-        float own[UF], dg[UF];
+    // The sums of a thread in float32 (in 64 bits from the first product on the kernel takes 767 instead of 725 us for 49.5M rows), and once
+    // more in 64 bits where they have left its range.
+    auto sums = [&](auto zero, bool store, double& pv_out, double& vv_out) {
+        using S = decltype(zero);
+        S pv = 0, vv = 0;
+        constexpr int UF = 4;
+        for (int d0 = 0; d0 < size; d0 += UF * T) {
+            int l[UF];
+            float own[UF], dg[UF];
 #pragma unroll
-        for (int q = 0; q < UF; ++q) {
-            const int d = d0 + q * T + (int)threadIdx.x;
-            const bool ok = d < size && first + d < n;
-            l[q] = ok ? len[first + d] : 0;
-            own[q] = ok ? p[first + d] : 0.f;
-            dg[q] = ok ? deg[first + d] : 0.f;
-        }
+            for (int q = 0; q < UF; ++q) {
+                const int d = d0 + q * T + (int)threadIdx.x;
+                const bool ok = d < size && first + d < n;
+                l[q] = ok ? len[first + d] : 0;
+                own[q] = ok ? p[first + d] : 0.f;
+                dg[q] = ok ? deg[first + d] : 0.f;
+            }
 #pragma unroll
-        for (int q = 0; q < UF; ++q) {
-            if (l[q] == 0) continue;
-            const int d = d0 + q * T + (int)threadIdx.x;
-            const float r = own[q] - (float)acc[d] * unit;
-            v[first + d] = r;
-            pv += (double)dg[q] * (double)(own[q] * r);
-            vv += (double)dg[q] * (double)(r * r);
+            for (int q = 0; q < UF; ++q) {
+                if (l[q] == 0) continue;
+                const int d = d0 + q * T + (int)threadIdx.x;
+                const float r = own[q] - (float)acc[d] * unit;
+                if (store) v[first + d] = r;
+                pv += (S)dg[q] * (S)own[q] * (S)r;
+                vv += (S)dg[q] * (S)r * (S)r;
+            }
         }
-    }
+        pv_out = (double)pv;
+        vv_out = (double)vv;
+    };
+    double pv, vv;
+    sums(0.f, true, pv, vv);
+    if (!(fabs(pv) < (double)INFINITY) || !(vv > 1e-28 && vv < (double)INFINITY)) sums(0.0, false, pv, vv);
     cg_add_product<T>(run, pv, vv);
 }
 

@@ -17,7 +17,8 @@
 // z' is: (z', z') = alpha^2 (v, v) - (z, z) by conjugacy (Meurant 1987).  alpha itself uses the (z, z) that was summed, which
 // keeps the recurrence from drifting.  The sums are formed in 64 bits from the first product with a degree on: weights may be
 // as large or as small as float32 has them, and a sum of products of degrees and squares leaves its range at both ends (labels
-// lost for weights of 1e36, no step taken for 1e-28).  An iteration is then two launches:
+// lost for weights of 1e36, no step taken for 1e-28; k_pb_product does so where a thread's sums in float32 show it).  An
+// iteration is then two launches:
 //   product   k_pk_product, k_pb_product or k_row_product: v, and the sums (p, v) and (v, v)
 //   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|.  The step is
 //             bound by its streams (seven with x's); x, which nothing reads in between, is updated in every second step only, by the
