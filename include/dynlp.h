@@ -23,8 +23,8 @@
  *     caller pointer after a call returns.
  *   - Work is enqueued on dynlp_options.stream (a hipStream_t; NULL = the default stream).  Each
  *     call returns after that work has completed, so outputs are readable on return.  A call that waits for
- *     counters of the GPU (once per eight rounds) polls for up to 20 ms before it sleeps, offering its core to
- *     other threads every few microseconds.
+ *     counters of the GPU (once per eight rounds) polls for up to 20 ms before it sleeps, from 0.2 ms on
+ *     offering its core to other threads every few microseconds.
  *   - No C++ exception crosses this boundary.  A failed call leaves the context as it was
  *     before the call (arguments are validated before anything is changed), except for
  *     DYNLP_ERR_OOM / DYNLP_ERR_DEVICE, after which the context may only be destroyed.

@@ -378,9 +378,10 @@ void write_bc(dynlp_ctx* c) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
 }
 
-// How long the counters are polled for before the runtime waits for the stream.  Every 64
-// polls, about 3 us, the thread offers its core to others: programs with more contexts than cores have use for it.
-constexpr float kPollMs = 20.f;
+// How long the counters are polled for before the runtime waits for the stream.  After kPollAloneMs (more than a chain of
+// short rounds takes, so that the few microseconds between looks do not show) the thread offers its core to others every 64 polls:
+// programs with more contexts than cores have use for it.
+constexpr float kPollMs = 20.f, kPollAloneMs = 0.2f;
 
 // Device records (whole multiples of 16 bytes, in up to two runs) to pinned host memory; waits for them, and with that for
 // everything the stream holds.
@@ -398,8 +399,9 @@ void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const v
             __builtin_ia32_pause();
             continue;
         }
-        if (ms_since(t0) < kPollMs) {
-            std::this_thread::yield();
+        const float waited = ms_since(t0);
+        if (waited < kPollMs) {
+            if (waited > kPollAloneMs) std::this_thread::yield();
             continue;
         }
         // (not a chain of rounds of a graph that waits show on: let the runtime wait)
