@@ -2805,9 +2805,10 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             last = done.last;
             converged = last <= tol;
             for (const dynlp_round_info& ri : c->log) edges += ri.entries_short + ri.entries_long;
-            // the sweeps that follow find the size of their row list in the last slot
-            HIPCHK(c, hipMemcpyAsync(&slot_of(c, it - 1)->next_count, &start->next_count, 2 * sizeof(unsigned int),
-                                     hipMemcpyDeviceToDevice, c->stream));
+            // sweeps that follow find the size of their row list in the last slot
+            if (!converged && it < max_iter)
+                HIPCHK(c, hipMemcpyAsync(&slot_of(c, it - 1)->next_count, &start->next_count, 2 * sizeof(unsigned int),
+                                         hipMemcpyDeviceToDevice, c->stream));
         }
         bool pb_fresh = true;  // the slots of the binned rounds do not yet hold the current labels
         // synchronous: sweep t reads buf[t & 1], writes buf[(t + 1) & 1]; in place: every sweep reads and writes F
@@ -2871,8 +2872,9 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             c->F = buf[it & 1];
             c->F2 = buf[(it + 1) & 1];
         }
-        // (the counters of the last sweep have arrived; the copy that ends the rounds over all rows and the events may not have)
-        if (relaxed || c->time_kernels) HIPCHK(c, hipStreamSynchronize(c->stream));
+        // (the counters of the last sweep have arrived, with everything before them, but the events may not have; no wait without
+        // them, it costs the release of a context 1 to 2 ms now and then)
+        if (c->time_kernels) HIPCHK(c, hipStreamSynchronize(c->stream));
         const float kernel_ms_total = c->time_kernels ? collect_kernel_ms(c) : 0.f;
         if (stats) {
             stats->iterations = it;
