@@ -15,10 +15,10 @@
 // that a row's columns keep the sum they have.  The step needs (p, v), (v, v) and (z, z), weighted by D: the product kernel
 // leaves the first two and the step before it the third, so that the second coefficient, (z', z') / (z, z), is known before
 // z' is: (z', z') = alpha^2 (v, v) - (z, z) by conjugacy (Meurant 1987).  alpha itself uses the (z, z) that was summed, which
-// keeps the recurrence from drifting.  The sums are formed in 64 bits from the first product with a degree on: weights may be
-// as large or as small as float32 has them, and a sum of products of degrees and squares leaves its range at both ends (labels
-// lost for weights of 1e36, no step taken for 1e-28; k_pb_product does so where a thread's sums in float32 show it).  An
-// iteration is then two launches:
+// keeps the recurrence from drifting.  Weights may be as large or as small as float32 has them, and a sum of products of
+// degrees and squares leaves its range at both ends (labels lost for weights of 1e36, no step taken for 1e-28): such products
+// are formed and added in 64 bits (in k_cg_step and k_pb_product where float32 has no room for them; 64 bits throughout: 36.1 ->
+// 37.2 us for 300,000 rows of 32 floats, 725 -> 767 us for 49.5M binned rows).  An iteration is then two launches:
 //   product   k_pk_product, k_pb_product or k_row_product: v, and the sums (p, v) and (v, v)
 //   step      k_cg_step: x += alpha p, z -= alpha v, p = z + beta p, and the sum (z, z), the largest |z| and |p|.  The step is
 //             bound by its streams (seven with x's); x, which nothing reads in between, is updated in every second step only, by the
@@ -104,6 +104,7 @@ __device__ inline void cg_add_product(const CgRun& r, double pv, double vv) {
 // What a row piece contributes to the records of the next iteration.
 struct CgTally {
     double zz = 0.0;
+    float zz_near = 0.f;  // what float32 has room for
     float zmax = 0.f, pmax = 0.f;
     unsigned int moved = 0;
 };
@@ -123,7 +124,9 @@ __device__ inline void cg_tally(CgTally& t, const Vec<CgShape<CP>::VEC>& z, cons
         m = fmaxf(m, fabsf(z.v[k]));
         t.pmax = fmaxf(t.pmax, fabsf(p.v[k]));
     }
-    t.zz += (double)d * (double)s;
+    const float x = d * s;
+    if (x > 1e-30f && x < 1e30f) t.zz_near += x;
+    else if (s != 0.f) t.zz += (double)d * (double)s;
     t.zmax = fmaxf(t.zmax, m);
 #pragma unroll
     for (int q = 1; q < CgShape<CP>::LPN; q <<= 1) m = fmaxf(m, __shfl_xor(m, q, CgShape<CP>::LPN));
@@ -134,7 +137,7 @@ __device__ inline void cg_add_tally(CgSlot* slot, const CgTally& t) {
     __shared__ double sm_z[kBlock / kWave];
     __shared__ float sm_m[2][kBlock / kWave];
     __shared__ unsigned int sm_n[kBlock / kWave];
-    const double zz = wave_sum(t.zz);
+    const double zz = wave_sum(t.zz + (double)t.zz_near);
     const float zmax = wave_max(t.zmax), pmax = wave_max(t.pmax);
     const unsigned int moved = wave_sum(t.moved);
     if (lane_id() == 0) {
