@@ -371,8 +371,11 @@ typedef struct dynlp_round_info {
     float max_delta;       /* max_u max_c |F'_u - F_u| (both: see launch_rounds) */
     float ms_update;       /* device time of the round's row-update launch or launches (0 unless time_kernels) */
     float launch_rounds;   /* 0: the round had launches of its own; else one launch ran this many rounds, this one among
-                              them (staged 4, and staged 1 where V_aff is small enough for one workgroup; ms_update is
-                              then that launch's time divided by its rounds); negative: an iteration of the conjugate
+                              them (staged 4, and where V_aff was small enough for one workgroup when the launch began;
+                              ms_update is then that launch's time divided by its rounds).  Rounds of graphs of some ten
+                              thousand vertices share launches on the CUs of one XCD whatever V_aff is: where it was larger,
+                              they are logged as the rounds they stand for (0 here; staged 1, 0 or 2), but for ms_update,
+                              which is the launch's time divided by its rounds.  Negative: an iteration of the conjugate
                               rounds (see dynlp_set_update_mode), two launches or, with staged 3, three: the product of the
                               graph with the search directions, then a pass over the vectors.  Rows and entries are the
                               product's, staged and group_lanes tell its kernel as they do for a round over the same

@@ -24,6 +24,7 @@
 #include "dynlp_components.h"
 #include "dynlp_binned.h"
 #include "dynlp_packed.h"
+#include "dynlp_xcd.h"
 
 using namespace dynlp;
 
@@ -160,6 +161,11 @@ struct dynlp_ctx {
     BatchCtr* h_bc = nullptr;    // (in h_start)
     unsigned int* h_flag = nullptr;  // pinned: number of the last k_to_host that has arrived
     unsigned int h_sent = 0;         // ... that was launched
+    void* h_fixed = nullptr;         // the one pinned allocation that h_slot, h_start, h_flag and h_xcd lie in
+    // rounds of small graphs on one XCD (dynlp_xcd.h)
+    XcdCtl* xcd = nullptr;
+    XcdResult* h_xcd = nullptr;      // pinned
+    unsigned int xcd_launches = 0;   // numbers them
 
     int update_mode = DYNLP_UPDATE_SYNCHRONOUS;
     bool final_check = false;  // dynlp_set_final_check
@@ -383,13 +389,8 @@ void write_bc(dynlp_ctx* c) {
 // programs with more contexts than cores have use for it.
 constexpr float kPollMs = 20.f, kPollAloneMs = 0.2f;
 
-// Device records (whole multiples of 16 bytes, in up to two runs) to pinned host memory; waits for them, and with that for
-// everything the stream holds.
-void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const void* b = nullptr, size_t bytes_b = 0) {
-    const unsigned int value = ++c->h_sent;
-    hipLaunchKernelGGL(k_to_host, dim3(1), dim3(kBlock), 0, c->stream, static_cast<const uint4*>(a), (unsigned int)(bytes_a / 16),
-                       static_cast<const uint4*>(b), (unsigned int)(bytes_b / 16), static_cast<uint4*>(to), c->h_flag, value);
-    HIPCHK(c, hipGetLastError());
+// Waits for a kernel that ends by setting the flag (k_to_host, k_xcd_rounds), the last work of the stream.
+void wait_for_flag(dynlp_ctx* c, unsigned int value) {
     // the flag comes with the last work of the stream, so the wait ends when that does; an error of the device, after which
     // the flag may never come, shows in the state of the stream
     auto arrived = [&]() { return __atomic_load_n(c->h_flag, __ATOMIC_ACQUIRE) == value; };
@@ -412,6 +413,16 @@ void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const v
             throw Fail{DYNLP_ERR_DEVICE};
         }
     }
+}
+
+// Device records (whole multiples of 16 bytes, in up to two runs) to pinned host memory; waits for them, and with that for
+// everything the stream holds.
+void read_to_host(dynlp_ctx* c, void* to, const void* a, size_t bytes_a, const void* b = nullptr, size_t bytes_b = 0) {
+    const unsigned int value = ++c->h_sent;
+    hipLaunchKernelGGL(k_to_host, dim3(1), dim3(kBlock), 0, c->stream, static_cast<const uint4*>(a), (unsigned int)(bytes_a / 16),
+                       static_cast<const uint4*>(b), (unsigned int)(bytes_b / 16), static_cast<uint4*>(to), c->h_flag, value);
+    HIPCHK(c, hipGetLastError());
+    wait_for_flag(c, value);
 }
 
 std::string format_validation(int code, long long index) {
@@ -882,6 +893,7 @@ void launch_update_pull(dynlp_ctx* c, int G, const Frontier& universe, const Pul
 
 // Rounds queued per host round trip.
 constexpr int kChain = 8;
+static_assert(kChain <= kXcdChain, "k_xcd_rounds keeps the counters of a chain");
 // A batch of more half-edges than one per kInOrderShare vertices lists the rows it touches by a pass over all vertices.
 constexpr int64_t kInOrderShare = 8;
 // Such a batch sorts what a row receives with 8 lanes instead of 16 where it holds fewer half-edges than this per vertex and
@@ -981,6 +993,104 @@ void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vert
     }
     HIPCHK(c, hipGetLastError());
     close_timed_span(c, e1);
+}
+
+// ---- rounds of small graphs on one XCD (k_xcd_rounds) -----------------------------------------------------------
+// One XCD has an eighth of the chip's CUs, so a round over all rows costs it more than the whole chip from some size on, which
+// the launches it saves make up for.  Whole calls, ms, ordinary launches / one XCD (planted blocks, 3 and 14 classes, tol =
+// 1e-6):
+//                          24,000 entries           80,000               160,000              280,000              400,000
+//   batches, synchronous   6.11/3.01  6.14/3.19     6.13/3.56  6.59/4.21  6.59/4.52  7.25/5.38  7.36/6.34  7.48/6.83  6.88/7.20  8.02/8.53
+//   batches, in place      6.11/2.74  6.64/2.84     6.38/3.17  6.65/3.78  6.30/3.64  7.56/4.03  6.80/5.48  7.53/5.14  7.38/5.84  7.91/6.36
+// (in place it also needs fewer rounds there: fewer rows are updated at the same time.)  Cold starts, 4 and 12 classes, whose
+// sweeps are one launch each: synchronous 16,000 entries 5.60/2.86 5.90/3.39, 96,000 6.38/5.08 6.80/6.00, 192,000 5.92/6.18
+// 6.89/7.57; in place 192,000 5.95/5.42 6.96/6.75, 200,000 7.37/5.85 8.56/7.00, 400,000 7.22/9.31 8.28/9.03.  At tol = 1e-4,
+// 8 to 25 rounds: 0.34/0.22 at 42,000 entries, 0.47/0.34 at 160,000, 0.36/0.31 at 280,000.
+// More than 16 columns were not tried: a row is two lines of the L2 then.
+int64_t xcd_max_entries(const dynlp_ctx* c, bool sweeps) {
+    const bool in_place = c->update_mode == DYNLP_UPDATE_IN_PLACE;
+    return sweeps ? (in_place ? 256000 : 128000) : (in_place ? 440000 : 300000);
+}
+
+bool xcd_rounds_pay(const dynlp_ctx* c, const Frontier& universe, int G, bool sweeps) {
+    if (c->group_lanes != 0 || c->persist > 0 || (c->CP == 1 && c->binned > 0) || c->CP > 16 || G > 16) return false;
+    if (universe.nl != 0 || universe.size() == 0 || c->n > kXcdMaxRows || c->entries > xcd_max_entries(c, sweeps)) return false;
+    // room for an eighth more than a workgroup's even share of the entries (the kernel has the last word)
+    const int64_t rows = c->n / kXcdGroups + 32, head = c->n / 8 + 64 + 7 * rows;
+    return head + c->entries / kXcdGroups * 9 / 8 * (int64_t)sizeof(Edge) <= (int64_t)kXcdLds;
+}
+
+template <int CP, int G>
+void launch_xcd_inst(dynlp_ctx* c, const XcdArgs& a) {
+    const void* kernel = reinterpret_cast<const void*>(&k_xcd_rounds<CP, G>);
+    // (always the same value: the attribute belongs to the kernel, not to this context)
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXcdLds) != hipSuccess) {
+        (void)hipGetLastError();
+        c->h_xcd->rounds = 0;
+        *c->h_flag = a.value;  // nothing was launched: refused
+        return;
+    }
+    hipLaunchKernelGGL((k_xcd_rounds<CP, G>), dim3(8 * a.want), dim3(kXcdThreads), kXcdLds, c->stream, a);
+}
+
+// Rounds [round, round + count) at most, from the list of parity `cur` (all_rows: over every updatable row); waits for them.
+// What they did is in c->h_xcd then; 0 rounds: they have to be launched one by one.
+void run_xcd(dynlp_ctx* c, int G, int cur, int round, int count, float* F_in, float* F_out, bool all_rows, bool lazy, float tol,
+             int chain_off, int same_run, const unsigned int (&sig)[3]) {
+    XcdArgs a{};
+    a.ctl = c->xcd;
+    a.result = c->h_xcd;
+    a.flag = c->h_flag;
+    a.value = ++c->h_sent;
+    if (c->xcd_launches == kXcdLaunches) {  // (the words of an exchange are told apart by the launch's number)
+        HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
+        c->xcd_launches = 0u;
+    }
+    ++c->xcd_launches;
+    a.launch = c->xcd_launches;
+    a.want = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(kXcdGroups, ceil_div(c->n, 64)));
+    a.ring = c->ring;
+    a.t0 = round;
+    a.rounds = count;
+    for (int i = 0; i < 2; ++i) a.front[i] = frontier_of(c, cur ^ i).front;
+    a.meta = c->meta;
+    a.pool = c->pool;
+    a.seed_class = c->seed_class;
+    a.F[0] = F_in;
+    a.F[1] = F_out;
+    a.n = (unsigned int)c->n;
+    a.all_rows = all_rows ? 1 : 0;
+    a.lazy = lazy ? 1 : 0;
+    a.tol = tol;
+    a.chain = kChain;
+    a.chain_off = chain_off;
+    a.len_lo = G == 4 || c->CP > 4 ? 0u : kGroupLen4;
+    a.len_hi = G == 4 ? kGroupLen4 : kGroupLen32;
+    a.same_run = same_run;
+    a.same_max = kSameRounds;
+    for (int i = 0; i < 3; ++i) a.sig[i] = sig[i];
+    hipEvent_t e1 = open_timed_span(c, round, count);
+    switch (c->CP) {
+        case 1: G == 4 ? launch_xcd_inst<1, 4>(c, a) : launch_xcd_inst<1, 16>(c, a); break;
+        case 2: G == 4 ? launch_xcd_inst<2, 4>(c, a) : launch_xcd_inst<2, 16>(c, a); break;
+        case 4: G == 4 ? launch_xcd_inst<4, 4>(c, a) : launch_xcd_inst<4, 16>(c, a); break;
+        case 8: launch_xcd_inst<8, 16>(c, a); break;
+        default: launch_xcd_inst<16, 16>(c, a); break;
+    }
+    HIPCHK(c, hipGetLastError());
+    close_timed_span(c, e1);
+    wait_for_flag(c, a.value);
+}
+
+// A round of such a launch as the round log has it.
+RoundCtr xcd_round(const XcdPart& p) {
+    RoundCtr r{};
+    r.executed = 1u;
+    r.rows_short = p.rows;
+    r.resid_bits = p.resid_bits;
+    r.changed = p.changed;
+    r.edges = p.entries;
+    return r;
 }
 
 // ---- several rounds per launch (k_rounds_persistent) ------------------------------------------------------------
@@ -2150,16 +2260,15 @@ void destroy_ctx(dynlp_ctx* c) {
     for (hipEvent_t e : c->init_ev)
         if (e) (void)hipEventDestroy(e);
     dev_free(c, c->ring);
+    dev_free(c, c->xcd);
     dev_free(c, c->persist_ctl);
     for (void* b : c->bounce)
         if (b) (void)hipHostFree(b);
     for (hipEvent_t e : c->ingest_ev)
         if (e) (void)hipEventDestroy(e);
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
-    if (c->h_slot) (void)hipHostFree(c->h_slot);
-    if (c->h_start) (void)hipHostFree(c->h_start);
+    if (c->h_fixed) (void)hipHostFree(c->h_fixed);
     if (c->h_io) (void)hipHostFree(c->h_io);
-    if (c->h_flag) (void)hipHostFree(c->h_flag);
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
@@ -2389,10 +2498,17 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->persist_ctl = static_cast<unsigned int*>(dev_alloc(c, kBarWords * sizeof(unsigned int)));
         c->ring = static_cast<RoundCtr*>(dev_alloc(c, sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)));
         c->bc = reinterpret_cast<BatchCtr*>(c->ring + kRing + 1);
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_slot), sizeof(RoundCtr) * kRing, hipHostMallocDefault));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_start), sizeof(dynlp_ctx::HostStart), hipHostMallocDefault));
+        c->xcd = static_cast<XcdCtl*>(dev_alloc(c, sizeof(XcdCtl)));
+        HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
+        constexpr size_t kSlotBytes = sizeof(RoundCtr) * kRing, kStartBytes = (sizeof(dynlp_ctx::HostStart) + 63) / 64 * 64;
+        constexpr size_t kResultBytes = (sizeof(XcdResult) + 63) / 64 * 64;
+        HIPCHK(c, hipHostMalloc(&c->h_fixed, kSlotBytes + kStartBytes + kResultBytes + 64, hipHostMallocDefault));
+        unsigned char* const fixed = static_cast<unsigned char*>(c->h_fixed);
+        c->h_slot = reinterpret_cast<RoundCtr*>(fixed);
+        c->h_start = reinterpret_cast<dynlp_ctx::HostStart*>(fixed + kSlotBytes);
         c->h_bc = &c->h_start->bc;
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_flag), sizeof(unsigned int), hipHostMallocDefault));
+        c->h_xcd = reinterpret_cast<XcdResult*>(fixed + kSlotBytes + kStartBytes);
+        c->h_flag = reinterpret_cast<unsigned int*>(fixed + kSlotBytes + kStartBytes + kResultBytes);
         *c->h_flag = 0u;
         for (auto& e : c->phase_ev) HIPCHK(c, hipEventCreate(&e));
         std::memset(c->h_bc, 0, sizeof(BatchCtr));
@@ -2814,7 +2930,28 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
         // synchronous: sweep t reads buf[t & 1], writes buf[(t + 1) & 1]; in place: every sweep reads and writes F
         float* const buf[2] = {c->F, in_place ? c->F : c->F2};
         if (binned) HIPCHK(c, hipMemsetAsync(c->moved[0], 0xff, (size_t)c->moved_words * sizeof(unsigned int), c->stream));
+        bool one_xcd = !relaxed && !binned && !packed && xcd_rounds_pay(c, all_rows, G, true);
         while (!converged && it < max_iter) {
+            if (one_xcd && it % kChain == 0) {
+                const unsigned int sig[3] = {0u, 0u, prev_bits};
+                const size_t first_pair = c->events_used / 2;
+                run_xcd(c, G, 0, it, std::min<int>(kXcdRounds, max_iter - it), buf[it & 1], buf[(it + 1) & 1], true, lazy, tol, 0, same_run, sig);
+                const int executed = (int)c->h_xcd->rounds;
+                if (c->time_kernels) trim_timed_spans(c, first_pair, it + executed);
+                if (executed == 0) one_xcd = false;
+                for (int i = 0; i < executed; ++i) {
+                    const RoundCtr rc = xcd_round(c->h_xcd->round[i]);
+                    std::memcpy(&last, &rc.resid_bits, sizeof(float));
+                    edges += (int64_t)rc.edges;
+                    c->log.push_back(round_info(rc, 0, G));
+                    same_run = rc.resid_bits == prev_bits ? same_run + 1 : 0;
+                    prev_bits = rc.resid_bits;
+                    if (same_run >= kSameRounds) lazy = true;
+                }
+                it += executed;
+                converged = executed > 0 && last <= tol;
+                continue;
+            }
             // a chain of sweeps; each checks on the device whether its predecessor already met the stop rule
             const int r = std::min<int>(kChain, max_iter - it);
             const bool chain_binned = binned && !lazy;  // the averaged sweeps of a limit cycle are ordinary ones
@@ -3127,11 +3264,54 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         int chain0 = 0, G = 16;
         // chains without a shared launch after one that found too many entries in its first list: 1, 2, 4, ... 64
         int tail_wait = 0, tail_refused = 0;
+        bool xcd_failed = false;  // rounds on one XCD were refused
+        bool xcd_dense = false;   // ... stand for rounds of a ping-pong stretch (round log)
         for (;;) {
         while (known > 0 && it < c->max_iter) {
             const int chain_off = (it - chain0) % kChain;
             const bool new_chain = chain_off == 0;
             if (new_chain) G = choose_group(c, avg_len);
+            if (!xcd_failed && !pingpong && xcd_rounds_pay(c, universe, G, false)) {
+                const bool few = tail_rounds_pay(c, known, known_before, avg_len);  // (V_aff of one workgroup's size)
+                const size_t first_pair = c->events_used / 2;
+                run_xcd(c, G, cur, it, std::min<int>(kXcdRounds - chain_off, c->max_iter - it), c->F, in_place ? c->F : c->F2, false, lazy,
+                        c->tol, chain_off, same_run, prev_sig);
+                const int executed = (int)c->h_xcd->rounds;
+                if (c->time_kernels) trim_timed_spans(c, first_pair, it + executed);
+                if (executed == 0) {
+                    xcd_failed = true;
+                    continue;
+                }
+                known_before = known;
+                for (int i = 0; i < executed; ++i) {
+                    const RoundCtr rc = xcd_round(c->h_xcd->round[i]);
+                    const unsigned int nq = rc.rows_short;
+                    std::memcpy(&last, &rc.resid_bits, sizeof(float));
+                    rows += nq;
+                    edges += (int64_t)rc.edges;
+                    avg_len = nq ? (double)rc.edges / (double)nq : avg_len;
+                    // the log has the kind of round this one stands for
+                    bool begins = false;
+                    if ((chain_off + i) % kChain == 0) {
+                        begins = !xcd_dense && (double)nq >= kDenseEnter * (double)universe.size();
+                        xcd_dense = xcd_dense ? (double)nq >= kDenseLeave * (double)universe.size() : begins;
+                    }
+                    c->log.push_back(round_info(rc, !xcd_dense ? 1 : begins ? 0 : 2, G));
+                    if (few) c->log.back().launch_rounds = (float)executed;
+                    if (it + i == check_round) verified = rc.changed == 0u;
+                    const unsigned int sig[3] = {nq, rc.changed, rc.resid_bits};
+                    same_run = std::memcmp(sig, prev_sig, sizeof sig) == 0 ? same_run + 1 : 0;
+                    std::memcpy(prev_sig, sig, sizeof sig);
+                    if (same_run >= kSameRounds) lazy = true;
+                    peak = std::max<int64_t>(peak, nq);
+                }
+                known = c->h_xcd->next;
+                if (!xcd_dense) peak = std::max<int64_t>(peak, known);  // (a stretch does not count the rows of the round after)
+                if (!in_place && (executed & 1)) std::swap(c->F, c->F2);
+                cur ^= executed & 1;
+                it += executed;
+                continue;
+            }
             const bool may_relax = new_chain && !relaxed && it != check_round &&
                                    (double)known >= kRelaxEnter * (double)universe.size() && relaxed_rounds_pay(c, universe, c->tol);
             const bool relax = may_relax && relax_now;

@@ -1,0 +1,121 @@
+"""Rounds of small graphs that share launches on the CUs of one XCD (k_xcd_rounds): the same V_aff, moves and labels, bit for
+bit, as ordinary launches (a fixed number of lanes per row keeps those), over the edges of what the kernel cuts the graph into:
+words of 32 rows, one word or many per workgroup, rows of 1 to 128 entries (longer ones end it), one to sixteen columns, 240
+rounds to a launch.  With kernel timing on, all rounds of a launch have the same time.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+import paper_2604_06596_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _shared(log):
+    """Rounds whose time is that of the round before: they shared its launch."""
+    t = np.array([r.ms_update for r in log])
+    return int(np.count_nonzero(t[1:] == t[:-1])) if len(t) > 1 else 0
+
+
+def _run(make, lanes, tol, cap, mode, scalar=False, want_lanes=0):
+    p, batches = make()
+    out, shared, rounds, used = [], 0, 0, set()
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, group_lanes=lanes, time_kernels=True,
+                 binary_scalar=scalar) as d:
+        d.set_update_mode(mode)
+        st, s = d.static_solve(tol, cap)
+        out.append((st, s.iterations, s.edges_traversed) + tuple(d.get_labels()) + tuple(d.round_log()))
+        d.set_params(tol, cap)
+        for b in batches:
+            st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            out.append((st, s.iterations, s.rows_updated, s.edges_traversed, s.frontier_initial, s.frontier_peak) +
+                       tuple(d.get_labels()) + tuple(d.round_log()))
+            log = d.round_log_full()
+            shared, rounds, used = shared + _shared(log), rounds + len(log), used | {int(r.group_lanes) for r in log}
+    if lanes == 0 and want_lanes:
+        assert used == {want_lanes}, "the case is meant to keep its lanes per row"
+    return out, shared, rounds
+
+
+def _random(n, C, deg):
+    def make():
+        p = W.small_random(n, C, deg, max(2, n // 50), 31 * n + C)
+        q = W.small_random(n, C, deg, max(2, n // 50), 31 * n + C)
+        return q, [W.small_random_batch(p, max(1, n // 40), max(1, int(deg)), 1, num_extra_edges=4, num_revealed=1),
+                   W.small_random_batch(p, 1, 2, 0, num_extra_edges=1)]
+    return make
+
+
+def _star(n, C, length):
+    """A vertex of `length` entries among short rows, and a batch that touches it."""
+    def make():
+        p, q = (W.small_random(n, C, 12.0, 40, 77 + length) for _ in range(2))
+        u = int(np.setdiff1d(np.arange(n), p.seed_vertex)[0])
+        near = p.col[p.row_ptr[u]:p.row_ptr[u + 1]]
+        others = np.setdiff1d(np.arange(n), np.append(near, u))[:length - len(near)].astype(np.int32)
+        none = np.zeros(0, np.int32)
+        first = W.Batch(0, np.full(len(others), u, np.int32), others, np.linspace(0.1, 1.0, len(others)).astype(np.float32), none, none)
+        return p, [first, W.small_random_batch(q, 2, 3, 0)]
+    return make
+
+
+# (n, C, mean degree, one float per vertex): lanes per row are 4 below a mean of 8 entries and up to four columns, else 16
+@pytest.mark.parametrize("n,C,deg,scalar,lanes", [
+    (5, 2, 2, True, 4), (31, 3, 3, False, 4), (33, 2, 3, False, 4), (64, 1, 12, False, 16), (65, 4, 12, False, 16),
+    (2047, 2, 12, True, 16), (2048, 5, 6, False, 16), (2049, 16, 6, False, 16), (2049, 3, 3, False, 4), (6001, 2, 3, True, 4),
+    (9001, 4, 12, False, 16), (9001, 9, 12, False, 16), (9001, 2, 12, False, 16), (22000, 8, 9, False, 16), (31500, 2, 3, True, 4)])
+@pytest.mark.parametrize("tol,cap", [(1e-4, 20000), (1e-6, 300), (1e-6, 13)])
+def test_the_same_rounds_as_ordinary_launches(n, C, deg, scalar, lanes, tol, cap):
+    one, shared, rounds = _run(_random(n, C, float(deg)), 0, tol, cap, P.UPDATE_SYNCHRONOUS, scalar, lanes)
+    own, shared0, _ = _run(_random(n, C, float(deg)), lanes, tol, cap, P.UPDATE_SYNCHRONOUS, scalar)
+    print(n, C, deg, "rounds", rounds, "that shared launches", shared, shared0)
+    assert rounds < 20 or 2 * shared > rounds, "the case is meant to share launches"
+    assert shared0 < shared or rounds < 20
+    for a, b in zip(one, own):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("length,shares", [(112, True), (127, True), (128, True), (129, False), (300, False)])
+@pytest.mark.parametrize("C", [1, 3, 6, 12])
+def test_rows_of_up_to_128_entries(length, shares, C):
+    one, shared, rounds = _run(_star(1500, C, length), 0, 1e-5, 20000, P.UPDATE_SYNCHRONOUS)
+    own, _, _ = _run(_star(1500, C, length), 16, 1e-5, 20000, P.UPDATE_SYNCHRONOUS)
+    assert not shares or shared > rounds // 2 or rounds < 20
+    for a, b in zip(one, own):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n,C,scalar", [(40, 2, False), (3001, 2, True), (12000, 12, False)])
+def test_rows_updated_in_place_end_under_the_same_rule(n, C, scalar):
+    """In place the path differs; where it ends is within the threshold times the steps of a walk to a labelled vertex."""
+    one, shared, _ = _run(_random(n, C, 9.0), 0, 1e-6, 20000, P.UPDATE_IN_PLACE, scalar)
+    own, _, _ = _run(_random(n, C, 9.0), 16, 1e-6, 20000, P.UPDATE_SYNCHRONOUS, scalar)
+    assert shared > 0
+    for i, (a, b) in enumerate(zip(one, own)):
+        k = 3 if i == 0 else 6  # the soft labels in the tuple
+        assert a[0] == b[0] == 0 and np.max(np.abs(a[k] - b[k])) <= 400 * 1e-6
+
+
+def test_two_contexts_take_turns_and_launches_are_told_apart():
+    """Each context numbers its launches; what one leaves behind is not taken for the other's, on whichever XCD they run."""
+    make = _random(2500, 4, 9.0)
+    want, _, _ = _run(make, 16, 1e-5, 20000, P.UPDATE_SYNCHRONOUS)
+    runs = []
+    ctx = []
+    for _ in range(2):
+        p, batches = make()
+        ctx.append((P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class), batches))
+    for d, _ in ctx:
+        d.static_solve(1e-5, 20000)
+        d.set_params(1e-5, 20000)
+    for i in range(2):
+        for d, batches in ctx:
+            b = batches[i]
+            d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            runs.append(d.get_labels()[0])
+            assert np.array_equal(runs[-1], want[1 + i][6])
+    for d, _ in ctx:
+        d.__exit__(None, None, None)
