@@ -88,7 +88,9 @@ typedef struct dynlp_options {
     int32_t group_lanes;     /* lanes cooperating on one frontier row: 0 = choose from the mean
                                 row length, else 4, 8, 16, 32 or 64 (tuning knob) */
     /* Optional allocator for device memory (e.g. a caching allocator); all three NULL selects
-       hipMalloc/hipFree.  alloc returns NULL on failure. */
+       hipMalloc/hipFree.  alloc returns NULL on failure.  Without them, arrays that a context gives back wait for the
+       next context of the process: at most an eighth of the device's memory, freed when an allocation of the library
+       fails, and after ten seconds without use by the next call that creates or destroys a context. */
     void* (*alloc)(size_t bytes, void* user);
     void (*dealloc)(void* ptr, void* user);
     void* alloc_user;
@@ -405,7 +407,7 @@ int64_t dynlp_round_log(const dynlp_ctx* ctx, int64_t cap, dynlp_round_info* out
  * thread).  Valid until the next call on the same context / thread.  Never NULL. */
 const char* dynlp_last_error(const dynlp_ctx* ctx);
 
-/* Release the context and all device memory it owns.  NULL is allowed. */
+/* Release the context and all device memory it owns (see dynlp_options.alloc).  NULL is allowed. */
 void dynlp_destroy(dynlp_ctx* ctx);
 
 #ifdef __cplusplus

@@ -102,8 +102,9 @@ struct dynlp_ctx {
     float slack = 1.25f;
     bool time_kernels = false;
     int group_lanes = 0;
-    std::unordered_set<void*> live;  // every device array handed out by dev_alloc and not yet freed: whatever an error
-                                     // path left behind goes back to the allocator when the context is destroyed
+    std::unordered_map<void*, size_t> live;  // every device array handed out by dev_alloc and not yet freed, and its bytes:
+                                             // whatever an error path left behind goes back when the context is destroyed
+    bool idle = false;  // nothing of this context is running or will be launched: its arrays may go to another one at once
     void* (*alloc_fn)(size_t, void*) = nullptr;
     void (*dealloc_fn)(void*, void*) = nullptr;
     void* alloc_user = nullptr;
@@ -162,6 +163,7 @@ struct dynlp_ctx {
     unsigned int* h_flag = nullptr;  // pinned: number of the last k_to_host that has arrived
     unsigned int h_sent = 0;         // ... that was launched
     void* h_fixed = nullptr;         // the one pinned allocation that h_slot, h_start, h_flag and h_xcd lie in
+    size_t h_fixed_bytes = 0;
     // rounds of small graphs on one XCD (dynlp_xcd.h)
     XcdCtl* xcd = nullptr;
     XcdResult* h_xcd = nullptr;      // pinned
@@ -270,18 +272,134 @@ struct Fail {
         }                                                                                              \
     } while (0)
 
+// ---- memory between contexts -----------------------------------------------------------------------
+// A context takes some forty arrays and gives them back when it is destroyed.  hipMalloc and hipFree cost 5 to 20 us each for
+// small arrays, about 7 ms together for a graph of 3M vertices, and much more once a process has handed out all of the device's
+// memory before: what is given back then has to be cleared before it is handed out again (50M vertices, 20 GB: 40 to 1,750 ms).
+// Arrays of contexts without an allocator of their own therefore wait here for the next context of the process.
+//   bounded     an eighth of the device's memory, 16 MB of pinned memory per device; what does not fit is freed at once
+//   given back  when an allocation fails (all of it), and by the first create or destroy after kKeepMs without use
+//   streams     an array comes here only when the stream of its context has run dry (as hipFree waits for it)
+//   threads     one lock; calls of the runtime that free memory are made outside it
+// Measured: 3M vertices create 0.66 / 0.20 ms, destroy 5.2 / 0.01; 400,000 with 100 sweeps, whole 10.1 / 8.9 ms; 50M 188 / 179 ms,
+// and 880 / 181 ms where the memory had been in use before.
+struct KeptBlock {
+    void* p;
+    size_t bytes;
+    int device;
+    bool pinned;
+    Clock::time_point since;
+};
+constexpr float kKeepMs = 10000.f;
+constexpr size_t kKeepShare = 8, kKeepPinned = (size_t)16 << 20;
+std::mutex g_kept_lock;
+std::vector<KeptBlock> g_kept;                                // guarded by g_kept_lock; oldest first
+std::unordered_map<int, size_t> g_kept_bytes[2], g_kept_cap;  // by device; [1]: pinned
+
+void release_blocks(const std::vector<KeptBlock>& blocks) {
+    for (const KeptBlock& b : blocks) (void)(b.pinned ? hipHostFree(b.p) : hipFree(b.p));
+}
+
+// A kept block of at least `bytes`, and not much more; NULL if there is none.
+void* take_kept(int device, bool pinned, size_t bytes, size_t* got) {
+    std::lock_guard<std::mutex> hold(g_kept_lock);
+    size_t best = g_kept.size();
+    for (size_t i = 0; i < g_kept.size(); ++i) {
+        const KeptBlock& b = g_kept[i];
+        if (b.device != device || b.pinned != pinned || b.bytes < bytes || b.bytes > bytes + bytes / 8 + 4096) continue;
+        if (best == g_kept.size() || b.bytes < g_kept[best].bytes) best = i;
+    }
+    if (best == g_kept.size()) return nullptr;
+    void* const p = g_kept[best].p;
+    *got = g_kept[best].bytes;
+    g_kept_bytes[pinned][device] -= *got;
+    g_kept.erase(g_kept.begin() + (ptrdiff_t)best);
+    return p;
+}
+
+// Takes the block in; false: the caller frees it.
+bool keep_block(int device, bool pinned, void* p, size_t bytes) {
+    std::lock_guard<std::mutex> hold(g_kept_lock);
+    size_t cap = kKeepPinned;
+    if (!pinned) {
+        size_t& known = g_kept_cap[device];
+        if (known == 0) {
+            size_t free_bytes = 0, total = 0;
+            if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {  // (of the current device, which is the context's)
+                (void)hipGetLastError();
+                return false;
+            }
+            known = std::max<size_t>(1, total / kKeepShare);
+        }
+        cap = known;
+    }
+    size_t& held = g_kept_bytes[pinned][device];
+    if (bytes > cap - std::min(cap, held)) return false;
+    try {
+        g_kept.push_back(KeptBlock{p, bytes, device, pinned, Clock::now()});
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    held += bytes;
+    return true;
+}
+
+// Gives back what has waited for more than `ms`; whether there was any.
+bool release_kept(float ms) {
+    std::vector<KeptBlock> old;
+    {
+        std::lock_guard<std::mutex> hold(g_kept_lock);
+        try {
+            old.reserve(g_kept.size());
+        } catch (const std::bad_alloc&) {
+            return false;
+        }
+        size_t left = 0;
+        for (const KeptBlock& b : g_kept) {
+            if (ms_since(b.since) < ms) {
+                g_kept[left++] = b;
+            } else {
+                old.push_back(b);
+                g_kept_bytes[b.pinned][b.device] -= b.bytes;
+            }
+        }
+        g_kept.erase(g_kept.begin() + (ptrdiff_t)left, g_kept.end());
+    }
+    release_blocks(old);
+    return !old.empty();
+}
+
 // NULL when the allocator has no memory left (nothing else changes).
 void* dev_try_alloc(dynlp_ctx* c, size_t bytes) {
     if (bytes == 0) bytes = 256;
     void* p = nullptr;
     if (c->alloc_fn) {
         p = c->alloc_fn(bytes, c->alloc_user);
-    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+    } else if (!(p = take_kept(c->device, false, bytes, &bytes)) && hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        if (release_kept(0.f) && hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+    }
+    if (p) c->live.emplace(p, bytes);
+    return p;
+}
+
+// Pinned memory, kept between contexts likewise.  *got: its size.
+void* pinned_try_alloc(dynlp_ctx* c, size_t bytes, size_t* got) {
+    *got = bytes;
+    void* p = take_kept(c->device, true, bytes, got);
+    if (!p && hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         p = nullptr;
     }
-    if (p) c->live.insert(p);
     return p;
+}
+
+void pinned_free(dynlp_ctx* c, void* p, size_t bytes) {  // (nothing of the context is running)
+    if (p && !keep_block(c->device, true, p, bytes)) (void)hipHostFree(p);
 }
 
 void free_binned(dynlp_ctx* c);
@@ -312,9 +430,17 @@ void* dev_alloc(dynlp_ctx* c, size_t bytes) {
 }
 
 void dev_free(dynlp_ctx* c, void* p) {
-    if (!p || c->live.erase(p) == 0) return;  // only what dev_try_alloc handed out and has not been freed yet
-    if (c->dealloc_fn) c->dealloc_fn(p, c->alloc_user);
-    else (void)hipFree(p);
+    const auto it = p ? c->live.find(p) : c->live.end();
+    if (it == c->live.end()) return;  // only what dev_try_alloc handed out and has not been freed yet
+    const size_t bytes = it->second;
+    c->live.erase(it);
+    if (c->dealloc_fn) {
+        c->dealloc_fn(p, c->alloc_user);
+        return;
+    }
+    const bool dry = c->idle || (hipStreamSynchronize(c->stream) == hipSuccess &&
+                                 (!c->copy_stream || hipStreamSynchronize(c->copy_stream) == hipSuccess));
+    if (!dry || !keep_block(c->device, false, p, bytes)) (void)hipFree(p);
 }
 
 template <typename T>
@@ -509,16 +635,13 @@ constexpr int64_t kIoOutBytes = (int64_t)128 << 10;  // labels that the kernel w
 bool ensure_pinned(dynlp_ctx* c, int64_t bytes) {
     if (bytes > kIoBytes) return false;
     if (bytes <= c->h_io_cap) return true;
-    if (c->h_io) (void)hipHostFree(c->h_io);  // (no copy from or to it is under way: every call ends with a wait)
-    c->h_io = nullptr;
+    pinned_free(c, c->h_io, (size_t)c->h_io_cap);  // (no copy from or to it is under way: every call ends with a wait)
     c->h_io_cap = 0;
+    size_t got = 0;
     const int64_t cap = std::min<int64_t>(kIoBytes, round_up(std::max<int64_t>(bytes + bytes / 2, 64 << 10), 4096));
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_io), (size_t)cap, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        c->h_io = nullptr;
-        return false;
-    }
-    c->h_io_cap = cap;
+    c->h_io = static_cast<unsigned char*>(pinned_try_alloc(c, (size_t)cap, &got));
+    if (!c->h_io) return false;
+    c->h_io_cap = (int64_t)got;
     return true;
 }
 
@@ -2245,7 +2368,8 @@ bool host_check_edges(std::string& err, int64_t m, int64_t n_total, const int32_
 void destroy_ctx(dynlp_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    if (c->stream || c->meta) (void)hipStreamSynchronize(c->stream);
+    if (c->stream || c->meta) c->idle = hipStreamSynchronize(c->stream) == hipSuccess;
+    if (c->copy_stream) c->idle = hipStreamSynchronize(c->copy_stream) == hipSuccess && c->idle;
     void* ptrs[] = {c->meta, c->pool, c->F, c->F2, c->seed_class, c->flag, c->queue[0], c->queue[1], c->queue[2], c->moved[0], c->moved[1], c->moved[2], c->add_cnt,
                     c->deg, c->touched, c->reloc_off, c->he_rank, c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del, c->d_io,
                     c->cc_par, c->cc_dense, c->cc_comp, c->cc_block, c->cc_kept, c->cc_W,
@@ -2253,7 +2377,8 @@ void destroy_ctx(dynlp_ctx* c) {
                     c->pb_first, c->pb_block, c->pb_bin, c->pb_table, c->pk_ent, c->pk_len, c->pk_deg, c->pk_tab,
                     c->cg_z, c->cg_p, c->cg_ring};
     for (void* p : ptrs) dev_free(c, p);
-    const std::vector<void*> left(c->live.begin(), c->live.end());  // arrays an interrupted call never got to free
+    std::vector<void*> left;  // arrays an interrupted call never got to free
+    for (const auto& l : c->live) left.push_back(l.first);
     for (void* p : left) dev_free(c, p);
     dev_free(c, c->cc_ctr);
     if (c->h_cc) (void)hipHostFree(c->h_cc);
@@ -2267,13 +2392,19 @@ void destroy_ctx(dynlp_ctx* c) {
     for (hipEvent_t e : c->ingest_ev)
         if (e) (void)hipEventDestroy(e);
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
-    if (c->h_fixed) (void)hipHostFree(c->h_fixed);
-    if (c->h_io) (void)hipHostFree(c->h_io);
+    if (c->idle) {
+        pinned_free(c, c->h_fixed, c->h_fixed_bytes);
+        pinned_free(c, c->h_io, (size_t)c->h_io_cap);
+    } else {
+        if (c->h_fixed) (void)hipHostFree(c->h_fixed);
+        if (c->h_io) (void)hipHostFree(c->h_io);
+    }
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->phase_ev)
         if (e) (void)hipEventDestroy(e);
     delete c;
+    (void)release_kept(kKeepMs);
 }
 
 // ---- Alg. 2 Step 1 (components of the sparsified batch-internal graph) + Step 2 (supernode rows) ----
@@ -2492,9 +2623,10 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->CP = CP;
         HIPCHK(c, hipSetDevice(c->device));
         resolve_static_scratch(c->device);  // for dynlp_get_labels_static; a failure is reported by that call
-        hipDeviceProp_t prop;
-        HIPCHK(c, hipGetDeviceProperties(&prop, c->device));
-        c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+        (void)release_kept(kKeepMs);
+        int cus = 0;  // (one attribute: all properties take 0.2 ms)
+        HIPCHK(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+        c->num_cu = cus > 0 ? cus : 256;
         c->persist_ctl = static_cast<unsigned int*>(dev_alloc(c, kBarWords * sizeof(unsigned int)));
         c->ring = static_cast<RoundCtr*>(dev_alloc(c, sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)));
         c->bc = reinterpret_cast<BatchCtr*>(c->ring + kRing + 1);
@@ -2502,7 +2634,11 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
         constexpr size_t kSlotBytes = sizeof(RoundCtr) * kRing, kStartBytes = (sizeof(dynlp_ctx::HostStart) + 63) / 64 * 64;
         constexpr size_t kResultBytes = (sizeof(XcdResult) + 63) / 64 * 64;
-        HIPCHK(c, hipHostMalloc(&c->h_fixed, kSlotBytes + kStartBytes + kResultBytes + 64, hipHostMallocDefault));
+        c->h_fixed = pinned_try_alloc(c, kSlotBytes + kStartBytes + kResultBytes + 64, &c->h_fixed_bytes);
+        if (!c->h_fixed) {
+            c->err = "allocation of pinned memory failed";
+            throw Fail{DYNLP_ERR_OOM};
+        }
         unsigned char* const fixed = static_cast<unsigned char*>(c->h_fixed);
         c->h_slot = reinterpret_cast<RoundCtr*>(fixed);
         c->h_start = reinterpret_cast<dynlp_ctx::HostStart*>(fixed + kSlotBytes);

@@ -1,0 +1,66 @@
+"""Device memory of destroyed contexts waits for the next context of the process: several threads and streams at once get the
+results of one, a context like the last takes no new memory, and no more than an eighth of the device waits."""
+import threading
+
+import numpy as np
+import pytest
+
+import workloads as W
+import paper_2604_06596_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(n, C):
+    p, q = (W.small_random(n, C, 8.0, n // 20, 600 + C) for _ in range(2))
+    return p, W.small_random_batch(q, n // 10, 7, 3, num_extra_edges=20)
+
+
+def _pass(p, b, stream=None):
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, stream=stream) as d:
+        d.static_solve(1e-6, 20000)
+        d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+        return d.get_labels()
+
+
+def test_threads_and_streams_share_it():
+    import torch
+
+    cases = [_problem(n, C) for n, C in ((3000, 4), (40000, 3), (9000, 12), (40000, 2))]
+    want = [_pass(p, b) for p, b in cases]
+    wrong = []
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        for i in range(8):
+            p, b = cases[(k + i) % len(cases)]
+            got = _pass(p, b, stream.cuda_stream)
+            if not all(np.array_equal(x, y) for x, y in zip(got, want[(k + i) % len(cases)])):
+                wrong.append((k, i))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
+def test_it_is_used_again_and_bounded():
+    import torch
+
+    p, b = _problem(200000, 10)
+    _pass(p, b)
+    torch.cuda.synchronize()
+    before, total = torch.cuda.mem_get_info()
+    for _ in range(4):
+        _pass(p, b)
+    torch.cuda.synchronize()
+    after, _ = torch.cuda.mem_get_info()
+    assert before - after <= 32 << 20, "a context like the last takes no new memory"
+    for n in (300000, 500000, 800000, 1200000):
+        p, b = _problem(n, 16)
+        _pass(p, b)
+    torch.cuda.synchronize()
+    last, _ = torch.cuda.mem_get_info()
+    assert before - last <= total // 8
