@@ -1339,10 +1339,29 @@ int pb_run_lanes(int nbins) {
     return lg;
 }
 
+// Receivers per bin (log2): the most (longer runs for the scatter pass) that leave two bins per CU, from 2^12 on.  A bin is a
+// workgroup of the gather pass, one to a CU with 2^15 receivers and two below; 3M vertices are 92 such bins.  us per round with
+// 2^15 / 14 / 13 / 12 / 11 receivers, synchronous (S) and conjugate (C): 2.2M of degree 5 S 92 / 66 / 70 / 67 / 73, 3M S 99 / 74 /
+// 77 / 78 / 97, C 139 / 108 / 106 / 104 / 106, 5M of degree 7 S 202 / 209 / 199 / 203 / 292, 10M of degree 5 S 313 / 288 / 291 / 401, C
+// 389 / 353 / 347 / 433, 20M S 564 / 556 / 774, C 765 / 742 / 947.
+int pb_bin_bits(const dynlp_ctx* c) {
+    if (c->binned > 0) return c->binned;
+    int bits = kPbMaxBinBits;
+    while (bits > 12 && ceil_div(c->n, (int64_t)1 << bits) < 2 * c->num_cu) --bits;
+    return bits;
+}
+
+// LDS for the gather workgroups of any bin (always the same value: the attribute belongs to the kernel).
+template <typename K>
+void allow_gather_lds(dynlp_ctx* c, K* kernel) {
+    HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)pb_gather_lds(kPbMaxBinBits)));
+}
+
 // Slots, per-slot receiver offsets and normalised weights for the graph as it stands.  False (and nothing kept)
 // when the arrays cannot be allocated: the caller then runs ordinary rounds.
 bool build_binned(dynlp_ctx* c) {
-    const int bits = c->binned > 0 ? c->binned : kPbMaxBinBits;
+    const int bits = pb_bin_bits(c);
     const int nbins = (int)ceil_div(std::max<int64_t>(c->n, 1), (int64_t)1 << bits);
     const int chunks = (int)ceil_div(std::max<int64_t>(c->entries, 1), kPbChunk);
     bool ok = true;
@@ -1436,7 +1455,10 @@ bool build_binned(dynlp_ctx* c) {
     // A range's gather runs one workgroup per bin and one workgroup fills a CU: ranges of about one bin per CU keep
     // the whole chip busy (50M vertices, 1,526 bins, in-place batch: 2 / 4 / 6 / 8 / 16 ranges give 802 / 681 / 616 /
     // 622 / 731 ms against 956 ms with one).  Graphs with fewer bins than CUs keep one range.
-    const int want_parts = c->update_mode == DYNLP_UPDATE_IN_PLACE ? (int)ceil_div(nbins, std::max(1, c->num_cu)) : 1;
+    // (in the largest bins, where two workgroups share a CU)
+    const int want_parts = c->update_mode != DYNLP_UPDATE_IN_PLACE ? 1
+                           : c->binned > 0                         ? (int)ceil_div(nbins, std::max(1, c->num_cu))
+                                           : (int)ceil_div(ceil_div(c->n, (int64_t)1 << kPbMaxBinBits), (int64_t)std::max(1, c->num_cu));
     const int parts = std::max(1, std::min({want_parts, kPbMaxParts, nbins}));
     c->pb_parts = parts;
     std::vector<unsigned int> first_at(parts + 1, 0u);
@@ -1489,7 +1511,8 @@ void launch_pb_scatter(dynlp_ctx* c, const RoundCtr* prev, int chunk0, int nchun
 // needed), as with any in-place round that reads rows the same round has already replaced.
 void launch_pb_gather(dynlp_ctx* c, const PullRoundArgs& a, int b0, int b1) {
     const unsigned int* bin_off = c->pb_bin + (kPbMaxBins + 1);
-    hipLaunchKernelGGL(k_pb_gather, dim3(b1 - b0), dim3(kPbGatherThreads), 0, c->stream, a.prev, c->n, c->pb_bits, (unsigned int)b0,
+    allow_gather_lds(c, k_pb_gather);
+    hipLaunchKernelGGL(k_pb_gather, dim3(b1 - b0), dim3(kPbGatherThreads), pb_gather_lds(c->pb_bits), c->stream, a.prev, c->n, c->pb_bits, (unsigned int)b0,
                        bin_off, c->pb_dst, c->pb_wn, c->pb_val, c->pb_len, a.F_in, a.F_out, a.moved_prev, a.moved_cur, a.tol,
                        a.flags, a.omega, a.ctr);
 }
@@ -2176,7 +2199,8 @@ void launch_product(dynlp_ctx* c, int G, const Frontier& universe, const CgRun& 
         else if (c->pb_packed_ok) DYNLP_SCATTER(kPbMaxBins, true, c->pb_sp);
         else DYNLP_SCATTER(kPbMaxBins, false, c->pb_src);
 #undef DYNLP_SCATTER
-        hipLaunchKernelGGL(k_pb_product, dim3(c->pb_bins), dim3(kPbGatherThreads), 0, c->stream, run, c->n, c->pb_bits, bin_off,
+        allow_gather_lds(c, k_pb_product);
+        hipLaunchKernelGGL(k_pb_product, dim3(c->pb_bins), dim3(kPbGatherThreads), pb_gather_lds(c->pb_bits), c->stream, run, c->n, c->pb_bits, bin_off,
                            c->pb_dst, c->pb_wn, reinterpret_cast<const float*>(c->pb_val), c->pb_len, c->deg, p, v);
     } else if (packed) {
         const PkProduct r{run, c->n, c->pk_rows, c->pk_tab + c->pk_parts + 4, c->Cs, packed_stride(c), c->pk_bits, c->pk_ent, c->pk_tab, c->pk_len, c->deg, p, v};

@@ -499,9 +499,12 @@ __global__ void __launch_bounds__(kPbScatterThreads) k_pb_scatter_product(CgRun 
                                        nullptr, val);
 }
 
-// Gather pass: one workgroup of kPbGatherThreads per bin (the accumulators take most of a CU's LDS, so the
-// one resident workgroup is made as wide as the hardware allows).
+// Gather pass: one workgroup of kPbGatherThreads per bin (the accumulators of the largest bins take most of a CU's LDS, so the
+// one resident workgroup is made as wide as the hardware allows; of smaller bins two share a CU).
 constexpr int kPbGatherThreads = 1024;
+
+// LDS of a gather workgroup: the accumulators of its bin, and two bits per receiver.
+__host__ __device__ inline unsigned int pb_gather_lds(int bin_bits) { return (4u << bin_bits) + (2u << bin_bits) / 8u; }
 
 __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* __restrict__ prev, int64_t n, int bin_bits,
                                                                unsigned int bin0,
@@ -515,9 +518,10 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_gather(const RoundCtr* 
                                                                int flags, float omega, RoundCtr* __restrict__ ctr) {
     constexpr int T = kPbGatherThreads;
     constexpr int NW = T / kWave;
-    __shared__ unsigned int acc[1 << kPbMaxBinBits];
-    __shared__ unsigned int nb[(1 << kPbMaxBinBits) / 32];
-    __shared__ unsigned int own[(1 << kPbMaxBinBits) / 32];
+    extern __shared__ __align__(16) unsigned int pb_lds[];  // pb_gather_lds(bin_bits)
+    unsigned int* const acc = pb_lds;
+    unsigned int* const nb = acc + (1 << bin_bits);
+    unsigned int* const own = nb + ((1 << bin_bits) >> 5);
     __shared__ float sm_r[NW];
     __shared__ unsigned long long sm_e[NW];
     __shared__ unsigned int sm_c[NW], sm_n[NW];
@@ -648,7 +652,8 @@ __global__ void __launch_bounds__(kPbGatherThreads) k_pb_product(CgRun run, int6
                                                                 const float* __restrict__ p, float* __restrict__ v) {
     constexpr int T = kPbGatherThreads;
     constexpr float kUnits = 2.f * kPbUnit;
-    __shared__ int acc[1 << kPbMaxBinBits];
+    extern __shared__ __align__(16) unsigned int pb_lds[];
+    int* const acc = reinterpret_cast<int*>(pb_lds);
     if (cg_done(run)) return;
     const float scale = cg_scale(run);
     const int size = 1 << bin_bits;

@@ -284,3 +284,23 @@ def test_binned_rounds_need_the_scalar_layout_and_a_valid_bin_size():
         assert d.static_solve(TOL, 20000)[0] == 0
         st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
         assert st == 0 and 3 not in [int(r.staged) for r in d.round_log_full()]
+
+
+@pytest.mark.parametrize("bits", [12, 13, 14, 15])
+def test_the_size_of_a_bin_changes_no_label(bits):
+    """From 2M vertices on binned rounds are chosen with bins that leave the gather pass two per CU; the sums are integers."""
+    rng = np.random.default_rng(77)
+    n, m = 2_400_000, 3_600_000
+    u, v = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    v = np.where(u == v, (v + 1) % n, v).astype(np.int32)
+    w = rng.uniform(0.1, 1.0, m).astype(np.float32)
+    seeds = np.arange(0, n, 100, dtype=np.int32)
+    runs = []
+    for b in (0, bits):
+        with P.DynLP(n, np.zeros(n + 1, np.int64), np.zeros(0, np.int32), np.zeros(0, np.float32), 2, seeds, (seeds // 100 % 2).astype(np.int32),
+                     binary_scalar=True, binned_rounds=b, reserve_edges=m) as d:
+            d.set_params(1e-6, 20)
+            d.apply_batch(0, u, v, w)
+            assert 3 in [int(r.staged) for r in d.round_log_full()]
+            runs.append(d.get_labels())
+    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
