@@ -23,6 +23,7 @@
 #include "dynlp_frontier.h"
 #include "dynlp_components.h"
 #include "dynlp_binned.h"
+#include "dynlp_insert.h"
 #include "dynlp_packed.h"
 #include "dynlp_xcd.h"
 
@@ -615,16 +616,19 @@ void alloc_vertex_arrays(dynlp_ctx* c, int64_t new_cap) {
     c->flag_cap = flag_cap;
 }
 
-void grow_pool(dynlp_ctx* c, int64_t min_cap) {
+// must: no memory is the end of the context; else the pool stays as it is and the result is false.
+bool grow_pool(dynlp_ctx* c, int64_t min_cap, bool must = true) {
     int64_t new_cap = std::max<int64_t>(min_cap, c->pool_cap + c->pool_cap / 2);
     new_cap = round_up(new_cap, kRowAlign);
-    Edge* p = dev_alloc_n<Edge>(c, new_cap);
+    Edge* p = must ? dev_alloc_n<Edge>(c, new_cap) : static_cast<Edge*>(dev_alloc_or_reclaim(c, (size_t)new_cap * sizeof(Edge)));
+    if (!p) return false;
     if (c->pool && c->pool_tail > 0)
         HIPCHK(c, hipMemcpyAsync(p, c->pool, (size_t)c->pool_tail * sizeof(Edge), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     dev_free(c, c->pool);
     c->pool = p;
     c->pool_cap = new_cap;
+    return true;
 }
 
 // Pinned memory for `bytes` of a small call with host arrays; false: too large a call, or no memory (nothing is lost but time).
@@ -658,13 +662,6 @@ void ensure_batch_scratch(dynlp_ctx* c, int64_t nd, int64_t m, int64_t s) {
         c->touched = dev_alloc_n<int32_t>(c, cap);
         c->reloc_off = dev_alloc_n<int64_t>(c, cap);
         c->touched_cap = cap;
-    }
-    // optional (the insertion falls back to a second atomic per half-edge without it)
-    if (2 * m > c->he_rank_cap) {
-        dev_free(c, c->he_rank);
-        c->he_rank_cap = 0;
-        c->he_rank = static_cast<int32_t*>(dev_try_alloc(c, (size_t)(3 * m) * sizeof(int32_t)));
-        if (c->he_rank) c->he_rank_cap = 3 * m;
     }
     if (!c->dev_ptrs) {
         if (nd > c->b_del_cap) {
@@ -1025,6 +1022,84 @@ constexpr int64_t kSortLanes8 = 8, kSortRows8 = 131072;
 constexpr int64_t kPlanItems = (int64_t)2 << 20;  // touched rows from which the plan takes several per thread (k_plan_reserve)
 // Rounds in a row that repeat themselves exactly before the rows are averaged (see dynlp_apply_update).
 constexpr int kSameRounds = 16;
+
+// Optional (the insertion falls back to a second atomic per half-edge without it).
+void ensure_ranks(dynlp_ctx* c, int64_t m) {
+    if (2 * m <= c->he_rank_cap) return;
+    dev_free(c, c->he_rank);
+    c->he_rank_cap = 0;
+    c->he_rank = static_cast<int32_t*>(dev_try_alloc(c, (size_t)(3 * m) * sizeof(int32_t)));
+    if (c->he_rank) c->he_rank_cap = 3 * m;
+}
+
+// ---- insertion through bins (dynlp_insert.h) --------------------------------------------------------------------
+// Scratch of one batch: freed where the call has waited for the insertion.
+struct BinnedInsert {
+    dynlp_ctx* c;
+    bool on = false;
+    int bits = 0, nbins = 0, chunks = 0;
+    unsigned short* row = nullptr;
+    int32_t* col = nullptr;
+    float* w = nullptr;
+    unsigned int *table = nullptr, *bins = nullptr;  // bins: counts, offsets, first slices
+    explicit BinnedInsert(dynlp_ctx* ctx) : c(ctx) {}
+    BinnedInsert(const BinnedInsert&) = delete;
+    BinnedInsert& operator=(const BinnedInsert&) = delete;
+    ~BinnedInsert() {
+        if (row) (void)hipStreamSynchronize(c->stream);  // (a call that ends early)
+        release();
+    }
+    void release() {
+        void* const all[] = {row, col, w, table, bins};
+        for (void* p : all) dev_free(c, p);
+        row = nullptr;
+        col = nullptr;
+        w = nullptr;
+        table = bins = nullptr;
+    }
+    // From so many half-edges on (insertion in us, atomics / bins, 4 half-edges per row and 1 per row: 2^19 105 / 123 and 133 / 143,
+    // 2^20 169 / 152 and 235 / 217, 2^21 301 / 238 and 349 / 282, 2^22 629 / 448 and 739 / 597; a quarter per row: 2^20 307 / 308,
+    // 2^22 1052 / 934).
+    static constexpr int64_t kMinHalfEdges = (int64_t)1 << 21;
+    // Whether m edges into n rows go this way (no memory for it: no).
+    void choose(int64_t m, int64_t n) {
+        bits = kHbMaxBits;
+        while (bits > 11 && ceil_div(n, (int64_t)1 << bits) < 2 * c->num_cu) --bits;
+        if (2 * m < kMinHalfEdges || ceil_div(n, (int64_t)1 << bits) > kPbMaxBins) return;
+        nbins = (int)ceil_div(n, (int64_t)1 << bits);
+        chunks = (int)ceil_div(2 * m, kHbChunk);
+        row = static_cast<unsigned short*>(dev_try_alloc(c, (size_t)(2 * m) * sizeof(unsigned short)));
+        col = row ? static_cast<int32_t*>(dev_try_alloc(c, (size_t)(2 * m) * sizeof(int32_t))) : nullptr;
+        w = col ? static_cast<float*>(dev_try_alloc(c, (size_t)(2 * m) * sizeof(float))) : nullptr;
+        table = w ? static_cast<unsigned int*>(dev_try_alloc(c, ((size_t)chunks + 1 + kPbSegs) * nbins * sizeof(unsigned int))) : nullptr;
+        bins = table ? static_cast<unsigned int*>(dev_try_alloc(c, (3 * (size_t)nbins + 2) * sizeof(unsigned int))) : nullptr;
+        on = bins != nullptr;
+        if (!on) release();
+    }
+    unsigned int* offsets() const { return bins + nbins; }
+    unsigned int* slices() const { return bins + 2 * nbins + 1; }
+    unsigned int most_slices(int64_t m) const { return (unsigned int)(nbins + ceil_div(2 * m, kHbSlice)); }
+    void launch_count(int64_t m, int64_t n, const int32_t* eu, const int32_t* ev, const float* ew) {
+        hipLaunchKernelGGL(k_hb_count, dim3(chunks), dim3(kHbThreads), 0, c->stream, m, n, bits, nbins, eu, ev, table);
+        unsigned int* const seg = table + ((size_t)chunks + 1) * nbins;
+        const dim3 columns(grid_for(nbins), kPbSegs);
+        hipLaunchKernelGGL(k_pb_seg_sums, columns, dim3(kBlock), 0, c->stream, nbins, chunks, table, seg);
+        hipLaunchKernelGGL(k_pb_seg_scan, dim3(grid_for(nbins)), dim3(kBlock), 0, c->stream, nbins, chunks, seg, table, bins);
+        hipLaunchKernelGGL(k_pb_chunk_bases, columns, dim3(kBlock), 0, c->stream, nbins, chunks, seg, table);
+        hipLaunchKernelGGL(k_pb_offsets, dim3(1), dim3(kBlock), 0, c->stream, nbins, bins, offsets());
+        hipLaunchKernelGGL(k_hb_slices, dim3(1), dim3(kBlock), 0, c->stream, nbins, bins, slices());
+        int lg = 2;  // lanes per run: about as many as it has half-edges
+        while (lg < 10 && ((int64_t)nbins << lg) < kHbChunk) ++lg;
+        hipLaunchKernelGGL(k_hb_place, dim3(8 * (unsigned int)ceil_div(chunks, 8)), dim3(kHbThreads), 0, c->stream, m, n, bits, nbins, lg, eu,
+                           ev, ew, table, offsets(), row, col, w);
+        hipLaunchKernelGGL(k_hb_rows, dim3(most_slices(m)), dim3(kHbThreads), 0, c->stream, n, bits, nbins, offsets(), slices(), row, c->add_cnt);
+    }
+    void launch_write(int64_t m, int64_t n, const BatchGate& gate) {
+        HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hb_write), hipFuncAttributeMaxDynamicSharedMemorySize, 8 << kHbMaxBits));
+        hipLaunchKernelGGL(k_hb_write, dim3(most_slices(m)), dim3(kHbThreads), 8u << bits, c->stream, n, bits, nbins, offsets(), slices(), row,
+                           col, w, c->meta, c->pool, gate);
+    }
+};
 
 // ---- many rounds over a small V_aff in one launch (k_tail_rounds) -----------------------------------------------
 // One CU gathers about 0.4 rows per clock and looks up every neighbour it marks; the launches of an ordinary round take
@@ -3240,8 +3315,13 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         reset_timed_spans(c);
         // ---- capacity for new vertices; their rows start empty, unlabelled, uniform ----
         if (n1 > c->n_cap) alloc_vertex_arrays(c, n1 + std::max<int64_t>(n1 / 2, 1024));
+        BinnedInsert bins(c);
+        const bool in_order = m > 0 && 2 * m >= n1 / kInOrderShare;  // many of the rows are touched
         ensure_batch_scratch(c, nd, m, s);
-        const bool use_rank = c->he_rank != nullptr;
+        if (in_order && !pipelined) bins.choose(m, n1);
+        if (!bins.on) ensure_ranks(c, m);
+        // (with ranks the rows' lengths stay what they are until the rows are sorted)
+        const bool use_rank = !bins.on && c->he_rank != nullptr;
         const int32_t *d_eu = eu, *d_ev = ev, *d_sv = sv, *d_sc = sc, *d_del = del;
         const float* d_ew = ew;
         c->ingest_chunks_last = 0;
@@ -3306,15 +3386,16 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                                dim3(kBlock), 0, c->stream, c->bc, dropping, c->meta, c->pool, c->seed_class, c->add_cnt, c->deg);
         }
         // where many of the rows are touched, they are listed in the order of their ids after the counting
-        const bool in_order = m > 0 && 2 * m >= n1 / kInOrderShare;
         int32_t* const as_touched = in_order ? nullptr : c->touched;
         if (pipelined) {
             ingest_edges(c, m, n1, eu, ev, ew, as_touched);
         } else if (m + nd > 0) {
-            const unsigned int count_blocks = m > 0 ? grid_for(ceil_div(2 * m, kAppendItems)) : 0u;
-            hipLaunchKernelGGL(k_count_halfedges, dim3(count_blocks + (nd > 0 ? grid_for(nd) : 0u)), dim3(kBlock), 0, c->stream, m, n1,
-                               d_eu, d_ev, c->add_cnt, as_touched, c->bc, use_rank ? c->he_rank : nullptr,
-                               use_rank ? c->he_rank + m : nullptr, count_blocks, nd, d_del, c->seed_class);
+            if (bins.on) bins.launch_count(m, n1, d_eu, d_ev, d_ew);
+            const unsigned int count_blocks = m > 0 && !bins.on ? grid_for(ceil_div(2 * m, kAppendItems)) : 0u;
+            if (count_blocks > 0 || nd > 0)
+                hipLaunchKernelGGL(k_count_halfedges, dim3(count_blocks + (nd > 0 ? grid_for(nd) : 0u)), dim3(kBlock), 0, c->stream, m, n1,
+                                   d_eu, d_ev, c->add_cnt, as_touched, c->bc, use_rank ? c->he_rank : nullptr,
+                                   use_rank ? c->he_rank + m : nullptr, count_blocks, nd, d_del, c->seed_class);
         }
         if (in_order)
             hipLaunchKernelGGL(k_list_touched, dim3(grid_for(ceil_div(n1, 16))), dim3(kBlock), 0, c->stream, n1, c->add_cnt, c->touched, c->bc);
@@ -3337,8 +3418,10 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             if (m > 0) {
                 hipLaunchKernelGGL(k_relocate, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0, c->stream,
                                    c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->pool, gate);
-                hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
-                                   c->meta, c->pool, use_rank ? c->he_rank : nullptr, gate);
+                if (bins.on) bins.launch_write(m, n1, gate);
+                else
+                    hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
+                                       c->meta, c->pool, use_rank ? c->he_rank : nullptr, gate);
                 // the batch's entries of every row in a fixed order, then degree, scratch and V_aff flag of the row (the
                 // relocation offsets are no longer needed: their array holds the lists of rows with long appended segments
                 // and of hubs)
@@ -3366,8 +3449,14 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             if (c->h_bc->err || (int64_t)c->h_bc->pool_tail <= c->pool_cap) break;
             // the pool is too small for the plan and nothing has been inserted yet
             const int64_t tail = (int64_t)c->h_bc->pool_tail;
-            grow_pool(c, tail + (tail - c->pool_tail) / 2);
+            const int64_t larger = tail + (tail - c->pool_tail) / 2;
+            if (bins.on && !grow_pool(c, larger, false)) {
+                bins.release();  // the graph needs their memory: places from atomics on the rows' lengths
+                bins.on = false;
+            }
+            if (c->pool_cap < tail) grow_pool(c, larger);
         }
+        bins.release();
         if (c->h_bc->err) {
             c->n = n0;
             const unsigned int nt = c->h_bc->touched;
