@@ -3525,7 +3525,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             const int chain_off = (it - chain0) % kChain;
             const bool new_chain = chain_off == 0;
             if (new_chain) G = choose_group(c, avg_len);
-            if (!xcd_failed && !pingpong && xcd_rounds_pay(c, universe, G, false)) {
+            // (32,768 vertices, none of them labelled: relaxed and conjugate rounds are possible and stay first)
+            if (!xcd_failed && !pingpong && xcd_rounds_pay(c, universe, G, false) && !relaxed_rounds_pay(c, universe, c->tol)) {
                 const bool few = tail_rounds_pay(c, known, known_before, avg_len);  // (V_aff of one workgroup's size)
                 const size_t first_pair = c->events_used / 2;
                 run_xcd(c, G, cur, it, std::min<int>(kXcdRounds - chain_off, c->max_iter - it), c->F, in_place ? c->F : c->F2, false, lazy,
