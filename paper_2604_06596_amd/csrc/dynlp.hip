@@ -25,6 +25,7 @@
 #include "dynlp_binned.h"
 #include "dynlp_insert.h"
 #include "dynlp_packed.h"
+#include "dynlp_small.h"
 #include "dynlp_xcd.h"
 
 using namespace dynlp;
@@ -1020,6 +1021,14 @@ constexpr int64_t kInOrderShare = 8;
 // the chip is full either way (20,000 rows: 11 us with 16 lanes, 14 with 8).
 constexpr int64_t kSortLanes8 = 8, kSortRows8 = 131072;
 constexpr int64_t kPlanItems = (int64_t)2 << 20;  // touched rows from which the plan takes several per thread (k_plan_reserve)
+// Batches whose steps share launches of one workgroup each (dynlp_small.h).  Deleted rows are taken 64 at a time, those of more
+// than 128 entries one after the other; how many entries they have only the mean tells.
+bool small_batch(const dynlp_ctx* c, int64_t nd, int64_t k, int64_t m, int64_t s) {
+    constexpr int64_t kDeleted = 128, kDeletedEntries = 2048, kSeeds = 1024, kNewLabels = 16384;
+    return 2 * m <= kSmallHalfEdges && nd <= kDeleted && nd * c->entries <= kDeletedEntries * std::max<int64_t>(1, c->n) && s <= kSeeds &&
+           k * c->CP <= kNewLabels;
+}
+
 // Rounds in a row that repeat themselves exactly before the rows are averaged (see dynlp_apply_update).
 constexpr int kSameRounds = 16;
 
@@ -1869,20 +1878,6 @@ void launch_compact(dynlp_ctx* c, const Frontier& out, unsigned int* count_short
     HIPCHK(c, hipGetLastError());
 }
 
-// The first frontier of a batch (its size goes to the start slot) and the list of all updatable vertices.
-void launch_compact_start(dynlp_ctx* c, const Frontier& out, const Frontier& universe, const BatchGate& gate) {
-    // few vertices: more workgroups, each with one trip to memory; many: fewer additions to the four counters (us with 4 / 8 / 16
-    // steps: 100,000 vertices 6.9 / 9.1 / 14.7, 300,000 9.6 / 10.0 / 14.3, 1M 18.5 / 15.8 / 17.7, 3M - / 33.3 / 29.5)
-    const int steps = c->n >= (16 << 20) ? 64 : c->n >= (2 << 20) ? 16 : c->n >= (512 << 10) ? 8 : 4;
-    const unsigned int blocks = (unsigned int)ceil_div(std::max<int64_t>(c->n, 1), start_block_rows(steps));
-    auto kernel = steps == 64   ? k_compact_start<64>
-                  : steps == 16 ? k_compact_start<16>
-                  : steps == 8  ? k_compact_start<8>
-                                : k_compact_start<4>;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, c->stream, (unsigned int)c->n, c->flag, c->seed_class, c->meta, out.front,
-                       out.back, c->ring + kRing, universe.front, universe.back, c->bc, gate);
-}
-
 // After a staged round over `f`: commit and next list (`out`; its counts as for launch_compact).
 void launch_commit_compact(dynlp_ctx* c, const Frontier& f, const RoundCtr* prev, int64_t rows_bound, const Frontier& out,
                            unsigned int* count_short, unsigned int* count_long) {
@@ -1996,6 +1991,27 @@ void read_slots(dynlp_ctx* c, int t0, int count) {
 // The start slot and the batch counters, in one copy.
 void read_start(dynlp_ctx* c) {
     read_to_host(c, c->h_start, c->ring + kRing, sizeof(dynlp_ctx::HostStart));
+}
+
+// The first frontier of a batch (its size goes to the start slot) and the list of all updatable vertices; waits for their sizes.
+void launch_compact_start(dynlp_ctx* c, const Frontier& out, const Frontier& universe, const BatchGate& gate) {
+    // few vertices: more workgroups, each with one trip to memory; many: fewer additions to the four counters (us with 4 / 8 / 16
+    // steps: 100,000 vertices 6.9 / 9.1 / 14.7, 300,000 9.6 / 10.0 / 14.3, 1M 18.5 / 15.8 / 17.7, 3M - / 33.3 / 29.5)
+    const int steps = c->n >= (16 << 20) ? 64 : c->n >= (2 << 20) ? 16 : c->n >= (512 << 10) ? 8 : 4;
+    const unsigned int blocks = (unsigned int)ceil_div(std::max<int64_t>(c->n, 1), start_block_rows(steps));
+    auto kernel = steps == 64   ? k_compact_start<64>
+                  : steps == 16 ? k_compact_start<16>
+                  : steps == 8  ? k_compact_start<8>
+                                : k_compact_start<4>;
+    // the sizes go to the host with the last of few workgroups (many would queue for the counter that tells which is the last)
+    const bool send = blocks <= 256;
+    const StartToHost to{reinterpret_cast<unsigned long long*>(c->h_start), (unsigned int)(sizeof(dynlp_ctx::HostStart) / 8),
+                         send ? c->h_flag : nullptr, send ? ++c->h_sent : 0u};
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, c->stream, (unsigned int)c->n, c->flag, c->seed_class, c->meta, out.front,
+                       out.back, c->ring + kRing, universe.front, universe.back, c->bc, gate, to);
+    HIPCHK(c, hipGetLastError());
+    if (send) wait_for_flag(c, to.value);
+    else read_start(c);
 }
 
 void read_slots_start(dynlp_ctx* c) {
@@ -3327,6 +3343,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         if (!bins.on) ensure_ranks(c, m);
         // (with ranks the rows' lengths stay what they are until the rows are sorted)
         const bool use_rank = !bins.on && c->he_rank != nullptr;
+        bool small = !pipelined && !bins.on && small_batch(c, nd, k, m, s);
+        unsigned int pieces = 0;  // of 16 bytes: the batch in pinned memory, which k_small_check fetches
         const int32_t *d_eu = eu, *d_ev = ev, *d_sv = sv, *d_sc = sc, *d_del = del;
         const float* d_ew = ew;
         c->ingest_chunks_last = 0;
@@ -3350,7 +3368,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             if (together) {
                 for (int i = 0; i < 6; ++i)
                     if (count[i] > 0) std::memcpy(c->h_io + at[i], from[i], (size_t)count[i] * 4);
-                HIPCHK(c, hipMemcpyAsync(c->d_io, c->h_io, (size_t)bytes, hipMemcpyHostToDevice, c->stream));
+                if (small) pieces = (unsigned int)(bytes / 16);
+                else HIPCHK(c, hipMemcpyAsync(c->d_io, c->h_io, (size_t)bytes, hipMemcpyHostToDevice, c->stream));
             } else {
                 void* const to[6] = {c->b_eu, c->b_ev, c->b_ew, c->b_sv, c->b_sc, c->b_del};
                 for (int i = 0; i < 6; ++i)
@@ -3370,21 +3389,30 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         // graph look at the result of the checks and at the planned size of the pool themselves (BatchGate).  Deletions come
         // first; the whole batch is checked before anything changes ----
         const unsigned int zero_words = (unsigned int)((sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)) / sizeof(unsigned int));
-        hipLaunchKernelGGL(k_batch_begin, dim3(64), dim3(kBlock), 0, c->stream, reinterpret_cast<unsigned int*>(c->ring), zero_words,
-                           c->bc, (unsigned long long)c->pool_tail);
-        const int64_t checked = nd + (pipelined ? 0 : m) + s;
-        if (checked > 0)
-            hipLaunchKernelGGL(k_validate_batch, dim3(grid_for(checked)), dim3(kBlock), 0, c->stream, nd, d_del, pipelined ? 0 : m, d_eu,
-                               d_ev, d_ew, s, d_sv, d_sc, n1, n0, c->C, c->seed_class, c->add_cnt, c->bc);
-        if (nd + s + k > 0)
-            hipLaunchKernelGGL(k_batch_prepare, dim3(grid_for(nd + s + k)), dim3(kBlock), 0, c->stream, c->bc, nd, d_del, s, d_sv, n1,
-                               c->add_cnt, n0, k, c->meta, c->deg, c->seed_class);
+        int32_t* const dropping = reinterpret_cast<int32_t*>(c->reloc_off);  // (not in use before the plan)
+        SmallBatch sb{reinterpret_cast<const uint4*>(c->h_io), reinterpret_cast<uint4*>(c->d_io), pieces,
+                      reinterpret_cast<uint4*>(c->ring), (unsigned int)(sizeof(RoundCtr) * (kRing + 1) / 16), (unsigned long long)c->pool_tail, nd, m, s, k, n0, n1, d_del, d_eu,
+                      d_ev, d_sv, d_sc, d_ew, c->C, c->Cs, c->coff, c->CP, c->slack, c->bc, c->meta, c->pool, (unsigned long long)c->pool_cap,
+                      c->seed_class, c->add_cnt, c->touched, dropping, use_rank ? c->he_rank : nullptr, c->reloc_off, c->flag, c->deg, c->F};
+        if (small) {
+            hipLaunchKernelGGL(k_small_check, dim3(1 + kSmallClear), dim3(kSmallThreads), 0, c->stream, sb);
+        } else {
+            hipLaunchKernelGGL(k_batch_begin, dim3(64), dim3(kBlock), 0, c->stream, reinterpret_cast<unsigned int*>(c->ring), zero_words,
+                               c->bc, (unsigned long long)c->pool_tail);
+            const int64_t checked = nd + (pipelined ? 0 : m) + s;
+            if (checked > 0)
+                hipLaunchKernelGGL(k_validate_batch, dim3(grid_for(checked)), dim3(kBlock), 0, c->stream, nd, d_del, pipelined ? 0 : m, d_eu,
+                                   d_ev, d_ew, s, d_sv, d_sc, n1, n0, c->C, c->seed_class, c->add_cnt, c->bc);
+            if (nd + s + k > 0)
+                hipLaunchKernelGGL(k_batch_prepare, dim3(grid_for(nd + s + k)), dim3(kBlock), 0, c->stream, c->bc, nd, d_del, s, d_sv, n1,
+                                   c->add_cnt, n0, k, c->meta, c->deg, c->seed_class);
+        }
         const unsigned int most_blocks = (unsigned int)c->num_cu * 32;  // of kernels that find the number of their rows on the device
         if (nd > 0) {
             mutated = true;
-            int32_t* dropping = reinterpret_cast<int32_t*>(c->reloc_off);  // (not in use before the plan)
-            hipLaunchKernelGGL(k_delete_rows, dim3(grid_for(nd * 16)), dim3(kBlock), 0, c->stream, nd, d_del, c->C, c->Cs, c->CP,
-                               c->meta, c->pool, c->seed_class, c->flag, c->add_cnt, dropping, c->deg, c->F, c->bc);
+            if (!small)
+                hipLaunchKernelGGL(k_delete_rows, dim3(grid_for(nd * 16)), dim3(kBlock), 0, c->stream, nd, d_del, c->C, c->Cs, c->CP,
+                                   c->meta, c->pool, c->seed_class, c->flag, c->add_cnt, dropping, c->deg, c->F, c->bc);
             // (rows that lose entries: as many as the deleted rows have entries, which the host does not know; the mean tells)
             const double guess = 16.0 * (double)nd * std::max(1.0, (double)c->entries / (double)std::max<int64_t>(1, c->n));
             hipLaunchKernelGGL(k_drop_deleted_entries, dim3(std::min<unsigned int>(grid_for((int64_t)std::min(guess, 1e9)), most_blocks)),
@@ -3392,7 +3420,9 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         }
         // where many of the rows are touched, they are listed in the order of their ids after the counting
         int32_t* const as_touched = in_order ? nullptr : c->touched;
-        if (pipelined) {
+        if (small) {
+            if (m + nd + k > 0) hipLaunchKernelGGL(k_small_insert, dim3(1), dim3(kSmallThreads), 0, c->stream, sb);
+        } else if (pipelined) {
             ingest_edges(c, m, n1, eu, ev, ew, as_touched);
         } else if (m + nd > 0) {
             if (bins.on) bins.launch_count(m, n1, d_eu, d_ev, d_ew);
@@ -3402,11 +3432,11 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                                    d_eu, d_ev, c->add_cnt, as_touched, c->bc, use_rank ? c->he_rank : nullptr,
                                    use_rank ? c->he_rank + m : nullptr, count_blocks, nd, d_del, c->seed_class);
         }
-        if (in_order)
+        if (in_order && !small)
             hipLaunchKernelGGL(k_list_touched, dim3(grid_for(ceil_div(n1, 16))), dim3(kBlock), 0, c->stream, n1, c->add_cnt, c->touched, c->bc);
         // room at the pool tail for the rows whose slack is too small
         const int64_t most_touched = std::min<int64_t>(2 * m, n1);
-        if (m > 0)
+        if (m > 0 && !small)
             hipLaunchKernelGGL((most_touched >= kPlanItems ? k_plan_reserve<kAppendItems> : k_plan_reserve<1>),
                                dim3(std::min<unsigned int>(grid_for(ceil_div(most_touched, most_touched >= kPlanItems ? kAppendItems : 1)), most_blocks)),
                                dim3(kBlock), 0, c->stream, c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->bc);
@@ -3417,14 +3447,15 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         c->n = n1;
         for (;;) {
             const BatchGate gate{c->bc, (unsigned long long)c->pool_cap};
-            if (k > 0)
+            if (k > 0 && !small)
                 hipLaunchKernelGGL(k_init_labels, dim3(grid_for(k * c->CP)), dim3(kBlock), 0, c->stream, n0, n1, c->C, c->Cs, c->coff,
                                    c->CP, c->seed_class, c->F);
             if (m > 0) {
-                hipLaunchKernelGGL(k_relocate, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0, c->stream,
-                                   c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->pool, gate);
+                if (!small)
+                    hipLaunchKernelGGL(k_relocate, dim3(std::min<unsigned int>(grid_for(most_touched), most_blocks)), dim3(kBlock), 0,
+                                       c->stream, c->touched, c->meta, c->add_cnt, c->slack, c->reloc_off, c->pool, gate);
                 if (bins.on) bins.launch_write(m, n1, gate);
-                else
+                else if (!small)
                     hipLaunchKernelGGL(k_write_halfedges, dim3(grid_for(2 * m)), dim3(kBlock), 0, c->stream, m, d_eu, d_ev, d_ew,
                                        c->meta, c->pool, use_rank ? c->he_rank : nullptr, gate);
                 // the batch's entries of every row in a fixed order, then degree, scratch and V_aff flag of the row (the
@@ -3449,8 +3480,6 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 hipLaunchKernelGGL(k_apply_seeds, dim3(grid_for(s * 16)), dim3(kBlock), 0, c->stream, s, d_sv, d_sc, c->Cs, c->coff, c->CP,
                                    c->seed_class, c->F, c->meta, c->pool, c->flag, gate);
             launch_compact_start(c, frontier_of(c, 0), universe, gate);
-            HIPCHK(c, hipGetLastError());
-            read_start(c);
             if (c->h_bc->err || (int64_t)c->h_bc->pool_tail <= c->pool_cap) break;
             // the pool is too small for the plan and nothing has been inserted yet
             const int64_t tail = (int64_t)c->h_bc->pool_tail;
@@ -3460,6 +3489,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 bins.on = false;
             }
             if (c->pool_cap < tail) grow_pool(c, larger);
+            small = false;  // (sb has the old pool)
         }
         bins.release();
         if (c->h_bc->err) {

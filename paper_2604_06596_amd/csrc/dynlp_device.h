@@ -81,6 +81,7 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned long long removed;      // CSR entries removed by the deletion step
     unsigned int sort_long;          // touched rows whose appended segment is sorted by a whole workgroup
     unsigned int finish_hubs;        // hubs whose degree is summed by a whole workgroup
+    unsigned int lists_done;         // workgroups of k_compact_start that have done their part
 };
 
 // Rounds over all updatable rows (see accelerate in dynlp.hip).  kRoundAll: every updatable row is updated, whatever moved
@@ -159,13 +160,13 @@ __device__ inline T wave_inclusive_scan(T v) {
     return v;
 }
 
-// Exclusive scan over the kBlock threads of a workgroup; *total receives the block sum.
-// smem must hold kBlock / kWave + 1 elements.  Contains barriers: call from all threads.
-template <typename T>
+// Exclusive scan over the NT threads of a workgroup; *total receives the block sum.
+// smem must hold NT / kWave + 1 elements.  Contains barriers: call from all threads.
+template <typename T, int NT = kBlock>
 __device__ inline T block_exclusive_scan(T v, T* smem, T* total) {
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
-    constexpr int nw = kBlock / kWave;
+    constexpr int nw = NT / kWave;
     T inc = wave_inclusive_scan(v);
     if (lane == kWave - 1) smem[wave] = inc;
     __syncthreads();
@@ -186,12 +187,13 @@ __device__ inline T block_exclusive_scan(T v, T* smem, T* total) {
 }
 
 // Append-slot reservation with one atomic per workgroup: every thread asks for `count` consecutive
-// slots (0 allowed) and gets the index of its first one.  smem must hold kBlock / kWave + 1 elements.
+// slots (0 allowed) and gets the index of its first one.  smem must hold NT / kWave + 1 elements.
 // Contains barriers: call from all threads of the workgroup.
+template <int NT = kBlock>
 __device__ inline unsigned int block_reserve(unsigned int* counter, unsigned int count, unsigned int* smem) {
     __shared__ unsigned int base;
     unsigned int total;
-    const unsigned int ex = block_exclusive_scan<unsigned int>(count, smem, &total);
+    const unsigned int ex = block_exclusive_scan<unsigned int, NT>(count, smem, &total);
     if (threadIdx.x == 0) base = total ? atomicAdd(counter, total) : 0u;
     __syncthreads();
     const unsigned int r = base + ex;

@@ -123,19 +123,41 @@ __global__ void __launch_bounds__(kBlock) k_compact(unsigned int n, uint8_t* __r
 // 8.9 / 5.3, 20,000 11.1 / 6.1, 100,000 12.1 / 6.9, 1M 19.8 / 15.8, 3M 78 / 30, 50M 1,885 / 329.)
 constexpr int start_block_rows(int steps) { return steps * kBlock; }
 
+// `words` words of 8 bytes from the start slot on for the host (pinned memory), then *flag = value; flag NULL: nothing.
+struct StartToHost {
+    unsigned long long* host;
+    unsigned int words;
+    unsigned int* flag;
+    unsigned int value;
+};
+
+// The last workgroup of a launch to get here sends what k_to_host otherwise sends in a launch of its own.  (The others' counters
+// have been added by then: each workgroup has waited for what its additions returned.  They are read at device scope.)
+__device__ inline void send_start(RoundCtr* start, BatchCtr* bc, const StartToHost& to) {
+    __shared__ bool last;
+    if (threadIdx.x == 0) last = atomicAdd(&bc->lists_done, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    unsigned long long* const from = reinterpret_cast<unsigned long long*>(start);
+    for (unsigned int i = threadIdx.x; i < to.words; i += kBlock)
+        to.host[i] = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        bc->lists_done = 0u;  // (the lists are made again where the pool was too small)
+        __hip_atomic_store(to.flag, to.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 template <int STEPS>
-__global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_t* __restrict__ flag,
-                                                         const int32_t* __restrict__ seed_class,
-                                                         const RowMeta* __restrict__ meta, int32_t* __restrict__ front,
-                                                         int32_t* __restrict__ back, RoundCtr* __restrict__ start,
-                                                         int32_t* __restrict__ ufront, int32_t* __restrict__ uback, BatchCtr* bc,
-                                                         BatchGate gate) {
+__device__ inline void compact_start(unsigned int n, uint8_t* __restrict__ flag, const int32_t* __restrict__ seed_class,
+                                     const RowMeta* __restrict__ meta, int32_t* __restrict__ front, int32_t* __restrict__ back,
+                                     RoundCtr* __restrict__ start, int32_t* __restrict__ ufront, int32_t* __restrict__ uback, BatchCtr* bc) {
     constexpr int UN = STEPS < 8 ? STEPS : 8;
     static_assert(STEPS <= kWave && STEPS % UN == 0, "a lane per step");
     static_assert(start_block_rows(STEPS) < 65536, "four counts in one 64-bit scan");
     __shared__ unsigned long long sm[kBlock / kWave + 1];
     __shared__ unsigned int sbase[4];
-    if (gate.closed()) return;
     const int lane = lane_id();
     const unsigned int w0 = (blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave) * (STEPS * kWave) + lane;
     unsigned long long listed = 0, keep = 0, is_long = 0;  // of step `lane`; bit l: lane l's vertex is updatable / flagged too / a long row
@@ -199,6 +221,16 @@ __global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_
             if (f) front[a0 + __popcll(bk & ~bg & below)] = v;
         }
     }
+}
+
+template <int STEPS>
+__global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_t* __restrict__ flag,
+                                                         const int32_t* __restrict__ seed_class,
+                                                         const RowMeta* __restrict__ meta, int32_t* __restrict__ front,
+                                                         int32_t* __restrict__ back, RoundCtr* start, int32_t* __restrict__ ufront,
+                                                         int32_t* __restrict__ uback, BatchCtr* bc, BatchGate gate, StartToHost to) {
+    if (!gate.closed()) compact_start<STEPS>(n, flag, seed_class, meta, front, back, start, ufront, uback, bc);
+    if (to.flag) send_start(start, bc, to);
 }
 
 // =================================================================================================

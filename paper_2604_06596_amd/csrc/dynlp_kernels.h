@@ -117,10 +117,8 @@ __global__ void __launch_bounds__(kBlock) k_row_degree(int64_t n, const RowMeta*
 // Rows [u0, u1): seed rows one-hot, others uniform 1/C, padding columns 0.
 // Stored column c holds class c + coff: coff = 0 and Cs = C normally; the binary scalar layout
 // (C = 2) stores only class 1 (Cs = 1, coff = 1), class 0 being 1 - F_u.
-__global__ void __launch_bounds__(kBlock) k_init_labels(int64_t u0, int64_t u1, int C, int Cs, int coff, int CP,
-                                                       const int32_t* __restrict__ seed_class,
-                                                       float* __restrict__ F) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+__device__ inline void init_label(int64_t i, int64_t u0, int64_t u1, int C, int Cs, int coff, int CP,
+                                  const int32_t* __restrict__ seed_class, float* __restrict__ F) {
     const int64_t u = u0 + i / CP;
     const int c = (int)(i % CP);
     if (u >= u1) return;
@@ -128,6 +126,12 @@ __global__ void __launch_bounds__(kBlock) k_init_labels(int64_t u0, int64_t u1, 
     float v = 0.f;
     if (c < Cs) v = sc < 0 ? 1.0f / (float)C : (c + coff == sc ? 1.0f : 0.0f);
     F[u * CP + c] = v;
+}
+
+__global__ void __launch_bounds__(kBlock) k_init_labels(int64_t u0, int64_t u1, int C, int Cs, int coff, int CP,
+                                                       const int32_t* __restrict__ seed_class,
+                                                       float* __restrict__ F) {
+    init_label((int64_t)blockIdx.x * kBlock + threadIdx.x, u0, u1, C, Cs, coff, CP, seed_class, F);
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill_i32(int64_t u0, int64_t u1, int32_t* __restrict__ a, int32_t v) {
@@ -272,23 +276,25 @@ __global__ void __launch_bounds__(kBlock) k_validate_edges(int64_t m, int64_t n_
 
 // ---- the steps of a batch that come before its edges are inserted -----------------------------------------------------
 // All counters a batch uses: `words` 32-bit words from `zero` on are cleared, then the pool's tail is set.
-__global__ void __launch_bounds__(kBlock) k_batch_begin(unsigned int* __restrict__ zero, unsigned int words,
-                                                       BatchCtr* bc, unsigned long long pool_tail) {
-    for (unsigned int i = blockIdx.x * kBlock + threadIdx.x; i < words; i += gridDim.x * kBlock) {
+__device__ inline void batch_begin(unsigned int first, unsigned int step, unsigned int* __restrict__ zero, unsigned int words,
+                                   const BatchCtr* bc, unsigned long long pool_tail) {
+    for (unsigned int i = first; i < words; i += step) {
         const unsigned int* tail = reinterpret_cast<const unsigned int*>(&bc->pool_tail);
         zero[i] = zero + i == tail ? (unsigned int)pool_tail : zero + i == tail + 1 ? (unsigned int)(pool_tail >> 32) : 0u;
     }
 }
 
+__global__ void __launch_bounds__(kBlock) k_batch_begin(unsigned int* __restrict__ zero, unsigned int words,
+                                                       BatchCtr* bc, unsigned long long pool_tail) {
+    batch_begin(blockIdx.x * kBlock + threadIdx.x, gridDim.x * kBlock, zero, words, bc, pool_tail);
+}
+
 // Every argument of a batch: nd deleted vertices, then m edges, then s seeds.
-__global__ void __launch_bounds__(kBlock) k_validate_batch(int64_t nd, const int32_t* __restrict__ del, int64_t m,
-                                                          const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
-                                                          const float* __restrict__ ew, int64_t s,
-                                                          const int32_t* __restrict__ sv, const int32_t* __restrict__ sc,
-                                                          int64_t n_total, int64_t n_existing, int C,
-                                                          const int32_t* __restrict__ seed_class, int32_t* __restrict__ tmp,
-                                                          BatchCtr* bc) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+__device__ inline void validate_batch_item(int64_t i, int64_t nd, const int32_t* __restrict__ del, int64_t m,
+                                           const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, const float* __restrict__ ew,
+                                           int64_t s, const int32_t* __restrict__ sv, const int32_t* __restrict__ sc, int64_t n_total,
+                                           int64_t n_existing, int C, const int32_t* __restrict__ seed_class, int32_t* __restrict__ tmp,
+                                           BatchCtr* bc) {
     if (i < nd) {
         if (del[i] < 0 || del[i] >= n_existing) report_error(bc, kErrDeleted, i);
         return;
@@ -302,16 +308,24 @@ __global__ void __launch_bounds__(kBlock) k_validate_batch(int64_t nd, const int
     if (i < s) validate_seed(i, n_total, n_existing, C, sv, sc, seed_class, tmp, bc);
 }
 
+__global__ void __launch_bounds__(kBlock) k_validate_batch(int64_t nd, const int32_t* __restrict__ del, int64_t m,
+                                                          const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                                          const float* __restrict__ ew, int64_t s,
+                                                          const int32_t* __restrict__ sv, const int32_t* __restrict__ sc,
+                                                          int64_t n_total, int64_t n_existing, int C,
+                                                          const int32_t* __restrict__ seed_class, int32_t* __restrict__ tmp,
+                                                          BatchCtr* bc) {
+    validate_batch_item((int64_t)blockIdx.x * kBlock + threadIdx.x, nd, del, m, eu, ev, ew, s, sv, sc, n_total, n_existing, C, seed_class,
+                        tmp, bc);
+}
+
 constexpr int32_t kDeletedMark = -2;  // seed_class value of a vertex while its batch deletes it
 
 // Deleted vertices marked (nd of them, if the checks have passed), the seeds' scratch cleared (s), empty rows for the new ids
 // n0 .. n0 + k - 1 (they are nobody's until the batch is done).
-__global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, int64_t nd, const int32_t* __restrict__ del,
-                                                         int64_t s, const int32_t* __restrict__ sv, int64_t n_total,
-                                                         int32_t* __restrict__ tmp, int64_t n0, int64_t k,
-                                                         RowMeta* __restrict__ meta, float* __restrict__ deg,
-                                                         int32_t* __restrict__ seed_class) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+__device__ inline void batch_prepare_item(int64_t i, const BatchCtr* bc, int64_t nd, const int32_t* __restrict__ del, int64_t s,
+                                          const int32_t* __restrict__ sv, int64_t n_total, int32_t* __restrict__ tmp, int64_t n0, int64_t k,
+                                          RowMeta* __restrict__ meta, float* __restrict__ deg, int32_t* __restrict__ seed_class) {
     if (i < nd) {
         if (bc->err == 0) seed_class[del[i]] = kDeletedMark;
         return;
@@ -334,6 +348,14 @@ __global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, in
     }
 }
 
+__global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, int64_t nd, const int32_t* __restrict__ del,
+                                                         int64_t s, const int32_t* __restrict__ sv, int64_t n_total,
+                                                         int32_t* __restrict__ tmp, int64_t n0, int64_t k,
+                                                         RowMeta* __restrict__ meta, float* __restrict__ deg,
+                                                         int32_t* __restrict__ seed_class) {
+    batch_prepare_item((int64_t)blockIdx.x * kBlock + threadIdx.x, bc, nd, del, s, sv, n_total, tmp, n0, k, meta, deg, seed_class);
+}
+
 // Half-edge i < m has source eu[i]; half-edge m + i has source ev[i].  Count the entries each row
 // will receive and list every row that receives any ("touched" rows).  Out-of-range sources are
 // skipped (the validation kernel reports them).  A workgroup takes kAppendItems * kBlock half-edges
@@ -341,26 +363,17 @@ __global__ void __launch_bounds__(kBlock) k_batch_prepare(const BatchCtr* bc, in
 // rank_u / rank_v (both or neither): what the counting atomic returned for half-edge i / m + i, i.e. the
 // half-edge's place among the entries this batch appends to its row; k_write_halfedges then needs no second atomic.
 // touched NULL: only counted, the rows are listed afterwards (k_list_touched).
-// Workgroups from count_blocks on take the marks from the nd deleted vertices again (if the checks have passed).
-__global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
-                                                           const int32_t* __restrict__ ev,
-                                                           int32_t* __restrict__ add_cnt,
-                                                           int32_t* __restrict__ touched, BatchCtr* bc,
-                                                           int32_t* __restrict__ rank_u, int32_t* __restrict__ rank_v,
-                                                           unsigned int count_blocks, int64_t nd,
-                                                           const int32_t* __restrict__ del, int32_t* __restrict__ seed_class) {
-    __shared__ unsigned int smem[kBlock / kWave + 1];
-    if (blockIdx.x >= count_blocks) {
-        const int64_t i = (int64_t)(blockIdx.x - count_blocks) * kBlock + threadIdx.x;
-        if (i < nd && bc->err == 0) seed_class[del[i]] = -1;
-        return;
-    }
-    const int64_t base = (int64_t)blockIdx.x * kBlock * kAppendItems;
-    int32_t srcs[kAppendItems];
+// One step of one workgroup: ITEMS * NT half-edges from `base` on.
+template <int NT, int ITEMS>
+__device__ inline void count_halfedges(int64_t base, int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
+                                       const int32_t* __restrict__ ev, int32_t* __restrict__ add_cnt, int32_t* __restrict__ touched,
+                                       BatchCtr* bc, int32_t* __restrict__ rank_u, int32_t* __restrict__ rank_v) {
+    __shared__ unsigned int smem[NT / kWave + 1];
+    int32_t srcs[ITEMS];
     unsigned int firstmask = 0;
 #pragma unroll
-    for (int k = 0; k < kAppendItems; ++k) {
-        const int64_t i = base + (int64_t)k * kBlock + threadIdx.x;
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t i = base + (int64_t)k * NT + threadIdx.x;
         int32_t src = -1;
         if (i < 2 * m) {
             src = i < m ? eu[i] : ev[i - m];
@@ -373,10 +386,27 @@ __global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n
         srcs[k] = src;
     }
     if (!touched) return;
-    unsigned int slot = block_reserve(&bc->touched, (unsigned int)__popc(firstmask), smem);
+    unsigned int slot = block_reserve<NT>(&bc->touched, (unsigned int)__popc(firstmask), smem);
 #pragma unroll
-    for (int k = 0; k < kAppendItems; ++k)
+    for (int k = 0; k < ITEMS; ++k)
         if ((firstmask >> k) & 1u) touched[slot++] = srcs[k];
+}
+
+// Workgroups from count_blocks on take the marks from the nd deleted vertices again (if the checks have passed).
+__global__ void __launch_bounds__(kBlock) k_count_halfedges(int64_t m, int64_t n_total, const int32_t* __restrict__ eu,
+                                                           const int32_t* __restrict__ ev,
+                                                           int32_t* __restrict__ add_cnt,
+                                                           int32_t* __restrict__ touched, BatchCtr* bc,
+                                                           int32_t* __restrict__ rank_u, int32_t* __restrict__ rank_v,
+                                                           unsigned int count_blocks, int64_t nd,
+                                                           const int32_t* __restrict__ del, int32_t* __restrict__ seed_class) {
+    if (blockIdx.x >= count_blocks) {
+        const int64_t i = (int64_t)(blockIdx.x - count_blocks) * kBlock + threadIdx.x;
+        if (i < nd && bc->err == 0) seed_class[del[i]] = -1;
+        return;
+    }
+    count_halfedges<kBlock, kAppendItems>((int64_t)blockIdx.x * kBlock * kAppendItems, m, n_total, eu, ev, add_cnt, touched, bc, rank_u,
+                                          rank_v);
 }
 
 // The rows that receive entries, in runs of ascending ids: rows that move to the pool's tail then lie there in the order of
@@ -410,18 +440,16 @@ __global__ void __launch_bounds__(kBlock) k_list_touched(int64_t n, const int32_
 // Rows whose slack cannot take the new entries get room at the pool tail (one tail atomic per workgroup: atomics
 // on one address run at about 1e8 per second); reloc_off[t] is the new offset or -1.  Touches no row: bc->pool_tail
 // afterwards tells the host how large the pool has to be before k_relocate may run.
-template <int ITEMS>
-__global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restrict__ touched,
-                                                        const RowMeta* __restrict__ meta,
-                                                        const int32_t* __restrict__ add_cnt, float slack,
-                                                        int64_t* __restrict__ reloc_off, BatchCtr* bc) {
-    __shared__ unsigned long long smem[kBlock / kWave + 1];
+template <int NT, int ITEMS>
+__device__ inline void plan_reserve(const int32_t* __restrict__ touched, const RowMeta* __restrict__ meta,
+                                    const int32_t* __restrict__ add_cnt, float slack, int64_t* __restrict__ reloc_off, BatchCtr* bc) {
+    __shared__ unsigned long long smem[NT / kWave + 1];
     __shared__ unsigned long long sbase;
     if (bc->err) return;
     const unsigned int nt = bc->touched;
     // ITEMS rows per thread: with one, 195,000 workgroups queue for the tail when 50M rows are touched (4.6 ms, with 8 1.4);
     // with 8, a few hundred thousand rows keep too few lanes busy (400,000: 6 us with one, 14 with 8)
-    for (unsigned int t0 = blockIdx.x * kBlock * ITEMS; t0 < nt; t0 += gridDim.x * kBlock * ITEMS) {  // uniform in the workgroup
+    for (unsigned int t0 = blockIdx.x * NT * ITEMS; t0 < nt; t0 += gridDim.x * NT * ITEMS) {  // uniform in the workgroup
         unsigned int caps[ITEMS];
         unsigned long long cap = 0;
         unsigned int moved = 0;
@@ -439,8 +467,8 @@ __global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restri
             moved += caps[k] ? 1u : 0u;
         }
         unsigned long long total, rows;
-        unsigned long long at = block_exclusive_scan<unsigned long long>(cap, smem, &total);
-        (void)block_exclusive_scan<unsigned long long>(moved, smem, &rows);
+        unsigned long long at = block_exclusive_scan<unsigned long long, NT>(cap, smem, &total);
+        (void)block_exclusive_scan<unsigned long long, NT>(moved, smem, &rows);
         if (threadIdx.x == 0) {
             sbase = total ? atomicAdd(&bc->pool_tail, total) : 0ull;
             if (rows) atomicAdd(&bc->relocated, (unsigned int)rows);
@@ -457,16 +485,23 @@ __global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restri
     }
 }
 
+template <int ITEMS>
+__global__ void __launch_bounds__(kBlock) k_plan_reserve(const int32_t* __restrict__ touched,
+                                                        const RowMeta* __restrict__ meta,
+                                                        const int32_t* __restrict__ add_cnt, float slack,
+                                                        int64_t* __restrict__ reloc_off, BatchCtr* bc) {
+    plan_reserve<kBlock, ITEMS>(touched, meta, add_cnt, slack, reloc_off, bc);
+}
+
 // Give every relocated row its new place.  One lane per touched row; rows that already hold entries (few, but
 // hubs among them) are copied by the whole wave, one row after the other.
-__global__ void __launch_bounds__(kBlock) k_relocate(const int32_t* __restrict__ touched,
-                                                    RowMeta* __restrict__ meta, const int32_t* __restrict__ add_cnt,
-                                                    float slack, const int64_t* __restrict__ reloc_off,
-                                                    Edge* __restrict__ pool, BatchGate gate) {
+template <int NT>
+__device__ inline void relocate_rows(const int32_t* __restrict__ touched, RowMeta* __restrict__ meta, const int32_t* __restrict__ add_cnt,
+                                     float slack, const int64_t* __restrict__ reloc_off, Edge* __restrict__ pool, const BatchGate& gate) {
     if (gate.closed()) return;
     const unsigned int nt = gate.bc->touched;
     const int lane = lane_id();
-    for (unsigned int t0 = blockIdx.x * kBlock; t0 < nt; t0 += gridDim.x * kBlock) {
+    for (unsigned int t0 = blockIdx.x * NT; t0 < nt; t0 += gridDim.x * NT) {
         const unsigned int t = t0 + threadIdx.x;
         const int64_t noff = t < nt ? reloc_off[t] : -1;
         int64_t ooff = 0;
@@ -493,17 +528,20 @@ __global__ void __launch_bounds__(kBlock) k_relocate(const int32_t* __restrict__
     }
 }
 
+__global__ void __launch_bounds__(kBlock) k_relocate(const int32_t* __restrict__ touched,
+                                                    RowMeta* __restrict__ meta, const int32_t* __restrict__ add_cnt,
+                                                    float slack, const int64_t* __restrict__ reloc_off,
+                                                    Edge* __restrict__ pool, BatchGate gate) {
+    relocate_rows<kBlock>(touched, meta, add_cnt, slack, reloc_off, pool, gate);
+}
+
 // Append both directions of every new edge.  With ranks (k_count_halfedges): the entry goes to position
 // len + rank of its row and the row's length stays as it was (k_sort_finish adds the batch's count); without: the
 // position comes from an atomic on the length.  Either way the order of one batch's entries inside a row is
 // unspecified until they are sorted.
-__global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int32_t* __restrict__ eu,
-                                                           const int32_t* __restrict__ ev,
-                                                           const float* __restrict__ ew, RowMeta* __restrict__ meta,
-                                                           Edge* __restrict__ pool, const int32_t* __restrict__ rank,
-                                                           BatchGate gate) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= 2 * m || gate.closed()) return;
+__device__ inline void write_halfedge(int64_t i, int64_t m, const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                      const float* __restrict__ ew, RowMeta* __restrict__ meta, Edge* __restrict__ pool,
+                                      const int32_t* __restrict__ rank) {
     const int64_t k = i < m ? i : i - m;
     const int32_t src = i < m ? eu[k] : ev[k];
     const int32_t dst = i < m ? ev[k] : eu[k];
@@ -517,6 +555,16 @@ __global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int
         const int slot = atomicAdd(&meta[src].len, 1);
         pool[meta[src].off + slot] = e;
     }
+}
+
+__global__ void __launch_bounds__(kBlock) k_write_halfedges(int64_t m, const int32_t* __restrict__ eu,
+                                                           const int32_t* __restrict__ ev,
+                                                           const float* __restrict__ ew, RowMeta* __restrict__ meta,
+                                                           Edge* __restrict__ pool, const int32_t* __restrict__ rank,
+                                                           BatchGate gate) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= 2 * m || gate.closed()) return;
+    write_halfedge(i, m, eu, ev, ew, meta, pool, rank);
 }
 
 // d(u) of a row by a whole workgroup, added in the order in which a 16-lane group adds it (lane j mod 16 takes entry j, then
@@ -858,21 +906,19 @@ __global__ void __launch_bounds__(kBlock) k_clear_counts(unsigned int nt, const 
 // longer rows are left to the whole workgroup (a hub of 50,000 entries walked by 16 lanes took 1.2 ms).
 constexpr int kDeleteRegs = 8;  // entries per lane: rows of up to 128
 
-__global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_t* __restrict__ del, int C, int Cs, int CP,
-                                                       RowMeta* meta, const Edge* __restrict__ pool,
-                                                       const int32_t* __restrict__ seed_class,
-                                                       uint8_t* __restrict__ flag, int32_t* __restrict__ add_cnt,
-                                                       int32_t* __restrict__ dropping, float* __restrict__ deg,
-                                                       float* __restrict__ F, BatchCtr* bc) {
+template <int NT>
+__device__ inline void delete_rows(unsigned int block, int64_t nd, const int32_t* __restrict__ del, int C, int Cs, int CP, RowMeta* meta,
+                                   const Edge* __restrict__ pool, const int32_t* __restrict__ seed_class, uint8_t* __restrict__ flag,
+                                   int32_t* __restrict__ add_cnt, int32_t* __restrict__ dropping, float* __restrict__ deg,
+                                   float* __restrict__ F, BatchCtr* bc) {
     constexpr int G = 16;
-    if (bc->err) return;
-    __shared__ unsigned int smem[kBlock / kWave + 1];
-    __shared__ int64_t long_off[kBlock / G];
-    __shared__ int long_len[kBlock / G];
+    __shared__ unsigned int smem[NT / kWave + 1];
+    __shared__ int64_t long_off[NT / G];
+    __shared__ int long_len[NT / G];
     __shared__ unsigned int nlong;
     if (threadIdx.x == 0) nlong = 0u;
     __syncthreads();
-    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
+    const int64_t i = ((int64_t)block * NT + threadIdx.x) / G;
     const int gl = threadIdx.x % G;
     int len = 0;
     int64_t off = 0;
@@ -909,14 +955,14 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
             removed += 1;  // the entry v -> u goes as well
             if (atomicAdd(&add_cnt[v[q]], 1) == 0) first |= 1u << q;
         }
-        unsigned int slot = block_reserve(&bc->dropping, (unsigned int)__popc(first), smem);
+        unsigned int slot = block_reserve<NT>(&bc->dropping, (unsigned int)__popc(first), smem);
 #pragma unroll
         for (int q = 0; q < kDeleteRegs; ++q)
             if ((first >> q) & 1u) dropping[slot++] = v[q];
     };
     take(off, gl, G, len);
     for (unsigned int k = 0; k < nlong; ++k)  // uniform in the workgroup (block_reserve has barriers)
-        for (int base = 0; base < long_len[k]; base += kDeleteRegs * kBlock) take(long_off[k], base + (int)threadIdx.x, kBlock, long_len[k]);
+        for (int base = 0; base < long_len[k]; base += kDeleteRegs * NT) take(long_off[k], base + (int)threadIdx.x, NT, long_len[k]);
     removed = wave_sum(removed);
     __shared__ unsigned long long block_removed;
     if (threadIdx.x == 0) block_removed = 0ull;
@@ -924,6 +970,16 @@ __global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_
     if (lane_id() == 0) atomicAdd(&block_removed, removed);
     __syncthreads();
     if (threadIdx.x == 0 && block_removed) atomicAdd(&bc->removed, block_removed);
+}
+
+__global__ void __launch_bounds__(kBlock) k_delete_rows(int64_t nd, const int32_t* __restrict__ del, int C, int Cs, int CP,
+                                                       RowMeta* meta, const Edge* __restrict__ pool,
+                                                       const int32_t* __restrict__ seed_class,
+                                                       uint8_t* __restrict__ flag, int32_t* __restrict__ add_cnt,
+                                                       int32_t* __restrict__ dropping, float* __restrict__ deg,
+                                                       float* __restrict__ F, BatchCtr* bc) {
+    if (bc->err) return;
+    delete_rows<kBlock>(blockIdx.x, nd, del, C, Cs, CP, meta, pool, seed_class, flag, add_cnt, dropping, deg, F, bc);
 }
 
 // Rows that lose entries (listed by k_delete_rows): drop the entries that point at deleted vertices, keeping the order of the others,
