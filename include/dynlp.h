@@ -66,9 +66,9 @@ typedef struct dynlp_stats {
     int64_t update_launches;  /* launches of the row-update kernel */
     float ms_update_kernel;   /* summed device time of those launches (HIP events on the stream);
                                  0 unless dynlp_options.time_kernels is set */
-    float ms_insert;          /* validation + edge insertion + degree update */
-    float ms_seed;            /* seed clamping + frontier seeding + first compaction */
-    float ms_iterate;         /* the propagation loop */
+    float ms_insert;          /* validation + edge insertion + degree update (device clock) */
+    float ms_seed;            /* seed clamping + frontier seeding + first compaction, and the host's wait for them */
+    float ms_iterate;         /* the propagation loop (host clock) */
     float ms_total;           /* whole call, host wall clock */
     int32_t final_checks;     /* rounds over all updatable rows that dynlp_set_final_check added (0 when it is off) */
     int32_t ingest_chunks;    /* chunks a host-resident edge list was sent in while earlier chunks were being validated

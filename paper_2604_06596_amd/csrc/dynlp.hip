@@ -253,7 +253,7 @@ struct dynlp_ctx {
     bool ev_adjacent = false;             // set by a caller: nothing was queued since the previous span was closed
     std::vector<int> ev_round, ev_count;  // rounds [ev_round[k], ev_round[k] + ev_count[k]) ran inside the k-th launch;
                                           // ev_round[k] < 0: the launch found nothing to do (queued past the end)
-    hipEvent_t phase_ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    int clock_khz = 0;  // of wall_clock64
     std::string err;
     bool poisoned = false;
 };
@@ -2521,8 +2521,6 @@ void destroy_ctx(dynlp_ctx* c) {
     }
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
-    for (hipEvent_t e : c->phase_ev)
-        if (e) (void)hipEventDestroy(e);
     delete c;
     (void)release_kept(kKeepMs);
 }
@@ -2766,7 +2764,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->h_xcd = reinterpret_cast<XcdResult*>(fixed + kSlotBytes + kStartBytes);
         c->h_flag = reinterpret_cast<unsigned int*>(fixed + kSlotBytes + kStartBytes + kResultBytes);
         *c->h_flag = 0u;
-        for (auto& e : c->phase_ev) HIPCHK(c, hipEventCreate(&e));
+        HIPCHK(c, hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, c->device));
         std::memset(c->h_bc, 0, sizeof(BatchCtr));
         write_bc(c);
         zero_ring(c);
@@ -3383,12 +3381,12 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             d_sc = static_cast<int32_t*>(where(4, c->b_sc));
             d_del = static_cast<int32_t*>(where(5, c->b_del));
         }
-        HIPCHK(c, hipEventRecord(c->phase_ev[0], c->stream));
+        const auto step1 = Clock::now();
 
         // ---- Alg. 2 Step 1.  Everything up to the first list of rows is queued without a wait: the kernels that change the
         // graph look at the result of the checks and at the planned size of the pool themselves (BatchGate).  Deletions come
         // first; the whole batch is checked before anything changes ----
-        const unsigned int zero_words = (unsigned int)((sizeof(RoundCtr) * (kRing + 1) + sizeof(BatchCtr)) / sizeof(unsigned int));
+        const unsigned int zero_words = (unsigned int)((sizeof(RoundCtr) * (kRing + 1)) / sizeof(unsigned int)) + kBatchClear;
         int32_t* const dropping = reinterpret_cast<int32_t*>(c->reloc_off);  // (not in use before the plan)
         SmallBatch sb{reinterpret_cast<const uint4*>(c->h_io), reinterpret_cast<uint4*>(c->d_io), pieces,
                       reinterpret_cast<uint4*>(c->ring), (unsigned int)(sizeof(RoundCtr) * (kRing + 1) / 16), (unsigned long long)c->pool_tail, nd, m, s, k, n0, n1, d_del, d_eu,
@@ -3473,7 +3471,6 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
                 hipLaunchKernelGGL(k_sort_long_segments, dim3((unsigned int)std::max<int64_t>(1, std::min<int64_t>(most_touched, 512))), dim3(kSortThreads), 0,
                                    c->stream, f);
             }
-            HIPCHK(c, hipEventRecord(c->phase_ev[1], c->stream));
             // seeds: clamp one-hot, their neighbours join V_aff; first frontier from the flags (its size goes to the start
             // slot), and the list of all updatable vertices
             if (s > 0)
@@ -3502,11 +3499,14 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         c->entries += 2 * m - (int64_t)c->h_bc->removed;
         c->pool_tail = (int64_t)c->h_bc->pool_tail;
         const int64_t relocated = c->h_bc->relocated;
+        const auto listed = Clock::now();
         if (c->init_mode == DYNLP_INIT_SUPERNODE && k > 0) run_supernode_init(c, n0, k, m, d_eu, d_ev, d_ew);
         universe.ns = c->h_bc->upd_short;
         universe.nl = c->h_bc->upd_long;
         unsigned int known = c->h_start->start.next_count + c->h_start->start.next_long;  // |V_aff| the host knows of
-        HIPCHK(c, hipEventRecord(c->phase_ev[2], c->stream));
+        // (the host has just waited for Step 1 and will wait for Step 3, so its clock does; four events in the stream and what they
+        // are asked for took 32 us of a call of 163, 5 to 20 of one of 270 to 1,500)
+        const auto step3 = Clock::now();
 
         // ---- Step 3: rounds over V_aff, queued in chains of kChain rounds per host round trip ----
         const int64_t frontier_initial = known;
@@ -3846,8 +3846,8 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
         }
         // not converged: max_iter cut the rounds, or cut them before a requested final check had passed
         const unsigned int nq = known > 0 ? known : (verified || universe.size() == 0 ? 0u : 1u);
-        HIPCHK(c, hipEventRecord(c->phase_ev[3], c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        const float ms_iterate = ms_since(step3);
         const float kernel_ms_total = c->time_kernels ? collect_kernel_ms(c) : 0.f;
         if (c->last_init.vertices > 0) (void)hipEventElapsedTime(&c->last_init.ms, c->init_ev[0], c->init_ev[1]);
         if (stats) {
@@ -3863,9 +3863,14 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             stats->final_checks = final_checks;
             stats->ingest_chunks = c->ingest_pinned_last ? c->ingest_chunks_last : -c->ingest_chunks_last;
             stats->ms_update_kernel = kernel_ms_total;
-            (void)hipEventElapsedTime(&stats->ms_insert, c->phase_ev[0], c->phase_ev[1]);
-            (void)hipEventElapsedTime(&stats->ms_seed, c->phase_ev[1], c->phase_ev[2]);
-            (void)hipEventElapsedTime(&stats->ms_iterate, c->phase_ev[2], c->phase_ev[3]);
+            const double insert = c->clock_khz > 0 ? (double)(c->h_bc->clock[1] - c->h_bc->clock[0]) / (double)c->clock_khz : 0.0;
+            double both = std::chrono::duration<double, std::milli>(step3 - step1).count();
+            // (what of the initialisation the device still had to do when the host went on)
+            const double late = std::max(0.0, c->last_init.ms - std::chrono::duration<double, std::milli>(step3 - listed).count());
+            both += std::min<double>(late, ms_iterate);
+            stats->ms_insert = (float)std::min(insert, both);
+            stats->ms_seed = (float)both - stats->ms_insert;
+            stats->ms_iterate = (float)(ms_iterate - std::min<double>(late, ms_iterate));
             stats->ms_total = ms_since(t0);
         }
         reset_timed_spans(c);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace dynlp {
@@ -82,7 +83,9 @@ struct __attribute__((aligned(64))) BatchCtr {
     unsigned int sort_long;          // touched rows whose appended segment is sorted by a whole workgroup
     unsigned int finish_hubs;        // hubs whose degree is summed by a whole workgroup
     unsigned int lists_done;         // workgroups of k_compact_start that have done their part
+    unsigned long long clock[2];     // the device's clock when the batch and when its first list began; not cleared
 };
+constexpr int kBatchClear = offsetof(BatchCtr, clock) / sizeof(unsigned int);  // words of a BatchCtr that a batch begins with as 0
 
 // Rounds over all updatable rows (see accelerate in dynlp.hip).  kRoundAll: every updatable row is updated, whatever moved
 // before; kRoundForce: the round runs even if its predecessor moved no row.

@@ -133,14 +133,14 @@ struct StartToHost {
 
 // The last workgroup of a launch to get here sends what k_to_host otherwise sends in a launch of its own.  (The others' counters
 // have been added by then: each workgroup has waited for what its additions returned.  They are read at device scope.)
-__device__ inline void send_start(RoundCtr* start, BatchCtr* bc, const StartToHost& to) {
+__device__ inline void send_start(RoundCtr* start, BatchCtr* bc, const StartToHost& to, unsigned long long began) {
     __shared__ bool last;
     if (threadIdx.x == 0) last = atomicAdd(&bc->lists_done, 1u) == gridDim.x - 1;
     __syncthreads();
     if (!last) return;
     unsigned long long* const from = reinterpret_cast<unsigned long long*>(start);
     for (unsigned int i = threadIdx.x; i < to.words; i += kBlock)
-        to.host[i] = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        to.host[i] = from + i == &bc->clock[1] ? began : __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __threadfence_system();
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -229,8 +229,10 @@ __global__ void __launch_bounds__(kBlock) k_compact_start(unsigned int n, uint8_
                                                          const RowMeta* __restrict__ meta, int32_t* __restrict__ front,
                                                          int32_t* __restrict__ back, RoundCtr* start, int32_t* __restrict__ ufront,
                                                          int32_t* __restrict__ uback, BatchCtr* bc, BatchGate gate, StartToHost to) {
+    const unsigned long long began = wall_clock64();
     if (!gate.closed()) compact_start<STEPS>(n, flag, seed_class, meta, front, back, start, ufront, uback, bc);
-    if (to.flag) send_start(start, bc, to);
+    if (to.flag) send_start(start, bc, to, began);
+    else if (blockIdx.x == 0 && threadIdx.x == 0) bc->clock[1] = began;
 }
 
 // =================================================================================================

@@ -276,12 +276,13 @@ __global__ void __launch_bounds__(kBlock) k_validate_edges(int64_t m, int64_t n_
 
 // ---- the steps of a batch that come before its edges are inserted -----------------------------------------------------
 // All counters a batch uses: `words` 32-bit words from `zero` on are cleared, then the pool's tail is set.
-__device__ inline void batch_begin(unsigned int first, unsigned int step, unsigned int* __restrict__ zero, unsigned int words,
-                                   const BatchCtr* bc, unsigned long long pool_tail) {
+__device__ inline void batch_begin(unsigned int first, unsigned int step, unsigned int* __restrict__ zero, unsigned int words, BatchCtr* bc,
+                                   unsigned long long pool_tail) {
     for (unsigned int i = first; i < words; i += step) {
         const unsigned int* tail = reinterpret_cast<const unsigned int*>(&bc->pool_tail);
         zero[i] = zero + i == tail ? (unsigned int)pool_tail : zero + i == tail + 1 ? (unsigned int)(pool_tail >> 32) : 0u;
     }
+    if (first == 0) bc->clock[0] = wall_clock64();
 }
 
 __global__ void __launch_bounds__(kBlock) k_batch_begin(unsigned int* __restrict__ zero, unsigned int words,

@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_check(SmallBatch b) {
         return;
     }
     for (unsigned int i = tid; i < b.pieces; i += kSmallThreads) b.to[i] = b.from[i];
-    batch_begin(tid, kSmallThreads, reinterpret_cast<unsigned int*>(b.bc), sizeof(BatchCtr) / 4, b.bc, b.pool_tail);
+    batch_begin(tid, kSmallThreads, reinterpret_cast<unsigned int*>(b.bc), kBatchClear, b.bc, b.pool_tail);
     __syncthreads();
     for (int64_t i = tid; i < b.nd + b.m + b.s; i += kSmallThreads)
         validate_batch_item(i, b.nd, b.del, b.m, b.eu, b.ev, b.ew, b.s, b.sv, b.sc, b.n1, b.n0, b.C, b.seed_class, b.add_cnt, b.bc);
