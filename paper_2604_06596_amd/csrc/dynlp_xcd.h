@@ -8,10 +8,9 @@
 // therefore runs up to kXcdRounds rounds in one launch on the workgroups of one XCD; those that start on the others leave at
 // once.
 //
-// Which XCD: the first workgroup that writes the launch's number into ctl->turn has its XCD chosen, and workgroups of that XCD
-// sign in until the first one closes the list, as soon as as many as wanted are there, or after a bounded wait.  Whoever has
-// signed in is running, so every wait for the others ends, whatever else the chip does meanwhile; rows are cut among as many as
-// came.  Where the entries of a workgroup's rows do not fit its LDS, no round is run and the host goes on with ordinary ones.
+// Which XCD, and which of its workgroups: see dynlp_signin.h.  Those that take part are running and agree on who they are, so
+// every wait for the others ends, whatever else the chip does meanwhile; rows are cut among as many as came.  Where the entries
+// of a workgroup's rows do not fit its LDS, no round is run and the host goes on with ordinary ones.
 //
 // Each workgroup keeps the entries and records of its rows in LDS, and one bit per vertex of the graph, "moved in the previous
 // round"; from that it lists its rows of V_aff (u moved or a neighbour did: Alg. 2 Step 3), gathers their neighbours' label
@@ -29,6 +28,7 @@
 #pragma once
 
 #include "dynlp_frontier.h"
+#include "dynlp_signin.h"
 
 namespace dynlp {
 
@@ -38,7 +38,7 @@ constexpr int kXcdRounds = 240;         // rounds per launch at most; exchanges 
 constexpr int kXcdChain = 8;            // rounds between two decisions at most
 constexpr unsigned int kXcdMaxRows = 32768;   // a moved word per thread
 constexpr unsigned int kXcdLds = 140u << 10;  // dynamic LDS of a workgroup
-constexpr unsigned int kXcdClosed = 0x80000000u;
+constexpr int kXcdLooks = 64;           // at the list before it is closed with fewer workgroups than wanted
 constexpr unsigned int kXcdLaunches = (1u << 24) - 1u;  // numbers of launches; the host clears XcdCtl before it starts again
 
 // Counters of a round: of one workgroup, or of all.
@@ -60,7 +60,9 @@ constexpr int kXcdPartWords = 3;  // a workgroup's counters in the exchange: max
 struct __attribute__((aligned(64))) XcdCtl {
     unsigned int turn;       // launch << 8 | XCD
     unsigned int pad0[31];
-    unsigned int signed_in[2][32];  // by parity of the launch: workgroups, kXcdClosed; 0 when its launch begins
+    unsigned int signed_in[2][32];  // [0]: by parity of the launch, workgroups that came, kListClosed; 0 when its launch begins
+    unsigned int groups;            // launch << 8 | workgroups that share its rounds
+    unsigned int pad1[31];
     unsigned long long part[2][kXcdPartWords][kXcdGroups];  // by parity of the exchange: launch << 8 | exchange, and 32 bits
     unsigned long long moved[2][kXcdMaxRows / 32];
 };
@@ -201,20 +203,27 @@ __device__ inline unsigned int xcd_get(unsigned long long* p, unsigned int tag) 
     return (unsigned int)x;
 }
 
-// Signs the workgroup in (thread 0).  Its place among those that share the launch's rounds, or -1; *chose: it chose the XCD and
-// has to close the list.  One atomic for those on other XCDs, two or three for the others.
-__device__ inline int xcd_sign_in(const XcdArgs& a, bool* chose) {
-    const unsigned int mine = a.launch << 8 | xcd_id();
-    unsigned int seen = __hip_atomic_fetch_add(&a.ctl->turn, a.zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *chose = false;
-    if (seen >> 8 != a.launch) {
-        *chose = __hip_atomic_compare_exchange_strong(&a.ctl->turn, &seen, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (*chose) seen = mine;
+// The words of dynlp_signin.h.  `turn` is reached from all XCDs, the others from one.
+struct XcdSignIn {
+    XcdCtl* ctl;
+    unsigned int zero;  // 0, unknown to the compiler
+    __device__ inline unsigned int read_turn() { return __hip_atomic_fetch_add(&ctl->turn, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ inline bool set_turn(unsigned int* seen, unsigned int value) {
+        return __hip_atomic_compare_exchange_strong(&ctl->turn, seen, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (seen != mine) return -1;
-    const unsigned int at = __hip_atomic_fetch_add(a.ctl->signed_in[a.launch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return at & kXcdClosed ? -1 : (int)at;
-}
+    __device__ inline unsigned int add(int p) { return __hip_atomic_fetch_add(ctl->signed_in[p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ inline unsigned int look(int p) { return __hip_atomic_fetch_add(ctl->signed_in[p], zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ inline unsigned int close(int p) {
+        return __hip_atomic_fetch_or(ctl->signed_in[p], kListClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ inline void clear(int p) { __hip_atomic_store(ctl->signed_in[p], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ inline void publish(unsigned int word) {
+        (void)__hip_atomic_exchange(&ctl->groups, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ inline unsigned int published() {
+        return __hip_atomic_fetch_add(&ctl->groups, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 
 template <int CP, int G>
 __global__ void __launch_bounds__(kXcdThreads) k_xcd_rounds(XcdArgs a) {
@@ -234,25 +243,10 @@ __global__ void __launch_bounds__(kXcdThreads) k_xcd_rounds(XcdArgs a) {
     const int tid = (int)threadIdx.x;
 
     if (tid == 0) {
-        bool chose;
-        sh_place = xcd_sign_in(a, &chose);
-        if (sh_place >= 0) {
-            unsigned int* const list = a.ctl->signed_in[a.launch & 1];
-            unsigned int t;
-            if (chose) {
-                a.ctl->signed_in[(a.launch & 1) ^ 1][0] = 0u;  // for the next launch
-                for (int i = 0; i < 64; ++i) {
-                    t = __hip_atomic_fetch_add(list, a.zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (t >= a.want) break;
-                }
-                t = __hip_atomic_fetch_or(list, kXcdClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {  // (the workgroup that chose is running: it will close the list)
-                do t = __hip_atomic_fetch_add(list, a.zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                while (!(t & kXcdClosed));
-            }
-            t &= ~kXcdClosed;
-            sh_groups = t < a.want ? t : a.want;
-        }
+        XcdSignIn words{a.ctl, a.zero};
+        const SignedIn in = sign_in(words, a.launch, xcd_id(), a.want, kXcdLooks);
+        sh_place = in.place;
+        sh_groups = in.groups;
         na = 0u;
         sh_resid = sh_moved = sh_entries = 0u;
     }
@@ -260,7 +254,6 @@ __global__ void __launch_bounds__(kXcdThreads) k_xcd_rounds(XcdArgs a) {
     const int place = sh_place;
     if (place < 0) return;
     const unsigned int P = sh_groups;
-    if ((unsigned int)place >= P) return;
     XcdCtl* const ctl = a.ctl;
 
     // ---- the workgroup's rows ----
