@@ -198,6 +198,17 @@ dynlp_status dynlp_set_update_mode(dynlp_ctx* ctx, int32_t mode);
 dynlp_status dynlp_set_final_check(dynlp_ctx* ctx, int32_t on);
 
 /*
+ * Tuning knob of the rounds that graphs of some ten thousand vertices run many to a launch, on the CUs of one XCD.
+ *   workgroups   that share a launch: 1 .. 32 at most so many, 0 as many as are useful (default), -1 none (the launch is refused
+ *                before it takes place, as where the device has no room for it).  Few have less room for the graph's entries;
+ *                where it is too little, or the launch is refused, the call goes on with launches for each round.  Labels are
+ *                the same bits in synchronous mode.
+ *   from_launch  the setting holds from this launch on, counted from 0 after this call
+ *   last_launch  number of the last launch, 0 .. 2^24 - 1, after which numbers begin again; -1 leaves it as it is
+ */
+dynlp_status dynlp_set_shared_rounds(dynlp_ctx* ctx, int32_t workgroups, int64_t from_launch, int32_t last_launch);
+
+/*
  * Starting rows of the vertices a batch inserts (Alg. 2 Step 1 "sparsification" and Step 2 "label
  * initialisation").  It changes where Step 3 starts, not the labels it converges to.
  *   DYNLP_INIT_UNIFORM    every inserted unlabelled row starts at 1/C (the paper's neutral 0.5).

@@ -71,7 +71,7 @@ EXPORTS = ["dynlp_default_options", "dynlp_create", "dynlp_static_solve", "dynlp
            "dynlp_round_log", "dynlp_last_error", "dynlp_destroy", "dynlp_set_initialiser",
            "dynlp_mean_edge_weight", "dynlp_last_components", "dynlp_set_update_mode", "dynlp_apply_update", "dynlp_storage_info",
            "dynlp_compact_storage", "dynlp_stream_bandwidth", "dynlp_get_labels_static", "dynlp_static_scratch_bytes",
-           "dynlp_set_final_check", "dynlp_gather_bandwidth"]
+           "dynlp_set_final_check", "dynlp_gather_bandwidth", "dynlp_set_shared_rounds"]
 
 _lib = None
 
@@ -133,6 +133,8 @@ def load_library(path: str | None = None):
     L.dynlp_set_update_mode.restype = ct.c_int
     L.dynlp_set_final_check.argtypes = [p, i32]
     L.dynlp_set_final_check.restype = ct.c_int
+    L.dynlp_set_shared_rounds.argtypes = [p, i32, i64, i32]
+    L.dynlp_set_shared_rounds.restype = ct.c_int
     L.dynlp_set_initialiser.argtypes = [p, i32, f32]
     L.dynlp_set_initialiser.restype = ct.c_int
     L.dynlp_mean_edge_weight.argtypes = [p, ct.POINTER(ct.c_double)]
@@ -270,6 +272,10 @@ class DynLP:
     def set_final_check(self, on=True):
         """dynlp_set_final_check: end every batch with a round over all rows that moves none by more than tol."""
         self._check(self._L.dynlp_set_final_check(self._h, 1 if on else 0))
+
+    def set_shared_rounds(self, workgroups=0, from_launch=0, last_launch=-1):
+        """dynlp_set_shared_rounds: workgroups that share the rounds of a small graph, and from which launch on."""
+        self._check(self._L.dynlp_set_shared_rounds(self._h, int(workgroups), int(from_launch), int(last_launch)))
 
     def set_initialiser(self, mode, tau=0.0):
         """dynlp_set_initialiser: INIT_UNIFORM or INIT_SUPERNODE with threshold tau."""

@@ -170,6 +170,8 @@ struct dynlp_ctx {
     XcdCtl* xcd = nullptr;
     XcdResult* h_xcd = nullptr;      // pinned
     unsigned int xcd_launches = 0;   // numbers them
+    int xcd_groups = 0;              // dynlp_set_shared_rounds, and launches asked for since
+    int64_t xcd_from = 0, xcd_asked = 0;
 
     int update_mode = DYNLP_UPDATE_SYNCHRONOUS;
     bool final_check = false;  // dynlp_set_final_check
@@ -1227,16 +1229,26 @@ bool xcd_rounds_pay(const dynlp_ctx* c, const Frontier& universe, int G, bool sw
     return head + c->entries / kXcdGroups * 9 / 8 * (int64_t)sizeof(Edge) <= (int64_t)kXcdLds;
 }
 
+// (A number is taken by a launch that takes place and by no other: each launch clears the list of the next number.)
+unsigned int next_xcd_launch(dynlp_ctx* c) {
+    if (c->xcd_launches == kXcdLaunches) {  // (the words of an exchange are told apart by the launch's number)
+        HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
+        c->xcd_launches = 0u;
+    }
+    return ++c->xcd_launches;
+}
+
 template <int CP, int G>
-void launch_xcd_inst(dynlp_ctx* c, const XcdArgs& a) {
+void launch_xcd_inst(dynlp_ctx* c, XcdArgs& a, bool refuse) {
     const void* kernel = reinterpret_cast<const void*>(&k_xcd_rounds<CP, G>);
     // (always the same value: the attribute belongs to the kernel, not to this context)
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXcdLds) != hipSuccess) {
+    if (refuse || hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXcdLds) != hipSuccess) {
         (void)hipGetLastError();
         c->h_xcd->rounds = 0;
         *c->h_flag = a.value;  // nothing was launched: refused
         return;
     }
+    a.launch = next_xcd_launch(c);
     hipLaunchKernelGGL((k_xcd_rounds<CP, G>), dim3(8 * a.want), dim3(kXcdThreads), kXcdLds, c->stream, a);
 }
 
@@ -1249,13 +1261,9 @@ void run_xcd(dynlp_ctx* c, int G, int cur, int round, int count, float* F_in, fl
     a.result = c->h_xcd;
     a.flag = c->h_flag;
     a.value = ++c->h_sent;
-    if (c->xcd_launches == kXcdLaunches) {  // (the words of an exchange are told apart by the launch's number)
-        HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
-        c->xcd_launches = 0u;
-    }
-    ++c->xcd_launches;
-    a.launch = c->xcd_launches;
-    a.want = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(kXcdGroups, ceil_div(c->n, 64)));
+    const int limit = c->xcd_asked++ >= c->xcd_from ? c->xcd_groups : 0;
+    const bool refuse = limit < 0;
+    a.want = (unsigned int)std::max<int64_t>(1, std::min<int64_t>(limit > 0 ? limit : kXcdGroups, ceil_div(c->n, 64)));
     a.ring = c->ring;
     a.t0 = round;
     a.rounds = count;
@@ -1278,11 +1286,11 @@ void run_xcd(dynlp_ctx* c, int G, int cur, int round, int count, float* F_in, fl
     for (int i = 0; i < 3; ++i) a.sig[i] = sig[i];
     hipEvent_t e1 = open_timed_span(c, round, count);
     switch (c->CP) {
-        case 1: G == 4 ? launch_xcd_inst<1, 4>(c, a) : launch_xcd_inst<1, 16>(c, a); break;
-        case 2: G == 4 ? launch_xcd_inst<2, 4>(c, a) : launch_xcd_inst<2, 16>(c, a); break;
-        case 4: G == 4 ? launch_xcd_inst<4, 4>(c, a) : launch_xcd_inst<4, 16>(c, a); break;
-        case 8: launch_xcd_inst<8, 16>(c, a); break;
-        default: launch_xcd_inst<16, 16>(c, a); break;
+        case 1: G == 4 ? launch_xcd_inst<1, 4>(c, a, refuse) : launch_xcd_inst<1, 16>(c, a, refuse); break;
+        case 2: G == 4 ? launch_xcd_inst<2, 4>(c, a, refuse) : launch_xcd_inst<2, 16>(c, a, refuse); break;
+        case 4: G == 4 ? launch_xcd_inst<4, 4>(c, a, refuse) : launch_xcd_inst<4, 16>(c, a, refuse); break;
+        case 8: launch_xcd_inst<8, 16>(c, a, refuse); break;
+        default: launch_xcd_inst<16, 16>(c, a, refuse); break;
     }
     HIPCHK(c, hipGetLastError());
     close_timed_span(c, e1);
@@ -3043,6 +3051,32 @@ dynlp_status dynlp_set_final_check(dynlp_ctx* ctx, int32_t on) {
         return DYNLP_ERR_INVALID_ARG;
     }
     ctx->final_check = on != 0;
+    return DYNLP_OK;
+}
+
+dynlp_status dynlp_set_shared_rounds(dynlp_ctx* c, int32_t workgroups, int64_t from_launch, int32_t last_launch) {
+    if (!c) return DYNLP_ERR_INVALID_ARG;
+    if (workgroups < -1 || workgroups > kXcdGroups || from_launch < 0 || last_launch < -1 || last_launch > (int32_t)kXcdLaunches) {
+        c->err = "workgroups must be in [-1, 32], from_launch >= 0 and last_launch in [-1, 2^24 - 1]";
+        return DYNLP_ERR_INVALID_ARG;
+    }
+    if (c->poisoned) {
+        c->err = "context is unusable after an earlier device or memory error";
+        return DYNLP_ERR_STATE;
+    }
+    try {
+        if (last_launch >= 0) {  // (numbers that do not follow each other: from cleared words)
+            HIPCHK(c, hipSetDevice(c->device));
+            HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+            c->xcd_launches = (unsigned int)last_launch;
+        }
+    } catch (const Fail& f) {
+        return f.st;
+    }
+    c->xcd_groups = workgroups;
+    c->xcd_from = from_launch;
+    c->xcd_asked = 0;
     return DYNLP_OK;
 }
 

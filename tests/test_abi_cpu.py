@@ -152,6 +152,7 @@ def test_bench_refuses_more_than_one_gpu():
 def test_new_entry_points_reject_null_handles(lib):
     assert lib.dynlp_apply_update(None, 0, None, 0, 0, None, None, None, 0, None, None, None) == -1
     assert lib.dynlp_set_update_mode(None, 0) == -1
+    assert lib.dynlp_set_shared_rounds(None, 0, 0, -1) == -1
     assert lib.dynlp_storage_info(None, None, None) == -1
     assert lib.dynlp_compact_storage(None) == -1
     assert lib.dynlp_stream_bandwidth(None, 1 << 20, 1, None, None) == -1

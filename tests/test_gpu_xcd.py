@@ -119,3 +119,45 @@ def test_two_contexts_take_turns_and_launches_are_told_apart():
             assert np.array_equal(runs[-1], want[1 + i][6])
     for d, _ in ctx:
         d.__exit__(None, None, None)
+
+
+def _solve_and_batches(make, lanes, tol, cap, mode, before=None):
+    """Static solve and batches; before[i] is called with the context ahead of step i.  Results, and the round logs."""
+    p, batches = make()
+    out, logs = [], []
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, group_lanes=lanes, time_kernels=True) as d:
+        d.set_update_mode(mode)
+        for i, b in enumerate([None, *batches]):
+            if before and i in before:
+                before[i](d)
+            if b is None:
+                st, s = d.static_solve(tol, cap)
+                d.set_params(tol, cap)
+            else:
+                st, s = d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
+            out.append((st, s.iterations, s.rows_updated, s.edges_traversed, s.frontier_initial, s.frontier_peak) +
+                       tuple(d.get_labels()) + tuple(d.round_log()))
+            logs.append(d.round_log_full())
+    return out, logs
+
+
+def _most_share(log):
+    """(Two launches of their own may take the same time too, and the last rounds of a batch share those of one workgroup.)"""
+    print("rounds", len(log), "that shared launches", _shared(log))
+    return 2 * _shared(log) > len(log)
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        for u, v in zip(x, y):
+            assert np.array_equal(u, v)
+
+
+def test_a_launch_that_is_refused_before_it_takes_place_leaves_no_gap_in_the_numbers():
+    """The sign-in list of a launch is cleared by the launch before it: after a refusal the next one finds it open all the same."""
+    make = _random(2500, 4, 9.0)
+    want, _ = _solve_and_batches(make, 16, 1e-6, 20000, P.UPDATE_SYNCHRONOUS)
+    got, logs = _solve_and_batches(make, 0, 1e-6, 20000, P.UPDATE_SYNCHRONOUS,
+                                   {1: lambda d: d.set_shared_rounds(-1), 2: lambda d: d.set_shared_rounds(0)})
+    _same(got, want)
+    assert [_most_share(log) for log in logs] == [True, False, True]
