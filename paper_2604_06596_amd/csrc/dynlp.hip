@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -93,6 +94,37 @@ void resolve_static_scratch(int device) {
     g_scratch_err[device] = e;
     if (e == hipSuccess) g_scratch_ptr[device] = ptr;
     else (void)hipGetLastError();
+}
+
+// Calls of this process at work on a device, and when two of them last were at the same time.
+struct CallsAtWork {
+    std::atomic<int> now{0};
+    std::atomic<Clock::rep> together{Clock::time_point::min().time_since_epoch().count()};
+};
+CallsAtWork g_at_work[kMaxDevices];
+constexpr float kTogetherMs = 100.f;
+
+class AtWork {
+    CallsAtWork* on;
+
+   public:
+    explicit AtWork(int device) : on(device >= 0 && device < kMaxDevices ? &g_at_work[device] : nullptr) {
+        if (on && on->now.fetch_add(1) > 0) on->together = Clock::now().time_since_epoch().count();
+    }
+    ~AtWork() {
+        if (on && on->now.fetch_sub(1) > 1) on->together = Clock::now().time_since_epoch().count();
+    }
+    AtWork(const AtWork&) = delete;
+    AtWork& operator=(const AtWork&) = delete;
+};
+
+// Whether other contexts have work for the device, as far as that can be told: a program that makes its calls one after the other
+// has one at a time, whatever contexts it holds.
+bool others_at_work(int device) {
+    if (device < 0 || device >= kMaxDevices) return true;
+    if (g_at_work[device].now > 1) return true;
+    const Clock::rep then = g_at_work[device].together;
+    return then > (Clock::now() - std::chrono::microseconds((int64_t)(kTogetherMs * 1000.f))).time_since_epoch().count();
 }
 
 }  // namespace
@@ -1227,6 +1259,23 @@ bool xcd_rounds_pay(const dynlp_ctx* c, const Frontier& universe, int G, bool sw
     // room for an eighth more than a workgroup's even share of the entries (the kernel has the last word)
     const int64_t rows = c->n / kXcdGroups + 32, head = c->n / 8 + 64 + 7 * rows;
     return head + c->entries / kXcdGroups * 9 / 8 * (int64_t)sizeof(Edge) <= (int64_t)kXcdLds;
+}
+
+// Rounds of one launch at most (whole chains), from round `it` of a call on.
+// A launch holds all registers of its XCD's CUs, and every other launch has workgroups for that XCD: those wait for its end, and
+// with them all that their stream holds (a kernel of another process or library too).  While other calls of this process are at work
+// launches are therefore short, and shorter still in a call that goes on for long.  us for a call (medians), of threads with a context
+// and a stream each; N = one vertex into 3,001, T = 37 into 20,011, K = 100 into 2,000 with 230 rounds, S = 30,000 into 300,007:
+//                                            K       N        K+K          N+N        T+T        K+N         T+K+N             S+N
+//   a launch for each round                  2,400   215      2,550 2,830  265 265    488 488    2,520  211  662 2,910  330    2,690 320
+//   240 rounds at once, whatever others do   1,130   139      2,230 2,280  161 161    383 384    1,157 1,107                   2,843 251
+//   16 rounds at once                        1,130   139      1,660 1,670  167 172    396 396    1,520  375  440 1,740  380    2,850 258
+//   16, from round 32 on 8 (here)            1,130   139      1,910 2,010  170 172    390 390    1,810  242  400 2,160  330    2,790 270
+//   16, from round 32 on launches for each   1,140   140      2,450 2,790  168 174    393 393    2,370  134  328 4,270  287    2,840 260
+constexpr int kXcdTogether = 32, kXcdTogetherFirst = 16, kXcdTogetherThen = 8;
+static_assert(kXcdTogetherFirst % kChain == 0 && kXcdTogetherThen % kChain == 0 && kXcdRounds % kChain == 0, "whole chains");
+int xcd_rounds_at_once(const dynlp_ctx* c, int it) {
+    return !others_at_work(c->device) ? kXcdRounds : it < kXcdTogether ? kXcdTogetherFirst : kXcdTogetherThen;
 }
 
 // (A number is taken by a launch that takes place and by no other: each launch clears the list of the next number.)
@@ -2727,6 +2776,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         g_create_error = "host allocation failed";
         return DYNLP_ERR_OOM;
     }
+    const AtWork at_work(o.device);
     dynlp_status result = DYNLP_OK;
     int64_t* block_sums = nullptr;
     try {
@@ -3163,6 +3213,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
     dynlp_status st = dynlp_set_params(c, tol, max_iter);
     if (st != DYNLP_OK) return st;
     const auto t0 = Clock::now();
+    const AtWork at_work(c->device);
     try {
         HIPCHK(c, hipSetDevice(c->device));
         conjugate_idle(c);
@@ -3223,7 +3274,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
             if (one_xcd && it % kChain == 0) {
                 const unsigned int sig[3] = {0u, 0u, prev_bits};
                 const size_t first_pair = c->events_used / 2;
-                run_xcd(c, G, 0, it, std::min<int>(kXcdRounds, max_iter - it), buf[it & 1], buf[(it + 1) & 1], true, lazy, tol, 0, same_run, sig);
+                run_xcd(c, G, 0, it, std::min<int>(xcd_rounds_at_once(c, it), max_iter - it), buf[it & 1], buf[(it + 1) & 1], true, lazy, tol, 0, same_run, sig);
                 const int executed = (int)c->h_xcd->rounds;
                 if (c->time_kernels) trim_timed_spans(c, first_pair, it + executed);
                 if (executed == 0) one_xcd = false;
@@ -3360,6 +3411,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             if (del[i] < 0 || del[i] >= n0) return bad(format_validation(kErrDeleted, i));
     }
     const auto t0 = Clock::now();
+    const AtWork at_work(c->device);
     bool mutated = false;
     try {
         HIPCHK(c, hipSetDevice(c->device));
@@ -3593,7 +3645,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
             if (!xcd_failed && !pingpong && xcd_rounds_pay(c, universe, G, false) && !relaxed_rounds_pay(c, universe, c->tol)) {
                 const bool few = tail_rounds_pay(c, known, known_before, avg_len);  // (V_aff of one workgroup's size)
                 const size_t first_pair = c->events_used / 2;
-                run_xcd(c, G, cur, it, std::min<int>(kXcdRounds - chain_off, c->max_iter - it), c->F, in_place ? c->F : c->F2, false, lazy,
+                run_xcd(c, G, cur, it, std::min<int>(xcd_rounds_at_once(c, it) - chain_off, c->max_iter - it), c->F, in_place ? c->F : c->F2, false, lazy,
                         c->tol, chain_off, same_run, prev_sig);
                 const int executed = (int)c->h_xcd->rounds;
                 if (c->time_kernels) trim_timed_spans(c, first_pair, it + executed);
@@ -3927,6 +3979,7 @@ dynlp_status dynlp_get_labels(dynlp_ctx* c, float* soft, int32_t* hard) {
     }
     const int64_t n = c->n;
     if (n == 0 || (!soft && !hard)) return DYNLP_OK;
+    const AtWork at_work(c->device);
     unsigned char* d_out = nullptr;
     dynlp_status st = DYNLP_OK;
     try {

@@ -24,7 +24,7 @@
 // L2 by then (xcd_drain).  What crosses workgroups is read at device scope, past the L1 of the CU.
 //
 // What bounds a round: latency, some four dependent trips to the L2; beyond some 100,000 entries the gathers.
-// Measured (whole calls, before / after): see xcd_rounds_pay in dynlp.hip.
+// Measured (whole calls, before / after): see xcd_rounds_pay in dynlp.hip; next to other contexts: xcd_rounds_at_once.
 #pragma once
 
 #include "dynlp_frontier.h"

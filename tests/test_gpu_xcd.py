@@ -3,6 +3,9 @@ bit, as ordinary launches (a fixed number of lanes per row keeps those), over th
 words of 32 rows, one word or many per workgroup, rows of 1 to 128 entries (longer ones end it), one to sixteen columns, 240
 rounds to a launch.  With kernel timing on, all rounds of a launch have the same time.
 """
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -121,11 +124,12 @@ def test_two_contexts_take_turns_and_launches_are_told_apart():
         d.__exit__(None, None, None)
 
 
-def _solve_and_batches(make, lanes, tol, cap, mode, before=None):
+def _solve_and_batches(make, lanes, tol, cap, mode, before=None, **options):
     """Static solve and batches; before[i] is called with the context ahead of step i.  Results, and the round logs."""
     p, batches = make()
     out, logs = [], []
-    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, group_lanes=lanes, time_kernels=True) as d:
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, group_lanes=lanes, time_kernels=True,
+                 **options) as d:
         d.set_update_mode(mode)
         for i, b in enumerate([None, *batches]):
             if before and i in before:
@@ -161,3 +165,69 @@ def test_a_launch_that_is_refused_before_it_takes_place_leaves_no_gap_in_the_num
                                    {1: lambda d: d.set_shared_rounds(-1), 2: lambda d: d.set_shared_rounds(0)})
     _same(got, want)
     assert [_most_share(log) for log in logs] == [True, False, True]
+
+
+def test_calls_of_several_contexts_at_the_same_time():
+    """While other calls are at work a launch has fewer rounds than alone.  Wherever it ends, rounds and labels are those of a call on
+    its own."""
+    import torch
+
+    cases = [(_random(2500, 4, 9.0), 1e-6), (_random(9001, 2, 12.0), 1e-6), (_random(20011, 3, 8.0), 1e-4), (_random(6001, 2, 3.0), 1e-6)]
+    want = [_solve_and_batches(make, 0, tol, 20000, P.UPDATE_SYNCHRONOUS)[0] for make, tol in cases]
+    wrong = []
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        for i in range(6):
+            j = (k + i * (k + 1)) % len(cases)
+            got = _solve_and_batches(cases[j][0], 0, cases[j][1], 20000, P.UPDATE_SYNCHRONOUS, stream=stream.cuda_stream)[0]
+            for a, b in zip(got, want[j]):
+                if not all(np.array_equal(x, y) for x, y in zip(a, b)):
+                    wrong.append((k, i, j, [q for q, (x, y) in enumerate(zip(a, b)) if not np.array_equal(x, y)]))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
+def _longest_launch(log):
+    """Rounds in a row with the same time: those of one launch (of two, where both took the same)."""
+    best = run = 1
+    for a, b in zip(log, log[1:]):
+        run = run + 1 if a.ms_update == b.ms_update else 1
+        best = max(best, run)
+    return best
+
+
+def test_a_call_does_not_keep_its_xcd_for_long_while_others_are_at_work():
+    """Every launch of another context has workgroups for that XCD, which wait for the launch that holds it."""
+    import torch
+
+    make = _random(2500, 4, 9.0)
+    time.sleep(0.3)  # (for a tenth of a second after calls have met, more of them are expected)
+    _, alone = _solve_and_batches(make, 0, 1e-6, 20000, P.UPDATE_SYNCHRONOUS)
+    assert _longest_launch(alone[0]) > 150
+    enough, at_work = threading.Event(), threading.Event()
+
+    def work():
+        stream = torch.cuda.Stream()
+        p, _ = _random(3001, 2, 6.0)()
+        with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, stream=stream.cuda_stream) as d:
+            while not enough.is_set():
+                d.static_solve(1e-5, 20000)
+                at_work.set()
+
+    other = threading.Thread(target=work)
+    other.start()
+    try:
+        assert at_work.wait(60)
+        stream = torch.cuda.Stream()
+        logs = [_solve_and_batches(make, 0, 1e-6, 20000, P.UPDATE_SYNCHRONOUS, stream=stream.cuda_stream)[1] for _ in range(4)][-1]
+    finally:
+        enough.set()
+        other.join()
+    print("rounds of the longest launch", _longest_launch(alone[0]), [_longest_launch(log) for log in logs])
+    assert _longest_launch(logs[0]) <= 48
