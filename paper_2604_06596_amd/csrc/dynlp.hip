@@ -25,6 +25,7 @@
 #include "dynlp_components.h"
 #include "dynlp_binned.h"
 #include "dynlp_insert.h"
+#include "dynlp_kept.h"
 #include "dynlp_packed.h"
 #include "dynlp_small.h"
 #include "dynlp_xcd.h"
@@ -308,134 +309,48 @@ struct Fail {
         }                                                                                              \
     } while (0)
 
-// ---- memory between contexts -----------------------------------------------------------------------
-// A context takes some forty arrays and gives them back when it is destroyed.  hipMalloc and hipFree cost 5 to 20 us each for
-// small arrays, about 7 ms together for a graph of 3M vertices, and much more once a process has handed out all of the device's
-// memory before: what is given back then has to be cleared before it is handed out again (50M vertices, 20 GB: 40 to 1,750 ms).
-// Arrays of contexts without an allocator of their own therefore wait here for the next context of the process.
-//   bounded     an eighth of the device's memory, 16 MB of pinned memory per device; what does not fit is freed at once
-//   given back  when an allocation fails (all of it), and by the first create or destroy after kKeepMs without use
-//   streams     an array comes here only when the stream of its context has run dry (as hipFree waits for it)
-//   threads     one lock; calls of the runtime that free memory are made outside it
-// Measured: 3M vertices create 0.66 / 0.20 ms, destroy 5.2 / 0.01; 400,000 with 100 sweeps, whole 10.1 / 8.9 ms; 50M 188 / 179 ms,
-// and 880 / 181 ms where the memory had been in use before.
-struct KeptBlock {
-    void* p;
-    size_t bytes;
-    int device;
-    bool pinned;
-    Clock::time_point since;
+// ---- memory between contexts (dynlp_kept.h) --------------------------------------------------------
+struct HipMemory {
+    void* allocate(bool pinned, size_t bytes) {
+        void* p = nullptr;
+        if ((pinned ? hipHostMalloc(&p, bytes, hipHostMallocDefault) : hipMalloc(&p, bytes)) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void release(bool pinned, void* p) { (void)(pinned ? hipHostFree(p) : hipFree(p)); }
+    std::chrono::steady_clock::time_point now() { return std::chrono::steady_clock::now(); }
 };
-constexpr float kKeepMs = 10000.f;
-constexpr size_t kKeepShare = 8, kKeepPinned = (size_t)16 << 20;
-std::mutex g_kept_lock;
-std::vector<KeptBlock> g_kept;                                // guarded by g_kept_lock; oldest first
-std::unordered_map<int, size_t> g_kept_bytes[2], g_kept_cap;  // by device; [1]: pinned
+KeptMemory<HipMemory> g_kept;
+constexpr float kKeepMs = 10000.f;  // looked at by each create and destroy
+constexpr size_t kKeepPinned = (size_t)16 << 20;
 
-void release_blocks(const std::vector<KeptBlock>& blocks) {
-    for (const KeptBlock& b : blocks) (void)(b.pinned ? hipHostFree(b.p) : hipFree(b.p));
-}
-
-// A kept block of at least `bytes`, and not much more; NULL if there is none.
-void* take_kept(int device, bool pinned, size_t bytes, size_t* got) {
-    std::lock_guard<std::mutex> hold(g_kept_lock);
-    size_t best = g_kept.size();
-    for (size_t i = 0; i < g_kept.size(); ++i) {
-        const KeptBlock& b = g_kept[i];
-        if (b.device != device || b.pinned != pinned || b.bytes < bytes || b.bytes > bytes + bytes / 8 + 4096) continue;
-        if (best == g_kept.size() || b.bytes < g_kept[best].bytes) best = i;
+// Bytes of device memory that may wait: an eighth of the device's.
+size_t kept_device_bytes(int device) {
+    static std::atomic<size_t> known[kMaxDevices];
+    const bool listed = device >= 0 && device < kMaxDevices;
+    if (listed && known[device] > 0) return known[device];
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {  // (of the current device, which is the context's)
+        (void)hipGetLastError();
+        return 0;
     }
-    if (best == g_kept.size()) return nullptr;
-    void* const p = g_kept[best].p;
-    *got = g_kept[best].bytes;
-    g_kept_bytes[pinned][device] -= *got;
-    g_kept.erase(g_kept.begin() + (ptrdiff_t)best);
-    return p;
-}
-
-// Takes the block in; false: the caller frees it.
-bool keep_block(int device, bool pinned, void* p, size_t bytes) {
-    std::lock_guard<std::mutex> hold(g_kept_lock);
-    size_t cap = kKeepPinned;
-    if (!pinned) {
-        size_t& known = g_kept_cap[device];
-        if (known == 0) {
-            size_t free_bytes = 0, total = 0;
-            if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {  // (of the current device, which is the context's)
-                (void)hipGetLastError();
-                return false;
-            }
-            known = std::max<size_t>(1, total / kKeepShare);
-        }
-        cap = known;
-    }
-    size_t& held = g_kept_bytes[pinned][device];
-    if (bytes > cap - std::min(cap, held)) return false;
-    try {
-        g_kept.push_back(KeptBlock{p, bytes, device, pinned, Clock::now()});
-    } catch (const std::bad_alloc&) {
-        return false;
-    }
-    held += bytes;
-    return true;
-}
-
-// Gives back what has waited for more than `ms`; whether there was any.
-bool release_kept(float ms) {
-    std::vector<KeptBlock> old;
-    {
-        std::lock_guard<std::mutex> hold(g_kept_lock);
-        try {
-            old.reserve(g_kept.size());
-        } catch (const std::bad_alloc&) {
-            return false;
-        }
-        size_t left = 0;
-        for (const KeptBlock& b : g_kept) {
-            if (ms_since(b.since) < ms) {
-                g_kept[left++] = b;
-            } else {
-                old.push_back(b);
-                g_kept_bytes[b.pinned][b.device] -= b.bytes;
-            }
-        }
-        g_kept.erase(g_kept.begin() + (ptrdiff_t)left, g_kept.end());
-    }
-    release_blocks(old);
-    return !old.empty();
+    if (listed) known[device] = total / 8;
+    return total / 8;
 }
 
 // NULL when the allocator has no memory left (nothing else changes).
 void* dev_try_alloc(dynlp_ctx* c, size_t bytes) {
     if (bytes == 0) bytes = 256;
-    void* p = nullptr;
-    if (c->alloc_fn) {
-        p = c->alloc_fn(bytes, c->alloc_user);
-    } else if (!(p = take_kept(c->device, false, bytes, &bytes)) && hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        p = nullptr;
-        if (release_kept(0.f) && hipMalloc(&p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
-    }
+    void* const p = c->alloc_fn ? c->alloc_fn(bytes, c->alloc_user) : g_kept.take(c->device, false, bytes, &bytes);
     if (p) c->live.emplace(p, bytes);
     return p;
 }
 
 // Pinned memory, kept between contexts likewise.  *got: its size.
-void* pinned_try_alloc(dynlp_ctx* c, size_t bytes, size_t* got) {
-    *got = bytes;
-    void* p = take_kept(c->device, true, bytes, got);
-    if (!p && hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        p = nullptr;
-    }
-    return p;
-}
+void* pinned_try_alloc(dynlp_ctx* c, size_t bytes, size_t* got) { return g_kept.take(c->device, true, bytes, got); }
 
 void pinned_free(dynlp_ctx* c, void* p, size_t bytes) {  // (nothing of the context is running)
-    if (p && !keep_block(c->device, true, p, bytes)) (void)hipHostFree(p);
+    if (p) g_kept.give(c->device, true, p, bytes, kKeepPinned);
 }
 
 void free_binned(dynlp_ctx* c);
@@ -476,7 +391,7 @@ void dev_free(dynlp_ctx* c, void* p) {
     }
     const bool dry = c->idle || (hipStreamSynchronize(c->stream) == hipSuccess &&
                                  (!c->copy_stream || hipStreamSynchronize(c->copy_stream) == hipSuccess));
-    if (!dry || !keep_block(c->device, false, p, bytes)) (void)hipFree(p);
+    g_kept.give(c->device, false, p, bytes, dry ? kept_device_bytes(c->device) : 0);
 }
 
 template <typename T>
@@ -2579,7 +2494,7 @@ void destroy_ctx(dynlp_ctx* c) {
     if (c->h_cg) (void)hipHostFree(c->h_cg);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     delete c;
-    (void)release_kept(kKeepMs);
+    (void)g_kept.release_older(kKeepMs);
 }
 
 // ---- Alg. 2 Step 1 (components of the sparsified batch-internal graph) + Step 2 (supernode rows) ----
@@ -2799,7 +2714,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->CP = CP;
         HIPCHK(c, hipSetDevice(c->device));
         resolve_static_scratch(c->device);  // for dynlp_get_labels_static; a failure is reported by that call
-        (void)release_kept(kKeepMs);
+        (void)g_kept.release_older(kKeepMs);
         int cus = 0;  // (one attribute: all properties take 0.2 ms)
         HIPCHK(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
         c->num_cu = cus > 0 ? cus : 256;
