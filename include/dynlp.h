@@ -89,8 +89,10 @@ typedef struct dynlp_options {
                                 row length, else 4, 8, 16, 32 or 64 (tuning knob) */
     /* Optional allocator for device memory (e.g. a caching allocator); all three NULL selects
        hipMalloc/hipFree.  alloc returns NULL on failure.  Without them, arrays that a context gives back wait for the
-       next context of the process: at most an eighth of the device's memory, freed when an allocation of the library
-       fails, and after ten seconds without use by the next call that creates or destroys a context. */
+       next context of the process: at most an eighth of the device's memory (and 16 MB of pinned memory).  All of it is
+       freed when hipMalloc or hipHostMalloc fails, or alloc returns NULL for an array that the call cannot do without
+       (alloc is then asked once more), and what has waited for ten seconds by the next call that creates or destroys a
+       context. */
     void* (*alloc)(size_t bytes, void* user);
     void (*dealloc)(void* ptr, void* user);
     void* alloc_user;

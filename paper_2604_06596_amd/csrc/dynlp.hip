@@ -346,8 +346,19 @@ void* dev_try_alloc(dynlp_ctx* c, size_t bytes) {
     return p;
 }
 
-// Pinned memory, kept between contexts likewise.  *got: its size.
+// Pinned memory, kept between contexts likewise.  *got: its size, at least `bytes`; pinned_free needs it.
 void* pinned_try_alloc(dynlp_ctx* c, size_t bytes, size_t* got) { return g_kept.take(c->device, true, bytes, got); }
+
+// As pinned_try_alloc, for an array that a call cannot do without.
+void* pinned_alloc(dynlp_ctx* c, size_t bytes, size_t* got) {
+    void* const p = pinned_try_alloc(c, bytes, got);
+    if (!p) {
+        c->err = "allocation of " + std::to_string(bytes) + " bytes of pinned memory failed";
+        c->poisoned = true;
+        throw Fail{DYNLP_ERR_OOM};
+    }
+    return p;
+}
 
 void pinned_free(dynlp_ctx* c, void* p, size_t bytes) {  // (nothing of the context is running)
     if (p) g_kept.give(c->device, true, p, bytes, kKeepPinned);
@@ -362,6 +373,8 @@ void free_conjugate(dynlp_ctx* c);
 // rounds.)
 void* dev_alloc_or_reclaim(dynlp_ctx* c, size_t bytes) {
     void* p = dev_try_alloc(c, bytes);
+    // (an allocator of the context's own may stand on the same device)
+    if (!p && c->alloc_fn && g_kept.release_older(0.f) > 0) p = dev_try_alloc(c, bytes);
     if (p || (!c->pk_ent && !c->pb_src && !c->cg_z)) return p;
     (void)hipStreamSynchronize(c->stream);
     free_packed(c);
@@ -695,7 +708,8 @@ void ingest_edges(dynlp_ctx* c, int64_t m, int64_t n_total, const int32_t* eu, c
             b = nullptr;
         }
         c->bounce_edges = 0;
-        for (void*& b : c->bounce) HIPCHK(c, hipHostMalloc(&b, (size_t)chunk * 12, hipHostMallocDefault));
+        size_t got = 0;
+        for (void*& b : c->bounce) b = pinned_alloc(c, (size_t)chunk * 12, &got);
         c->bounce_edges = chunk;
     }
     // the copies must not start before earlier work on the main stream that still reads the device buffers is done
@@ -2180,11 +2194,9 @@ bool conjugate_arrays(dynlp_ctx* c, const Frontier& universe, float** z, float**
         if (!c->cg_ring) return false;
     }
     if (!c->h_cg) {
-        if (hipHostMalloc(reinterpret_cast<void**>(&c->h_cg), sizeof(CgSlot) * kChain, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            c->h_cg = nullptr;
-            return false;
-        }
+        size_t got = 0;
+        c->h_cg = static_cast<CgSlot*>(pinned_try_alloc(c, sizeof(CgSlot) * kChain, &got));
+        if (!c->h_cg) return false;
     }
     if (c->CP == 1) {  // one float per vertex: the two arrays of row lists that are idle meanwhile
         float* idle[2];
@@ -2501,7 +2513,8 @@ void destroy_ctx(dynlp_ctx* c) {
 void ensure_init_scratch(dynlp_ctx* c, int64_t k, int64_t m) {
     if (!c->cc_ctr) {
         c->cc_ctr = static_cast<InitCtr*>(dev_alloc(c, sizeof(InitCtr)));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_cc), sizeof(InitCtr), hipHostMallocDefault));
+        size_t got = 0;
+        c->h_cc = static_cast<InitCtr*>(pinned_alloc(c, sizeof(InitCtr), &got));
         for (hipEvent_t& e : c->init_ev) HIPCHK(c, hipEventCreate(&e));
     }
     if (k > c->cc_vcap) {
@@ -2725,11 +2738,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         HIPCHK(c, hipMemsetAsync(c->xcd, 0, sizeof(XcdCtl), c->stream));
         constexpr size_t kSlotBytes = sizeof(RoundCtr) * kRing, kStartBytes = (sizeof(dynlp_ctx::HostStart) + 63) / 64 * 64;
         constexpr size_t kResultBytes = (sizeof(XcdResult) + 63) / 64 * 64;
-        c->h_fixed = pinned_try_alloc(c, kSlotBytes + kStartBytes + kResultBytes + 64, &c->h_fixed_bytes);
-        if (!c->h_fixed) {
-            c->err = "allocation of pinned memory failed";
-            throw Fail{DYNLP_ERR_OOM};
-        }
+        c->h_fixed = pinned_alloc(c, kSlotBytes + kStartBytes + kResultBytes + 64, &c->h_fixed_bytes);
         unsigned char* const fixed = static_cast<unsigned char*>(c->h_fixed);
         c->h_slot = reinterpret_cast<RoundCtr*>(fixed);
         c->h_start = reinterpret_cast<dynlp_ctx::HostStart*>(fixed + kSlotBytes);

@@ -7,6 +7,7 @@ import pytest
 
 import workloads as W
 import paper_2604_06596_amd as P
+from test_gpu_allocator import TorchAllocator
 
 pytestmark = pytest.mark.gpu
 
@@ -16,8 +17,8 @@ def _problem(n, C):
     return p, W.small_random_batch(q, n // 10, 7, 3, num_extra_edges=20)
 
 
-def _pass(p, b, stream=None):
-    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, stream=stream) as d:
+def _pass(p, b, stream=None, **options):
+    with P.DynLP(p.n, p.row_ptr, p.col, p.w, p.C, p.seed_vertex, p.seed_class, stream=stream, **options) as d:
         d.static_solve(1e-6, 20000)
         d.apply_batch(b.num_new_vertices, b.eu, b.ev, b.ew, b.seed_vertex, b.seed_class)
         return d.get_labels()
@@ -64,3 +65,21 @@ def test_it_is_used_again_and_bounded():
     torch.cuda.synchronize()
     last, _ = torch.cuda.mem_get_info()
     assert before - last <= total // 8
+
+
+def test_an_allocator_that_has_no_memory_is_asked_again_after_kept_memory_went_back():
+    """What destroyed contexts left waiting stands on the same device as the allocator of the next one."""
+    import torch
+
+    p, b = _problem(200000, 10)
+    want = _pass(p, b)
+    torch.cuda.synchronize()
+    held = torch.cuda.mem_get_info()[0]
+    a = TorchAllocator()
+    a.refuse = lambda nbytes: a.refused == 0 and a.calls > 5
+    got = _pass(p, b, allocator=a)
+    torch.cuda.synchronize()
+    assert a.refused == 1 and not a.live
+    assert all(np.array_equal(x, y) for x, y in zip(got, want))
+    torch.cuda.empty_cache()
+    assert torch.cuda.mem_get_info()[0] - held > 32 << 20
