@@ -88,11 +88,12 @@ typedef struct dynlp_options {
     int32_t group_lanes;     /* lanes cooperating on one frontier row: 0 = choose from the mean
                                 row length, else 4, 8, 16, 32 or 64 (tuning knob) */
     /* Optional allocator for device memory (e.g. a caching allocator); all three NULL selects
-       hipMalloc/hipFree.  alloc returns NULL on failure.  Without them, arrays that a context gives back wait for the
-       next context of the process: at most an eighth of the device's memory (and 16 MB of pinned memory).  All of it is
-       freed when hipMalloc or hipHostMalloc fails, or alloc returns NULL for an array that the call cannot do without
-       (alloc is then asked once more), and what has waited for ten seconds by the next call that creates or destroys a
-       context. */
+       hipMalloc/hipFree.  alloc returns NULL on failure.  Without them, the arrays of a destroyed context, and those that
+       live within one call, wait for the next context or call of the process: at most an eighth of the device's memory (and
+       16 MB of pinned memory).  What has waited for ten seconds is freed by the next call that creates or destroys a
+       context, solves or inserts; all of it by dynlp_compact_storage and dynlp_release_kept_memory, and when hipMalloc or
+       hipHostMalloc fails or alloc returns NULL for an array that the call cannot do without (alloc is then asked once
+       more). */
     void* (*alloc)(size_t bytes, void* user);
     void (*dealloc)(void* ptr, void* user);
     void* alloc_user;
@@ -350,7 +351,7 @@ dynlp_status dynlp_export_graph(dynlp_ctx* ctx, int64_t* row_ptr, int32_t* col, 
  * out again in id order, each with fresh slack, in a new pool of the size that needs (plus a quarter
  * for growth) and releases the old one; graph, labels and every later result are unchanged.  It needs
  * room for both pools at once.  The two label matrices of the conjugate steps are given back as well
- * (see dynlp_set_update_mode).
+ * (see dynlp_set_update_mode), and what waits for the next context or call (see dynlp_options.alloc).
  */
 dynlp_status dynlp_storage_info(const dynlp_ctx* ctx, int64_t* pool_used, int64_t* pool_capacity);
 dynlp_status dynlp_compact_storage(dynlp_ctx* ctx);
@@ -420,8 +421,16 @@ int64_t dynlp_round_log(const dynlp_ctx* ctx, int64_t cap, dynlp_round_info* out
  * thread).  Valid until the next call on the same context / thread.  Never NULL. */
 const char* dynlp_last_error(const dynlp_ctx* ctx);
 
-/* Release the context and all device memory it owns (see dynlp_options.alloc).  NULL is allowed. */
+/* Release the context and all device memory it owns (see dynlp_options.alloc: some of it may wait for the next context).  NULL is
+ * allowed. */
 void dynlp_destroy(dynlp_ctx* ctx);
+
+/*
+ * Free the memory that waits for the next context or call of the process, on all devices (see dynlp_options.alloc); how many bytes.
+ * Contexts keep what they have.  After the last dynlp_destroy nothing else does this: a program that then wants the memory for
+ * something else, or resets a device (hipDeviceReset takes the memory from under the library), calls it first.  From any thread.
+ */
+int64_t dynlp_release_kept_memory(void);
 
 #ifdef __cplusplus
 }

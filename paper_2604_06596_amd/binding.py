@@ -71,7 +71,8 @@ EXPORTS = ["dynlp_default_options", "dynlp_create", "dynlp_static_solve", "dynlp
            "dynlp_round_log", "dynlp_last_error", "dynlp_destroy", "dynlp_set_initialiser",
            "dynlp_mean_edge_weight", "dynlp_last_components", "dynlp_set_update_mode", "dynlp_apply_update", "dynlp_storage_info",
            "dynlp_compact_storage", "dynlp_stream_bandwidth", "dynlp_get_labels_static", "dynlp_static_scratch_bytes",
-           "dynlp_set_final_check", "dynlp_gather_bandwidth", "dynlp_set_shared_rounds"]
+           "dynlp_set_final_check", "dynlp_gather_bandwidth", "dynlp_set_shared_rounds",
+           "dynlp_release_kept_memory"]
 
 _lib = None
 
@@ -141,6 +142,8 @@ def load_library(path: str | None = None):
     L.dynlp_mean_edge_weight.restype = ct.c_int
     L.dynlp_last_components.argtypes = [p, i64, p, ct.POINTER(InitInfo)]
     L.dynlp_last_components.restype = ct.c_int
+    L.dynlp_release_kept_memory.argtypes = []
+    L.dynlp_release_kept_memory.restype = i64
     L.dynlp_last_error.argtypes = [p]
     L.dynlp_last_error.restype = ct.c_char_p
     L.dynlp_destroy.argtypes = [p]
@@ -151,6 +154,11 @@ def load_library(path: str | None = None):
 
 def _is_torch(a) -> bool:
     return a is not None and type(a).__module__.startswith("torch")
+
+
+def release_kept_memory():
+    """dynlp_release_kept_memory: frees what waits for the next context or call of the process.  Returns the bytes."""
+    return int(load_library().dynlp_release_kept_memory())
 
 
 class DynLP:

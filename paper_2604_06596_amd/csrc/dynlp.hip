@@ -321,7 +321,7 @@ struct HipMemory {
     std::chrono::steady_clock::time_point now() { return std::chrono::steady_clock::now(); }
 };
 KeptMemory<HipMemory> g_kept;
-constexpr float kKeepMs = 10000.f;  // looked at by each create and destroy
+constexpr float kKeepMs = 10000.f;  // looked at by each create, destroy, solve and batch
 constexpr size_t kKeepPinned = (size_t)16 << 20;
 
 // Bytes of device memory that may wait: an eighth of the device's.
@@ -393,18 +393,30 @@ void* dev_alloc(dynlp_ctx* c, size_t bytes) {
     return p;
 }
 
-void dev_free(dynlp_ctx* c, void* p) {
+// Ends the life of an array; 0: it is none that dev_try_alloc handed out and that has not been freed yet, or its allocator has it
+// back; else its bytes.
+size_t dev_forget(dynlp_ctx* c, void* p) {
     const auto it = p ? c->live.find(p) : c->live.end();
-    if (it == c->live.end()) return;  // only what dev_try_alloc handed out and has not been freed yet
+    if (it == c->live.end()) return 0;
     const size_t bytes = it->second;
     c->live.erase(it);
-    if (c->dealloc_fn) {
-        c->dealloc_fn(p, c->alloc_user);
-        return;
-    }
-    const bool dry = c->idle || (hipStreamSynchronize(c->stream) == hipSuccess &&
-                                 (!c->copy_stream || hipStreamSynchronize(c->copy_stream) == hipSuccess));
+    if (!c->dealloc_fn) return bytes;
+    c->dealloc_fn(p, c->alloc_user);
+    return 0;
+}
+
+// The memory goes back to the device; where the context is being destroyed, it may wait for the next one.
+void dev_free(dynlp_ctx* c, void* p) {
+    if (const size_t bytes = dev_forget(c, p)) g_kept.give(c->device, false, p, bytes, c->idle ? kept_device_bytes(c->device) : 0);
+}
+
+// An array that lives within a call and that the next such call takes again (2^28 half-edges of a batch: 2.5 GB): waits likewise.
+void scratch_free(dynlp_ctx* c, void* p) {
+    const size_t bytes = dev_forget(c, p);
+    if (!bytes) return;
+    const bool dry = hipStreamSynchronize(c->stream) == hipSuccess && (!c->copy_stream || hipStreamSynchronize(c->copy_stream) == hipSuccess);
     g_kept.give(c->device, false, p, bytes, dry ? kept_device_bytes(c->device) : 0);
+    (void)g_kept.release_older(kKeepMs);
 }
 
 template <typename T>
@@ -459,7 +471,7 @@ struct DevIn {
     ~DevIn() {
         if (owned) {
             (void)hipStreamSynchronize(c->stream);
-            dev_free(c, owned);
+            scratch_free(c, owned);
         }
     }
 };
@@ -1023,7 +1035,7 @@ struct BinnedInsert {
     }
     void release() {
         void* const all[] = {row, col, w, table, bins};
-        for (void* p : all) dev_free(c, p);
+        for (void* p : all) scratch_free(c, p);
         row = nullptr;
         col = nullptr;
         w = nullptr;
@@ -2840,7 +2852,7 @@ dynlp_status dynlp_create(dynlp_ctx** out, int64_t n, const int64_t* row_ptr, co
         c->err = "host allocation failed";
         result = DYNLP_ERR_OOM;
     }
-    if (block_sums) dev_free(c, block_sums);
+    if (block_sums) scratch_free(c, block_sums);
     if (result != DYNLP_OK) {
         g_create_error = c->err;
         destroy_ctx(c);
@@ -2996,6 +3008,7 @@ dynlp_status dynlp_compact_storage(dynlp_ctx* c) {
         c->pool = pool_new.release();
         c->pool_cap = cap;
         c->pool_tail = tail;
+        (void)g_kept.release_older(0.f);
         return DYNLP_OK;
     } catch (const SoftOom&) {
         (void)hipStreamSynchronize(c->stream);
@@ -3027,6 +3040,8 @@ dynlp_status dynlp_set_final_check(dynlp_ctx* ctx, int32_t on) {
     ctx->final_check = on != 0;
     return DYNLP_OK;
 }
+
+int64_t dynlp_release_kept_memory(void) { return (int64_t)g_kept.release_older(0.f); }
 
 dynlp_status dynlp_set_shared_rounds(dynlp_ctx* c, int32_t workgroups, int64_t from_launch, int32_t last_launch) {
     if (!c) return DYNLP_ERR_INVALID_ARG;
@@ -3140,6 +3155,7 @@ dynlp_status dynlp_static_solve(dynlp_ctx* c, float tol, int32_t max_iter, dynlp
     const AtWork at_work(c->device);
     try {
         HIPCHK(c, hipSetDevice(c->device));
+        (void)g_kept.release_older(kKeepMs);
         conjugate_idle(c);
         c->log.clear();
         reset_timed_spans(c);
@@ -3339,6 +3355,7 @@ dynlp_status dynlp_apply_update(dynlp_ctx* c, int64_t nd, const int32_t* del, in
     bool mutated = false;
     try {
         HIPCHK(c, hipSetDevice(c->device));
+        (void)g_kept.release_older(kKeepMs);
         conjugate_idle(c);
         c->log.clear();
         reset_timed_spans(c);
@@ -3935,7 +3952,7 @@ dynlp_status dynlp_get_labels(dynlp_ctx* c, float* soft, int32_t* hard) {
     } catch (const Fail& f) {
         st = f.st;
     }
-    dev_free(c, d_out);
+    scratch_free(c, d_out);
     return st;
 }
 

@@ -1,9 +1,10 @@
-// Memory that waits for the next context of the process.
+// Memory that waits for the next context or call of the process.
 //
 // A context takes some forty arrays and gives them back when it is destroyed.  hipMalloc and hipFree cost 5 to 20 us each for
 // small arrays, about 7 ms together for a graph of 3M vertices, and much more once a process has handed out all of the device's
 // memory before: what is given back then has to be cleared before it is handed out again (50M vertices, 20 GB: 40 to 1,750 ms).
-// Arrays of destroyed contexts without an allocator of their own therefore wait here.
+// Arrays of destroyed contexts without an allocator of their own therefore wait here, and arrays that live within one call; what a
+// living context has no use for any more does not.
 //   bounded     so many bytes per device and kind of memory as the caller of give() says, and kMostBlocks; what does not fit goes back
 //               to the runtime at once
 //   given back  when the runtime has none left (all of it, see take), and what has waited for too long (release_older)
