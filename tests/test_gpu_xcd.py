@@ -167,6 +167,81 @@ def test_a_launch_that_is_refused_before_it_takes_place_leaves_no_gap_in_the_num
     assert [_most_share(log) for log in logs] == [True, False, True]
 
 
+def _longest_launch(log):
+    """Rounds in a row with the same time: those of one launch (of two, where both took the same)."""
+    best = run = 1
+    for a, b in zip(log, log[1:]):
+        run = run + 1 if a.ms_update == b.ms_update else 1
+        best = max(best, run)
+    return best
+
+
+def _crowded(n, C, hubs):
+    """`hubs` vertices of some 100 entries come first, the others have a few: the first workgroup's entries outgrow its LDS though the
+    graph as a whole is small enough for rounds on one XCD."""
+    def make():
+        rng = np.random.default_rng(n + C)
+        a = rng.integers(0, hubs, 44 * hubs)
+        b = (a + 1 + rng.integers(0, hubs - 1, 44 * hubs)) % hubs
+        u = np.concatenate([a, np.arange(n - 1)])
+        v = np.concatenate([b, np.arange(1, n)])
+        w = (rng.integers(1, 17, len(u)) / 16).astype(np.float32)
+        order = np.argsort(np.concatenate([u, v]), kind="stable")
+        row_ptr = np.concatenate([[0], np.cumsum(np.bincount(np.concatenate([u, v]), minlength=n))]).astype(np.int64)
+        assert np.diff(row_ptr).max() <= 128
+        seeds = np.arange(0, n, 11).astype(np.int32)
+        p = W.Problem(n, C, row_ptr, np.concatenate([v, u])[order].astype(np.int32), np.concatenate([w, w])[order], seeds,
+                      (seeds % C).astype(np.int32), np.zeros(n, np.int32))
+        none = np.zeros(0, np.int32)
+        x = rng.integers(hubs, n - 1, 300).astype(np.int32)
+        return p, [W.Batch(0, x[:150], x[150:][::-1] + (x[:150] == x[150:][::-1]), np.full(150, 0.5, np.float32), none, none)]
+    return make
+
+
+@pytest.mark.parametrize("C", [2, 3, 12])
+@pytest.mark.parametrize("mode", [P.UPDATE_SYNCHRONOUS, P.UPDATE_IN_PLACE])
+def test_a_graph_that_one_workgroup_has_no_room_for(C, mode):
+    make = _crowded(20000, C, 600)
+    want, logs0 = _solve_and_batches(make, 0, 1e-6, 20000, mode, {0: lambda d: d.set_shared_rounds(-1)})
+    got, logs = _solve_and_batches(make, 0, 1e-6, 20000, mode)
+    print([(len(a), _shared(a), len(b), _shared(b)) for a, b in zip(logs, logs0)])
+    assert all(_shared(a) <= _shared(b) + len(a) // 4 for a, b in zip(logs, logs0)), "the kernel is meant to refuse"
+    assert any(len(a) >= 40 for a in logs)
+    if mode == P.UPDATE_SYNCHRONOUS:
+        _same(got, want)
+    for a, b in zip(got, want):
+        k = 3 if len(a) < 8 else 6
+        assert a[0] == b[0] == 0 and np.max(np.abs(a[k] - b[k])) <= 400 * 1e-6
+
+
+# (24,000 entries: 70 KB for three workgroups, too much for one)
+@pytest.mark.parametrize("workgroups,from_launch,shared", [(3, 0, 240), (31, 0, 240), (1, 0, 0), (1, 1, 240), (-1, 1, 240), (2, 1, 240)])
+@pytest.mark.parametrize("C,deg", [(4, 9.0), (2, 9.5), (9, 9.0)])
+def test_fewer_workgroups_than_wanted_and_launches_refused_amid_a_call(workgroups, from_launch, shared, C, deg):
+    """From launch `from_launch` of each call on: where the entries do not fit, the call goes on with ordinary rounds from the lists,
+    the counters and the label buffers that the launches before have left."""
+    make = _random(2600, C, deg)
+    want, _ = _solve_and_batches(make, 16, 1e-6, 20000, P.UPDATE_SYNCHRONOUS)
+    few = lambda d: d.set_shared_rounds(workgroups, from_launch)
+    got, logs = _solve_and_batches(make, 0, 1e-6, 20000, P.UPDATE_SYNCHRONOUS, {0: few, 1: few, 2: few})
+    print([(len(log), _longest_launch(log)) for log in logs])
+    for log in logs[:2]:
+        assert len(log) > 240 + 64 and (_longest_launch(log) >= 240) == (shared == 240)
+        if from_launch == 1 and workgroups != 2:
+            assert _longest_launch(log[240:]) < 64
+    _same(got, want)
+
+
+def test_launches_are_numbered_anew_after_the_last_number():
+    make = _random(2600, 4, 9.0)
+    want, _ = _solve_and_batches(make, 16, 1e-6, 20000, P.UPDATE_SYNCHRONOUS)
+    for last in ((1 << 24) - 1, (1 << 24) - 2, (1 << 24) - 3, 254, 255):
+        number = lambda d: d.set_shared_rounds(last_launch=last)
+        got, logs = _solve_and_batches(make, 0, 1e-6, 20000, P.UPDATE_SYNCHRONOUS, {0: number, 1: number})
+        assert all(_longest_launch(log) >= 240 for log in logs[:2])
+        _same(got, want)
+
+
 def test_calls_of_several_contexts_at_the_same_time():
     """While other calls are at work a launch has fewer rounds than alone.  Wherever it ends, rounds and labels are those of a call on
     its own."""
@@ -191,15 +266,6 @@ def test_calls_of_several_contexts_at_the_same_time():
     for t in threads:
         t.join()
     assert not wrong
-
-
-def _longest_launch(log):
-    """Rounds in a row with the same time: those of one launch (of two, where both took the same)."""
-    best = run = 1
-    for a, b in zip(log, log[1:]):
-        run = run + 1 if a.ms_update == b.ms_update else 1
-        best = max(best, run)
-    return best
 
 
 def test_a_call_does_not_keep_its_xcd_for_long_while_others_are_at_work():
