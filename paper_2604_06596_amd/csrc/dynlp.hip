@@ -1188,7 +1188,10 @@ void launch_tail(dynlp_ctx* c, int G, int cur, int round, int count, int by_vert
 // sweeps are one launch each: synchronous 16,000 entries 5.60/2.86 5.90/3.39, 96,000 6.38/5.08 6.80/6.00, 192,000 5.92/6.18
 // 6.89/7.57; in place 192,000 5.95/5.42 6.96/6.75, 200,000 7.37/5.85 8.56/7.00, 400,000 7.22/9.31 8.28/9.03.  At tol = 1e-4,
 // 8 to 25 rounds: 0.34/0.22 at 42,000 entries, 0.47/0.34 at 160,000, 0.36/0.31 at 280,000.
-// More than 16 columns were not tried: a row is two lines of the L2 then.
+// More than 16 columns (a row is two lines of the L2 or four) are left to ordinary launches, because kernels for them are not built:
+// with two more of them 24 and 50 classes took, at 25,000 / 81,000 / 162,000 / 287,000 / 406,000 entries, synchronous 8.2/3.8 6.6/4.8
+// 7.2/6.1 5.5/7.5 10.4/13.9 and 7.7/4.4 7.6/6.9 5.0/8.5 10.2/18.7 13.0/28.3, in place 7.6/3.4 6.7/3.9 7.1/4.1 9.8/5.8 10.0/6.5 and
+// 7.4/3.8 7.6/4.6 8.8/6.0 10.4/9.8 12.0/14.7 (batches, tol = 1e-6).
 int64_t xcd_max_entries(const dynlp_ctx* c, bool sweeps) {
     const bool in_place = c->update_mode == DYNLP_UPDATE_IN_PLACE;
     return sweeps ? (in_place ? 256000 : 128000) : (in_place ? 440000 : 300000);
@@ -2064,7 +2067,7 @@ void read_slots_start(dynlp_ctx* c) {
 // 10.5 / 2.1 / 2.5; 5e-6: 5.1 / 8.3 / 4.0, 3.5 / 3.8 / 2.2, 21 / 6.2 / 5.5, 12.6 / 4.2 / 4.5, 12.6 / 2.3 / 2.7; 3e-6: 6.8 /
 // 8.3 / 12.6, 8.5 / 4.4 / 4.7, 26 / 6.8 / 5.9, 14.6 / 4.2 / 4.8, 14.4 / 2.6 / 2.7; 2e-6, without / at once: 1M 24 / 9.5).
 // kRelaxMinRows is where packed rounds begin; smaller graphs would gain as well (8,000 planted vertices 8.2 -> 1.2 ms,
-// 16,000 kNN 7.1 -> 1.2 ms).
+// 16,000 kNN 7.1 -> 1.2 ms), but in-place calls on them are held to the number of rounds of the synchronous method.
 constexpr unsigned int kRelaxMinRows = 32768;
 constexpr float kRelaxMinTol = 2e-7f, kRelaxNowTol = 4e-6f, kRelaxMaxTol = 1e-5f;
 constexpr double kRelaxStuck = 0.99;
